@@ -215,13 +215,15 @@ int32_t dc_probe_mfma_rate(int32_t lds_reads, void* scratch_dev, size_t scratch_
  *  - the matching of a frame runs on a stream of its own, next to whatever is still queued of
  *    the previous frame, and only the matching is waited for (without a handle the call waits
  *    for the caller's stream);
- *  - with dc_overlap_pipeline(handle, 2) two frames are in flight: consecutive calls enqueue
- *    their layers on two alternating internal streams, layer i of a frame waiting for layer i of
- *    the previous frame (its cache) and for the previous frame's readers of any tensor it
- *    overwrites.  The caller's stream is made to wait for the end of the frame, so synchronising
- *    it still yields the frame's results.  In this mode the inputs (frames, weights) must be
- *    complete in memory when the call is made, and the caller's own streams must be done with the
- *    tensors handed over; the device workspace holds two sets of plans and scratch.
+ *  - with dc_overlap_pipeline(handle, 2) several frames are in flight: the layers of the stack
+ *    are cut into up to four stages of about equal time, every stage runs on a stream of its own
+ *    (the last one on the caller's), and stage s of a frame overlaps stage s + 1 of the frame
+ *    before it.  A layer's cache is the previous frame's output of the same layer, so it belongs
+ *    to the same stage and stream.  A tensor that crosses from one stage to a later one should
+ *    alternate between two buffers: its writer waits for the readers of the frame that last used
+ *    the buffer.  Synchronising the caller's stream yields the frame's results.  In this mode the
+ *    inputs (frames, weights) must be complete in memory when the call is made, and the caller's
+ *    own streams must be done with the tensors handed over.
  * Callers that may not create streams simply pass no handle.
  */
 int32_t dc_overlap_create(void** overlap);
@@ -466,8 +468,8 @@ int32_t dc_stack_workspace_bytes(const dc_layer* layers, int32_t n_layers, int32
  *   tensors_cur     host array [n_layers+1] of dev pointers, every tensor of this frame
  *                   (written).  Conv outputs are the cache values of the next frame.  The other
  *                   tensors may be the same buffers for every frame; with a pipelined overlap
- *                   handle a caller that alternates them between two sets as well saves the
- *                   library one cross-stream wait and one event per such tensor and frame.
+ *                   handle a caller that alternates them between two sets as well lets the
+ *                   library cut the stack into stages anywhere.
  *   tensors_prev    host array [n_layers+1] of dev pointers: the previous frame's tensors;
  *                   only conv-layer outputs are read.  Must not alias tensors_cur for them.
  *                   Written only in an in-place frame (see in_place).

@@ -11,6 +11,9 @@
 
 namespace dc {
 
+inline size_t dtype_size(int dtype) { return dtype == DC_BF16 ? 2 : 4; }
+inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
+
 // ---- device-side plan records -------------------------------------------------
 // One reusable rectangle of a conv layer's output, with its stream and source offset.
 struct RectDev {
@@ -268,33 +271,38 @@ struct Profile {
     std::vector<uint8_t> used;
 };
 
+// ---- dc_run_stack's pipeline (dc_stack.hip) ---------------------------------------
+// With an overlap handle in pipeline mode the layers of a stack are cut into up to kMaxStages contiguous stages, and
+// every stage runs on a stream of its own (the last one on the caller's): stage s of frame f follows stage s - 1 of
+// the same frame (one event) and stage s of frame f - 1 (same stream, no event).  A layer's cache is the previous
+// frame's output of the same layer, hence of the same stage, so the frames in flight need no waits per layer.
+constexpr int kMaxStages = 4;              // streams: the process has four hardware queues
+constexpr int kFramesInFlight = 4;         // plan areas and frame records that take turns
+struct StackPlan;                          // what dc_run_stack derives from a stack's description (dc_stack.hip)
+struct FrameRecord {
+    hipEvent_t done[kMaxStages] = {};      // that stage of the frame has finished
+    bool valid = false;
+    const StackPlan* plan = nullptr;
+    int partition = 0;                     // StackPlan::partition of the frame
+    int n_stages = 0;
+    hipStream_t caller = nullptr;
+    std::vector<const void*> bufs;         // where its tensors are
+};
+
 // Streams and events of an overlap handle (Section 7.6: the stages can be carried out asynchronously).
-//  - aux: the matching of a frame and the read-back of its mask run here, next to the previous frame's layers;
-//  - pipeline: consecutive frames alternate between two work streams; layer i of a frame waits for layer i of
-//    the previous frame (its cache) and for the previous frame's readers of every single-buffered tensor it
-//    overwrites, so two frames are in flight and the second fills the CUs the first leaves idle.  A tensor
-//    whose buffer is not the previous frame's but that of the frame before it (a caller that alternates all
-//    its tensors, not only the conv outputs) was last used on this same stream and needs neither wait nor event.
 struct Overlap {
-    hipStream_t aux = nullptr;
+    hipStream_t aux = nullptr;                        // matching (and, planned on the GPU, stage 0)
+    hipStream_t work[2] = {nullptr, nullptr};         // further stages
     hipEvent_t match_done = nullptr;                  // mask and motion of the current frame are in host memory
+    hipEvent_t plan_done = nullptr;                   // no pipeline, planned on the GPU: the frame's plan is complete
     hipEvent_t upload_done[2] = {nullptr, nullptr};   // plan upload from staging half 0 / 1 has completed
     bool pending[2] = {false, false};
     int parity = 0;
     bool pipeline = false;
-    hipStream_t work[2] = {nullptr, nullptr};
-    hipEvent_t frame_done[2] = {nullptr, nullptr};
-    std::vector<hipEvent_t> layer_done[2];            // [frame parity][layer]
-    std::vector<char> recorded[2];                    // [frame parity][layer]: that frame recorded layer_done
-    bool frame_recorded[2] = {false, false};          // that frame recorded frame_done
-    std::vector<const void*> last_cur[2];             // [frame parity]: tensors_cur of that stream's last frame
-    int frame_parity = 0;
-    // planning on the GPU: matching and planning kernels of consecutive frames run on `aux`, ahead of the layers;
-    // a frame's plan lives in one of three areas (two frames in flight and one being planned)
-    hipEvent_t plan_done[3] = {nullptr, nullptr, nullptr};   // the plan in that area is complete
-    hipEvent_t area_free[3] = {nullptr, nullptr, nullptr};   // the layers of the frame that used the area are done
-    bool area_recorded[3] = {false, false, false};
-    int plan_counter = 0;
+    FrameRecord ring[kFramesInFlight];
+    uint64_t frame_no = 0;
+    hipStream_t head = nullptr;                       // stream of the last frame's matching and planning on the GPU
+    std::vector<StackPlan*> plans;                    // most recently used first
     // look-ahead matching: the arguments of a match already started for the next frame
     struct Prefetch {
         bool valid = false;
@@ -305,7 +313,42 @@ struct Overlap {
     } prefetch;
 };
 
-inline size_t dtype_size(int dtype) { return dtype == DC_BF16 ? 2 : 4; }
-inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
+// ---- shared by the entry points (dc_api.hip) ---------------------------------------
+inline hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s); }
+#define DC_TRY_HIP(expr)                      \
+    do {                                      \
+        hipError_t e__ = (expr);              \
+        if (e__ != hipSuccess) return DC_ERR_HIP; \
+    } while (0)
+// Bytes of plan data for one conv layer planned on the host, worst case.
+size_t plan_bytes(int n_streams, int Hout, int Wout, const ConvTiling& t, int max_rects);
+// A plan serialised into host staging at `host`; the device addresses it will have once copied to `dev` (same offsets).
+struct PlanAddr {
+    const TileDev* tiles;
+    const RectDev* rects;
+    const RangeDev* ranges;
+    size_t bytes;
+};
+PlanAddr pack_plan(const LayerPlan& plan, unsigned char* host, unsigned char* dev);
+struct Bracket {   // records a profile slot around a launch when a profile is attached
+    Profile* p; int slot; hipStream_t st;
+    Bracket(Profile* p_, int slot_, hipStream_t st_) : p(p_), slot(slot_), st(st_) {
+        if (p && slot >= 0 && (size_t)slot < p->used.size()) { (void)hipEventRecord(p->ev[2 * slot], st); }
+        else p = nullptr;
+    }
+    ~Bracket() {
+        if (p) { (void)hipEventRecord(p->ev[2 * slot + 1], st); p->used[slot] = 1; }
+    }
+};
+// Copy + conv launches of one layer given its packed plan on the device.
+int run_conv_planned(const dc_layer& l, const void* in, const void* w, const float* bias,
+                     const void* cache_prev, void* out, int n_streams, int Hin, int Win, int dtype,
+                     const ConvTiling& tiling, const LayerPlan* plan, const PlanAddr* addr, hipStream_t st,
+                     Profile* prof = nullptr, int gemm_slot = -1, int copy_slot = -1, int* kernel_id = nullptr,
+                     bool copy_done = false, void* scratch = nullptr, size_t scratch_bytes = 0,
+                     const void* w_packed = nullptr, const TileDev* dev_tiles = nullptr, int dev_capacity = 0,
+                     const int* dev_count = nullptr, long dev_hint = -1, const int32_t* in_origin = nullptr,
+                     const int32_t* out_origin = nullptr, int origin_stride = 0);
+
 
 }  // namespace dc

@@ -657,7 +657,8 @@ constexpr int kCopyUnitsPerGroup = 64;     // most units a workgroup of the per-
 struct CopyUnitsArgs {
     CopyUnitsLayer L[kCopyUnitsMaxLayers];
     const int32_t* dxy;
-    int32_t n_tensors, pad;
+    int32_t n_tensors, n_layers;
+    int32_t first[kCopyUnitsMaxLayers];    // first workgroup (blockIdx.x) of every layer
 };
 
 // Section 5 "Reuse", step 1, from the unit masks: every pixel whose bit is set receives the previous frame's
@@ -666,9 +667,12 @@ struct CopyUnitsArgs {
 // next pixel of the unit's row (contiguous in memory); the four items of a thread are loaded before any is stored.
 template <typename V>
 __global__ __launch_bounds__(256) void shifted_copy_units_kernel(CopyUnitsArgs A) {
-    const CopyUnitsLayer& L = A.L[blockIdx.z];
+    // the layers of a launch may have maps of very different sizes: their workgroups lie one after another in blockIdx.x
+    int layer = 0;
+    while (layer + 1 < A.n_layers && (int)blockIdx.x >= A.first[layer + 1]) ++layer;
+    const CopyUnitsLayer& L = A.L[layer];
     const int stream = blockIdx.y, tid = threadIdx.x;
-    const int units = L.units_x * L.units_y, upb = L.units_per_group, u0 = blockIdx.x * upb;
+    const int units = L.units_x * L.units_y, upb = L.units_per_group, u0 = ((int)blockIdx.x - A.first[layer]) * upb;
     if (u0 >= units) return;
     __shared__ unsigned short s_m[kCopyUnitsPerGroup];
     __shared__ int s_px0[kCopyUnitsPerGroup];          // pixel index (within the stream's map) of the unit's first pixel
@@ -803,7 +807,7 @@ hipError_t launch_shifted_copy_units(const CopyUnitsLayer* layers, int n_layers,
     for (int l0 = 0; l0 < n_layers; l0 += kCopyUnitsMaxLayers) {
         const int nl = n_layers - l0 < kCopyUnitsMaxLayers ? n_layers - l0 : kCopyUnitsMaxLayers;
         CopyUnitsArgs A{};
-        int max_groups = 0;
+        int groups = 0;
         for (int i = 0; i < nl; ++i) {
             A.L[i] = layers[l0 + i];
             // about sixteen items (vectors) per thread: 4096 per workgroup, 16 * vec_per_px per unit
@@ -812,11 +816,11 @@ hipError_t launch_shifted_copy_units(const CopyUnitsLayer* layers, int n_layers,
             upb = upb < 1 ? 1 : (upb > kCopyUnitsPerGroup ? kCopyUnitsPerGroup : upb);
             A.L[i].units_per_group = upb;
             A.L[i].vec_shift = (pv & (pv - 1)) == 0 ? __builtin_ctz((unsigned)pv) : -1;
-            const int groups = (A.L[i].units_x * A.L[i].units_y + upb - 1) / upb;
-            max_groups = groups > max_groups ? groups : max_groups;
+            A.first[i] = groups;
+            groups += (A.L[i].units_x * A.L[i].units_y + upb - 1) / upb;
         }
-        A.dxy = dxy; A.n_tensors = n_tensors;
-        const dim3 grid((unsigned)max_groups, (unsigned)n_streams, (unsigned)nl);
+        A.dxy = dxy; A.n_tensors = n_tensors; A.n_layers = nl;
+        const dim3 grid((unsigned)groups, (unsigned)n_streams);
         if (vec_bytes == 16) hipLaunchKernelGGL(shifted_copy_units_kernel<uint4>, grid, dim3(256), 0, st, A);
         else if (vec_bytes == 4) hipLaunchKernelGGL(shifted_copy_units_kernel<uint32_t>, grid, dim3(256), 0, st, A);
         else hipLaunchKernelGGL(shifted_copy_units_kernel<uint16_t>, grid, dim3(256), 0, st, A);
