@@ -211,7 +211,7 @@ int32_t dc_probe_mfma_rate(int32_t lds_reads, void* scratch_dev, size_t scratch_
 
 /*
  * Overlap handle (Section 7.6: matching and inference can run asynchronously): streams and
- * events owned by the library object.  Passed to dc_run_stack,
+ * events owned by the library (the streams are one set per GPU, shared by its handles).  Passed to dc_run_stack,
  *  - the matching of a frame runs on a stream of its own, next to whatever is still queued of
  *    the previous frame, and only the matching is waited for (without a handle the call waits
  *    for the caller's stream);

@@ -291,6 +291,7 @@ struct FrameRecord {
 
 // Streams and events of an overlap handle (Section 7.6: the stages can be carried out asynchronously).
 struct Overlap {
+    int device = -1;                                  // the GPU whose stage streams these are
     hipStream_t aux = nullptr;                        // matching (and, planned on the GPU, stage 0)
     hipStream_t work[2] = {nullptr, nullptr};         // further stages
     hipEvent_t match_done = nullptr;                  // mask and motion of the current frame are in host memory

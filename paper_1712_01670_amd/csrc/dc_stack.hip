@@ -490,6 +490,59 @@ void StackPlan::cut(int max_stages) {
 
 namespace {
 
+// The streams of the stages, one set per GPU for all overlap handles: the process has four hardware queues, and with
+// the caller's stream these three fill them.  With streams of their own, several handles' streams shared queues in the
+// order of their creation, so that stages of one handle landed in one queue and ran one after another (three runners
+// taking turns, a ResNet-50 stream each: 438 us per frame against 360 for one runner alone).  All waits are for work
+// that was queued earlier, so sharing cannot lock up.  The set lives as long as a handle uses it.
+struct StageStreams {
+    int users = 0;
+    hipStream_t st[kMaxStages - 1] = {};
+};
+constexpr int kMaxGpus = 64;
+StageStreams g_stage_streams[kMaxGpus];
+std::mutex g_stage_streams_mutex;
+
+bool acquire_stage_streams(Overlap* o) {
+    if (hipGetDevice(&o->device) != hipSuccess || o->device < 0 || o->device >= kMaxGpus) { o->device = -1; return false; }
+    std::lock_guard<std::mutex> guard(g_stage_streams_mutex);
+    StageStreams& S = g_stage_streams[o->device];
+    if (S.users == 0)
+        for (hipStream_t& st : S.st)
+            if (hipStreamCreateWithFlags(&st, hipStreamNonBlocking) != hipSuccess) {
+                for (hipStream_t& made : S.st) {
+                    if (made) (void)hipStreamDestroy(made);
+                    made = nullptr;
+                }
+                o->device = -1;
+                return false;
+            }
+    ++S.users;
+    o->aux = S.st[0]; o->work[0] = S.st[1]; o->work[1] = S.st[2];
+    return true;
+}
+void release_stage_streams(Overlap* o) {
+    if (o->device < 0) return;
+    std::lock_guard<std::mutex> guard(g_stage_streams_mutex);
+    StageStreams& S = g_stage_streams[o->device];
+    if (--S.users == 0)
+        for (hipStream_t& st : S.st) {
+            (void)hipStreamDestroy(st);
+            st = nullptr;
+        }
+    o->device = -1;
+}
+
+// Waits for everything that was queued through the handle.
+hipError_t drain(Overlap* o) {
+    hipError_t e = hipSuccess;
+    for (hipStream_t st : {o->aux, o->work[0], o->work[1]})
+        if (st && e == hipSuccess) e = hipStreamSynchronize(st);
+    for (FrameRecord& r : o->ring)
+        if (r.valid && e == hipSuccess) e = hipEventSynchronize(r.done[r.n_stages - 1]);
+    return e;
+}
+
 void release_plan(StackPlan* p) { delete p; }
 
 // One dc_run_stack call: the arguments, then the steps in the order in which they run.
@@ -1121,9 +1174,8 @@ int32_t dc_overlap_create(void** overlap) {
     if (!overlap) return DC_ERR_NULL_PTR;
     Overlap* o = new (std::nothrow) Overlap();
     if (!o) return DC_ERR_WORKSPACE;
-    bool ok = hipStreamCreateWithFlags(&o->aux, hipStreamNonBlocking) == hipSuccess;
+    bool ok = acquire_stage_streams(o);
     for (int i = 0; i < 2 && ok; ++i) ok = hipEventCreateWithFlags(&o->upload_done[i], hipEventDisableTiming) == hipSuccess;
-    for (int i = 0; i < 2 && ok; ++i) ok = hipStreamCreateWithFlags(&o->work[i], hipStreamNonBlocking) == hipSuccess;
     ok = ok && hipEventCreateWithFlags(&o->match_done, hipEventDisableTiming) == hipSuccess;
     ok = ok && hipEventCreateWithFlags(&o->plan_done, hipEventDisableTiming) == hipSuccess;
     if (!ok) {
@@ -1134,31 +1186,19 @@ int32_t dc_overlap_create(void** overlap) {
     return DC_OK;
 }
 
-// Waits for everything that was queued through the handle.
-static hipError_t drain(Overlap* o) {
-    hipError_t e = hipSuccess;
-    for (hipStream_t st : {o->aux, o->work[0], o->work[1]})
-        if (st && e == hipSuccess) e = hipStreamSynchronize(st);
-    for (FrameRecord& r : o->ring)
-        if (r.valid && e == hipSuccess) e = hipEventSynchronize(r.done[r.n_stages - 1]);
-    return e;
-}
-
 int32_t dc_overlap_destroy(void* overlap) {
     if (!overlap) return DC_ERR_NULL_PTR;
     Overlap* o = static_cast<Overlap*>(overlap);
     (void)drain(o);
     for (StackPlan* p : o->plans) release_plan(p);
-    for (int i = 0; i < 2; ++i) {
-        if (o->upload_done[i]) (void)hipEventDestroy(o->upload_done[i]);
-        if (o->work[i]) (void)hipStreamDestroy(o->work[i]);
-    }
+    for (hipEvent_t e : o->upload_done)
+        if (e) (void)hipEventDestroy(e);
     for (FrameRecord& r : o->ring)
         for (hipEvent_t e : r.done)
             if (e) (void)hipEventDestroy(e);
     if (o->match_done) (void)hipEventDestroy(o->match_done);
     if (o->plan_done) (void)hipEventDestroy(o->plan_done);
-    if (o->aux) (void)hipStreamDestroy(o->aux);
+    release_stage_streams(o);
     delete o;
     return DC_OK;
 }
