@@ -185,6 +185,8 @@ int concat_inputs(const dc_layer& l, int* ids);
 //   plan_masks_kernel    per conv layer, stream and 256 units: the 16-bit mask of reusable pixels of every 4x4 unit
 //   plan_lists_kernel    compacts the units with a non-reusable pixel into the layer's list (stream-major, raster
 //                        order: the order of the host path) and leaves the list lengths and the work counters
+// With exact reuse maps two: plan_erode_kernel (bitmaps of every tensor, and the counts of units), plan_lists_kernel
+// (which cuts the unit masks out of the bitmaps).
 // The convolutions are then launched for the longest possible list and read its length from memory; the reusable
 // pixels are copied per unit from the masks (shifted_copy_units_kernel).
 constexpr int kPlanMaxTensors = 192;     // tensors of a stack the device tables hold
@@ -198,8 +200,27 @@ struct PlanTensorDev { int32_t h, w, cum_stride, bm_off; };   // bm_off: first w
 struct PlanConvDev {                     // one conv layer's share of the plan area (offsets in bytes from its start)
     int32_t tensor, Hout, Wout, units_x, units_y, n_chunks;
     int32_t no_reuse;                    // 1: this layer is computed in full on every frame (its unit masks are all zero)
-    int32_t pad1;
-    int64_t umask_off, count_off, list_off, pad2;
+    int32_t chunk_base;                  // chunks of the conv layers before this one
+    int64_t umask_off, count_off, list_off;
+    int32_t bm_off, pad;                 // first word of the output tensor's bitmap
+};
+// One step of the exact reuse maps: a tensor's bitmap from earlier ones.  Layers that leave the map as it is (1x1 / stride 1
+// convolutions, activations, LRN over channels) have none: their tensors share the producer's bitmap.  The steps are
+// sorted by depth, so that those of one depth (the branches of an inception module) run without a barrier in between.
+enum { kPlanOpZero = 0, kPlanOpAnd2 = 1, kPlanOpAnd = 2,          // AND of two, of three or four
+       kPlanOp3x3 = 3, kPlanOp2x2 = 4,                            // windows 3x3 / stride 1 and 2x2 / stride 2 without dilation,
+       kPlanOpStride1 = 5, kPlanOpStride2 = 6, kPlanOpStride8 = 7,   // others of up to 32 columns with strides 1, 2, 3 .. 8,
+       kPlanOpSlow = 8 };                                         // and the rest
+struct PlanOpDev {
+    int32_t kind, run_end;               // run_end > 0: a small step; the first step after the run of small ones that it belongs to
+    int32_t src0, dst, words;            // first words of the producer's and of the tensor's bitmap; h * words per row
+    int32_t wpr;                         // words per row
+    uint32_t wpr_magic;                  // ceil(2^32 / wpr)
+    int32_t depth_end;                   // 1: the last step of a depth
+    int32_t row_lo, row_hi, col_lo, col_hi;   // pixels whose source lies inside the map (the stream's motion: set in the kernel)
+    int32_t h_in, w_in, wpr_in, src[3];  // further producers' bitmaps (unused: -1)
+    int32_t kh, kw, s, ph, pw, dil;
+    int32_t h, w, cum_stride, pad;
 };
 // What the list kernel leaves for the host, per frame: {reusable blocks, overflowed streams, 0, 0}, then per conv
 // layer {reused pixels (int64), list length (int32), 0}.
@@ -209,7 +230,10 @@ struct PlanDev {                         // device addresses of one frame's plan
     const PlanLayerDev* layers;
     const PlanTensorDev* tensors;
     const PlanConvDev* convs;
+    const PlanOpDev* ops;                // exact reuse maps
     int32_t n_layers, n_convs, n_streams, cap;
+    int32_t n_ops, n_chunks;             // n_chunks: of all conv layers together (per stream)
+    int32_t want_umasks;                 // 0: nothing is copied from the previous frame, the unit masks are not needed
     dc_rect* rects;                      // [stream][tensor][cap]
     int32_t* nrect;                      // [stream][tensor]
     int32_t* dxy;                        // [stream][tensor][2]
@@ -233,8 +257,8 @@ __host__ __device__ inline int torus_wrap(int v, int o, int n) { const int p = v
 hipError_t launch_plan(const PlanDev& P, const uint8_t* block_mask, const int32_t* gmv, int gh, int gw, int block,
                        int extend_borders, int max_chunks, hipStream_t st);
 // The same with exact reuse maps instead of rectangles: plan_erode_kernel (one workgroup per stream) derives every
-// tensor's bitmap from its producers' (a pixel is reusable iff every tap of its window is), then the unit masks are
-// cut out of the bitmaps and listed as above.  with_lists = false stops after the bitmaps.
+// tensor's bitmap from its producers' (a pixel is reusable iff every tap of its window is) and counts the dirty units,
+// then the unit masks are cut out of the bitmaps and listed.  with_lists = false stops after the bitmaps.
 hipError_t launch_plan_exact(const PlanDev& P, const uint8_t* block_mask, const int32_t* gmv, int gh, int gw, int block,
                              int extend_borders, int max_chunks, bool with_lists, hipStream_t st);
 // The same for one conv layer whose rectangles come from the host and are small enough to travel as kernel arguments

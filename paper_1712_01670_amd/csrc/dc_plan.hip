@@ -12,6 +12,7 @@
 //   every tensor has one source offset round(M / cumulative stride); rectangles are clipped so that the source
 //   stays inside the map
 #include <atomic>
+#include <cstddef>
 
 #include "dc_internal.h"
 
@@ -316,19 +317,8 @@ __device__ __forceinline__ unsigned inside_mask(int Hout, int Wout, int ty, int 
 
 // ---- exact reuse maps -------------------------------------------------------------------------------------
 constexpr int kErodeThreads = 1024;
-constexpr int kErodeLdsWords = 32 * 1024;      // bitmaps of one stream up to this size (128 KB) stay in LDS
+constexpr int kErodeLdsWords = 38 * 1024;      // bitmaps and counters of one stream up to this size (152 KB) stay in LDS
 
-// word i of a bitmap row of w pixels; words outside the row, and bits beyond w, read as `outside`;
-// row == nullptr: the whole row lies outside the map
-__device__ __forceinline__ unsigned row_word(const uint32_t* row, int wpr, int w, int i, bool outside) {
-    unsigned x = outside ? ~0u : 0u;
-    if (row && i >= 0 && i < wpr) {
-        x = row[i];
-        const int valid = w - 32 * i;                      // bits of this word that lie inside the row
-        if (outside && valid < 32) x |= ~0u << valid;
-    }
-    return x;
-}
 // even bits of x packed into the low half
 __device__ __forceinline__ unsigned even_bits(unsigned long long x) {
     x &= 0x5555555555555555ull;
@@ -347,22 +337,254 @@ __device__ __forceinline__ unsigned column_range(int x0, int lo, int hi) {
     return upto_b & ~((1u << a) - 1u);
 }
 
-// The maps of one stream, tensor after tensor (a barrier in between: a layer reads the bitmaps of earlier tensors).
-// Every thread computes whole 32-pixel words of the output bitmap:
-//   windowed layers (conv, pooling, LRN over pixels)  AND over the k x k window, word-parallel for strides 1 and 2
-//     (the k shifted copies of an input row are ANDed, for stride 2 every second bit is kept), bit by bit otherwise;
-//     taps outside the map read 0, or 1 for a stream that did not move when the border case is on;
-//   add / concat  AND of the inputs;   FC / softmax  nothing;   others  a copy;
-// and every tensor is cut to the pixels whose source at +(dx, dy) lies inside the map.
-// `maps` is the stream's bitmap area: LDS when it fits (a layer is a few LDS round trips then, not a few trips to
-// the L2), the workspace otherwise.
-__device__ __forceinline__ void erode_stream(uint32_t* maps, const PlanLayerDev* s_layers, const PlanTensorDev* s_tensors,
-                                             int n_layers, int32_t* dxy, const uint8_t* m, int gh, int gw, int B, int mx, int my,
-                                             bool ext, int tid) {
+// One 32-pixel word (row y, first column x0) of a windowed layer's map: bit b is set iff every tap of the window of
+// output column x0 + b is.  The rows of the window are ANDed word by word first, then the columns of the result: a run of
+// kw set taps by doubling (2, 4, 8, ... and the rest), once per word and not once per kernel row.  Stride s needs the
+// window starts of 32 s input columns: s pieces of 32, of which every s-th bit is kept.  KH, KW, S > 0: compile-time sizes
+// without dilation (0: the step's own).  EXT (a stream that did not move, border case on): taps in the padding are
+// ignored, they read as set; otherwise they read as not set.
+template <bool EXT, int KH, int KW, int S>
+__device__ __forceinline__ unsigned window_word(const uint32_t* in, const PlanOpDev& op, int y, int x0) {
+    const int kh = KH ? KH : op.kh, kw = KW ? KW : op.kw, s = S ? S : op.s, dil = KH ? 1 : op.dil;     // (S = 0: strides up to 8)
+    const int c0 = x0 * s - op.pw, w0 = c0 >> 5, sh = c0 & 31;          // arithmetic shift: floor for negative starts
+    constexpr int kMaxS = S ? S : 8;
+    unsigned v[kMaxS + 2];
+#pragma unroll
+    for (int j = 0; j < kMaxS + 2; ++j) v[j] = ~0u;
+    const unsigned tail = (op.w_in & 31) ? ~0u << (op.w_in & 31) : 0u;      // bits of a row's last word beyond the map
+#pragma unroll
+    for (int ky = 0; ky < kh; ++ky) {
+        const int iy = y * s - op.ph + ky * dil;
+        const bool row_in = (unsigned)iy < (unsigned)op.h_in;
+        const uint32_t* row = in + iy * op.wpr_in;
+#pragma unroll
+        for (int j = 0; j < kMaxS + 2; ++j) {
+            if (!S && j >= s + 2) continue;
+            const int i = w0 + j;
+            unsigned x = EXT ? ~0u : 0u;
+            if (row_in && (unsigned)i < (unsigned)op.wpr_in) {
+                x = row[i];
+                if (EXT && i == op.wpr_in - 1) x |= tail;
+            }
+            v[j] &= x;
+        }
+    }
+    unsigned bits = 0;
+    unsigned long long pair = 0;
+#pragma unroll
+    for (int j = 0; j < kMaxS; ++j) {
+        if (!S && j >= s) continue;
+        const unsigned long long a = ((unsigned long long)v[j + 1] << 32) | v[j];
+        unsigned long long r = sh ? (a >> sh) | ((unsigned long long)v[j + 2] << (64 - sh)) : a;     // 64 columns from c0 + 32 j
+        int len = 1;
+#pragma unroll
+        for (int d = 0; d < 5; ++d)
+            if (2 * len <= kw) { r &= r >> (len * dil); len *= 2; }
+        if (len < kw) r &= r >> ((kw - len) * dil);
+        const unsigned start = (unsigned)r;                     // bit i: a whole run starts at column c0 + 32 j + i
+        if (s == 1) bits = start;
+        else if (S == 2 || s == 2) {
+            if (j == 0) pair = start;
+            else bits = even_bits(pair | (unsigned long long)start << 32);
+        } else {
+            for (int b = (32 * j + s - 1) / s; b * s < 32 * (j + 1) && b < 32; ++b) bits |= ((start >> (b * s - 32 * j)) & 1u) << b;
+        }
+    }
+    return bits;
+}
+// The same bit by bit, for windows that the words above cannot hold (strides beyond 8, spans beyond 32 columns).
+template <bool EXT>
+__device__ __forceinline__ unsigned window_word_slow(const uint32_t* in, const PlanOpDev& op, int y, int x0) {
+    unsigned bits = 0;
+    for (int b = 0; b < 32 && x0 + b < op.w; ++b) {
+        bool ok = true;
+        for (int ky = 0; ky < op.kh && ok; ++ky)
+            for (int kx = 0; kx < op.kw && ok; ++kx) {
+                const int iy = y * op.s - op.ph + ky * op.dil, ix = (x0 + b) * op.s - op.pw + kx * op.dil;
+                if (iy < 0 || iy >= op.h_in || ix < 0 || ix >= op.w_in) { ok = EXT; continue; }
+                ok = (in[iy * op.wpr_in + (ix >> 5)] >> (ix & 31)) & 1u;
+            }
+        if (ok) bits |= 1u << b;
+    }
+    return bits;
+}
+
+// Records of a table in LDS, read by whole wavefronts: lane l fetches dword l, the fields then go to scalar registers.
+template <typename T>
+__device__ __forceinline__ int table_dword(const int* table, int j, int n) {
+    constexpr int kDwords = (int)sizeof(T) / 4;
+    static_assert(kDwords <= 64, "a record per wavefront load");
+    const int lane = threadIdx.x & 63;
+    return j < n && lane < kDwords ? table[j * kDwords + lane] : 0;
+}
+template <typename T>
+__device__ __forceinline__ T table_entry(int dword) {
+    constexpr int kDwords = (int)sizeof(T) / 4;
+    union { T entry; int d[kDwords]; } u;
+#pragma unroll
+    for (int i = 0; i < kDwords; ++i) u.d[i] = __builtin_amdgcn_readlane(dword, i);
+    return u.entry;
+}
+
+// The maps of one stream, step after step: a step reads the bitmaps of earlier depths, every thread computes whole 32-pixel
+// words, and every tensor is cut to the pixels whose source at +(dx, dy) lies inside the map.  The steps are one serial
+// chain, so what counts is their number (layers that change nothing have none, the branches of a module share a barrier)
+// and the latency of one:
+//  - its record comes from LDS, fetched while the step before runs (a scalar load from memory took 0.8 us);
+//  - everything that does not depend on the word is in the record (with the window's sizes known only at run time and
+//    the offsets rounded in the loop, a step took 1.9 us however small: every wavefront works through the preamble);
+//  - small steps (two words per lane at most) are left to one wavefront, without a barrier, while the others wait.
+// `maps` is the stream's bitmap area: LDS when it fits, the workspace otherwise.
+// 224x224, one stream, the whole kernel: VGG-16 55 -> 22 us, ResNet-50 trunk 137 -> 32, GoogLeNet 190 -> 40.
+template <bool EXT, bool IN_LDS>
+__device__ __forceinline__ void erode_stream(uint32_t* maps, const int* ops, int n_ops, int tid) {
+    constexpr int kDwords = (int)sizeof(PlanOpDev) / 4;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    auto fetch = [&](int j) { return j < n_ops && lane < kDwords ? ops[j * kDwords + lane] : 0; };
+    auto step = [&](int rec, int first, int stride) {
+        auto field = [&](size_t byte) { return __builtin_amdgcn_readlane(rec, (int)byte / 4); };
+#define DC_OP(name) field(offsetof(PlanOpDev, name))
+        const int kind = DC_OP(kind), words = DC_OP(words), wpr = DC_OP(wpr), dst = DC_OP(dst);
+        const uint32_t magic = (uint32_t)DC_OP(wpr_magic);
+        const int row_lo = DC_OP(row_lo), row_hi = DC_OP(row_hi), col_lo = DC_OP(col_lo), col_hi = DC_OP(col_hi);
+        const uint32_t* in = maps + DC_OP(src0);
+        auto each = [&](auto word) {
+            for (int i = first; i < words; i += stride) {
+                const int y = wpr == 1 ? i : (int)__umulhi((uint32_t)i, magic), x0 = (i - y * wpr) * 32;
+                const unsigned bits = word(i, y, x0);
+                maps[dst + i] = y >= row_lo && y < row_hi ? bits & column_range(x0, col_lo, col_hi) : 0u;
+            }
+        };
+        if (kind == kPlanOpZero) {
+            each([](int, int, int) { return 0u; });
+        } else if (kind <= kPlanOpAnd) {
+            const int b = DC_OP(src[0]), c = DC_OP(src[1]), d = DC_OP(src[2]);
+            if (kind == kPlanOpAnd2) each([&](int i, int, int) { return in[i] & maps[b + i]; });
+            else each([&](int i, int, int) { return in[i] & maps[b + i] & maps[c + i] & (d >= 0 ? maps[d + i] : ~0u); });
+        } else {
+            PlanOpDev op;      // the fields of a window
+            op.h_in = DC_OP(h_in); op.w_in = DC_OP(w_in); op.wpr_in = DC_OP(wpr_in); op.ph = DC_OP(ph); op.pw = DC_OP(pw);
+            if (kind == kPlanOp3x3) {
+                each([&](int, int y, int x0) { return window_word<EXT, 3, 3, 1>(in, op, y, x0); });
+            } else if (kind == kPlanOp2x2) {
+                each([&](int, int y, int x0) { return window_word<EXT, 2, 2, 2>(in, op, y, x0); });
+            } else {
+                op.kh = DC_OP(kh); op.kw = DC_OP(kw); op.s = DC_OP(s); op.dil = DC_OP(dil); op.w = DC_OP(w);
+                if (kind == kPlanOpStride1) each([&](int, int y, int x0) { return window_word<EXT, 0, 0, 1>(in, op, y, x0); });
+                else if (kind == kPlanOpStride2) each([&](int, int y, int x0) { return window_word<EXT, 0, 0, 2>(in, op, y, x0); });
+                else if (kind == kPlanOpStride8) each([&](int, int y, int x0) { return window_word<EXT, 0, 0, 0>(in, op, y, x0); });
+                else each([&](int, int y, int x0) { return window_word_slow<EXT>(in, op, y, x0); });
+            }
+        }
+    };
+    int base = 0;                 // threads taken by the earlier steps of this depth: the next one starts behind them
+    int rec = fetch(0);
+    for (int j = 0; j < n_ops;) {
+        const int run_end = __builtin_amdgcn_readlane(rec, (int)offsetof(PlanOpDev, run_end) / 4);
+        if (IN_LDS && run_end > 0) {
+            if (wave == 0) {
+                for (int i = j; i < run_end; ++i) {
+                    const int next = fetch(i + 1);
+                    step(rec, lane, 64);
+                    __builtin_amdgcn_wave_barrier();      // (LDS operations of a wavefront stay in order)
+                    rec = next;
+                }
+            } else {
+                rec = fetch(run_end);
+            }
+            j = run_end;
+            __syncthreads();
+            continue;
+        }
+        const int next = fetch(j + 1);
+        int first = tid - base;
+        if (first < 0) first += kErodeThreads;
+        step(rec, first, kErodeThreads);
+        base = (base + __builtin_amdgcn_readlane(rec, (int)offsetof(PlanOpDev, words) / 4)) & (kErodeThreads - 1);
+        if (__builtin_amdgcn_readlane(rec, (int)offsetof(PlanOpDev, depth_end) / 4) ) {
+            base = 0;
+            __syncthreads();
+        }
+        rec = next;
+        ++j;
+    }
+#undef DC_OP
+}
+
+// One workgroup per stream.  IN_LDS: the stream's bitmaps are built in dynamic LDS (bm_words words) and written to
+// the workspace in one pass at the end.  With lists, the dirty units and the reused pixels of every chunk of 256 units are
+// counted here as well, eight units of a word at a time.
+constexpr int kErodeMask = 4096;                // block mask bytes kept in LDS
+template <bool IN_LDS>
+__global__ __launch_bounds__(kErodeThreads) void plan_erode_kernel(PlanDev P, const uint8_t* __restrict__ block_mask,
+                                                                   const int32_t* __restrict__ gmv, int gh, int gw, int B, int ext_opt, int with_lists) {
+    const int stream = blockIdx.x, tid = threadIdx.x;
+    const int nt = P.n_layers + 1;
+    __shared__ int s_cnt[kErodeThreads / 64];
+    __shared__ uint8_t s_mask[kErodeMask];
+    extern __shared__ uint32_t s_dyn_words[];      // [steps][conv layers][counters][bitmaps]
+    // counters of this stream, [chunk of every conv layer]{dirty units, reused pixels}: in LDS with the bitmaps, or where
+    // they end up (a frame so large that its bitmaps do not fit)
+    constexpr int kOpDwords = (int)sizeof(PlanOpDev) / 4, kConvDwords = (int)sizeof(PlanConvDev) / 4;
+    int* const ops = reinterpret_cast<int*>(s_dyn_words);
+    int* const convs = ops + P.n_ops * kOpDwords;
+    int* const counts = convs + P.n_convs * kConvDwords;
+    auto counters = [&](const PlanConvDev& cv) {
+        return IN_LDS ? counts + 2 * cv.chunk_base
+                      : reinterpret_cast<int*>(P.area + cv.count_off) + (size_t)stream * cv.n_chunks * 2;
+    };
+    uint32_t* const g_maps = P.bitmaps + (size_t)stream * P.bm_words;
+    uint32_t* const maps = IN_LDS ? reinterpret_cast<uint32_t*>(counts) + (with_lists ? 2 * P.n_chunks : 0) : g_maps;
+    for (int j = tid; j < P.n_ops * kOpDwords; j += kErodeThreads) ops[j] = reinterpret_cast<const int*>(P.ops)[j];
+    for (int j = tid; j < P.n_convs * kConvDwords; j += kErodeThreads) convs[j] = reinterpret_cast<const int*>(P.convs)[j];
+    const int mx = gmv[2 * stream], my = gmv[2 * stream + 1];
+    const bool ext = ext_opt != 0 && mx == 0 && my == 0;
+    int32_t* const dxy = P.dxy + (size_t)stream * nt * 2;
+    const uint8_t* m = block_mask + (size_t)stream * gh * gw;
+    const bool mask_in_lds = gh * gw <= kErodeMask;
+    {   // the stream's number of reusable blocks
+        int reusable = 0;
+        for (int j = tid; j < gh * gw; j += kErodeThreads) {
+            const uint8_t v = m[j];
+            reusable += v ? 1 : 0;
+            if (mask_in_lds) s_mask[j] = v;
+        }
+        for (int off = 32; off > 0; off >>= 1) reusable += __shfl_xor(reusable, off);
+        if ((tid & 63) == 0) s_cnt[tid >> 6] = reusable;
+        if (with_lists && IN_LDS)
+            for (int j = tid; j < 2 * P.n_chunks; j += kErodeThreads) counts[j] = 0;
+        if (with_lists && !IN_LDS)
+            for (int c = 0; c < P.n_convs; ++c) {
+                const PlanConvDev cv = P.convs[c];
+                int* cnt = counters(cv);
+                for (int j = tid; j < 2 * cv.n_chunks; j += kErodeThreads) cnt[j] = 0;
+            }
+    }
+    // offsets, (empty) rectangle lists and origins of every tensor
+    for (int t = tid; t < nt; t += kErodeThreads) {
+        const PlanTensorDev tt = P.tensors[t];
+        const int dx = round_half_away(mx, tt.cum_stride), dy = round_half_away(my, tt.cum_stride);
+        dxy[2 * t] = dx; dxy[2 * t + 1] = dy;
+        P.nrect[(size_t)stream * nt + t] = 0;
+        if (P.origin) write_origin(P, stream, nt, t, torus_tensor(P, t, t > 0 ? P.layers[t - 1].type : -1), dx, dy, tt.w, tt.h);
+    }
+    __syncthreads();
+    if (tid == 0) {
+        int total = 0;
+        for (int j = 0; j < kErodeThreads / 64; ++j) total += s_cnt[j];
+        P.stream_info[2 * stream] = total; P.stream_info[2 * stream + 1] = 0;
+    }
+    // every step's pixels whose source lies inside the map
+    for (int j = tid; j < P.n_ops; j += kErodeThreads) {
+        PlanOpDev& op = reinterpret_cast<PlanOpDev*>(ops)[j];
+        const int dx = round_half_away(mx, op.cum_stride), dy = round_half_away(my, op.cum_stride);
+        op.row_lo = dy < 0 ? -dy : 0; op.row_hi = dy > 0 ? op.h - dy : op.h;
+        op.col_lo = dx < 0 ? -dx : 0; op.col_hi = dx > 0 ? op.w - dx : op.w;
+    }
     {   // tensor 0: the pixels of the blocks that passed Step 4
-        const PlanTensorDev t0 = s_tensors[0];
+        const PlanTensorDev t0 = P.tensors[0];
         const int wpr = (t0.w + 31) >> 5;
-        const int col_lo = -mx < 0 ? 0 : -mx, col_hi = t0.w - mx < t0.w ? t0.w - mx : t0.w;
+        const int col_lo = mx < 0 ? -mx : 0, col_hi = mx > 0 ? t0.w - mx : t0.w;
         for (int i = tid; i < t0.h * wpr; i += kErodeThreads) {
             const int y = i / wpr, x0 = (i - y * wpr) * 32;
             const int by = y / B;
@@ -370,195 +592,54 @@ __device__ __forceinline__ void erode_stream(uint32_t* maps, const PlanLayerDev*
             if (by < gh && y + my >= 0 && y + my < t0.h) {
                 const int bx_hi = (x0 + 31) / B < gw - 1 ? (x0 + 31) / B : gw - 1;
                 for (int bx = x0 / B; bx <= bx_hi; ++bx)
-                    if (m[by * gw + bx]) bits |= column_range(x0, bx * B, bx * B + B);
+                    if (mask_in_lds ? s_mask[by * gw + bx] : m[by * gw + bx]) bits |= column_range(x0, bx * B, bx * B + B);
             }
             maps[t0.bm_off + i] = bits & column_range(x0, col_lo, col_hi);
         }
     }
     __syncthreads();
-    for (int li = 0; li < n_layers; ++li) {
-        const PlanLayerDev L = s_layers[li];
-        const PlanTensorDev ta = s_tensors[L.in0], tt = s_tensors[li + 1];
-        const int dx = round_half_away(mx, tt.cum_stride), dy = round_half_away(my, tt.cum_stride);
-        if (tid == 0) { dxy[2 * (li + 1)] = dx; dxy[2 * (li + 1) + 1] = dy; }
-        const uint32_t* in = maps + ta.bm_off;
-        uint32_t* out = maps + tt.bm_off;
-        const int wpr_in = (ta.w + 31) >> 5, wpr = (tt.w + 31) >> 5;
-        const bool windowed = L.type == DC_CONV || L.type == DC_MAXPOOL || L.type == DC_AVGPOOL;
-        const bool lrn_px = L.type == DC_LRN && L.within != 0;
-        // taps of the window: kh x kw, dil pixels apart, paddings ph / pw
-        const int kh = (windowed || lrn_px) ? L.k : 1, kw = windowed ? L.kw : (lrn_px ? L.k : 1), dil = windowed ? L.dil : 1;
-        const int s = windowed ? L.s : 1;
-        const int ph = windowed ? L.p : (lrn_px ? (L.k - 1) / 2 : 0), pw = windowed ? L.pw : (lrn_px ? (L.k - 1) / 2 : 0);
-        const int ew = (kw - 1) * dil + 1;
-        const int col_lo = -dx < 0 ? 0 : -dx, col_hi = tt.w - dx < tt.w ? tt.w - dx : tt.w;
-        for (int i = tid; i < tt.h * wpr; i += kErodeThreads) {
-            const int y = i / wpr, x0 = (i - y * wpr) * 32;
-            unsigned bits;
-            if (L.type == DC_FC || L.type == DC_SOFTMAX) {
-                bits = 0;
-            } else if (L.type == DC_ADD) {
-                bits = in[i] & maps[s_tensors[L.in1].bm_off + i];
-            } else if (L.type == DC_CONCAT) {
-                bits = in[i] & maps[s_tensors[L.in1].bm_off + i];
-                if (L.in2 >= 0) bits &= maps[s_tensors[L.in2].bm_off + i];
-                if (L.in2 >= 0 && L.in3 >= 0) bits &= maps[s_tensors[L.in3].bm_off + i];
-            } else if (kh == 1 && kw == 1 && s == 1 && ph == 0 && pw == 0) {
-                bits = in[i];
-            } else if (s <= 2 && ew <= 32) {
-                // bit b of acc: the whole window that starts at input column c0 + b.  Stride 1 needs 32 + k - 1 input
-                // columns from c0 (three words), stride 2 needs 64 + k - 1 (four).
-                unsigned long long acc = ~0ull;
-                const int c0 = x0 * s - pw;
-                const int w0 = c0 >> 5, sh = c0 & 31;           // arithmetic shift: floor for negative starts
-                for (int ky = 0; ky < kh; ++ky) {
-                    const int iy = y * s - ph + ky * dil;
-                    const bool row_in = iy >= 0 && iy < ta.h;
-                    if (!row_in && ext) continue;               // taps in the padding are ignored
-                    const uint32_t* row = row_in ? in + (size_t)iy * wpr_in : nullptr;
-                    const unsigned v0 = row_word(row, wpr_in, ta.w, w0, ext), v1 = row_word(row, wpr_in, ta.w, w0 + 1, ext);
-                    const unsigned v2 = row_word(row, wpr_in, ta.w, w0 + 2, ext);
-                    const unsigned v3 = s == 2 ? row_word(row, wpr_in, ta.w, w0 + 3, ext) : 0u;
-                    const unsigned long long a = ((unsigned long long)v1 << 32) | v0, b = ((unsigned long long)v3 << 32) | v2;
-                    const unsigned long long lo = sh ? (a >> sh) | (b << (64 - sh)) : a;    // columns c0 .. c0 + 63
-                    const unsigned long long hi = b >> sh;                                  // columns c0 + 64 .. (at least 33 of them)
-                    unsigned long long r = lo;
-                    for (int kx = 1; kx < kw; ++kx) r &= (lo >> (kx * dil)) | (hi << (64 - kx * dil));
-                    acc &= r;
-                }
-                bits = s == 1 ? (unsigned)acc : even_bits(acc);
-            } else if (s <= 8 && ew <= 32) {
-                // larger strides: the same AND of shifted rows for all 32 s start columns of the word (up to four
-                // 64-column pieces), then every s-th bit is kept
-                unsigned long long acc[4] = {~0ull, ~0ull, ~0ull, ~0ull};
-                const int c0 = x0 * s - pw;
-                const int pieces = (32 * s + 63) >> 6;
-                for (int ky = 0; ky < kh; ++ky) {
-                    const int iy = y * s - ph + ky * dil;
-                    const bool row_in = iy >= 0 && iy < ta.h;
-                    if (!row_in && ext) continue;
-                    const uint32_t* row = row_in ? in + (size_t)iy * wpr_in : nullptr;
+    if (ext) erode_stream<true, IN_LDS>(maps, ops, P.n_ops, tid);
+    else erode_stream<false, IN_LDS>(maps, ops, P.n_ops, tid);
+    if (IN_LDS)
+        for (int64_t j = tid; j < P.bm_words; j += kErodeThreads) g_maps[j] = maps[j];
+    if (!with_lists) return;
+    for (int c = tid >> 6; c < P.n_convs; c += kErodeThreads / 64) {      // a wavefront per conv layer
+        const PlanConvDev cv = table_entry<PlanConvDev>(table_dword<PlanConvDev>(convs, c, P.n_convs));
+        const int wpr = (cv.Wout + 31) >> 5;
+        const uint32_t* map = maps + cv.bm_off;
+        int* const conv_counts = counters(cv);
+        for (int i = tid & 63; i < cv.units_y * wpr; i += 64) {
+            const int ty = i / wpr, wc = i - ty * wpr;
+            const int valid = cv.Wout - 32 * wc;                       // columns of this word inside the map
+            const unsigned in_row = valid >= 32 ? ~0u : (1u << valid) - 1u;
+            unsigned whole = ~0u, px[4];
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        if (j >= pieces) continue;
-                        const int c = c0 + 64 * j, w0 = c >> 5, sh = c & 31;
-                        unsigned v[5];
-#pragma unroll
-                        for (int q = 0; q < 5; ++q) v[q] = row_word(row, wpr_in, ta.w, w0 + q, ext);
-                        const unsigned long long a = ((unsigned long long)v[1] << 32) | v[0], b = ((unsigned long long)v[3] << 32) | v[2];
-                        const unsigned long long lo = sh ? (a >> sh) | (b << (64 - sh)) : a;
-                        const unsigned long long hi = sh ? (b >> sh) | ((unsigned long long)v[4] << (64 - sh)) : b;
-                        unsigned long long r = lo;
-                        for (int kx = 1; kx < kw; ++kx) r &= (lo >> (kx * dil)) | (hi << (64 - kx * dil));
-                        acc[j] &= r;
-                    }
-                }
-                bits = 0;
-                for (int b = 0; b < 32; ++b) {
-                    const int at = b * s, piece = at >> 6;
-                    const unsigned long long word = piece == 0 ? acc[0] : (piece == 1 ? acc[1] : (piece == 2 ? acc[2] : acc[3]));
-                    bits |= (unsigned)((word >> (at & 63)) & 1ull) << b;
-                }
-            } else {                                        // anything else: bit by bit
-                bits = 0;
-                for (int b = 0; b < 32 && x0 + b < tt.w; ++b) {
-                    bool ok = true;
-                    for (int ky = 0; ky < kh && ok; ++ky)
-                        for (int kx = 0; kx < kw && ok; ++kx) {
-                            const int iy = y * s - ph + ky * dil, ix = (x0 + b) * s - pw + kx * dil;
-                            if (iy < 0 || iy >= ta.h || ix < 0 || ix >= ta.w) { ok = ext; continue; }
-                            ok = (in[(size_t)iy * wpr_in + (ix >> 5)] >> (ix & 31)) & 1u;
-                        }
-                    if (ok) bits |= 1u << b;
-                }
+            for (int r = 0; r < 4; ++r) {
+                px[r] = ty * 4 + r < cv.Hout && !cv.no_reuse ? map[(ty * 4 + r) * wpr + wc] : 0u;
+                if (ty * 4 + r < cv.Hout) whole &= px[r] | ~in_row;
             }
-            const bool row_ok = y + dy >= 0 && y + dy < tt.h;
-            out[i] = row_ok ? (bits & column_range(x0, col_lo, col_hi)) : 0u;
+            // bit 4 u: every pixel of the word's unit u that lies inside the map is reusable
+            const unsigned clean = whole & (whole >> 1) & (whole >> 2) & (whole >> 3) & 0x11111111u;
+            const int n_u = cv.units_x - 8 * wc < 8 ? cv.units_x - 8 * wc : 8;
+            const int u0 = ty * cv.units_x + 8 * wc, cut = kPlanChunk - (u0 & (kPlanChunk - 1));     // units before the next chunk
+            for (int part = 0; part < 2; ++part) {
+                const int from = part ? cut : 0, to = part ? n_u : (n_u < cut ? n_u : cut);
+                if (from >= to) continue;
+                const unsigned sel = (to >= 8 ? ~0u : (1u << (4 * to)) - 1u) & ~((1u << (4 * from)) - 1u);
+                const int dirty = __popc(~clean & 0x11111111u & sel);
+                const int reused = __popc(px[0] & sel) + __popc(px[1] & sel) + __popc(px[2] & sel) + __popc(px[3] & sel);
+                int* cnt = conv_counts + 2 * ((u0 + from) / kPlanChunk);
+                if (dirty) atomicAdd(cnt, dirty);
+                if (reused) atomicAdd(cnt + 1, reused);
+            }
         }
-        __syncthreads();
     }
-}
-
-// One workgroup per stream.  IN_LDS: the stream's bitmaps are built in dynamic LDS (bm_words words) and written to
-// the workspace in one pass at the end.
-template <bool IN_LDS>
-__global__ __launch_bounds__(kErodeThreads) void plan_erode_kernel(PlanDev P, const uint8_t* __restrict__ block_mask,
-                                                                   const int32_t* __restrict__ gmv, int gh, int gw, int B, int ext_opt) {
-    const int stream = blockIdx.x, tid = threadIdx.x;
-    const int nt = P.n_layers + 1;
-    __shared__ PlanLayerDev s_layers[kPlanMaxTensors];
-    __shared__ PlanTensorDev s_tensors[kPlanMaxTensors];
-    __shared__ int s_cnt[kErodeThreads / 64];
-    extern __shared__ uint32_t s_maps[];
-    {
-        const uint4* src = reinterpret_cast<const uint4*>(P.layers);
-        uint4* dst = reinterpret_cast<uint4*>(s_layers);
-        for (int j = tid; j < P.n_layers * 3; j += kErodeThreads) dst[j] = src[j];
-        const uint4* tsrc = reinterpret_cast<const uint4*>(P.tensors);
-        uint4* tdst = reinterpret_cast<uint4*>(s_tensors);
-        for (int j = tid; j < nt; j += kErodeThreads) tdst[j] = tsrc[j];
-    }
-    const int mx = gmv[2 * stream], my = gmv[2 * stream + 1];
-    const bool ext = ext_opt != 0 && mx == 0 && my == 0;
-    uint32_t* const g_maps = P.bitmaps + (size_t)stream * P.bm_words;
-    int32_t* const dxy = P.dxy + (size_t)stream * nt * 2;
-    const uint8_t* m = block_mask + (size_t)stream * gh * gw;
-    {   // the stream's number of reusable blocks
-        int reusable = 0;
-        for (int j = tid; j < gh * gw; j += kErodeThreads) reusable += m[j] ? 1 : 0;
-        for (int off = 32; off > 0; off >>= 1) reusable += __shfl_xor(reusable, off);
-        if ((tid & 63) == 0) s_cnt[tid >> 6] = reusable;
-    }
+    if (!IN_LDS) return;
     __syncthreads();
-    if (tid == 0) {
-        int total = 0;
-        for (int j = 0; j < kErodeThreads / 64; ++j) total += s_cnt[j];
-        P.stream_info[2 * stream] = total; P.stream_info[2 * stream + 1] = 0; dxy[0] = mx; dxy[1] = my;
-    }
-    if (IN_LDS) {
-        erode_stream(s_maps, s_layers, s_tensors, P.n_layers, dxy, m, gh, gw, B, mx, my, ext, tid);
-        for (int64_t j = tid; j < P.bm_words; j += kErodeThreads) g_maps[j] = s_maps[j];
-    } else {
-        erode_stream(g_maps, s_layers, s_tensors, P.n_layers, dxy, m, gh, gw, B, mx, my, ext, tid);
-    }
-    for (int t = tid; t < nt; t += kErodeThreads) P.nrect[(size_t)stream * nt + t] = 0;      // no rectangles in this mode
-    if (P.origin) {
-        __syncthreads();          // the offsets of all tensors are written
-        for (int t = tid; t < nt; t += kErodeThreads)
-            write_origin(P, stream, nt, t, torus_tensor(P, t, t > 0 ? s_layers[t - 1].type : -1), dxy[2 * t], dxy[2 * t + 1], s_tensors[t].w, s_tensors[t].h);
-    }
-}
-
-// The 16-bit unit masks of every conv layer cut out of the bitmaps (grid and outputs as plan_masks_kernel).
-__global__ __launch_bounds__(kPlanChunk) void plan_masks_exact_kernel(PlanDev P) {
-    const int chunk = blockIdx.x, stream = blockIdx.y, c = blockIdx.z, tid = threadIdx.x;
-    const PlanConvDev cv = P.convs[c];
-    if (chunk >= cv.n_chunks) return;
-    __shared__ long long s_tmp[4];
-    const PlanTensorDev tt = P.tensors[cv.tensor];
-    const uint32_t* map = P.bitmaps + (size_t)stream * P.bm_words + tt.bm_off;
-    const int wpr = (cv.Wout + 31) >> 5;
-    const int units = cv.units_x * cv.units_y;
-    const int u = chunk * kPlanChunk + tid;
-    unsigned mask = 0;
-    int dirty = 0;
-    if (u < units) {
-        const int ty = u / cv.units_x, tx = u - ty * cv.units_x;
-        const int x0 = tx * 4;                               // a unit's four columns lie in one word
-        for (int r = 0; r < 4; ++r) {
-            const int y = ty * 4 + r;
-            if (y < cv.Hout) mask |= ((map[(size_t)y * wpr + (x0 >> 5)] >> (x0 & 31)) & 0xfu) << (4 * r);
-        }
-        if (cv.no_reuse) mask = 0;                           // a layer that does not use the cache
-        const unsigned inside = inside_mask(cv.Hout, cv.Wout, ty, tx);
-        dirty = (mask & inside) != inside ? 1 : 0;
-        reinterpret_cast<uint16_t*>(P.area + cv.umask_off)[(size_t)stream * units + u] = (uint16_t)mask;
-    }
-    const long long both_sums = block_sum(((long long)dirty << 32) | (long long)__popc(mask), s_tmp);
-    if (tid == 0) {
-        int32_t* cnt = reinterpret_cast<int32_t*>(P.area + cv.count_off) + ((size_t)stream * cv.n_chunks + chunk) * 2;
-        cnt[0] = (int32_t)(both_sums >> 32);
-        cnt[1] = (int32_t)(both_sums & 0xffffffffll);
+    for (int c = tid >> 6; c < P.n_convs; c += kErodeThreads / 64) {
+        const PlanConvDev cv = table_entry<PlanConvDev>(table_dword<PlanConvDev>(convs, c, P.n_convs));
+        int32_t* cnt = reinterpret_cast<int32_t*>(P.area + cv.count_off) + (size_t)stream * cv.n_chunks * 2;
+        for (int j = tid & 63; j < 2 * cv.n_chunks; j += 64) cnt[j] = counts[2 * cv.chunk_base + j];
     }
 }
 
@@ -604,6 +685,8 @@ __global__ __launch_bounds__(kPlanChunk) void plan_masks_kernel(PlanDev P) {
     }
 }
 
+// EXACT: the unit's mask is cut out of the tensor's bitmap here (and stored for the shifted copies, if there are any).
+template <bool EXACT>
 __global__ __launch_bounds__(kPlanChunk) void plan_lists_kernel(PlanDev P) {
     const int chunk = blockIdx.x, stream = blockIdx.y, c = blockIdx.z, tid = threadIdx.x;
     const PlanConvDev cv = P.convs[c];
@@ -628,7 +711,18 @@ __global__ __launch_bounds__(kPlanChunk) void plan_lists_kernel(PlanDev P) {
     int ty = 0, tx = 0;
     if (u < units) {
         ty = u / cv.units_x; tx = u - ty * cv.units_x;
-        mask = reinterpret_cast<const uint16_t*>(P.area + cv.umask_off)[(size_t)stream * units + u];
+        uint16_t* const umask = reinterpret_cast<uint16_t*>(P.area + cv.umask_off) + (size_t)stream * units + u;
+        if (EXACT) {
+            const uint32_t* map = P.bitmaps + (size_t)stream * P.bm_words + cv.bm_off + ((tx * 4) >> 5);   // a unit's columns lie in one word
+            const int wpr = (cv.Wout + 31) >> 5;
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (ty * 4 + r < cv.Hout) mask |= ((map[(ty * 4 + r) * wpr] >> ((tx * 4) & 31)) & 0xfu) << (4 * r);
+            if (cv.no_reuse) mask = 0;                       // a layer that does not use the cache
+            if (P.want_umasks) *umask = (uint16_t)mask;
+        } else {
+            mask = *umask;
+        }
         const unsigned inside = inside_mask(cv.Hout, cv.Wout, ty, tx);
         dirty = (mask & inside) != inside;
     }
@@ -742,7 +836,7 @@ hipError_t launch_plan(const PlanDev& P, const uint8_t* block_mask, const int32_
     hipLaunchKernelGGL(plan_masks_kernel, grid, dim3(kPlanChunk), 0, st, P);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(plan_lists_kernel, grid, dim3(kPlanChunk), 0, st, P);
+    hipLaunchKernelGGL(plan_lists_kernel<false>, grid, dim3(kPlanChunk), 0, st, P);
     return hipGetLastError();
 }
 
@@ -770,7 +864,7 @@ hipError_t launch_plan_from_args(const PlanDev& P, const PlanConvDev& conv, cons
     hipLaunchKernelGGL(plan_masks_kernel, grid, dim3(kPlanChunk), 0, st, P);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(plan_lists_kernel, grid, dim3(kPlanChunk), 0, st, P);
+    hipLaunchKernelGGL(plan_lists_kernel<false>, grid, dim3(kPlanChunk), 0, st, P);
     return hipGetLastError();
 }
 
@@ -778,7 +872,11 @@ hipError_t launch_plan_exact(const PlanDev& P, const uint8_t* block_mask, const 
                              int extend_borders, int max_chunks, bool with_lists, hipStream_t st) {
     if (P.n_layers + 1 > kPlanMaxTensors || !P.bitmaps || gh < 1 || gw < 1) return hipErrorInvalidValue;
     hipError_t e;
-    if (P.bm_words <= kErodeLdsWords) {
+    const int lists = with_lists && P.n_convs > 0 ? 1 : 0;
+    const size_t count_bytes = lists ? (size_t)P.n_chunks * 2 * sizeof(int) : 0;
+    const size_t table_bytes = (size_t)P.n_ops * sizeof(PlanOpDev) + (size_t)P.n_convs * sizeof(PlanConvDev);
+    const size_t lds = (size_t)P.bm_words * sizeof(uint32_t) + count_bytes + table_bytes;
+    if (lds <= kErodeLdsWords * sizeof(uint32_t)) {
         static std::atomic<bool> raised{false};       // more than 64 KB of dynamic LDS has to be asked for once
         if (!raised.load(std::memory_order_acquire)) {
             e = hipFuncSetAttribute(reinterpret_cast<const void*>(&plan_erode_kernel<true>), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -786,19 +884,16 @@ hipError_t launch_plan_exact(const PlanDev& P, const uint8_t* block_mask, const 
             if (e != hipSuccess) return e;
             raised.store(true, std::memory_order_release);
         }
-        hipLaunchKernelGGL(plan_erode_kernel<true>, dim3(P.n_streams), dim3(kErodeThreads), (size_t)P.bm_words * sizeof(uint32_t), st,
-                           P, block_mask, gmv, gh, gw, block, extend_borders);
+        hipLaunchKernelGGL(plan_erode_kernel<true>, dim3(P.n_streams), dim3(kErodeThreads), lds, st, P, block_mask, gmv, gh, gw, block,
+                           extend_borders, lists);
     } else {
-        hipLaunchKernelGGL(plan_erode_kernel<false>, dim3(P.n_streams), dim3(kErodeThreads), 0, st, P, block_mask, gmv, gh, gw, block,
-                           extend_borders);
+        hipLaunchKernelGGL(plan_erode_kernel<false>, dim3(P.n_streams), dim3(kErodeThreads), table_bytes, st, P, block_mask, gmv, gh, gw, block,
+                           extend_borders, lists);
     }
     e = hipGetLastError();
-    if (e != hipSuccess || !with_lists || P.n_convs == 0) return e;
+    if (e != hipSuccess || !lists) return e;
     const dim3 grid((unsigned)max_chunks, (unsigned)P.n_streams, (unsigned)P.n_convs);
-    hipLaunchKernelGGL(plan_masks_exact_kernel, grid, dim3(kPlanChunk), 0, st, P);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(plan_lists_kernel, grid, dim3(kPlanChunk), 0, st, P);
+    hipLaunchKernelGGL(plan_lists_kernel<true>, grid, dim3(kPlanChunk), 0, st, P);
     return hipGetLastError();
 }
 

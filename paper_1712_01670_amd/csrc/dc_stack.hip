@@ -100,12 +100,13 @@ struct DevPlanLayout {
     std::vector<PlanLayerDev> layers;
     std::vector<PlanTensorDev> tensors;
     std::vector<PlanConvDev> convs;
+    std::vector<PlanOpDev> ops;                 // exact reuse maps
     std::vector<int> conv_layer;                // layer index of every conv
-    size_t table_bytes = 0, off_tensors = 0, off_convs = 0;
+    size_t table_bytes = 0, off_tensors = 0, off_convs = 0, off_ops = 0;
     size_t frame_bytes = 0, off_nrect = 0, off_dxy = 0, off_origin = 0, off_info = 0, off_nunits = 0, off_stats = 0, off_area = 0;
     size_t off_bitmaps = 0;
     int64_t bm_words = 0;                       // words of all bitmaps of one stream (exact reuse maps)
-    int cap = 0, max_chunks = 0;
+    int cap = 0, max_chunks = 0, n_chunks = 0;
     bool ok = false;
 };
 
@@ -117,7 +118,8 @@ void device_plan_layout(const dc_layer* L, int n_layers, const std::vector<int>&
     const int nt = n_layers + 1;
     if (nt > kPlanMaxTensors) return;
     d.cap = max_rects < kPlanMaxRects ? max_rects : kPlanMaxRects;
-    d.layers.resize(n_layers); d.tensors.resize(nt); d.convs.clear(); d.conv_layer.clear();
+    d.layers.resize(n_layers); d.tensors.resize(nt); d.convs.clear(); d.conv_layer.clear(); d.ops.clear();
+    std::vector<int> depth(nt, 0);
     d.tensors[0] = PlanTensorDev{hs[0], ws[0], 1, 0};
     int64_t bm = ((int64_t)hs[0] * ((ws[0] + 31) / 32) + 63) / 64 * 64;          // every bitmap starts on a 256-byte line
     for (int i = 0; i < n_layers; ++i) {
@@ -128,7 +130,6 @@ void device_plan_layout(const dc_layer* L, int n_layers, const std::vector<int>&
         const int cum = d.tensors[l.in0].cum_stride * (windowed ? l.s : 1);
         if (bm > 0x7fffffffll) return;
         d.tensors[i + 1] = PlanTensorDev{hs[i + 1], ws[i + 1], cum, (int32_t)bm};
-        bm += ((int64_t)hs[i + 1] * ((ws[i + 1] + 31) / 32) + 63) / 64 * 64;
         if (l.type == DC_ADD && d.tensors[l.in1].cum_stride != d.tensors[l.in0].cum_stride) return;
         if (l.type == DC_CONCAT) {
             int ids[4];
@@ -137,11 +138,56 @@ void device_plan_layout(const dc_layer* L, int n_layers, const std::vector<int>&
                 if (d.tensors[ids[j]].cum_stride != d.tensors[l.in0].cum_stride) return;
         }
         if (l.type == DC_CONV) d.conv_layer.push_back(i);
+        // the step that makes the tensor's bitmap, if it differs from the producer's (same size, stride and offset)
+        PlanOpDev op{};
+        op.src0 = d.tensors[l.in0].bm_off; op.src[0] = op.src[1] = op.src[2] = -1;
+        const bool lrn_px = l.type == DC_LRN && l.within != 0;
+        depth[i + 1] = depth[l.in0];
+        if (l.type == DC_FC || l.type == DC_SOFTMAX) {
+            op.kind = kPlanOpZero;
+        } else if (l.type == DC_ADD || l.type == DC_CONCAT) {
+            int ids[4] = {l.in0, l.in1, -1, -1};
+            const int m = l.type == DC_CONCAT ? concat_inputs(l, ids) : 2;
+            op.kind = m == 2 ? kPlanOpAnd2 : kPlanOpAnd;
+            for (int j = 1; j < m; ++j) {
+                op.src[j - 1] = d.tensors[ids[j]].bm_off;
+                depth[i + 1] = std::max(depth[i + 1], depth[ids[j]]);
+            }
+        } else if ((windowed && !(wg.kh == 1 && wg.kw == 1 && l.s == 1 && wg.ph == 0 && wg.pw == 0)) || lrn_px) {
+            op.kh = lrn_px ? l.k : wg.kh; op.kw = lrn_px ? l.k : wg.kw; op.s = windowed ? l.s : 1; op.dil = windowed ? wg.dil : 1;
+            op.ph = lrn_px ? (l.k - 1) / 2 : wg.ph; op.pw = lrn_px ? (l.k - 1) / 2 : wg.pw;
+            const bool words = (op.kw - 1) * op.dil < 32;
+            op.kind = op.kh == 3 && op.kw == 3 && op.s == 1 && op.dil == 1 ? kPlanOp3x3
+                    : op.kh == 2 && op.kw == 2 && op.s == 2 && op.dil == 1 ? kPlanOp2x2
+                    : words && op.s == 1 ? kPlanOpStride1 : words && op.s == 2 ? kPlanOpStride2 : words && op.s <= 8 ? kPlanOpStride8 : kPlanOpSlow;
+        } else {
+            d.tensors[i + 1].bm_off = d.tensors[l.in0].bm_off;
+            continue;
+        }
+        bm += ((int64_t)hs[i + 1] * ((ws[i + 1] + 31) / 32) + 63) / 64 * 64;
+        ++depth[i + 1];
+        op.dst = d.tensors[i + 1].bm_off;
+        op.h_in = hs[l.in0]; op.w_in = ws[l.in0]; op.wpr_in = (ws[l.in0] + 31) / 32;
+        op.h = hs[i + 1]; op.w = ws[i + 1]; op.wpr = (ws[i + 1] + 31) / 32;
+        op.words = op.h * op.wpr;
+        op.cum_stride = cum;
+        op.wpr_magic = (uint32_t)((0x100000000ull + (uint64_t)op.wpr - 1) / (uint64_t)op.wpr);
+        op.depth_end = depth[i + 1];                // (sorted by it below)
+        d.ops.push_back(op);
+    }
+    std::stable_sort(d.ops.begin(), d.ops.end(), [](const PlanOpDev& a, const PlanOpDev& b) { return a.depth_end < b.depth_end; });
+    for (size_t j = 0; j < d.ops.size(); ++j) d.ops[j].depth_end = j + 1 == d.ops.size() || d.ops[j + 1].depth_end != d.ops[j].depth_end ? 1 : 0;
+    for (size_t j = d.ops.size(); j-- > 0;) {           // runs of small steps
+        const bool small = d.ops[j].words <= 128;
+        const bool goes_on = j + 1 < d.ops.size() && d.ops[j + 1].run_end > 0;
+        d.ops[j].run_end = !small ? 0 : goes_on ? d.ops[j + 1].run_end : (int32_t)j + 1;
+        if (!small && goes_on) d.ops[j].depth_end = 1;             // a run may go on to greater depths
     }
     if ((int)d.conv_layer.size() > kPlanMaxConvs) return;
     d.off_tensors = align_up((size_t)n_layers * sizeof(PlanLayerDev), 256);
     d.off_convs = d.off_tensors + align_up((size_t)nt * sizeof(PlanTensorDev), 256);
-    d.table_bytes = d.off_convs + align_up(d.conv_layer.size() * sizeof(PlanConvDev), 256);
+    d.off_ops = d.off_convs + align_up(d.conv_layer.size() * sizeof(PlanConvDev), 256);
+    d.table_bytes = d.off_ops + align_up(d.ops.size() * sizeof(PlanOpDev), 256);
     size_t off = align_up((size_t)n_streams * nt * d.cap * sizeof(dc_rect), 256);
     d.off_nrect = off; off += align_up((size_t)n_streams * nt * sizeof(int32_t), 256);
     d.off_dxy = off; off += align_up((size_t)n_streams * nt * 2 * sizeof(int32_t), 256);
@@ -153,7 +199,7 @@ void device_plan_layout(const dc_layer* L, int n_layers, const std::vector<int>&
     d.off_bitmaps = off; off += align_up((size_t)n_streams * (size_t)bm * sizeof(uint32_t), 256);
     d.off_area = off;
     size_t area = 0;
-    d.max_chunks = 0;
+    d.max_chunks = d.n_chunks = 0;
     for (int layer : d.conv_layer) {
         PlanConvDev c{};
         c.tensor = layer + 1; c.Hout = hs[layer + 1]; c.Wout = ws[layer + 1];
@@ -162,6 +208,8 @@ void device_plan_layout(const dc_layer* L, int n_layers, const std::vector<int>&
         const size_t units = (size_t)c.units_x * c.units_y;
         c.n_chunks = (int)((units + kPlanChunk - 1) / kPlanChunk);
         d.max_chunks = c.n_chunks > d.max_chunks ? c.n_chunks : d.max_chunks;
+        c.chunk_base = d.n_chunks; d.n_chunks += c.n_chunks;
+        c.bm_off = d.tensors[layer + 1].bm_off;
         c.umask_off = (int64_t)area; area += align_up((size_t)n_streams * units * sizeof(uint16_t), 256);
         c.count_off = (int64_t)area; area += align_up((size_t)n_streams * c.n_chunks * 2 * sizeof(int32_t), 256);
         c.list_off = (int64_t)area; area += align_up((size_t)n_streams * units * sizeof(TileDev), 256);
@@ -411,6 +459,7 @@ int make_plan(StackPlan& P, const dc_layer* layers, int n_layers, int n_streams,
         std::memcpy(P.tables.data(), P.dl.layers.data(), P.dl.layers.size() * sizeof(PlanLayerDev));
         std::memcpy(P.tables.data() + P.dl.off_tensors, P.dl.tensors.data(), P.dl.tensors.size() * sizeof(PlanTensorDev));
         if (!P.dl.convs.empty()) std::memcpy(P.tables.data() + P.dl.off_convs, P.dl.convs.data(), P.dl.convs.size() * sizeof(PlanConvDev));
+        if (!P.dl.ops.empty()) std::memcpy(P.tables.data() + P.dl.off_ops, P.dl.ops.data(), P.dl.ops.size() * sizeof(PlanOpDev));
     }
     P.signature = fnv1a(0xcbf29ce484222325ull, layers, (size_t)n_layers * sizeof(dc_layer));
     const int32_t shape[8] = {n_streams, H, W, C, block, P.dl.cap, dtype, n_layers};
@@ -733,7 +782,10 @@ int StackCall::prepare_device_plan() {
     pd.layers = reinterpret_cast<const PlanLayerDev*>(tables_dev);
     pd.tensors = reinterpret_cast<const PlanTensorDev*>(tables_dev + dl.off_tensors);
     pd.convs = reinterpret_cast<const PlanConvDev*>(tables_dev + dl.off_convs);
+    pd.ops = reinterpret_cast<const PlanOpDev*>(tables_dev + dl.off_ops);
     pd.n_layers = n_layers; pd.n_convs = (int32_t)dl.convs.size(); pd.n_streams = n_streams; pd.cap = dl.cap;
+    pd.n_ops = (int32_t)dl.ops.size(); pd.n_chunks = dl.n_chunks;
+    pd.want_umasks = P.torus ? 0 : 1;
     pd.rects = reinterpret_cast<dc_rect*>(frame);
     pd.nrect = reinterpret_cast<int32_t*>(frame + dl.off_nrect);
     pd.dxy = reinterpret_cast<int32_t*>(frame + dl.off_dxy);
@@ -1402,13 +1454,16 @@ int32_t dc_propagate_masks(const dc_layer* layers, int32_t n_layers, int32_t n_s
         std::vector<unsigned char> tables(dl.table_bytes, 0);
         std::memcpy(tables.data(), dl.layers.data(), dl.layers.size() * sizeof(PlanLayerDev));
         std::memcpy(tables.data() + dl.off_tensors, dl.tensors.data(), dl.tensors.size() * sizeof(PlanTensorDev));
+        if (!dl.ops.empty()) std::memcpy(tables.data() + dl.off_ops, dl.ops.data(), dl.ops.size() * sizeof(PlanOpDev));
         unsigned char* const table_dev = static_cast<unsigned char*>(ws_dev);
         DC_TRY_HIP(hipMemcpyAsync(table_dev, tables.data(), dl.table_bytes, hipMemcpyHostToDevice, st));
         DC_TRY_HIP(hipStreamSynchronize(st));          // `tables` goes away with this scope
         PlanDev pd{};
         pd.layers = reinterpret_cast<const PlanLayerDev*>(table_dev);
         pd.tensors = reinterpret_cast<const PlanTensorDev*>(table_dev + dl.off_tensors);
+        pd.ops = reinterpret_cast<const PlanOpDev*>(table_dev + dl.off_ops);
         pd.n_layers = n_layers; pd.n_convs = 0; pd.n_streams = n_streams; pd.cap = 1;
+        pd.n_ops = (int32_t)dl.ops.size();
         pd.dxy = dxy;
         // the kernel also leaves a block count and empty rectangle lists: into the tail of the workspace
         int32_t* tail = reinterpret_cast<int32_t*>(table_dev + dl.table_bytes);
