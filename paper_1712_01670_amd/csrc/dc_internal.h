@@ -305,7 +305,8 @@ constexpr int kFramesInFlight = 4;         // plan areas and frame records that 
 struct StackPlan;                          // what dc_run_stack derives from a stack's description (dc_stack.hip)
 struct FrameRecord {
     hipEvent_t done[kMaxStages] = {};      // that stage of the frame has finished
-    bool valid = false;
+    hipEvent_t start[kMaxStages] = {};     // (timed frames) its first kernel may start
+    bool valid = false, timed = false;
     const StackPlan* plan = nullptr;
     int partition = 0;                     // StackPlan::partition of the frame
     int n_stages = 0;

@@ -334,6 +334,10 @@ struct dc::StackPlan {
     float head_us = 0.f;
     std::vector<char> single;               // tensors whose buffer is the same for consecutive frames: no cut may cross them
     std::vector<int> crossing;              // tensors that a later stage than their writer's reads
+    // The layers' times are rough: the first frames after a cut are timed stage by stage, the times of a stage's layers are
+    // scaled to what it took, and the layers are cut again if that promises a shorter longest stage.
+    int recuts_left = 3, timed_frames = 0;
+    float timed_us[kMaxStages] = {};
     int stage_of(int layer) const {
         int s = 0;
         while (s + 1 < n_stages && layer >= first[s + 1]) ++s;
@@ -345,6 +349,17 @@ struct dc::StackPlan {
     }
     bool uses_cache(int i) const { return cache_other && (layers[i].type == DC_MAXPOOL || layers[i].type == DC_ADD); }
     void cut(int max_stages);
+    float longest() const {                 // by layer_us
+        float most = 0.f;
+        for (int s = 0; s < n_stages; ++s) most = std::max(most, stage_us(s));
+        return most;
+    }
+    float stage_us(int s) const {
+        float us = s == 0 && device_plan ? head_us : 0.f;
+        for (int i = first[s]; i < first[s + 1]; ++i) us += layer_us[i];
+        return us;
+    }
+    void calibrate(int max_stages);
 };
 
 namespace {
@@ -425,7 +440,7 @@ float layer_cost(const StackPlan& P, int i) {
         const double flops = 2.0 * g.kh * g.kw * l.cin * l.cout * out_px;
         // the general kernels reach a quarter of the rate and walk over the taps one stage after another
         const bool gemm = plain_square(l) && ((l.k == 3 && l.s == 1) || l.k == 1);
-        us = 5.0 + (gemm ? 0.0 : 0.8 * g.kh * g.kw) + std::max(bytes / 3.5e6, flops / ((P.dtype == DC_BF16 ? 0.9e9 : 0.1e9) * (gemm ? 1.0 : 0.25)));
+        us = 5.0 + (gemm ? 0.0 : 0.8 * g.kh * g.kw) + g.kh * g.kw * l.cin * l.cout * esz / 0.8e6 * std::min(1.0, 400.0 / out_px) + std::max(bytes / 3.5e6, flops / ((P.dtype == DC_BF16 ? 0.9e9 : 0.1e9) * (gemm ? 1.0 : 0.25)));
     } else if (l.type == DC_FC) {
         us = 8.0 + (double)P.hs[l.in0] * P.ws[l.in0] * P.cs[l.in0] * l.cout * esz * (1.0 + n / 6.0) / 4e6;
     } else if (l.type == DC_LRN) {
@@ -487,7 +502,7 @@ int make_plan(StackPlan& P, const dc_layer* layers, int n_layers, int n_streams,
     // rough times, and the tensors that are one buffer for all frames
     const double px = (double)n_streams * H * W, cand = (2.0 * radius + 1) * (2.0 * radius + 1);
     const bool diamond = o && o->method == DC_MATCH_DIAMOND;
-    P.head_us = (float)((diamond ? 50.0 + px / 25e3 : 15.0 + px * C * cand / 60e6) + (P.device_plan ? 30.0 + 0.8 * n_layers : 0.0));
+    P.head_us = (float)((diamond ? 50.0 + px / 25e3 : 15.0 + px * C * cand / 60e6) + (P.device_plan ? 25.0 + 0.4 * P.dl.ops.size() : 0.0));
     P.single.assign(n_layers + 1, 0);
     for (int i = 0; i < n_layers; ++i) {
         P.layer_us.push_back(layer_cost(P, i));
@@ -500,10 +515,11 @@ int make_plan(StackPlan& P, const dc_layer* layers, int n_layers, int n_streams,
 
 // Cuts the layers into at most max_stages stages of about equal time such that no tensor with a single buffer is
 // written in one stage and read in a later one (the writer's next frame would have to wait for the reader).  A stage
-// costs the host a cross-stream wait (8-12 us) per frame, so a stage shorter than that is not worth having.
+// costs the host a cross-stream wait (8-12 us) per frame, and planned on the host a frame waits for its matching anyway, so
+// short stages are not worth having.
 void StackPlan::cut(int max_stages) {
     const int n = (int)layers.size();
-    constexpr float kStageUs = 30.f;
+    const float stage_us_min = device_plan ? 40.f : 80.f;
     std::vector<char> allowed(n, 1);       // allowed[i]: a stage may start with layer i
     for (int t = 0; t <= n; ++t)
         if (single[t])
@@ -511,7 +527,7 @@ void StackPlan::cut(int max_stages) {
     const float head = device_plan ? head_us : 0.f;
     float total = head;
     for (float v : layer_us) total += v;
-    int k = (int)(total / kStageUs);
+    int k = (int)(total / stage_us_min);
     k = k < 1 ? 1 : (k > max_stages ? max_stages : k);
     // best[s][i]: smallest possible longest stage when layers 0 .. i - 1 form s stages
     std::vector<float> sum(n + 1, head);
@@ -535,6 +551,34 @@ void StackPlan::cut(int max_stages) {
     for (int t = 0; t <= n; ++t)
         if (last_reader[t] >= 0 && stage_of(last_reader[t]) > writer_stage(t)) crossing.push_back(t);
     ++partition;
+}
+
+// After kTimedFrames timed frames: scales the layers' times by what their stages took and cuts again if that pays.
+constexpr int kTimedFrames = 4;
+void StackPlan::calibrate(int max_stages) {
+    if (timed_frames < kTimedFrames) return;
+    float now = 0.f;
+    for (int s = 0; s < n_stages; ++s) {
+        const float took = timed_us[s] / timed_frames, ratio = took / std::max(stage_us(s), 1.f);
+        for (int i = first[s]; i < first[s + 1]; ++i) layer_us[i] *= ratio;
+        if (s == 0 && device_plan) head_us *= ratio;
+        now = std::max(now, took);
+        timed_us[s] = 0.f;
+    }
+    timed_frames = 0;
+    const int old_stages = n_stages, old_partition = partition;
+    int old_first[kMaxStages + 1];
+    std::copy(first, first + kMaxStages + 1, old_first);
+    std::vector<int> old_crossing = crossing;
+    cut(max_stages);
+    if (longest() < 0.93f * now) {
+        --recuts_left;
+    } else {                                // as good as it gets
+        recuts_left = 0;
+        n_stages = old_stages; partition = old_partition;
+        std::copy(old_first, old_first + kMaxStages + 1, first);
+        crossing.swap(old_crossing);
+    }
 }
 
 namespace {
@@ -704,7 +748,21 @@ int StackCall::begin() {
     pipe = ov && ov->pipeline;
     // With a pipeline and planning on the GPU, matching and planning head stage 0; planned on the host they run on aux,
     // because the host waits for them.
-    if (pipe && P.partition == 0) P.cut(P.device_plan ? kMaxStages : kMaxStages - 1);
+    const int most = P.device_plan ? kMaxStages : kMaxStages - 1;
+    if (pipe && P.partition == 0) P.cut(most);
+    if (pipe && P.recuts_left > 0) {
+        FrameRecord& old = ov->ring[ov->frame_no % kFramesInFlight];
+        if (old.valid && old.timed && old.plan == &P && old.partition == P.partition) {
+            DC_TRY_HIP(hipEventSynchronize(old.done[old.n_stages - 1]));      // (the first few frames only)
+            for (int s = 0; s < old.n_stages; ++s) {
+                float ms = 0.f;
+                DC_TRY_HIP(hipEventElapsedTime(&ms, old.start[s], old.done[s]));
+                P.timed_us[s] += ms * 1e3f;
+            }
+            ++P.timed_frames;
+            P.calibrate(most);
+        }
+    }
     const int k = pipe ? P.n_stages : 1;
     if (pipe) {
         hipStream_t inner[kMaxStages - 1] = {ov->aux, ov->work[0], ov->work[1]};
@@ -724,8 +782,10 @@ int StackCall::begin() {
     if (P.torus && cached && !devplan) return DC_ERR_UNSUPPORTED;      // a torus frame is planned on the GPU or not at all
     if (!ov) return DC_OK;
     FrameRecord& rec = ov->ring[area];
-    for (int s = 0; s < k; ++s)
-        if (!rec.done[s]) DC_TRY_HIP(hipEventCreateWithFlags(&rec.done[s], hipEventDisableTiming));
+    for (int s = 0; s < k; ++s) {
+        if (!rec.done[s]) DC_TRY_HIP(hipEventCreate(&rec.done[s]));
+        if (!rec.start[s]) DC_TRY_HIP(hipEventCreate(&rec.start[s]));
+    }
     // the plan area's (and the record's) last frame has to be over
     hipStream_t head = devplan && !pipe ? ov->aux : stage_st[0];
     if (rec.valid) DC_TRY_HIP(wait(head, rec.done[rec.n_stages - 1]));
@@ -1142,6 +1202,8 @@ int StackCall::run() {
     const int k = pipe ? P.n_stages : 1;
     FrameRecord* const rec = ov ? &ov->ring[area] : nullptr;
     if (rec) rec->valid = false;
+    const bool timed = devplan && pipe && P.recuts_left > 0;      // (planned on the host, a stage takes what the host takes to issue it)
+    if (timed) DC_TRY_HIP(hipEventRecord(rec->start[0], stage_st[0]));
 
     // ---- matching and planning ----
     hipStream_t head = devplan && ov && !pipe ? ov->aux : stage_st[0];
@@ -1203,7 +1265,10 @@ int StackCall::run() {
             }
     DC_TRY_HIP(launch_frame_to_tensor(frames_cur, eff[0], (size_t)n_streams * H * W, C, P.c_tensor, dtype, stage_st[0]));
     for (int s = 0; s < k; ++s) {
-        if (s > 0) DC_TRY_HIP(wait(stage_st[s], rec->done[s - 1]));
+        if (s > 0) {
+            DC_TRY_HIP(wait(stage_st[s], rec->done[s - 1]));
+            if (timed) DC_TRY_HIP(hipEventRecord(rec->start[s], stage_st[s]));
+        }
         rc = emit_stage(s, stage_st[s]);
         if (rc) return rc;
         if (rec) DC_TRY_HIP(hipEventRecord(rec->done[s], stage_st[s]));
@@ -1211,10 +1276,15 @@ int StackCall::run() {
     if (rec) {
         rec->plan = &P; rec->partition = P.partition; rec->n_stages = k; rec->caller = caller;
         rec->bufs.assign(eff.begin(), eff.end());
+        rec->timed = timed;
         rec->valid = true;
         ++ov->frame_no;
     }
-    if (recut) P.cut(P.device_plan ? kMaxStages : kMaxStages - 1);
+    if (recut) {
+        P.cut(P.device_plan ? kMaxStages : kMaxStages - 1);
+        P.timed_frames = 0;
+        std::fill(P.timed_us, P.timed_us + kMaxStages, 0.f);
+    }
     return DC_OK;
 }
 
@@ -1246,8 +1316,10 @@ int32_t dc_overlap_destroy(void* overlap) {
     for (hipEvent_t e : o->upload_done)
         if (e) (void)hipEventDestroy(e);
     for (FrameRecord& r : o->ring)
-        for (hipEvent_t e : r.done)
-            if (e) (void)hipEventDestroy(e);
+        for (int s = 0; s < kMaxStages; ++s) {
+            if (r.done[s]) (void)hipEventDestroy(r.done[s]);
+            if (r.start[s]) (void)hipEventDestroy(r.start[s]);
+        }
     if (o->match_done) (void)hipEventDestroy(o->match_done);
     if (o->plan_done) (void)hipEventDestroy(o->plan_done);
     release_stage_streams(o);
