@@ -302,6 +302,7 @@ struct Profile {
 // frame's output of the same layer, hence of the same stage, so the frames in flight need no waits per layer.
 constexpr int kMaxStages = 4;              // streams: the process has four hardware queues
 constexpr int kFramesInFlight = 4;         // plan areas and frame records that take turns
+struct FrameGraphs;
 struct StackPlan;                          // what dc_run_stack derives from a stack's description (dc_stack.hip)
 struct FrameRecord {
     hipEvent_t done[kMaxStages] = {};      // that stage of the frame has finished

@@ -305,6 +305,32 @@ std::mutex g_frame_plan_mutex;
 
 }  // namespace
 
+// The launches of one kind of frame recorded as HIP graphs, one per stage, for stacks whose frames are bound by the host
+// issuing launches (StackPlan::replay).  A kernel node costs the host 0.3 us where a launch costs 2.5-3.5, but every graph
+// costs its stream about 10 us on the GPU, which a frame that is bound by the GPU pays for nothing.  What the kernels' arguments
+// depend on is the key; frames of a steady video go round through a handful of keys (buffer sets x plan areas).  The
+// first frames of a key are launched one kernel at a time (recording costs about 5 us per kernel), later ones replay.
+// The launch shapes in a graph follow the list lengths seen when it was recorded; when those of the video have moved
+// away for good the graphs are dropped and recorded again.
+struct dc::FrameGraphs {
+    std::vector<uint64_t> key;
+    uint64_t hash = 0, last_use = 0;
+    int uses = 0, off_shape = 0;            // frames of this key so far; consecutive frames whose lists had other lengths
+    bool ready = false;
+    hipGraphExec_t exec[kMaxStages] = {};
+    std::vector<int32_t> kernel_id;         // [layer]
+    std::vector<long> hint;                 // [conv]
+    void drop() {
+        for (hipGraphExec_t& e : exec) {
+            if (e) (void)hipGraphExecDestroy(e);
+            e = nullptr;
+        }
+        ready = false;
+        uses = off_shape = 0;
+    }
+    ~FrameGraphs() { drop(); }
+};
+
 // ---- what dc_run_stack derives from a stack's description ------------------------------------------------------
 // Depends on the layer table, the sizes and the options, not on the frame, its buffers or the weights.  An overlap
 // handle keeps the last few (a caller runs one stack, frame after frame); without a handle it is made on every call.
@@ -338,6 +364,22 @@ struct dc::StackPlan {
     // scaled to what it took, and the layers are cut again if that promises a shorter longest stage.
     int recuts_left = 3, timed_frames = 0;
     float timed_us[kMaxStages] = {};
+    std::vector<std::unique_ptr<dc::FrameGraphs>> graphs;
+    bool no_graphs = false;                 // recording failed once
+    // Replaying pays while issuing a frame kernel by kernel takes the host longer than the GPU takes per frame: the first is
+    // measured on frames that are issued that way, with what the caller spends between two calls, the second is the
+    // distance of consecutive frames' ends (a frame bound by the host shows the two about equal).
+    bool replay = false;
+    float host_us = 0.f, between_us = 0.f, period_us = 0.f;   // running means (0: nothing measured yet)
+    std::chrono::steady_clock::time_point left;               // end of the last call
+    int gaps = 0;                           // consecutive frame distances that were no measure of the GPU (a pause in between)
+    void measured(float& mean, float us) { mean = mean > 0.f ? mean + 0.125f * (us - mean) : us; }
+    void measured_period(float us) {
+        if (period_us > 0.f && us > 2.f * period_us && ++gaps < 8) return;
+        gaps = 0;
+        measured(period_us, us);
+    }
+    void decide() { replay = host_us > 0.f && period_us > 0.f && host_us + between_us > (replay ? 1.f : 0.97f) * period_us; }
     int stage_of(int layer) const {
         int s = 0;
         while (s + 1 < n_stages && layer >= first[s + 1]) ++s;
@@ -698,6 +740,8 @@ struct StackCall {
     int emit_copies(int s, hipStream_t st);
     int emit_layer(int i, hipStream_t st);
     int emit_stage(int s, hipStream_t st);
+    dc::FrameGraphs* find_graphs();
+    int record_graphs(dc::FrameGraphs& g);
     int run();
     hipError_t wait(hipStream_t st, hipEvent_t e) const { return hipStreamWaitEvent(st, e, 0); }     // free when e is complete
     bool prefetched() const {
@@ -789,6 +833,12 @@ int StackCall::begin() {
     // the plan area's (and the record's) last frame has to be over
     hipStream_t head = devplan && !pipe ? ov->aux : stage_st[0];
     if (rec.valid) DC_TRY_HIP(wait(head, rec.done[rec.n_stages - 1]));
+    const FrameRecord& next = ov->ring[(area + 1) % kFramesInFlight];
+    if (pipe && rec.valid && next.valid && rec.plan == &P && next.plan == &P && hipEventQuery(next.done[next.n_stages - 1]) == hipSuccess) {
+        float ms = 0.f;
+        if (hipEventElapsedTime(&ms, rec.done[rec.n_stages - 1], next.done[next.n_stages - 1]) == hipSuccess) P.measured_period(ms * 1e3f);
+        P.decide();
+    }
     const FrameRecord& prev = ov->ring[(area + kFramesInFlight - 1) % kFramesInFlight];
     if (prev.valid && (prev.plan != &P || prev.partition != P.partition || prev.n_stages != k || prev.caller != caller)) {
         // other stages or streams than the previous frame's: its end comes first, on every stream
@@ -836,7 +886,7 @@ int StackCall::prepare_device_plan() {
         const int32_t v = *reinterpret_cast<const volatile int32_t*>(&seen[c].n_units);
         unit_hint[c] = v > 0 ? v : -1;
     }
-    const int slot = hdr->last_slot ^ 1;
+    const int slot = ov ? area & 1 : hdr->last_slot ^ 1;
     tables_dev = plan_dev;
     unsigned char* const frame = plan_dev + align_up(dl.table_bytes, 256);
     pd.layers = reinterpret_cast<const PlanLayerDev*>(tables_dev);
@@ -1182,7 +1232,80 @@ int StackCall::emit_stage(int s, hipStream_t st) {
     return rc;
 }
 
+constexpr size_t kMaxFrameGraphs = 16;       // keys kept per stack
+constexpr int kGraphUses = 2;               // frames of a key that are launched kernel by kernel before it is recorded
+constexpr int kGraphOffShape = 8;           // consecutive frames with other list lengths before a graph is recorded anew
+
+// The entry for this frame's key, or nullptr if the frame cannot be replayed from a graph: everything its kernels take
+// as arguments has to be part of the key, and nothing may wait for the host or go through a copy in between.
+dc::FrameGraphs* StackCall::find_graphs() {
+    if (!pipe || !P.replay || (cached && !devplan) || prof || regions_out || P.no_graphs) return nullptr;
+    if (cached && (!host_alias || (P.torus && opt->origins_out))) return nullptr;
+    const size_t n = n_layers;
+    std::vector<uint64_t> key;
+    key.reserve(5 * n + 16);
+    auto put = [&](const void* const* v, size_t m) {
+        for (size_t i = 0; i < m; ++i) key.push_back(v ? reinterpret_cast<uint64_t>(v[i]) : 0);
+    };
+    put(weights, n); put(packed, n); put(reinterpret_cast<const void* const*>(bias), n);
+    put(tensors_cur, n + 1);
+    put(cached ? tensors_prev : nullptr, n + 1);
+    key.push_back(reinterpret_cast<uint64_t>(scratch));
+    if (cached)
+        for (const void* v : {static_cast<const void*>(plan_dev), static_cast<const void*>(host_alias), static_cast<const void*>(tables_host),
+                              static_cast<const void*>(pd.stats), static_cast<const void*>(pd.origin_prev),
+                              static_cast<const void*>(block_mask), static_cast<const void*>(gmv)})
+            key.push_back(reinterpret_cast<uint64_t>(v));
+    key.push_back((uint64_t)P.partition << 32 | (cached ? 1 : 0) | (opt->extend_borders ? 2 : 0));
+    uint64_t h = 0x9e3779b97f4a7c15ull;
+    for (uint64_t v : key) { h = (h ^ v) * 0xff51afd7ed558ccdull; h ^= h >> 32; }
+    for (auto& g : P.graphs)
+        if (g->hash == h && g->key == key) {
+            g->last_use = ov->frame_no;
+            return g.get();
+        }
+    if (P.graphs.size() >= kMaxFrameGraphs) {        // the least recently used entry goes
+        size_t old = 0;
+        for (size_t i = 1; i < P.graphs.size(); ++i)
+            if (P.graphs[i]->last_use < P.graphs[old]->last_use) old = i;
+        if (P.graphs[old]->ready && drain(ov) != hipSuccess) return nullptr;      // (its graphs may still be running)
+        P.graphs.erase(P.graphs.begin() + old);
+    }
+    P.graphs.emplace_back(new dc::FrameGraphs());
+    dc::FrameGraphs* g = P.graphs.back().get();
+    g->key.swap(key);
+    g->hash = h;
+    g->last_use = ov->frame_no;
+    return g;
+}
+
+// Records the launches of every stage (nothing is executed).
+int StackCall::record_graphs(dc::FrameGraphs& g) {
+    g.kernel_id.assign(n_layers, -1);
+    int32_t* const caller_ids = local.layer_kernel_id;
+    local.layer_kernel_id = g.kernel_id.data();
+    hipStream_t st = ov->work[0];            // recording takes any stream that is not the default one
+    int rc = DC_OK;
+    for (int s = 0; s < P.n_stages && !rc; ++s) {
+        hipGraph_t graph = nullptr;
+        if (hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal) != hipSuccess) { rc = DC_ERR_HIP; break; }
+        if (s == 0 && cached) rc = emit_device_plan(st);
+        if (!rc) rc = emit_stage(s, st);
+        if (hipStreamEndCapture(st, &graph) != hipSuccess || !graph) rc = DC_ERR_HIP;
+        size_t nodes = 0;
+        if (!rc && hipGraphGetNodes(graph, nullptr, &nodes) != hipSuccess) rc = DC_ERR_HIP;
+        if (!rc && nodes && hipGraphInstantiate(&g.exec[s], graph, nullptr, nullptr, 0) != hipSuccess) rc = DC_ERR_HIP;
+        if (graph) (void)hipGraphDestroy(graph);
+    }
+    local.layer_kernel_id = caller_ids;
+    g.hint = unit_hint;
+    if (rc) { g.drop(); (void)hipGetLastError(); }
+    g.ready = rc == DC_OK;
+    return rc;
+}
+
 int StackCall::run() {
+    const auto t_start = std::chrono::steady_clock::now();
     int rc = check();
     if (rc) return rc;
     // a look-ahead match is for the very next call only (the caller may reuse its frame buffers after that)
@@ -1217,14 +1340,7 @@ int StackCall::run() {
             rc = launch_match(head);
             if (rc) return rc;
         }
-        rc = emit_device_plan(head);
-        if (!rc) rc = read_back_plan(head);
-        if (rc) return rc;
         if (P.torus && opt->origins_dev_out) *opt->origins_dev_out = pd.origin;
-        if (head != stage_st[0]) {
-            DC_TRY_HIP(hipEventRecord(ov->plan_done, head));
-            DC_TRY_HIP(wait(stage_st[0], ov->plan_done));
-        }
         if (ov) ov->head = head;
     } else if (cached) {
         rc = plan_on_host();
@@ -1263,16 +1379,53 @@ int StackCall::run() {
                 if (g == 1 && !P.single[t]) { P.single[t] = 1; recut = true; }
                 break;
             }
+    dc::FrameGraphs* g = find_graphs();
+    if (g && g->ready && cached) {      // a graph is kept while the lists are about as long as when it was recorded
+        long apart = 0, most = 1;
+        for (size_t c = 0; c < unit_hint.size(); ++c) {
+            const long a = std::max(unit_hint[c], 0l), b = std::max(g->hint[c], 0l);
+            apart += std::abs(a - b);
+            most += std::max(a, b);
+        }
+        g->off_shape = apart * 4 > most ? g->off_shape + 1 : 0;
+        if (g->off_shape >= kGraphOffShape) {
+            DC_TRY_HIP(drain(ov));
+            g->drop();
+        }
+    }
+    const bool recorded = g && !g->ready && g->uses++ >= kGraphUses;
+    if (recorded && record_graphs(*g) != DC_OK) P.no_graphs = true;
+    const bool replay = g && g->ready;
+
     DC_TRY_HIP(launch_frame_to_tensor(frames_cur, eff[0], (size_t)n_streams * H * W, C, P.c_tensor, dtype, stage_st[0]));
+    if (devplan && !replay) {
+        rc = emit_device_plan(head);
+        if (!rc) rc = read_back_plan(head);
+        if (rc) return rc;
+        if (head != stage_st[0]) {
+            DC_TRY_HIP(hipEventRecord(ov->plan_done, head));
+            DC_TRY_HIP(wait(stage_st[0], ov->plan_done));
+        }
+    }
     for (int s = 0; s < k; ++s) {
         if (s > 0) {
             DC_TRY_HIP(wait(stage_st[s], rec->done[s - 1]));
             if (timed) DC_TRY_HIP(hipEventRecord(rec->start[s], stage_st[s]));
         }
-        rc = emit_stage(s, stage_st[s]);
+        if (!replay) rc = emit_stage(s, stage_st[s]);
+        else if (g->exec[s]) DC_TRY_HIP(hipGraphLaunch(g->exec[s], stage_st[s]));
         if (rc) return rc;
         if (rec) DC_TRY_HIP(hipEventRecord(rec->done[s], stage_st[s]));
     }
+    if (pipe && P.device_plan) {
+        const auto t_end = std::chrono::steady_clock::now();
+        auto us = [](auto a, auto b) { return std::chrono::duration<float, std::micro>(b - a).count(); };
+        if (!replay && !recorded) P.measured(P.host_us, us(t_start, t_end));
+        const float between = us(P.left, t_start);
+        if (between < 50.f) P.measured(P.between_us, between);
+        P.left = t_end;
+    }
+    if (replay && local.layer_kernel_id) std::copy(g->kernel_id.begin(), g->kernel_id.end(), local.layer_kernel_id);
     if (rec) {
         rec->plan = &P; rec->partition = P.partition; rec->n_stages = k; rec->caller = caller;
         rec->bufs.assign(eff.begin(), eff.end());

@@ -861,3 +861,89 @@ def test_lookahead_matching_without_synchronisation():
     for a, b in zip(finals[False], finals[True]):
         for x, y in zip(a, b):
             assert torch.equal(x, y)
+
+
+def _max_rel(a, b):
+    a, b = a.float(), b.float()
+    return float((a - b).abs().max() / b.abs().max().clamp_min(1e-30))
+
+
+@pytest.mark.parametrize("net,plan", [("vgg", dict(torus=True)), ("googlenet", {}), ("resnet", dict(cache_pool_add=True))])
+def test_long_pipelined_runs_stay_with_the_plain_path(net, plan):
+    """Pipelined frames planned on the GPU over a run long enough for the stages to be cut anew from measured times and
+    for frames to be replayed from graphs: the tensors of the last frame of runs that end at different places are those
+    of the plain path (one stream, no handle), which takes neither.  fp32; the lists' lengths are known to the launches
+    with different delays, so partial sums of a split K may be added in another grouping: K <= 4608 products, relative
+    error of a sum up to sqrt(K) 2^-24 per layer, over at most 60 layers below 3e-4."""
+    H = W = 96
+    if net == "vgg":
+        layers = synth.small_vgg()
+    elif net == "googlenet":
+        layers = synth.resolve_global_pooling(synth.googlenet(n_classes=40, width=0.25), H, W, 3)
+    else:
+        layers = synth.resnet50_trunk()[:44]
+    ws, bs = synth.he_weights(layers, 3, bias_scale=0.05, residual_scale=0.5, input_shape=(H, W, 3))
+    T = 12
+    video = torch.from_numpy(synth.panning_video(83, n_frames=T, H=H, W=W, fg=((24, 24), (16, 32)))).to(DEV)
+    frames = [video[t:t + 1].contiguous() for t in range(T)]
+    torch.cuda.synchronize()
+    finals = {}
+    for mode, kw in (("pipeline", dict(overlap=True, pipeline=True)), ("plain", dict(overlap=False))):
+        print(f"[long run] {net} {mode}", flush=True)
+        runner = binding.StackRunner(layers, ws, bs, 1, H, W, 3, block=16, radius=16, dtype=binding.DC_F32, expiry=6,
+                                     device_plan=True, exact_masks=True, want_origins=False, **plan, **kw)
+        kept = []
+        for stop in (5, 61, 90, 11):
+            runner.reset()
+            for t in range(stop):
+                if t % T == 0:
+                    runner.reset()
+                tensors = runner.step(frames[t % T])
+            last = [runner.read_tensor(i, tensors) if (not runner.torus or runner.layers[i - 1]["type"] == synth.CONV) else tensors[i]
+                    for i in range(1, len(layers) + 1)]
+            torch.cuda.synchronize()
+            kept.append([x.clone() for x in last] + [runner.mask.clone(), runner.gmv.clone()])
+        finals[mode] = kept
+        del runner
+    for f, (a, b) in enumerate(zip(finals["pipeline"], finals["plain"])):
+        assert torch.equal(a[-1], b[-1]) and torch.equal(a[-2], b[-2]), f
+        for i, (x, y) in enumerate(zip(a[:-2], b[:-2])):
+            assert _max_rel(x, y) <= 3e-4, (f, i)
+
+
+def test_one_handle_for_two_stacks_and_two_caller_streams():
+    """A handle that is handed from one stack to another and called on changing streams orders every frame behind the
+    earlier ones: same tensors as with a handle of their own.  (Stages of different stacks use the same streams, and the
+    last stage runs on the caller's.)"""
+    H = W = 96
+    stacks = [synth.small_vgg(), synth.vgg16()[:10]]
+    T = 10
+    video = torch.from_numpy(synth.panning_video(84, n_frames=T, H=H, W=W, fg=((24, 24), (16, 32)))).to(DEV)
+    frames = [video[t:t + 1].contiguous() for t in range(T)]
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    torch.cuda.synchronize()
+
+    def make():
+        return [binding.StackRunner(L, *synth.he_weights(L, 3, bias_scale=0.05), 1, H, W, 3, block=16, radius=16,
+                                    dtype=binding.DC_F32, expiry=6) for L in stacks]
+    want = []
+    for r in make():
+        for t in range(T):
+            tensors = r.step(frames[t])
+        torch.cuda.synchronize()
+        want.append([x.clone() for x in tensors])
+    runners = make()
+    own = runners[1].overlap
+    runners[1].overlap = runners[0].overlap
+    try:
+        for t in range(T):
+            for k, r in enumerate(runners):
+                with torch.cuda.stream(streams[(t // 3 + k) % 2]):
+                    tensors = r.step(frames[t])
+                if t == T - 1:
+                    torch.cuda.synchronize()
+                    for i, (x, y) in enumerate(zip(tensors, want[k])):
+                        assert torch.equal(x, y), (k, i)
+    finally:
+        torch.cuda.synchronize()
+        runners[1].overlap = own
