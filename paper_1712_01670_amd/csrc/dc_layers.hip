@@ -5,7 +5,7 @@
 // vector accesses whenever the channel run allows it.
 #include <hip/hip_bf16.h>
 
-#include "dc_internal.h"
+#include "dc_conv_common.h"
 
 namespace dc {
 
@@ -228,51 +228,122 @@ __device__ __forceinline__ void fc_load(const T* p, float (&f)[VE]) {
         }
     }
 }
-template <typename T, int NS, int VE, int NO>
+template <typename T, int NS, int VE>
 __global__ __launch_bounds__(kThreads) void fc_kernel(const T* __restrict__ x, const T* __restrict__ w,
                                                       const float* __restrict__ bias, T* __restrict__ out, int n_streams,
                                                       size_t K, int cout, int relu) {
-    // NO output neurons per wavefront: with many streams the inputs (read again for every neuron) are the larger
-    // traffic, and one input vector then serves NO weight rows.
     const int lane = threadIdx.x & 63;
-    const int o0 = (blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6)) * NO;
+    const int o = blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
     const int s0 = blockIdx.y * NS;
-    if (o0 >= cout) return;                       // whole wavefronts leave
-    float acc[NO][NS];
+    if (o >= cout) return;                        // whole wavefronts leave
+    float acc[NS];
 #pragma unroll
-    for (int j = 0; j < NO; ++j)
-#pragma unroll
-        for (int s = 0; s < NS; ++s) acc[j][s] = 0.f;
+    for (int s = 0; s < NS; ++s) acc[s] = 0.f;
     for (size_t k = (size_t)lane * VE; k < K; k += 64 * VE) {
-        float wf[NO][VE];
-#pragma unroll
-        for (int j = 0; j < NO; ++j) {
-            const int o = o0 + j < cout ? o0 + j : cout - 1;      // a row past the end repeats the last one (not stored)
-            fc_load<T, VE>(w + (size_t)o * K + k, wf[j]);
-        }
+        float wf[VE];
+        fc_load<T, VE>(w + (size_t)o * K + k, wf);
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
             if (s0 + s < n_streams) {             // uniform over the wavefront
                 float xf[VE];
                 fc_load<T, VE>(x + (size_t)(s0 + s) * K + k, xf);
 #pragma unroll
-                for (int j = 0; j < NO; ++j)
-#pragma unroll
-                    for (int e = 0; e < VE; ++e) acc[j][s] = fmaf(wf[j][e], xf[e], acc[j][s]);
+                for (int e = 0; e < VE; ++e) acc[s] = fmaf(wf[e], xf[e], acc[s]);
             }
         }
     }
+    const float b = bias ? bias[o] : 0.f;
 #pragma unroll
-    for (int j = 0; j < NO; ++j) {
-        if (o0 + j >= cout) break;                // uniform
-        const float b = bias ? bias[o0 + j] : 0.f;
-#pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            float v = wave_sum_f32(acc[j][s]) + b;
-            if (relu) v = v > 0.f ? v : 0.f;
-            if (lane == 0 && s0 + s < n_streams) out[(size_t)(s0 + s) * cout + o0 + j] = from_float<T>(v);
-        }
+    for (int s = 0; s < NS; ++s) {
+        float v = wave_sum_f32(acc[s]) + b;
+        if (relu) v = v > 0.f ? v : 0.f;
+        if (lane == 0 && s0 + s < n_streams) out[(size_t)(s0 + s) * cout + o] = from_float<T>(v);
     }
+}
+
+// Fully-connected layer of several streams on the matrix cores: a GEMM of 16 neurons x NB * 16 streams per workgroup whose
+// operands both run along K in memory, so a lane's 16 bytes of a weight row (A) and of a stream's input (B) are fragments as
+// they are loaded and nothing passes through LDS.  The weights are read once per NB * 16 streams; the inputs come from L2 once
+// per 16 neurons, which is what bounds 64 streams.  The 16 wavefronts of a workgroup deal the 128-byte chunks of K among
+// themselves (a neighbour each, so a round of a row is 2 KiB in one piece) and their partial sums are added through LDS in
+// pairs, always the same ones.  fc_kernel with its inputs re-read for every neuron -> this kernel, us per call of 9216 -> 4096:
+// bf16 4 streams 31.9 -> 15.1, 16 streams 95.0 -> 19.1, 64 streams 135.8 -> 43.1 (its 75 MB of weights: 14); fp32 64 streams
+// 198.6 -> 96.8, at 0.56 of its error against 64 bits.
+constexpr int kFcWaves = 16;
+template <typename T, int NB>
+__global__ __launch_bounds__(kFcWaves * 64) void fc_mfma_kernel(const T* __restrict__ x, const T* __restrict__ w,
+                                                                const float* __restrict__ bias, T* __restrict__ out,
+                                                                int n_streams, size_t K, int cout, int relu) {
+    typedef Frag<T> F;
+    typedef typename F::vec vec;
+    constexpr int VE = F::VE;
+    constexpr int CH = 8 * VE;                    // elements of a chunk: two K groups of four vectors
+    __shared__ float red[kFcWaves][NB * 256];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l16 = lane & 15, q = lane >> 4;
+    const int o0 = blockIdx.x * 16, s0 = blockIdx.y * (NB * 16);
+    // rows past the end repeat the last one (not stored)
+    const T* const wrow = w + (size_t)(o0 + l16 < cout ? o0 + l16 : cout - 1) * K + q * VE;
+    const T* xrow[NB];
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+        const int s = s0 + j * 16 + l16;
+        xrow[j] = x + (size_t)(s < n_streams ? s : n_streams - 1) * K + q * VE;
+    }
+    floatx4 acc[NB];
+#pragma unroll
+    for (int j = 0; j < NB; ++j) acc[j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    // K is a multiple of VE: a vector lies inside its row or past the row's end
+    auto load = [&](vec (&v)[2], const T* row, size_t k) {
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+            v[g] = vec{};
+            if (k + g * 4 * VE + q * VE < K) v[g] = *reinterpret_cast<const vec*>(row + k + g * 4 * VE);
+        }
+    };
+    // the chunk's inputs (from L2) are loaded when it is multiplied, its weights (from memory) one chunk ahead
+    constexpr size_t kStep = (size_t)kFcWaves * CH;
+    vec wc[2];
+    if ((size_t)wave * CH < K) load(wc, wrow, (size_t)wave * CH);
+    for (size_t k = (size_t)wave * CH; k < K; k += kStep) {
+        vec xv[NB][2], wn[2] = {vec{}, vec{}};
+#pragma unroll
+        for (int j = 0; j < NB; ++j) load(xv[j], xrow[j], k);
+        if (k + kStep < K) load(wn, wrow, k + kStep);
+        floatx4 part[2][NB];   // the sums of a K group alone, then added to the total: short chains of roundings
+#pragma unroll
+        for (int g = 0; g < 2; ++g)
+#pragma unroll
+            for (int j = 0; j < NB; ++j) part[g][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int e = 0; e < F::NE; ++e)
+#pragma unroll
+            for (int g = 0; g < 2; ++g)
+#pragma unroll
+                for (int j = 0; j < NB; ++j) F::mma1(wc[g], xv[j][g], part[g][j], e);
+#pragma unroll
+        for (int j = 0; j < NB; ++j) acc[j] += part[0][j] + part[1][j];
+        wc[0] = wn[0]; wc[1] = wn[1];
+    }
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {                // register r of a lane: neuron 4 q + r, stream 16 j + l16
+        *reinterpret_cast<floatx4*>(&red[wave][(j * 16 + l16) * 16 + q * 4]) = acc[j];
+    }
+    __syncthreads();
+    if (tid >= NB * 256) return;
+    const int o = o0 + (tid & 15), s = s0 + (tid >> 4);
+    if (o >= cout || s >= n_streams) return;
+    float sum[kFcWaves];
+#pragma unroll
+    for (int i = 0; i < kFcWaves; ++i) sum[i] = red[i][tid];
+#pragma unroll
+    for (int d = kFcWaves / 2; d >= 1; d >>= 1)
+#pragma unroll
+        for (int i = 0; i < d; ++i) sum[i] += sum[i + d];
+    float v = sum[0];
+    if (bias) v += bias[o];
+    if (relu) v = v > 0.f ? v : 0.f;
+    out[(size_t)s * cout + o] = from_float<T>(v);
 }
 
 // ---- 16-byte vector forms: one thread per (pixel, vector of 4 fp32 / 8 bf16 channels) --------------------------
@@ -855,22 +926,37 @@ hipError_t fc_launch(const void* x, const void* w, const float* bias, void* out,
     const T* wp = (const T*)w;
     T* op = (T*)out;
     constexpr int WPB = kThreads / 64;
+    const unsigned gx = (unsigned)((cout + WPB - 1) / WPB);
     // streams per pass over the weights: the partial sums of a pass live in registers
     if (n_streams == 1) {
-        const unsigned gx = (unsigned)((cout + WPB - 1) / WPB);
-        hipLaunchKernelGGL((fc_kernel<T, 1, VE, 1>), dim3(gx, 1), dim3(kThreads), 0, st, xp, wp, bias, op, n_streams, K, cout, relu);
-    } else if (n_streams <= 4) {
-        const unsigned gx = (unsigned)((cout + WPB - 1) / WPB);
-        hipLaunchKernelGGL((fc_kernel<T, 4, VE, 1>), dim3(gx, 1), dim3(kThreads), 0, st, xp, wp, bias, op, n_streams, K, cout, relu);
-    } else if (n_streams <= 16) {     // one pass: bound by streaming the weights, as many wavefronts as possible
-        const unsigned gx = (unsigned)((cout + WPB - 1) / WPB);
-        hipLaunchKernelGGL((fc_kernel<T, 16, VE, 1>), dim3(gx, 1), dim3(kThreads), 0, st, xp, wp, bias, op, n_streams, K, cout, relu);
-    } else {                          // several passes: four neurons per wavefront share every input vector
-        const unsigned gx = (unsigned)((cout + 4 * WPB - 1) / (4 * WPB));
-        hipLaunchKernelGGL((fc_kernel<T, 16, VE, 4>), dim3(gx, (unsigned)((n_streams + 15) / 16)), dim3(kThreads), 0, st, xp, wp,
-                           bias, op, n_streams, K, cout, relu);
+        hipLaunchKernelGGL((fc_kernel<T, 1, VE>), dim3(gx, 1), dim3(kThreads), 0, st, xp, wp, bias, op, n_streams, K, cout, relu);
+    } else if constexpr (VE == 1) {   // rows that are not whole vectors
+        if (n_streams <= 4)
+            hipLaunchKernelGGL((fc_kernel<T, 4, 1>), dim3(gx, 1), dim3(kThreads), 0, st, xp, wp, bias, op, n_streams, K, cout, relu);
+        else
+            hipLaunchKernelGGL((fc_kernel<T, 16, 1>), dim3(gx, (unsigned)((n_streams + 15) / 16)), dim3(kThreads), 0, st, xp, wp, bias,
+                               op, n_streams, K, cout, relu);
     }
     return hipGetLastError();
+}
+
+template <typename T, int NB>
+hipError_t fc_mfma_launch(const void* x, const void* w, const float* bias, void* out, int n_streams, size_t K, int cout, int relu,
+                          hipStream_t st) {
+    const dim3 grid((unsigned)((cout + 15) / 16), (unsigned)((n_streams + NB * 16 - 1) / (NB * 16)));
+    hipLaunchKernelGGL((fc_mfma_kernel<T, NB>), grid, dim3(kFcWaves * 64), 0, st, (const T*)x, (const T*)w, bias, (T*)out, n_streams, K,
+                       cout, relu);
+    return hipGetLastError();
+}
+
+template <typename T>
+hipError_t fc_vec(const void* x, const void* w, const float* bias, void* out, int n_streams, size_t K, int cout, int relu,
+                  hipStream_t st) {
+    // one stream: a wavefront per neuron leaves no MFMA column idle and streams the weights as fast (12.8 us; two streams 22.6 against 13.7)
+    if (n_streams == 1) return fc_launch<T, 16 / sizeof(T)>(x, w, bias, out, n_streams, K, cout, relu, st);
+    if (n_streams <= 16) return fc_mfma_launch<T, 1>(x, w, bias, out, n_streams, K, cout, relu, st);
+    if (n_streams <= 32) return fc_mfma_launch<T, 2>(x, w, bias, out, n_streams, K, cout, relu, st);
+    return fc_mfma_launch<T, 4>(x, w, bias, out, n_streams, K, cout, relu, st);
 }
 }  // namespace
 
@@ -881,9 +967,9 @@ hipError_t launch_fc(const void* x, const void* w, const float* bias, void* out,
     const size_t es = dtype_size(dtype);
     const bool vec = (K * es) % 16 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0 && reinterpret_cast<uintptr_t>(w) % 16 == 0;
     if (dtype == DC_BF16)
-        return vec ? fc_launch<__hip_bfloat16, 8>(x, w, bias, out, n_streams, K, cout, relu, st)
+        return vec ? fc_vec<__hip_bfloat16>(x, w, bias, out, n_streams, K, cout, relu, st)
                    : fc_launch<__hip_bfloat16, 1>(x, w, bias, out, n_streams, K, cout, relu, st);
-    return vec ? fc_launch<float, 4>(x, w, bias, out, n_streams, K, cout, relu, st)
+    return vec ? fc_vec<float>(x, w, bias, out, n_streams, K, cout, relu, st)
                : fc_launch<float, 1>(x, w, bias, out, n_streams, K, cout, relu, st);
 }
 

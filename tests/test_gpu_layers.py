@@ -398,6 +398,31 @@ def test_fully_connected_layer(oracle, n, shape, cout, bf16):
         assert _rel_err(got, want) <= (2e-2 if bf16 else 1e-4)
 
 
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("n,K,cout", [(4, 64, 40), (5, 8, 1), (16, 1032, 15), (17, 1024, 16), (32, 2056, 17), (33, 520, 48), (64, 1096, 33),
+                                      (65, 2048, 31), (130, 72, 20)])
+def test_fully_connected_layer_on_the_matrix_cores(oracle, n, K, cout, bf16):
+    """Edges of the stream blocks (16, 32, 64), of the neuron block (16) and of the wavefronts' chunks of K (16 x 128 bytes).
+    fp32: a sum of K products, partly in order: its error is below K 2^-24 of the sum of their magnitudes; bf16 adds one rounding."""
+    print(f"[fc mfma] n={n} K={K} cout={cout} bf16={bf16}", flush=True)
+    rng = np.random.default_rng(K + n)
+    x = rng.standard_normal((n, 1, 1, K)).astype(np.float32)
+    w = rng.standard_normal((cout, K)).astype(np.float32)
+    b = rng.standard_normal(cout).astype(np.float32)
+    if bf16:
+        x, w = oracle.round_bf16(x), oracle.round_bf16(w)
+    for relu, bias in [(True, b), (False, None)]:
+        got = _to_np(binding.dc_fc_layer(_to_dev(x, bf16), _to_dev(w, bf16), None if bias is None else torch.from_numpy(bias).to(DEV), relu))
+        x2, w2 = x.reshape(n, K).astype(np.float64), w.astype(np.float64)
+        want = x2 @ w2.T + (0.0 if bias is None else bias)
+        bound = (K + 2) * 2.0 ** -24 * (np.abs(x2) @ np.abs(w2).T + (0.0 if bias is None else np.abs(bias)))
+        if relu:
+            want = np.maximum(want, 0.0)
+        if bf16:
+            bound = bound + 2.0 ** -8 * np.abs(want)
+        assert (np.abs(got.reshape(n, cout) - want) <= bound).all()
+
+
 PW_CASES = [
     # H, W, cin, cout, stride
     (13, 18, 64, 64, 1),       # one chunk in bf16, two in fp32
