@@ -5,6 +5,8 @@
 // vector accesses whenever the channel run allows it.
 #include <hip/hip_bf16.h>
 
+#include <algorithm>
+
 #include "dc_conv_common.h"
 
 namespace dc {
@@ -380,39 +382,85 @@ struct Vec16 {
     }
 };
 
-// Max or average pooling, CV vectors per pixel.
+// Max or average pooling, CV vectors per pixel.  grid.y walks the (stream, output row) pairs, grid.x the Wout * CV vectors of a
+// row, so the only division per vector is one of 32 bits.  The loads of a group of kPoolGroup window columns go out together: a
+// window is otherwise a chain of memory latencies (7x7 over 7x7x1024, 16 bf16 streams: one load at a time 19.0 us).
+constexpr int kPoolGroup = 4;
 template <typename T, bool AVG>
 __global__ __launch_bounds__(kThreads) void pool_vec_kernel(const uint4* __restrict__ in, uint4* __restrict__ out,
-                                                            int n_streams, int Hin, int Win, int CV, int Hout, int Wout,
+                                                            unsigned n_rows, int Hin, int Win, int CV, int Hout, int Wout,
                                                             int k, int s, int p) {
     constexpr int VE = Vec16<T>::VE;
-    const size_t total = (size_t)n_streams * Hout * Wout * CV;
-    size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x;
-    const size_t stride = (size_t)gridDim.x * kThreads;
-    for (; i < total; i += stride) {
-        const int cv = (int)(i % CV);
-        const size_t pix = i / CV;
-        const int x = (int)(pix % Wout);
-        const size_t t = pix / Wout;
-        const int y = (int)(t % Hout);
-        const size_t map = (t / Hout) * Hin;
-        float acc[VE];
+    const unsigned row_vecs = (unsigned)Wout * (unsigned)CV;
+    for (unsigned row = blockIdx.y; row < n_rows; row += gridDim.y) {
+        const unsigned stream = row / (unsigned)Hout;
+        const int y = (int)(row - stream * (unsigned)Hout);
+        const int y0 = max(y * s - p, 0), y1 = min(y * s - p + k, Hin);
+        const uint4* const map = in + (size_t)stream * Hin * Win * CV;
+        uint4* const orow = out + (size_t)row * row_vecs;
+        for (unsigned i = blockIdx.x * kThreads + threadIdx.x; i < row_vecs; i += gridDim.x * kThreads) {
+            const int x = (int)(i / (unsigned)CV), cv = (int)(i - (unsigned)x * (unsigned)CV);
+            const int x0 = max(x * s - p, 0), x1 = min(x * s - p + k, Win);
+            float acc[VE];
 #pragma unroll
-        for (int e = 0; e < VE; ++e) acc[e] = AVG ? 0.f : -INFINITY;
-        const int y0 = max(y * s - p, 0), y1 = min(y * s - p + k, Hin), x0 = max(x * s - p, 0), x1 = min(x * s - p + k, Win);
-        for (int iy = y0; iy < y1; ++iy)
-            for (int ix = x0; ix < x1; ++ix) {
-                float f[VE];
-                Vec16<T>::load(in + ((map + iy) * Win + ix) * CV + cv, f);
+            for (int e = 0; e < VE; ++e) acc[e] = AVG ? 0.f : -INFINITY;
+            for (int iy = y0; iy < y1; ++iy) {
+                const uint4* const line = map + (size_t)iy * Win * CV + cv;
+                for (int ix = x0; ix < x1; ix += kPoolGroup) {
+                    float f[kPoolGroup][VE];
 #pragma unroll
-                for (int e = 0; e < VE; ++e) acc[e] = AVG ? acc[e] + f[e] : fmaxf(acc[e], f[e]);
+                    for (int d = 0; d < kPoolGroup; ++d) Vec16<T>::load(line + (size_t)min(ix + d, x1 - 1) * CV, f[d]);   // past the end: the last one again, not used
+#pragma unroll
+                    for (int d = 0; d < kPoolGroup; ++d)
+                        if (ix + d < x1) {
+#pragma unroll
+                            for (int e = 0; e < VE; ++e) acc[e] = AVG ? acc[e] + f[d][e] : fmaxf(acc[e], f[d][e]);
+                        }
+                }
             }
-        if (AVG) {
-            const int cnt = (y1 - y0) * (x1 - x0);
+            if (AVG) {
+                const int cnt = (y1 - y0) * (x1 - x0);
 #pragma unroll
-            for (int e = 0; e < VE; ++e) acc[e] = cnt > 0 ? acc[e] / (float)cnt : 0.f;
+                for (int e = 0; e < VE; ++e) acc[e] = cnt > 0 ? acc[e] / (float)cnt : 0.f;
+            }
+            Vec16<T>::store(orow + i, acc);
         }
-        Vec16<T>::store(out + i, acc);
+    }
+}
+
+// Max-pooling over 3x3 windows that all reach into the map (padding below 3), in the manner of pool_vec_kernel with the nine
+// loads of a window in flight together.  A tap outside the map reads the nearest one of the window's own inside it, which a
+// maximum does not see.  55x55x96 stride 1, 64 bf16 streams: 39.0 us with three 64-bit divisions per vector and a load at a
+// time, 24.3 now; 27x27x256: 24.8 -> 15.6.
+template <typename T>
+__global__ __launch_bounds__(kThreads) void maxpool3x3_vec_kernel(const uint4* __restrict__ in, uint4* __restrict__ out,
+                                                                  unsigned n_rows, int Hin, int Win, int CV, int Hout, int Wout,
+                                                                  int s, int p) {
+    constexpr int VE = Vec16<T>::VE;
+    const unsigned row_vecs = (unsigned)Wout * (unsigned)CV;
+    for (unsigned row = blockIdx.y; row < n_rows; row += gridDim.y) {
+        const unsigned stream = row / (unsigned)Hout;
+        const int y = (int)(row - stream * (unsigned)Hout);
+        const uint4* const map = in + (size_t)stream * Hin * Win * CV;
+        size_t line[3];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) line[d] = (size_t)min(max(y * s - p + d, 0), Hin - 1) * Win;
+        uint4* const orow = out + (size_t)row * row_vecs;
+        for (unsigned i = blockIdx.x * kThreads + threadIdx.x; i < row_vecs; i += gridDim.x * kThreads) {
+            const int x = (int)(i / (unsigned)CV), cv = (int)(i - (unsigned)x * (unsigned)CV);
+            float f[9][VE];
+#pragma unroll
+            for (int t = 0; t < 9; ++t)
+                Vec16<T>::load(map + (line[t / 3] + min(max(x * s - p + t % 3, 0), Win - 1)) * CV + cv, f[t]);
+            float acc[VE];
+#pragma unroll
+            for (int e = 0; e < VE; ++e) acc[e] = -INFINITY;
+#pragma unroll
+            for (int t = 0; t < 9; ++t)
+#pragma unroll
+                for (int e = 0; e < VE; ++e) acc[e] = fmaxf(acc[e], f[t][e]);
+            Vec16<T>::store(orow + i, acc);
+        }
     }
 }
 
@@ -589,17 +637,29 @@ __global__ __launch_bounds__(kThreads) void frame_to_tensor_px_kernel(const uint
     }
 }
 
+// x^-beta of an LRN denominator.  The exponent of the published models, 3/4, is a product of two hardware roots (each good to
+// one unit in the last place, so it is also the more accurate form); others go through the base-2 logarithm.
+template <bool B34>
+__device__ __forceinline__ float lrn_power(float x, float beta) {
+    if constexpr (B34) {
+        const float r = __builtin_amdgcn_rsqf(x);
+        return r * __builtin_amdgcn_sqrtf(r);
+    }
+    return __powf(x, -beta);
+}
+
 // LRN over channels with radius R <= VE: the thread's vector and its two neighbours hold every channel of the window.
-template <typename T, int R>
+// Should be bound by memory; what it spent its time on was the arithmetic around it (a 64-bit division per vector, the power
+// as logarithm and exponential), so the vectors of a launch are counted in 32 bits.  55x55x96, 64 bf16 streams: 73.7 -> 16.2 us
+// (its 74 MB at the 5.5 TB/s of a large copy: 13.5); 56x56x192, 16 streams: 36.1 -> 9.4.  Exponents other than 3/4: unchanged.
+template <typename T, int R, bool B34>
 __global__ __launch_bounds__(kThreads) void lrn_vec_kernel(const uint4* __restrict__ in, uint4* __restrict__ out,
-                                                           size_t n_pixels, int CV, float alpha_n, float beta, float kappa) {
+                                                           unsigned total, unsigned CV, float alpha_n, float beta, float kappa) {
     constexpr int VE = Vec16<T>::VE;
     static_assert(R <= VE, "window inside the neighbouring vectors");
-    const size_t total = n_pixels * CV;
-    size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x;
-    const size_t stride = (size_t)gridDim.x * kThreads;
-    for (; i < total; i += stride) {
-        const int cv = (int)(i % CV);
+    const unsigned stride = gridDim.x * kThreads;
+    for (unsigned i = blockIdx.x * kThreads + threadIdx.x; i < total; i += stride) {
+        const unsigned cv = i % CV;
         float f[3][VE];
         Vec16<T>::load(in + i, f[1]);
         if (cv > 0) Vec16<T>::load(in + i - 1, f[0]);
@@ -617,7 +677,7 @@ __global__ __launch_bounds__(kThreads) void lrn_vec_kernel(const uint4* __restri
             float S = 0.f;
 #pragma unroll
             for (int d = -R; d <= R; ++d) S += sq[VE + e + d];
-            o[e] = f[1][e] * __powf(kappa + alpha_n * S, -beta);
+            o[e] = f[1][e] * lrn_power<B34>(kappa + alpha_n * S, beta);
         }
         Vec16<T>::store(out + i, o);
     }
@@ -756,7 +816,8 @@ hipError_t launch_pool(const void* in, void* out, int n_streams, int Hin, int Wi
     const int Hout = (Hin + 2 * p - k) / s + 1, Wout = (Win + 2 * p - k) / s + 1;
     const size_t n = (size_t)n_streams * Hout * Wout * C;
     if (n == 0) return hipSuccess;
-    if ((C * dtype_size(dtype)) % 16 == 0 && reinterpret_cast<uintptr_t>(in) % 16 == 0 && reinterpret_cast<uintptr_t>(out) % 16 == 0) {
+    if ((C * dtype_size(dtype)) % 16 == 0 && reinterpret_cast<uintptr_t>(in) % 16 == 0 && reinterpret_cast<uintptr_t>(out) % 16 == 0 &&
+        (size_t)Wout * C < 0x7fffffffull) {
         const int cv = (int)(C * dtype_size(dtype) / 16);
         const size_t nv = (size_t)n_streams * Hout * Wout * cv;
         if (!AVG && k == 2 && s == 2 && p == 0 && (size_t)n_streams * Hout <= 65535 && (size_t)Hin * Win * cv < 0x7fffffffull) {
@@ -769,12 +830,26 @@ hipError_t launch_pool(const void* in, void* out, int n_streams, int Hin, int Wi
                                    Win, cv, Hout, Wout);
             return hipGetLastError();
         }
-        if (dtype == DC_BF16)
-            hipLaunchKernelGGL((pool_vec_kernel<__hip_bfloat16, AVG>), dim3(grid_for(nv)), dim3(kThreads), 0, st,
-                               (const uint4*)in, (uint4*)out, n_streams, Hin, Win, cv, Hout, Wout, k, s, p);
-        else
-            hipLaunchKernelGGL((pool_vec_kernel<float, AVG>), dim3(grid_for(nv)), dim3(kThreads), 0, st, (const uint4*)in,
-                               (uint4*)out, n_streams, Hin, Win, cv, Hout, Wout, k, s, p);
+        // (stream, row) pairs are counted in 32 bits: larger batches go out in several launches of whole streams
+        const int per_launch = (int)std::min<size_t>((size_t)n_streams, std::max<size_t>(1, 0x7fffffffu / (size_t)Hout));
+        const size_t in_map = (size_t)Hin * Win * cv, out_map = (size_t)Hout * Wout * cv;
+        for (int s0 = 0; s0 < n_streams; s0 += per_launch) {
+            const unsigned rows = (unsigned)std::min(per_launch, n_streams - s0) * (unsigned)Hout;
+            const size_t gx = ((size_t)Wout * cv + kThreads - 1) / kThreads;
+            const dim3 grid((unsigned)std::min<size_t>(gx, 65535), std::min(rows, 65535u));
+            const uint4* const ip = (const uint4*)in + (size_t)s0 * in_map;
+            uint4* const op = (uint4*)out + (size_t)s0 * out_map;
+            if (!AVG && k == 3 && p < 3) {
+                if (dtype == DC_BF16)
+                    hipLaunchKernelGGL(maxpool3x3_vec_kernel<__hip_bfloat16>, grid, dim3(kThreads), 0, st, ip, op, rows, Hin, Win, cv, Hout, Wout, s, p);
+                else
+                    hipLaunchKernelGGL(maxpool3x3_vec_kernel<float>, grid, dim3(kThreads), 0, st, ip, op, rows, Hin, Win, cv, Hout, Wout, s, p);
+            } else if (dtype == DC_BF16) {
+                hipLaunchKernelGGL((pool_vec_kernel<__hip_bfloat16, AVG>), grid, dim3(kThreads), 0, st, ip, op, rows, Hin, Win, cv, Hout, Wout, k, s, p);
+            } else {
+                hipLaunchKernelGGL((pool_vec_kernel<float, AVG>), grid, dim3(kThreads), 0, st, ip, op, rows, Hin, Win, cv, Hout, Wout, k, s, p);
+            }
+        }
         return hipGetLastError();
     }
     if (dtype == DC_BF16)
@@ -862,11 +937,18 @@ hipError_t launch_lrn(const void* in, void* out, int n_streams, int H, int W, in
         reinterpret_cast<uintptr_t>(out) % 16 == 0) {
         const int cv = (int)(C * dtype_size(dtype) / 16);
         const size_t px = (size_t)n_streams * H * W;
-        const dim3 grid(grid_for(px * cv));
-#define DC_LRN_VEC(T, R) hipLaunchKernelGGL((lrn_vec_kernel<T, R>), grid, dim3(kThreads), 0, st, (const uint4*)in, \
-                                            (uint4*)out, px, cv, alpha_n, beta, kappa)
-        if (dtype == DC_BF16) { if (r == 1) DC_LRN_VEC(__hip_bfloat16, 1); else DC_LRN_VEC(__hip_bfloat16, 2); }
-        else { if (r == 1) DC_LRN_VEC(float, 1); else DC_LRN_VEC(float, 2); }
+        const size_t per_launch = std::max<size_t>(1, 0x40000000u / (size_t)cv);      // pixels: a launch counts its vectors in 32 bits
+        for (size_t p0 = 0; p0 < px; p0 += per_launch) {
+            const unsigned total = (unsigned)(std::min(per_launch, px - p0) * cv);
+            const uint4* const ip = (const uint4*)in + p0 * cv;
+            uint4* const op = (uint4*)out + p0 * cv;
+            const dim3 grid(grid_for(total));
+#define DC_LRN_B(T, R, B34) hipLaunchKernelGGL((lrn_vec_kernel<T, R, B34>), grid, dim3(kThreads), 0, st, ip, op, total, (unsigned)cv, alpha_n, beta, kappa)
+#define DC_LRN_VEC(T, R) do { if (beta == 0.75f) DC_LRN_B(T, R, true); else DC_LRN_B(T, R, false); } while (0)
+            if (dtype == DC_BF16) { if (r == 1) DC_LRN_VEC(__hip_bfloat16, 1); else DC_LRN_VEC(__hip_bfloat16, 2); }
+            else { if (r == 1) DC_LRN_VEC(float, 1); else DC_LRN_VEC(float, 2); }
+        }
+#undef DC_LRN_B
 #undef DC_LRN_VEC
         return hipGetLastError();
     }

@@ -423,6 +423,46 @@ def test_fully_connected_layer_on_the_matrix_cores(oracle, n, K, cout, bf16):
         assert (np.abs(got.reshape(n, cout) - want) <= bound).all()
 
 
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("H,W,ch,k,s,p", [(13, 17, 24, 3, 1, 1), (14, 9, 8, 3, 2, 0), (5, 6, 520, 3, 2, 2), (1, 1, 8, 3, 1, 1), (2, 7, 2056, 3, 3, 2),
+                                          (7, 7, 1024, 7, 1, 0), (9, 5, 16, 5, 1, 2), (8, 11, 8, 4, 3, 1), (11, 12, 40, 9, 2, 4)])
+def test_pooling_windows(oracle, H, W, ch, k, s, p, bf16):
+    """3x3 windows on every side of the padding, windows with whole and partial groups of columns, rows longer than a workgroup;
+    values of the type's extremes and infinities."""
+    print(f"[pool] {H}x{W}x{ch} k={k} s={s} p={p} bf16={bf16}", flush=True)
+    rng = np.random.default_rng(H * 100 + ch)
+    x = (rng.standard_normal((3, H, W, ch)) * 4).astype(np.float32)
+    if bf16:
+        x = oracle.round_bf16(x)
+    got = _to_np(binding.dc_avgpool_layer(_to_dev(x, bf16), k, s, p))
+    for i in range(3):
+        assert _rel_err(got[i], oracle.avgpool(x[i], k, s, p, bf16=bf16)) <= (2e-2 if bf16 else 1e-4)
+    x[0, 0, 0, :4] = [-np.inf, np.inf, -3.3895314e38, 3.3895314e38]
+    x[1, :, :, 0] = -np.inf
+    x[2, :, :, 1] = -3.3895314e38
+    if bf16:
+        x = oracle.round_bf16(x)
+    got = _to_np(binding.dc_maxpool_layer(_to_dev(x, bf16), k, s, p))
+    for i in range(3):
+        assert np.array_equal(got[i], oracle.maxpool(x[i], k, s, p))
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("ch,size,beta,kappa", [(8, 5, 0.75, 2.0), (96, 5, 0.75, 1.0), (24, 3, 0.75, 1e-3), (40, 5, 0.5, 1.0)])
+def test_lrn_power(oracle, ch, size, beta, kappa, bf16):
+    """The exponent 3/4 (two roots) and another one (logarithm).  fp32: the sum of at most five squares, two roots and two
+    products are each off by at most a few 2^-24; the logarithm form by |beta log2 x| 2^-22 more."""
+    print(f"[lrn] ch={ch} size={size} beta={beta} kappa={kappa} bf16={bf16}", flush=True)
+    rng = np.random.default_rng(ch)
+    x = (rng.standard_normal((2, 9, 11, ch)) * np.exp(rng.uniform(-6, 6, (2, 9, 11, 1)))).astype(np.float32)
+    if bf16:
+        x = oracle.round_bf16(x)
+    got = _to_np(binding.dc_lrn_layer(_to_dev(x, bf16), size, 0.7, beta, kappa, False))
+    want = np.stack([oracle.lrn(x[i], size, 0.7, beta, kappa, False, bf16=bf16) for i in range(2)]).astype(np.float64)
+    rel = 2.0 ** -7 if bf16 else (16 * 2.0 ** -24 if beta == 0.75 else 40 * 2.0 ** -24)
+    assert (np.abs(got - want) <= rel * np.abs(want)).all()
+
+
 PW_CASES = [
     # H, W, cin, cout, stride
     (13, 18, 64, 64, 1),       # one chunk in bf16, two in fp32
