@@ -1,6 +1,7 @@
 // Cache-aware convolution (Section 5 "Reuse", steps 2-3), the kernels for the common layer shape: 3x3 taps,
 // stride 1.  Three kernels share this file:
-//   conv_fast_kernel   channel counts that are whole 64-byte rows, 64 or 128 output channels per workgroup;
+//   conv_fast_kernel   channel counts that are whole 64-byte rows, 64 or 128 output channels per workgroup (5x5 taps
+//                      as well, in bf16);
 //   conv_regw_kernel   64 input channels in bf16 and many units: persistent, weights in registers (see there);
 //   conv_first_kernel  input pixels of one 16-byte vector (the padded first layer), nothing staged (see there).
 //
@@ -11,9 +12,9 @@
 //
 //   workgroup  = g units (g <= WM*UPW, a launch parameter) x NT channels x a range of channel chunks
 //   wavefront  = UPW units (slots wave_m, wave_m + WM, ...) x NBW 16-channel blocks
-//   stage      = one kernel row (3 taps) x one channel chunk (KC channels)
+//   stage      = one kernel row (3 or 5 taps) x one channel chunk (KC channels)
 //
-// LDS: the patch of a unit is 6 lines of 8 row slots (6 used), one row = KC channels = RB bytes.  Chunk c
+// LDS: the patch of a unit is 6 lines of 8 row slots (6 used; 5x5 taps: 8 lines, all used), one row = KC channels = RB bytes.  Chunk c
 // (16 bytes) of the row at (line py, slot px) sits at chunk position c ^ sw(py, px), of weight row r at
 // c ^ (r / 2) % NVEC.  sw = (2 py + px / 4) % 4 for 64-byte rows, (py % 4) * 2 + (px % 4) / 2 for 128-byte rows:
 // these are the swizzles for which SQ_LDS_BANK_CONFLICT stays at zero for every tap (a 16-byte read of a
@@ -132,7 +133,7 @@ __global__ __launch_bounds__(WM* WN * 64) void conv_fast_kernel(ConvParams P) {
     constexpr int PBYTES = P_INSTR * 1024;
     constexpr int WBYTES = W_INSTR * 1024;
     constexpr int NS = KSZ * GPC;               // K steps per stage
-    static_assert(KSZ == 3 && RB >= 64 && RB <= 128 && (G * PR) % RPI == 0 && (KSZ * NT) % RPI == 0, "shape");
+    static_assert((KSZ == 3 || KSZ == 5) && RB >= 64 && RB <= 128 && (G * PR) % RPI == 0 && (KSZ * NT) % RPI == 0, "shape");
 
     extern __shared__ __align__(16) unsigned char smem[];
     const FastHeader<G> H(smem);
@@ -235,11 +236,13 @@ __global__ __launch_bounds__(WM* WN * 64) void conv_fast_kernel(ConvParams P) {
     };
 
     // ---- read side: byte address of this lane's row and chunk for every tap and K group
-    int paddr[KSZ * KSZ][GPC];
+    // (the swizzle of 64-byte rows repeats every two lines: kernel row ky is row ky % 2 plus an immediate offset)
+    constexpr int PK = RB == 64 ? 2 : KSZ;      // kernel rows with addresses of their own
+    int paddr[PK * KSZ][GPC];
     {
         const int oy = l16 >> 2, ox = l16 & 3;
 #pragma unroll
-        for (int t = 0; t < KSZ * KSZ; ++t) {
+        for (int t = 0; t < PK * KSZ; ++t) {
             const int py = oy + t / KSZ, px = ox + t % KSZ;
             const int sw = patch_swizzle<RB>(py, px);
 #pragma unroll
@@ -265,8 +268,8 @@ __global__ __launch_bounds__(WM* WN * 64) void conv_fast_kernel(ConvParams P) {
     for (int j = 0; j < NBW; ++j)
         bias[j] = P.bias ? *reinterpret_cast<const floatx4*>(P.bias + chan + j * 16) : floatx4{0.f, 0.f, 0.f, 0.f};
 
-    // Loads of stage s = 3 c + ky (c counts this workgroup's chunks): the weights of kernel row ky and a
-    // third of a patch: stage 3c+1, 3c+2 and 3c+3 bring parts 0, 1 and 2 of chunk c+1.  They are issued
+    // Loads of stage s = KSZ c + ky (c counts this workgroup's chunks): the weights of kernel row ky and one of KSZ
+    // parts of a patch: 3x3 stages 3c+1, 3c+2 and 3c+3 bring parts 0, 1 and 2 of chunk c+1.  They are issued
     // two stages ahead, right after the barrier that ends the reads of the buffers they overwrite.
     const int n_ch = ce - cb;
     auto issue_stage = [&](int c, int ky, int s) {     // ky is a compile-time constant at every call
@@ -282,7 +285,7 @@ __global__ __launch_bounds__(WM* WN * 64) void conv_fast_kernel(ConvParams P) {
         vec x[2][NU > 0 ? NU : 1], w[2][NBW];
         auto frag = [&](int pbuf, int wbuf, int ky, int st, int b) {
             const int kx = st / GPC, g = st % GPC;
-            const unsigned char* xp = patch0 + pbuf * PBYTES + paddr[ky * KSZ + kx][g];
+            const unsigned char* xp = patch0 + pbuf * PBYTES + paddr[ky % PK * KSZ + kx][g] + (ky - ky % PK) * (PWP * RB);
 #pragma unroll
             for (int u = 0; u < NU; ++u) x[b][u] = *reinterpret_cast<const vec*>(xp + u * (WM * PR * RB));
             const unsigned char* wp = wts0 + wbuf * WBYTES + waddr[g] + kx * (NT * RB);
@@ -320,8 +323,8 @@ __global__ __launch_bounds__(WM* WN * 64) void conv_fast_kernel(ConvParams P) {
                 // its last fragments of this stage in registers and the loads of the next stage are in LDS.
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
                 __syncthreads();
-                if (ky == 0) issue_stage(c, 2, sidx + 2);
-                else issue_stage(c + 1, ky - 1, sidx + 2);
+                if (ky + 2 < KSZ) issue_stage(c, ky + 2, sidx + 2);
+                else issue_stage(c + 1, ky + 2 - KSZ, sidx + 2);
                 if (ky + 1 < KSZ) frag(pbuf, (sidx + 1) & 1, ky + 1, 0, ((ky + 1) * NS) & 1);
                 else if (c + 1 < n_ch) frag(pbuf ^ 1, (sidx + 1) & 1, 0, 0, (KSZ * NS) & 1);
                 __builtin_amdgcn_sched_barrier(0);
@@ -1099,16 +1102,16 @@ constexpr int kNumGeom = 4;
 constexpr Geom kGeom[kNumGeom] = {{2, 4, 1, 8}, {4, 2, 4, 4}, {4, 2, 2, 4}, {6, 2, 4, 3}};
 inline int geom_nt(int geom) { return kGeom[geom].wn * kGeom[geom].nbw * 16; }
 
-template <typename T, int KC, int U, int WM, int WN, int NBW>
+template <typename T, int KC, int U, int WM, int WN, int NBW, int KSZ = 3>
 hipError_t fast_launch_one(dim3 grid, size_t lds, hipStream_t st, const ConvParams& P) {
-    auto fn = conv_fast_kernel<T, 3, KC, U, WM, WN, NBW>;
+    auto fn = conv_fast_kernel<T, KSZ, KC, U, WM, WN, NBW>;
     static std::atomic<bool> raised{false};   // per instantiation: the attribute is raised once, to the CU's whole LDS
     if (lds > 64 * 1024 && !raised.load()) {
         hipError_t a = hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes);
         if (a != hipSuccess) return a;
         raised.store(true);
     }
-    hipLaunchKernelGGL((conv_fast_kernel<T, 3, KC, U, WM, WN, NBW>), grid, dim3(WM * WN * 64), lds, st, P);
+    hipLaunchKernelGGL((conv_fast_kernel<T, KSZ, KC, U, WM, WN, NBW>), grid, dim3(WM * WN * 64), lds, st, P);
     return hipGetLastError();
 }
 template <typename T, int KC>
@@ -1153,9 +1156,27 @@ hipError_t fast_launch(bool bf16, int geom, int kci, int upw, dim3 grid, size_t 
     return kci ? fast_launch_narrow<float, 32>(upw, grid, lds, st, P) : fast_launch_narrow<float, 16>(upw, grid, lds, st, P);
 }
 
-size_t fast_lds_bytes(int geom, int kci, int upw) {
+// 5x5 layers (bf16): a unit's patch is 8 x 8 rows and a stage holds five taps, so the wide arrangement has room for two
+// units per wavefront (145 KB) and wide64 for three.  Against the general kernel, which computes every LDS address of its
+// inner loop, us per layer: 27x27 96->256 on 64 streams 182 -> 96, on 16 streams 71 -> 40, 56x56 128->128 on 8 streams
+// 85 -> 46, and no smaller one measured was slower, so every such layer with whole 64-byte rows comes here.  fp32 stays on
+// the general kernel (bound by the MFMA stream there, and its two half sums round less).
+hipError_t fast_launch5(int geom, int upw, dim3 grid, size_t lds, hipStream_t st, const ConvParams& P) {
+    typedef __hip_bfloat16 B;
+    if (geom == 1) return upw == 1 ? fast_launch_one<B, 32, 1, 4, 2, 4, 5>(grid, lds, st, P) : fast_launch_one<B, 32, 2, 4, 2, 4, 5>(grid, lds, st, P);
+    return upw == 1 ? fast_launch_one<B, 32, 1, 4, 2, 2, 5>(grid, lds, st, P)
+         : upw == 2 ? fast_launch_one<B, 32, 2, 4, 2, 2, 5>(grid, lds, st, P) : fast_launch_one<B, 32, 3, 4, 2, 2, 5>(grid, lds, st, P);
+}
+// instantiations: k = 3 or 5, arrangement, chunk index, units per wavefront
+bool fast_built(int k, bool bf16, int geom, int kci, int upw) {
+    if (upw < 1 || upw > kGeom[geom].max_upw || (geom != 0 && !bf16)) return false;
+    if (k == 5) return bf16 && kci == 0 && ((geom == 1 && upw <= 2) || (geom == 2 && upw <= 3));
+    return geom != 3 || (upw == 3 && kci == 0);      // one of the tall arrangement
+}
+
+size_t fast_lds_bytes(int k, int geom, int kci, int upw) {
     const int rpi = 16 >> kci;            // rows per load instruction: RB = 64 << kci
-    return kHeaderBytes + 2 * (size_t)(kGeom[geom].wm * upw * 48 / rpi) * 1024 + 2 * (size_t)(3 * geom_nt(geom) / rpi) * 1024;
+    return kHeaderBytes + 2 * (size_t)(kGeom[geom].wm * upw * (3 + k) * 8 / rpi) * 1024 + 2 * (size_t)(k * geom_nt(geom) / rpi) * 1024;
 }
 
 struct FastChoice { int g, ks, kci; double cost; int geom; };
@@ -1180,7 +1201,7 @@ FastChoice choose_fast(const ConvLaunch& c, long n_units, long n_cap, size_t scr
     // bytes per clock and CU from L2 to LDS, fixed cycles per stage / workgroup / reduction launch (fitted to sweeps)
     constexpr double bw = 32, stage_fix = 250, wg_fix = 4500, red_fix = 13000, occ1_penalty = 1.08, lds_cap_kb = 160;
     const bool bf16 = c.dtype == DC_BF16;
-    const int esz = bf16 ? 2 : 4, kg = bf16 ? 32 : 16;
+    const int esz = bf16 ? 2 : 4, kg = bf16 ? 32 : 16, k = c.k;
     FastChoice best{0, 0, 0, 1e300, 0};
     for (int geom = 0; geom < kNumGeom; ++geom) {
         const Geom& G = kGeom[geom];
@@ -1195,9 +1216,9 @@ FastChoice choose_fast(const ConvLaunch& c, long n_units, long n_cap, size_t scr
             const int n_chunks = c.Cin / kc, gpc = 1 << kci, rb = kc * esz;
             for (int g = 1; g <= G.wm * G.max_upw; ++g) {
                 const int upw = (g + G.wm - 1) / G.wm;
-                if (geom == 3 && (upw != 3 || kci != 0)) continue;      // the one instantiation of the tall arrangement
-                if (fast_lds_bytes(geom, kci, upw) > 160 * 1024) continue;
-                if (geom == 0 && !bf16 && fast_lds_bytes(geom, kci, upw) > (size_t)(lds_cap_kb * 1024)) continue;
+                if (!fast_built(k, bf16, geom, kci, upw)) continue;
+                if (fast_lds_bytes(k, geom, kci, upw) > 160 * 1024) continue;
+                if (geom == 0 && !bf16 && fast_lds_bytes(k, geom, kci, upw) > (size_t)(lds_cap_kb * 1024)) continue;
                 const long groups = (n_units + g - 1) / g;
                 int last_cps = 0;
                 for (int ks = 1; ks <= n_chunks && ks <= 64; ++ks) {
@@ -1214,17 +1235,17 @@ FastChoice choose_fast(const ConvLaunch& c, long n_units, long n_cap, size_t scr
                                  : G.wm == 6 ? (nu(0) + nu(2) + nu(4) > nu(1) + nu(3) + nu(5) ? nu(0) + nu(2) + nu(4) : nu(1) + nu(3) + nu(5))
                                              : (nu(0) + nu(2) > nu(1) + nu(3) ? nu(0) + nu(2) : nu(1) + nu(3));
                     // (the tall arrangement needs 5 % more per unit than the wide one when both fill their rounds: measured)
-                    const double mfma = (geom == 3 ? 1.18 : 1.12) * (bf16 ? 16.0 : 128.0) * su * G.nbw * 3 * gpc;
-                    const double ldsr = (double)(G.wm * G.wn) * (upw + G.nbw) * 3 * gpc * 4 * 1.3;
-                    const double load = ((double)g * 36 * rb / 3 + 3.0 * nt * rb) / bw;
+                    const double mfma = (geom == 3 ? 1.18 : 1.12) * (bf16 ? 16.0 : 128.0) * su * G.nbw * k * gpc;
+                    const double ldsr = (double)(G.wm * G.wn) * (upw + G.nbw) * k * gpc * 4 * 1.3;
+                    const double load = ((double)g * (3 + k) * (3 + k) * rb / k + (double)k * nt * rb) / bw;
                     double stage = mfma > load ? mfma : load;
                     if (ldsr > stage) stage = ldsr;
-                    const double work = cps * 3 * stage;
-                    const double fixed = wg_fix + 400.0 * upw * G.nbw + cps * 3 * stage_fix;
+                    const double work = cps * k * stage;
+                    const double fixed = wg_fix + 400.0 * upw * G.nbw + cps * k * stage_fix;
                     const long wgs = groups * R * ks_eff;
                     const long per_cu = (wgs + 255) / 256;
                     const int vgprs = (kci ? 64 : 44) + (geom ? 10 * G.nbw * upw + 6 * G.nbw : (kci ? 18 : 16) * upw);
-                    long occ = (long)(160 * 1024 / fast_lds_bytes(geom, kci, upw));
+                    long occ = (long)(160 * 1024 / fast_lds_bytes(k, geom, kci, upw));
                     if (occ > 512 / vgprs / 2) occ = 512 / vgprs / 2;
                     if (occ > 4) occ = 4;
                     if (occ < 1) occ = 1;
@@ -1257,6 +1278,11 @@ void conv_fast_kernel_name(int id, char* buf, size_t n) {
     if (id == 129) { snprintf(buf, n, "conv_fast_kernel<__hip_bfloat16, 3, 32, 3, 6, 2, 4>"); return; }     // the tall arrangement
     if (id == 127 || id == 128 || id == 108 || id == 109) {      // 108 + bf16 (64 x 64 tile), 127 + bf16 (128 x 128): conv_pw_kernel (1x1)
         snprintf(buf, n, "conv_pw_kernel<%s, %d>", id == 109 || id == 128 ? "__hip_bfloat16" : "float", id >= 127 ? 4 : 2);
+        return;
+    }
+    if (id >= 132) {  // 132 + arrangement * 8 + UPW - 1: 5x5 layers
+        const Geom& G = kGeom[(id - 132) / 8 % kNumGeom];
+        snprintf(buf, n, "conv_fast_kernel<__hip_bfloat16, 5, 32, %d, %d, %d, %d>", (id - 132) % 8 + 1, G.wm, G.wn, G.nbw);
         return;
     }
     if (id >= 110) {  // 110 + (arrangement - 1) * 8 + kci * 4 + UPW - 1: the wide bf16 arrangements
@@ -1412,12 +1438,12 @@ bool launch_conv_fast(const ConvLaunch& c, long n_cap, long n_units, hipStream_t
             return true;
         }
     }
-    if (!enabled || c.k != 3 || c.s != 1 || c.Cout % geom_nt(0) != 0 || c.Cin % (64 / esz) != 0) return false;
+    if (!enabled || (c.k != 3 && !(c.k == 5 && c.dtype == DC_BF16 && !torus)) || c.s != 1 || c.Cout % geom_nt(0) != 0 || c.Cin % (64 / esz) != 0) return false;
     if (reinterpret_cast<uintptr_t>(c.in) % 16 || reinterpret_cast<uintptr_t>(c.w) % 16) return false;
     if (reinterpret_cast<uintptr_t>(c.out) % 16 || (c.bias && reinterpret_cast<uintptr_t>(c.bias) % 16)) return false;
     if ((double)c.n_streams * c.Hout * c.Wout * c.Cout >= 2147483648.0) return false;      // 32-bit output offsets
     // 64 input channels in bf16 and enough units to keep persistent workgroups busy: the weights go to registers
-    if (c.dtype == DC_BF16 && c.Cin == 64 && c.relu != 2 && (!torus || c.n_streams <= kRegwTorusStreams) && (g_tune[0] == 3 || (g_tune[0] < 0 && g_tune[1] < 0 && n_units >= 4096))) {
+    if (c.dtype == DC_BF16 && c.k == 3 && c.Cin == 64 && c.relu != 2 && (!torus || c.n_streams <= kRegwTorusStreams) && (g_tune[0] == 3 || (g_tune[0] < 0 && g_tune[1] < 0 && n_units >= 4096))) {
         ConvParams P{};
         P.in = c.in; P.w = c.w; P.bias = c.bias; P.out = c.out;
         P.Hin = c.Hin; P.Win = c.Win; P.Cin = c.Cin; P.Hout = c.Hout; P.Wout = c.Wout; P.Cout = c.Cout;
@@ -1445,20 +1471,20 @@ bool launch_conv_fast(const ConvLaunch& c, long n_cap, long n_units, hipStream_t
     if (scratch > kConvScratchBytes) scratch = kConvScratchBytes;
     // The model costs about 2 us per call on the host; the same layers come back every frame with the same or a
     // recently seen unit count, so its answers are kept in a small direct-mapped table.
-    struct Memo { int dtype, cin, cout, tune[4]; long n_units, n_cap; size_t scratch; FastChoice ch; bool used; };
+    struct Memo { int dtype, k, cin, cout, tune[4]; long n_units, n_cap; size_t scratch; FastChoice ch; bool used; };
     static Memo memo[256];
     static std::mutex memo_mutex;
     FastChoice ch;
     {
         std::lock_guard<std::mutex> guard(memo_mutex);
-        Memo& slot = memo[((unsigned long)n_units * 2654435761ul + (unsigned)c.Cin * 40503u + (unsigned)c.Cout * 97u + (unsigned)c.dtype) % 256];
-        if (slot.used && slot.dtype == c.dtype && slot.cin == c.Cin && slot.cout == c.Cout && slot.n_units == n_units && slot.n_cap == n_cap &&
+        Memo& slot = memo[((unsigned long)n_units * 2654435761ul + (unsigned)c.Cin * 40503u + (unsigned)c.Cout * 97u + (unsigned)c.dtype + (unsigned)c.k * 31u) % 256];
+        if (slot.used && slot.dtype == c.dtype && slot.k == c.k && slot.cin == c.Cin && slot.cout == c.Cout && slot.n_units == n_units && slot.n_cap == n_cap &&
             slot.scratch == scratch && slot.tune[0] == g_tune[0] && slot.tune[1] == g_tune[1] && slot.tune[2] == g_tune[2] &&
             slot.tune[3] == g_tune[3]) {
             ch = slot.ch;
         } else {
             ch = choose_fast(c, n_units, n_cap, scratch, g_tune[0] == 4 ? 3 : g_tune[0]);    // tuning 3 names another kernel
-            slot = Memo{c.dtype, c.Cin, c.Cout, {g_tune[0], g_tune[1], g_tune[2], g_tune[3]}, n_units, n_cap, scratch, ch, true};
+            slot = Memo{c.dtype, c.k, c.Cin, c.Cout, {g_tune[0], g_tune[1], g_tune[2], g_tune[3]}, n_units, n_cap, scratch, ch, true};
         }
     }
     if (g_tune[1] > 0 && ch.g > 0) {    // forced shape within the arrangement the model picked
@@ -1466,8 +1492,8 @@ bool launch_conv_fast(const ConvLaunch& c, long n_cap, long n_units, hipStream_t
         const Geom& G = kGeom[ch.geom];
         const int kc = (c.dtype == DC_BF16 ? 32 : 16) << f_kci;
         const int upw = (f_g + G.wm - 1) / G.wm;
-        if (f_g <= G.wm * G.max_upw && f_kci < 2 && c.Cin % kc == 0 && fast_lds_bytes(ch.geom, f_kci, upw) <= 160 * 1024 &&
-            (ch.geom != 3 || (upw == 3 && f_kci == 0))) {
+        if (f_kci < 2 && c.Cin % kc == 0 && fast_built(c.k, c.dtype == DC_BF16, ch.geom, f_kci, upw) &&
+            fast_lds_bytes(c.k, ch.geom, f_kci, upw) <= 160 * 1024) {
             const int n_chunks = c.Cin / kc;
             int ks = f_ks < 1 ? 1 : (f_ks > n_chunks ? n_chunks : f_ks);
             const int cps = (n_chunks + ks - 1) / ks;
@@ -1486,12 +1512,12 @@ bool launch_conv_fast(const ConvLaunch& c, long n_cap, long n_units, hipStream_t
     P.k = c.k; P.s = c.s; P.p = c.p; P.relu = c.relu;
     P.units = c.tiles; P.n_units = (int)n_cap; P.n_units_dev = n_dev; P.rects = c.rects; P.ranges = c.ranges;
     P.units_x = units_x; P.units_y = units_y;
-    P.ph = 6; P.pw = 6;
+    P.ph = 3 + c.k; P.pw = 3 + c.k;
     P.npix_magic = (uint32_t)((0x100000000ull + (uint64_t)(units_x * units_y) - 1) / (uint64_t)(units_x * units_y));
     P.pw_magic = (uint32_t)((0x100000000ull + (uint64_t)units_x - 1) / (uint64_t)units_x);
     P.g_rt = ch.g;
     P.in_bytes = (uint32_t)((size_t)c.n_streams * c.Hin * c.Win * c.Cin * esz);
-    P.w_bytes = (uint32_t)((size_t)c.Cout * 9 * c.Cin * esz);
+    P.w_bytes = (uint32_t)((size_t)c.Cout * c.k * c.k * c.Cin * esz);
     P.out_vec = 1;
     P.n_chunks = c.Cin / kc;
     P.R = c.Cout / geom_nt(ch.geom);
@@ -1499,14 +1525,15 @@ bool launch_conv_fast(const ConvLaunch& c, long n_cap, long n_units, hipStream_t
     P.chunks_per_split = (P.n_chunks + ch.ks - 1) / ch.ks;
     P.partial = ch.ks > 1 ? static_cast<float*>(c.scratch) : nullptr;
     P.in_origin = c.in_origin; P.out_origin = c.out_origin; P.origin_stride = c.origin_stride;
-    if (c.w_packed && reinterpret_cast<uintptr_t>(c.w_packed) % 16 == 0) { P.w = c.w_packed; P.w_packed = 1; }
+    if (c.k == 3 && c.w_packed && reinterpret_cast<uintptr_t>(c.w_packed) % 16 == 0) { P.w = c.w_packed; P.w_packed = 1; }
 
-    if (c.kernel_id) *c.kernel_id = ch.geom == 3 ? 129 : ch.geom ? 110 + (ch.geom - 1) * 8 + ch.kci * 4 + upw - 1 : 64 + ((c.dtype == DC_BF16 ? 2 : 0) + ch.kci) * 8 + upw - 1;
+    if (c.kernel_id) *c.kernel_id = c.k == 5 ? 132 + ch.geom * 8 + upw - 1 : ch.geom == 3 ? 129 : ch.geom ? 110 + (ch.geom - 1) * 8 + ch.kci * 4 + upw - 1 : 64 + ((c.dtype == DC_BF16 ? 2 : 0) + ch.kci) * 8 + upw - 1;
     const long groups = (n_cap + ch.g - 1) / ch.g;
     const long wgx = groups * P.R;
     if (wgx > 2147483647L || ch.ks > 65535) { *err = hipErrorInvalidValue; return true; }
-    *err = fast_launch(c.dtype == DC_BF16, ch.geom, ch.kci, upw, dim3((unsigned)wgx, (unsigned)ch.ks),
-                       fast_lds_bytes(ch.geom, ch.kci, upw), st, P);
+    const dim3 grid((unsigned)wgx, (unsigned)ch.ks);
+    const size_t lds = fast_lds_bytes(c.k, ch.geom, ch.kci, upw);
+    *err = c.k == 5 ? fast_launch5(ch.geom, upw, grid, lds, st, P) : fast_launch(c.dtype == DC_BF16, ch.geom, ch.kci, upw, grid, lds, st, P);
     if (*err != hipSuccess || ch.ks == 1) return true;
     const size_t total = (size_t)n_cap * 16 * (c.Cout / 4);
     if (c.dtype == DC_BF16)

@@ -463,6 +463,43 @@ def test_lrn_power(oracle, ch, size, beta, kappa, bf16):
     assert (np.abs(got - want) <= rel * np.abs(want)).all()
 
 
+# 5x5 stride-1 bf16 layers on the 3x3 GEMM kernel's frame: both arrangements, every number of units per wavefront, a wavefront
+# row with a unit less, paddings other than 2, ragged maps, one and several chunks, a K split.
+@pytest.mark.parametrize("cached", [False, True])
+@pytest.mark.parametrize("case", [(22, 30, 32, 128, 2, (1, 3, 1, 0)), (22, 30, 96, 128, 2, (1, 8, 1, 0)), (13, 17, 64, 256, 2, (1, 7, 1, 0)),
+                                  (22, 30, 96, 64, 2, (2, 4, 1, 0)), (19, 23, 32, 192, 0, (2, 7, 1, 0)), (19, 23, 64, 64, 4, (2, 12, 1, 0)),
+                                  (14, 14, 128, 128, 1, (1, 5, 3, 0)), (22, 30, 64, 64, 2, (-1, -1, -1, -1)), (21, 13, 96, 256, 2, (-1, -1, -1, -1))])
+def test_5x5_conv_kernel_shapes(oracle, case, cached):
+    H, W, cin, cout, p, tuning = case
+    print(f"[5x5 conv] case={case} cached={cached}", flush=True)
+    rng = np.random.default_rng(H * 1000 + W * 10 + cin + cout)
+    n, Ho, Wo = 3, H + 2 * p - 4, W + 2 * p - 4
+    x = oracle.round_bf16(rng.standard_normal((n, H, W, cin)).astype(np.float32))
+    w = oracle.round_bf16((rng.standard_normal((cout, 5, 5, cin)) * np.sqrt(2.0 / (cin * 25))).astype(np.float32))
+    b = (rng.standard_normal(cout) * 0.1).astype(np.float32)
+    cache = oracle.round_bf16(rng.standard_normal((n, Ho, Wo, cout)).astype(np.float32))
+    regions = None
+    if cached:
+        regions = [(np.array([[1, 2, Wo - 7, Ho - 6], [Wo - 5, 1, 3, 4]], np.int32), (2, -1)),
+                   (np.array([[0, 0, Wo - 1, Ho - 3]], np.int32), (1, 2)), (np.zeros((0, 4), np.int32), (0, 0))]
+    binding.dc_conv_tuning(*tuning)
+    try:
+        got = _to_np(binding.dc_cached_conv_layer(_layer(cin, cout, 5, 1, p, True), _to_dev(x, True), _to_dev(w, True), torch.from_numpy(b).to(DEV),
+                                                  cache_prev=_to_dev(cache, True) if cached else None, regions=regions))
+    finally:
+        binding.dc_conv_tuning()
+    for i in range(n):
+        if cached:
+            mask = oracle.rasterize(regions[i][0], Ho, Wo)
+            want = oracle.conv_cached(x[i], w, b, 5, 1, p, True, cache_prev=cache[i], mask=mask, dxy=regions[i][1], bf16=True)
+            m = mask.astype(bool)
+            assert np.array_equal(got[i][m], want[m]), "copied pixels must be bit-identical"
+        else:
+            want = oracle.conv_cached(x[i], w, b, 5, 1, p, True, bf16=True)
+        # a bf16 rounding of the result (2^-9) and fp32 sums that may round to the neighbour
+        assert (np.abs(got[i].astype(np.float64) - want) <= 2.0 ** -7 * np.abs(want) + 1e-5 * np.abs(want).max()).all(), (case, i)
+
+
 PW_CASES = [
     # H, W, cin, cout, stride
     (13, 18, 64, 64, 1),       # one chunk in bf16, two in fp32
