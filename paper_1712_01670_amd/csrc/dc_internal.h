@@ -320,6 +320,7 @@ struct Overlap {
     int device = -1;                                  // the GPU whose stage streams these are
     hipStream_t aux = nullptr;                        // matching (and, planned on the GPU, stage 0)
     hipStream_t work[2] = {nullptr, nullptr};         // further stages
+    hipStream_t record = nullptr;                     // graphs are recorded here (made for the first one)
     hipEvent_t match_done = nullptr;                  // mask and motion of the current frame are in host memory
     hipEvent_t plan_done = nullptr;                   // no pipeline, planned on the GPU: the frame's plan is complete
     hipEvent_t upload_done[2] = {nullptr, nullptr};   // plan upload from staging half 0 / 1 has completed

@@ -1284,8 +1284,11 @@ int StackCall::record_graphs(dc::FrameGraphs& g) {
     g.kernel_id.assign(n_layers, -1);
     int32_t* const caller_ids = local.layer_kernel_id;
     local.layer_kernel_id = g.kernel_id.data();
-    hipStream_t st = ov->work[0];            // recording takes any stream that is not the default one
-    int rc = DC_OK;
+    // The handle's own stream, on which nothing is executed: what another thread's handle launches on a stage stream while
+    // that stream is captured would end up in this graph.
+    if (!ov->record && hipStreamCreateWithFlags(&ov->record, hipStreamNonBlocking) != hipSuccess) ov->record = nullptr;
+    const hipStream_t st = ov->record;
+    int rc = st ? DC_OK : DC_ERR_HIP;
     for (int s = 0; s < P.n_stages && !rc; ++s) {
         hipGraph_t graph = nullptr;
         if (hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal) != hipSuccess) { rc = DC_ERR_HIP; break; }
@@ -1475,6 +1478,7 @@ int32_t dc_overlap_destroy(void* overlap) {
         }
     if (o->match_done) (void)hipEventDestroy(o->match_done);
     if (o->plan_done) (void)hipEventDestroy(o->plan_done);
+    if (o->record) (void)hipStreamDestroy(o->record);
     release_stage_streams(o);
     delete o;
     return DC_OK;

@@ -1,6 +1,8 @@
 """GPU parity of dc_run_stack (whole per-frame path) against the oracle: match results,
 reuse masks and propagated rectangles bit-exact; every tensor within 1e-4 (fp32) or
 2e-2 (bf16) of the oracle, relative to the tensor's largest magnitude."""
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -947,3 +949,47 @@ def test_one_handle_for_two_stacks_and_two_caller_streams():
     finally:
         torch.cuda.synchronize()
         runners[1].overlap = own
+
+
+def test_two_threads_with_a_stack_each():
+    """Handles of two threads share the stage streams of the GPU, and both threads record graphs while the other one issues
+    frames: same tensors as one after the other.  (A recording takes nothing but its own stack's launches.)"""
+    H = W = 96
+    T = 12
+    layers = synth.resnet50_trunk()[:44]
+    ws, bs = synth.he_weights(layers, 3, bias_scale=0.05, residual_scale=0.5)
+    video = torch.from_numpy(synth.panning_video(85, n_frames=T, H=H, W=W, fg=((24, 24), (16, 32)))).to(DEV)
+    frames = [[video[t:t + 1].contiguous() for t in range(T)], [video[T - 1 - t:T - t].contiguous() for t in range(T)]]
+    torch.cuda.synchronize()
+    results, errors = {}, []
+
+    def work(key, mine):
+        try:
+            torch.cuda.set_device(0)
+            with torch.cuda.stream(torch.cuda.Stream()):
+                runner = binding.StackRunner(layers, ws, bs, 1, H, W, 3, block=16, radius=16, dtype=binding.DC_F32, expiry=6,
+                                             device_plan=True, exact_masks=True)
+                for t in range(10 * T):
+                    if t % T == 0:
+                        runner.reset()
+                    tensors = runner.step(mine[t % T])
+                torch.cuda.current_stream().synchronize()
+                results[key] = [x.clone() for x in tensors[1:]] + [runner.mask.clone(), runner.gmv.clone()]
+                torch.cuda.current_stream().synchronize()
+        except Exception as e:                       # noqa: BLE001 (reported by the main thread)
+            errors.append(e)
+    for k in range(2):
+        print(f"[threads] alone {k}", flush=True)
+        work(("alone", k), frames[k])
+    print("[threads] together", flush=True)
+    threads = [threading.Thread(target=work, args=(("together", k), frames[k])) for k in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors, errors
+    for k in range(2):
+        a, b = results["alone", k], results["together", k]
+        assert torch.equal(a[-1], b[-1]) and torch.equal(a[-2], b[-2]), k
+        for i, (x, y) in enumerate(zip(a[:-2], b[:-2])):
+            assert _max_rel(x, y) <= 3e-4, (k, i)    # (partial sums of a split K: see the test of long runs)
