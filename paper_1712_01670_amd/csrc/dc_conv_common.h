@@ -128,11 +128,12 @@ __device__ __forceinline__ void activate4(floatx4& v, int mode) {
     v[0] = activate(v[0], mode); v[1] = activate(v[1], mode); v[2] = activate(v[2], mode); v[3] = activate(v[3], mode);
 }
 
-__device__ __forceinline__ int fast_div(int n, uint32_t magic) { return (int)__umulhi((uint32_t)n, magic); }
-// floor(n / d) for any 0 <= n < 2^31 with magic = ceil(2^32 / d): the product above is exact while n d < 2^32 and one
+// n / d with magic = ceil(2^32 / d), kept in 32 bits: 0 stands for d = 1 (a map of one unit column, a map of one unit).
+__device__ __forceinline__ int fast_div(int n, uint32_t magic) { return magic ? (int)__umulhi((uint32_t)n, magic) : n; }
+// floor(n / d) for any 0 <= n < 2^31 with the same magic: the product above is exact while n d < 2^32 and one
 // too large at most beyond that (the stream of a raster position in a large batch).
 __device__ __forceinline__ int fast_div_any(int n, uint32_t magic, int d) {
-    const uint32_t q = __umulhi((uint32_t)n, magic);
+    const uint32_t q = (uint32_t)fast_div(n, magic);
     return (int)(q * (uint32_t)d > (uint32_t)n ? q - 1 : q);
 }
 

@@ -500,6 +500,29 @@ def test_5x5_conv_kernel_shapes(oracle, case, cached):
         assert (np.abs(got[i].astype(np.float64) - want) <= 2.0 ** -7 * np.abs(want) + 1e-5 * np.abs(want).max()).all(), (case, i)
 
 
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("H,W", [(4, 4), (2, 3), (9, 4), (5, 1), (1, 7), (4, 13)])
+@pytest.mark.parametrize("cin,cout,k,tuning", [(0, 64, 3, None), (64, 64, 3, None), (64, 64, 3, (3, 4, 1, 1)), (64, 128, 1, None), (128, 128, 5, None)])
+def test_conv_on_maps_of_one_unit_column(oracle, cin, cout, k, tuning, H, W, bf16):
+    """Maps of a single 4x4 unit, unit column or unit row, several streams, in full: every pixel of every stream is written."""
+    cin = cin or (8 if bf16 else 4)                   # (a pixel of one 16-byte vector: the first-layer kernel)
+    print(f"[one unit column] {H}x{W} {cin}->{cout} k={k} bf16={bf16} tuning={tuning}", flush=True)
+    rng = np.random.default_rng(H * 100 + W + cin + k)
+    x = rng.standard_normal((5, H, W, cin)).astype(np.float32)
+    w = (rng.standard_normal((cout, k, k, cin)) * np.sqrt(2.0 / (cin * k * k))).astype(np.float32)
+    if bf16:
+        x, w = oracle.round_bf16(x), oracle.round_bf16(w)
+    b = (rng.standard_normal(cout) * 0.1).astype(np.float32)
+    if tuning:
+        binding.dc_conv_tuning(*tuning)
+    try:
+        got = _to_np(binding.dc_cached_conv_layer(_layer(cin, cout, k, 1, k // 2, True), _to_dev(x, bf16), _to_dev(w, bf16), torch.from_numpy(b).to(DEV)))
+    finally:
+        binding.dc_conv_tuning()
+    for i in range(5):
+        assert _rel_err(got[i], oracle.conv_cached(x[i], w, b, k, 1, k // 2, True, bf16=bf16)) <= (2e-2 if bf16 else 1e-4), i
+
+
 PW_CASES = [
     # H, W, cin, cout, stride
     (13, 18, 64, 64, 1),       # one chunk in bf16, two in fp32
