@@ -499,24 +499,59 @@ __device__ __forceinline__ int round_half_away(int num, int den) {
     return num < 0 ? -q : q;
 }
 
-// One wavefront per block: Step 3 (redundantly per workgroup) then Step 4 for this block.
-__global__ __launch_bounds__(64) void motion_retest_kernel(
+// Step 3 (redundantly per workgroup), then Step 4: one wavefront per block, four blocks per workgroup.  What bounded it was
+// instructions: a mean over all vectors of the stream per block, and a byte of the block at a time with a division each.  Now four
+// blocks share a mean, its reads are dealt to 256 threads, and the samples are compared E = 4 bytes at a time where a block row is a
+// whole number of them (unaligned loads: the moved block starts at any byte; a sample never leaves its block row); the
+// current block's samples are on their way before the mean is known.  416x416 in 16x16 blocks, 16 streams: 22.0 -> 8.9 us.
+constexpr int kRetestWaves = 4;
+template <int E>
+__global__ __launch_bounds__(kRetestWaves * 64) void motion_retest_kernel(
     const uint8_t* __restrict__ cur, const uint8_t* __restrict__ prev, int H, int W, int C, int B,
     int gw, int gh, uint32_t max_ssd, int16_t* mv, uint32_t* best_ssd, int32_t* __restrict__ gmv,
-    int32_t* __restrict__ n_pass, uint8_t* __restrict__ mask, int k_skip) {
-    const int lane = threadIdx.x;
-    const int blk_id = blockIdx.x, stream = blockIdx.y;
+    int32_t* __restrict__ n_pass, uint8_t* __restrict__ mask, int k_skip, uint32_t row_magic) {
+    constexpr int U = 4;                                 // independent loads per lane at a time
+    __shared__ int part[kRetestWaves][3];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int stream = blockIdx.y;
     const int nb = gh * gw;
+    const int blk_id = (int)blockIdx.x * kRetestWaves + wave;
+    const bool real = blk_id < nb;                       // (uniform over the wavefront)
+    const int by = real ? blk_id / gw : 0, bx = real ? blk_id - by * gw : 0;
+    const int x0 = bx * B, y0 = by * B;
+    const size_t frame_bytes = (size_t)H * W * C, pitch = (size_t)W * C;
+    const uint8_t* const cb = cur + stream * frame_bytes + y0 * pitch + (size_t)x0 * C;
+    const int per_row = B * C / E, n_elem = B * per_row; // samples of E bytes
+    // place of sample i from the block's first byte; past the end: the first sample
+    auto place = [&](int i) {
+        if (i >= n_elem) i = 0;
+        uint32_t r = row_magic ? __umulhi((uint32_t)i, row_magic) : (uint32_t)i;      // (0: one sample a row)
+        if (r * (uint32_t)per_row > (uint32_t)i) --r;    // the product is one too large at most
+        return r * pitch + (size_t)((uint32_t)i - r * (uint32_t)per_row) * E;
+    };
+    auto load = [](const uint8_t* p) {
+        if constexpr (E == 4) {
+            uint32_t v;
+            __builtin_memcpy(&v, p, 4);
+            return v;
+        } else {
+            return (uint32_t)*p;
+        }
+    };
+    uint32_t first[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) first[u] = load(cb + place(u * 64 + lane));
+
     int16_t* smv = mv + (size_t)stream * nb * 2;
     uint32_t* sbest = best_ssd + (size_t)stream * nb;
     int sx = 0, sy = 0, K = 0;
-    for (int base = 0; base < nb; base += 4 * 64) {     // four independent loads per lane at a time
-        uint32_t bs[4];
-        int vx[4], vy[4];
-        bool has[4];
+    for (int base = 0; base < nb; base += U * kRetestWaves * 64) {
+        uint32_t bs[U];
+        int vx[U], vy[U];
+        bool has[U];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int i = base + u * 64 + lane;
+        for (int u = 0; u < U; ++u) {
+            const int i = base + u * (kRetestWaves * 64) + tid;
             // with k-skip only the blocks on every k-th grid row and column carry a vector; the entries of the others
             // are written further down by their own workgroups and are not read here
             const bool in = i < nb && (k_skip == 1 || ((i / gw) % k_skip == 0 && (i % gw) % k_skip == 0));
@@ -526,7 +561,7 @@ __global__ __launch_bounds__(64) void motion_retest_kernel(
             vy[u] = in ? smv[2 * i + 1] : 0;
         }
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
+        for (int u = 0; u < U; ++u) {
             const bool pass = has[u] && bs[u] <= max_ssd;
             sx += pass ? vx[u] : 0;
             sy += pass ? vy[u] : 0;
@@ -536,6 +571,15 @@ __global__ __launch_bounds__(64) void motion_retest_kernel(
     sx = wave_sum_i32(sx);
     sy = wave_sum_i32(sy);
     K = wave_sum_i32(K);
+    if (lane == 0) { part[wave][0] = sx; part[wave][1] = sy; part[wave][2] = K; }
+    __syncthreads();
+    if (!real) return;
+    sx = sy = K = 0;
+#pragma unroll
+    for (int w = 0; w < kRetestWaves; ++w) { sx += part[w][0]; sy += part[w][1]; K += part[w][2]; }
+    sx = __builtin_amdgcn_readfirstlane(sx);
+    sy = __builtin_amdgcn_readfirstlane(sy);
+    K = __builtin_amdgcn_readfirstlane(K);
     int mx = 0, my = 0;
     if (K > 0) {
         mx = round_half_away(sx, K);
@@ -546,38 +590,54 @@ __global__ __launch_bounds__(64) void motion_retest_kernel(
         gmv[2 * stream + 1] = my;
         n_pass[stream] = K;
     }
-    const int bx = blk_id % gw, by = blk_id / gw;
     if (k_skip > 1 && (bx % k_skip != 0 || by % k_skip != 0) && lane == 0) {
         // not searched: no vector (no workgroup reads these entries: the mean above leaves them out)
         smv[2 * blk_id] = 0; smv[2 * blk_id + 1] = 0;
         sbest[blk_id] = 0xffffffffu;
     }
-    const int x0 = bx * B, y0 = by * B;
     bool inside = K > 0 && x0 + mx >= 0 && y0 + my >= 0 && x0 + mx + B <= W && y0 + my + B <= H;
     uint32_t ssd = 0;
     if (inside) {
-        const size_t frame_bytes = (size_t)H * W * C;
-        const uint8_t* cf = cur + stream * frame_bytes;
-        const uint8_t* pf = prev + stream * frame_bytes;
-        const int rb = B * C;
-        for (int base = 0; base < B * rb; base += 8 * 64) {   // eight independent byte pairs per lane at a time
-            int a[8], b[8];
+        const uint8_t* const pb = prev + stream * frame_bytes + (size_t)(y0 + my) * pitch + (size_t)(x0 + mx) * C;
+        for (int base = 0; base < n_elem; base += U * 64) {
+            uint32_t a[U], b[U];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int i = base + u * 64 + lane;
-                const int r = i / rb, j = i - r * rb;
-                const bool in = i < B * rb;
-                a[u] = in ? cf[((size_t)(y0 + r) * W + x0) * C + j] : 0;
-                b[u] = in ? pf[((size_t)(y0 + my + r) * W + x0 + mx) * C + j] : 0;
+            for (int u = 0; u < U; ++u) {
+                const size_t at = place(base + u * 64 + lane);
+                b[u] = load(pb + at);
+                a[u] = base == 0 ? first[u] : load(cb + at);
             }
 #pragma unroll
-            for (int u = 0; u < 8; ++u) ssd += (uint32_t)((a[u] - b[u]) * (a[u] - b[u]));
+            for (int u = 0; u < U; ++u) {
+                if (base + u * 64 + lane >= n_elem) a[u] = b[u] = 0;
+                if constexpr (E == 4) {      // sum (a - b)^2, modulo 2^32
+                    ssd = udot4(a[u], a[u], udot4(b[u], b[u], ssd)) - 2u * udot4(a[u], b[u], 0u);
+                } else {
+                    const int d = (int)a[u] - (int)b[u];
+                    ssd += (uint32_t)(d * d);
+                }
+            }
         }
         ssd = (uint32_t)wave_sum_i32((int)ssd);
     }
     if (lane == 0) mask[(size_t)stream * nb + blk_id] = (inside && ssd <= max_ssd) ? 1 : 0;
 }
-
+// Both searches end here.
+hipError_t launch_motion_retest(const uint8_t* cur, const uint8_t* prev, int n_streams, int H, int W, int C, int B, int gw, int gh,
+                                uint32_t max_ssd, int16_t* mv, uint32_t* best_ssd, int32_t* gmv, int32_t* n_pass, uint8_t* mask,
+                                int k_skip, hipStream_t st) {
+    const bool words = (B * C) % 4 == 0;
+    const uint64_t per_row = (uint64_t)(words ? B * C / 4 : B * C);
+    const uint32_t magic = (uint32_t)((0x100000000ull + per_row - 1) / per_row);      // 2^32 (one sample a row) becomes 0
+    const dim3 grid((unsigned)((gh * gw + kRetestWaves - 1) / kRetestWaves), (unsigned)n_streams);
+    if (words)
+        hipLaunchKernelGGL(motion_retest_kernel<4>, grid, dim3(kRetestWaves * 64), 0, st, cur, prev, H, W, C, B, gw, gh, max_ssd, mv,
+                           best_ssd, gmv, n_pass, mask, k_skip, magic);
+    else
+        hipLaunchKernelGGL(motion_retest_kernel<1>, grid, dim3(kRetestWaves * 64), 0, st, cur, prev, H, W, C, B, gw, gh, max_ssd, mv,
+                           best_ssd, gmv, n_pass, mask, k_skip, magic);
+    return hipGetLastError();
+}
 
 // ---- diamond search (Section 4, Step 2 as the paper runs it) with k-skip ----------------------
 // One wavefront per block of the grid.  The walk is sequential, so what counts is the latency of a round:
@@ -811,9 +871,7 @@ hipError_t launch_match(const uint8_t* cur, const uint8_t* prev, int n_streams, 
 #undef DC_MATCH_LAUNCH
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(motion_retest_kernel, dim3(gh * gw, n_streams), dim3(64), 0, st, cur, prev, H, W, C, B, gw, gh,
-                       max_ssd, mv, best_ssd, gmv, n_pass, mask, k_skip);
-    return hipGetLastError();
+    return launch_motion_retest(cur, prev, n_streams, H, W, C, B, gw, gh, max_ssd, mv, best_ssd, gmv, n_pass, mask, k_skip, st);
 }
 
 hipError_t launch_match_diamond(const uint8_t* cur, const uint8_t* prev, int n_streams, int H, int W, int C, int B,
@@ -835,9 +893,7 @@ hipError_t launch_match_diamond(const uint8_t* cur, const uint8_t* prev, int n_s
                            H, W, C, B, R, gw, gh, k_skip, cap, 0, rb_magic, mv, best_ssd);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(motion_retest_kernel, dim3(gh * gw, n_streams), dim3(64), 0, st, cur, prev, H, W, C, B, gw, gh,
-                       max_ssd, mv, best_ssd, gmv, n_pass, mask, k_skip);
-    return hipGetLastError();
+    return launch_motion_retest(cur, prev, n_streams, H, W, C, B, gw, gh, max_ssd, mv, best_ssd, gmv, n_pass, mask, k_skip, st);
 }
 
 }  // namespace dc

@@ -109,3 +109,19 @@ def test_k_skip(oracle, k):
             assert got["gmv"][s].tolist() == want["gmv"].tolist()
             assert int(got["n_pass"][s]) == want["n_pass"]
             assert np.array_equal(got["mask"][s], want["mask"])
+
+
+# Step 4 compares four samples at a time where a block row is a whole number of words, 256 per round and wavefront, four blocks
+# per workgroup: rows of whole words and of odd bytes, one sample a row, a second round, block counts that are no multiple of four.
+@pytest.mark.parametrize("H,W,C,B,R", [(37, 53, 3, 5, 3), (33, 41, 1, 7, 4), (30, 30, 4, 1, 2), (60, 101, 3, 20, 6), (45, 63, 3, 8, 5),
+                                       (64, 50, 1, 16, 8), (50, 90, 2, 25, 3), (21, 19, 3, 16, 2), (224, 224, 3, 16, 16)])
+def test_retest_sample_shapes(oracle, H, W, C, B, R):
+    rng = np.random.default_rng(H * W + B)
+    base = rng.integers(40, 216, (2, H + 8, W + 8, C)).astype(np.int64)
+    prev = base[:, 4:4 + H, 4:4 + W].astype(np.uint8)
+    level = np.kron(rng.integers(0, 12, (2, H // B + 1, W // B + 1)), np.ones((B, B), np.int64))[:, :H, :W, None]
+    noise = rng.integers(-1, 2, (2, H, W, C)) * level
+    cur = (base[:, 5:5 + H, 3:3 + W] + noise).astype(np.uint8)      # every block moved by (-1, 1), each under noise of its own
+    ssd = np.sort(np.concatenate([oracle.match_blocks(cur[s], prev[s], B, R, 0)["best_ssd"].ravel() for s in range(2)]))
+    for thr in {int(ssd[len(ssd) // 2]), int(ssd[-1]), int(ssd[len(ssd) // 4])}:      # a block exactly at the limit each time
+        _compare(oracle, cur, prev, B, R, thr, "retest")
