@@ -637,21 +637,28 @@ __global__ __launch_bounds__(kThreads) void frame_to_tensor_px_kernel(const uint
     }
 }
 
-// x^-beta of an LRN denominator.  The exponent of the published models, 3/4, is a product of two hardware roots (each good to
-// one unit in the last place, so it is also the more accurate form); others go through the base-2 logarithm.
+// x^-beta of an LRN denominator.  The exponent of the published models, 3/4, is a product of two hardware roots; each is good to
+// one unit in the last place only, so what they miss (r of x^-1/2 by e / 2, q of r^1/2 by h s / 2, the product by lo; fused
+// multiply-adds give all three) is put back in one step.  fp32 error of a layer against 64 bits, 2-norm: the bare roots 5.1e-8 to
+// 7.9e-8, logarithm and exponential 4.0e-8 to 5.8e-8, this 4.0e-8 to 5.6e-8 and at no setting more.  Other exponents go through the base-2 logarithm.
 template <bool B34>
 __device__ __forceinline__ float lrn_power(float x, float beta) {
     if constexpr (B34) {
-        const float r = __builtin_amdgcn_rsqf(x);
-        return r * __builtin_amdgcn_sqrtf(r);
+#pragma clang fp contract(off)     // p is the rounded product: fused into the last sum it would count lo twice
+        const float r = __builtin_amdgcn_rsqf(x), q = __builtin_amdgcn_sqrtf(r), p = r * q;
+        const float s = x * r;                                                    // x^1/2, that is 1 / r
+        const float e = fmaf(-s, r, 1.f) - fmaf(x, r, -s) * r;                    // 1 - x r^2
+        const float h = fmaf(-q, q, r), lo = fmaf(r, q, -p);
+        const float c = fmaf(0.75f, e, 0.5f * h * s);
+        return fabsf(c) < 1.f ? p + fmaf(p, c, lo) : p;                           // (0, infinity and NaN: as the roots have them)
     }
     return __powf(x, -beta);
 }
 
 // LRN over channels with radius R <= VE: the thread's vector and its two neighbours hold every channel of the window.
 // Should be bound by memory; what it spent its time on was the arithmetic around it (a 64-bit division per vector, the power
-// as logarithm and exponential), so the vectors of a launch are counted in 32 bits.  55x55x96, 64 bf16 streams: 73.7 -> 16.2 us
-// (its 74 MB at the 5.5 TB/s of a large copy: 13.5); 56x56x192, 16 streams: 36.1 -> 9.4.  Exponents other than 3/4: unchanged.
+// as logarithm and exponential), so the vectors of a launch are counted in 32 bits.  55x55x96, 64 bf16 streams: 63.2 -> 18.9 us
+// (its 74 MB at the 5.5 TB/s of a large copy: 13.5); 56x56x192, 16 streams: 34.2 -> 11.1.  Exponents other than 3/4: unchanged.
 template <typename T, int R, bool B34>
 __global__ __launch_bounds__(kThreads) void lrn_vec_kernel(const uint4* __restrict__ in, uint4* __restrict__ out,
                                                            unsigned total, unsigned CV, float alpha_n, float beta, float kappa) {

@@ -463,6 +463,21 @@ def test_lrn_power(oracle, ch, size, beta, kappa, bf16):
     assert (np.abs(got - want) <= rel * np.abs(want)).all()
 
 
+@pytest.mark.parametrize("size,alpha,kappa,ch", [(5, 1e-4, 2.0, 192), (5, 1.0, 1.0, 64), (3, 5e-2, 1.0, 64)])
+def test_lrn_fp32_is_rounded_like_three_operations(size, alpha, kappa, ch):
+    """fp32, exponent 3/4, against 64 bits: what is left is the rounding of the product (rms at most 2^-24 / sqrt(3) of the
+    value), of the power (the same) and of the denominator and its sum of squares (three roundings, times 3/4): together
+    2^-24 / sqrt(3) * sqrt(1 + 1 + 3 * 9/16) = 6.6e-8.  Two hardware roots without correction: 7.2e-8 to 7.9e-8."""
+    print(f"[lrn precision] size={size} alpha={alpha} kappa={kappa} ch={ch}", flush=True)
+    x = (np.random.default_rng(ch).standard_normal((2, 32, 32, ch)) * 8).astype(np.float32)
+    got = _to_np(binding.dc_lrn_layer(_to_dev(x, False), size, alpha, 0.75, kappa, False)).astype(np.float64)
+    sq = np.pad(x.astype(np.float64) ** 2, ((0, 0), (0, 0), (0, 0), (size // 2, size // 2)))
+    total = sum(sq[..., i:i + ch] for i in range(size))
+    want = x * (np.float64(np.float32(kappa)) + np.float64(np.float32(alpha) / np.float32(size)) * total) ** -0.75
+    rms = float(np.sqrt(np.mean(((got - want) / want) ** 2)))
+    assert rms <= 6.6e-8, rms
+
+
 # 5x5 stride-1 bf16 layers on the 3x3 GEMM kernel's frame: both arrangements, every number of units per wavefront, a wavefront
 # row with a unit less, paddings other than 2, ragged maps, one and several chunks, a K split.
 @pytest.mark.parametrize("cached", [False, True])
