@@ -261,6 +261,9 @@ __global__ __launch_bounds__(WM* WN * 64) void conv_fast_kernel(ConvParams P) {
 #pragma unroll
         for (int j = 0; j < NBW; ++j) acc[u][j] = floatx4{0.f, 0.f, 0.f, 0.f};
 
+    // 5x5: the sums of a stage alone, then added to the total, so that no chain of roundings is longer than a stage's few
+    // taps and the stages (the general kernel, which these layers came from, splits their K into up to eight sums)
+    constexpr bool SHORT = KSZ == 5;
     // epilogue operands that do not depend on the accumulators
     const int chan = n0 + wave_n * NBW * 16 + 4 * q;
     floatx4 bias[NBW];
@@ -292,13 +295,14 @@ __global__ __launch_bounds__(WM* WN * 64) void conv_fast_kernel(ConvParams P) {
 #pragma unroll
             for (int j = 0; j < NBW; ++j) w[b][j] = *reinterpret_cast<const vec*>(wp + j * (16 * RB));
         };
-        auto mma = [&](int b) {
+        typedef floatx4 Sums[UPW][NBW];
+        auto mma = [&](int b, Sums& sum) {
 #pragma unroll
             for (int e = 0; e < F::NE; ++e)
 #pragma unroll
                 for (int u = 0; u < NU; ++u)
 #pragma unroll
-                    for (int j = 0; j < NBW; ++j) F::mma1(w[b][j], x[b][u], acc[u][j], e);
+                    for (int j = 0; j < NBW; ++j) F::mma1(w[b][j], x[b][u], sum[u][j], e);
         };
 
         issue_p(cb, -1, 0);
@@ -312,11 +316,13 @@ __global__ __launch_bounds__(WM* WN * 64) void conv_fast_kernel(ConvParams P) {
 #pragma unroll
             for (int ky = 0; ky < KSZ; ++ky, ++sidx) {
                 // fragments of step 0 of this stage are on their way (buffer (ky * NS) & 1)
+                Sums part = {};                                   // (SHORT) of this stage
+                Sums& sum = SHORT ? part : acc;
 #pragma unroll
                 for (int st = 0; st + 1 < NS; ++st) {
                     frag(pbuf, sidx & 1, ky, st + 1, (ky * NS + st + 1) & 1);
                     __builtin_amdgcn_sched_barrier(0);
-                    mma((ky * NS + st) & 1);
+                    mma((ky * NS + st) & 1, sum);
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 // Last step: first end the stage for the memory system.  After the barrier every wavefront has
@@ -328,7 +334,16 @@ __global__ __launch_bounds__(WM* WN * 64) void conv_fast_kernel(ConvParams P) {
                 if (ky + 1 < KSZ) frag(pbuf, (sidx + 1) & 1, ky + 1, 0, ((ky + 1) * NS) & 1);
                 else if (c + 1 < n_ch) frag(pbuf ^ 1, (sidx + 1) & 1, 0, 0, (KSZ * NS) & 1);
                 __builtin_amdgcn_sched_barrier(0);
-                mma((ky * NS + NS - 1) & 1);
+                mma((ky * NS + NS - 1) & 1, sum);
+                if constexpr (SHORT) {
+#pragma unroll
+                    for (int u = 0; u < NU; ++u)
+#pragma unroll
+                        for (int j = 0; j < NBW; ++j) {
+                            acc[u][j] += part[u][j];
+                            asm volatile("" : "+v"(acc[u][j]));      // now: put off, the sums of five stages need registers at once
+                        }
+                }
                 __builtin_amdgcn_sched_barrier(0);
             }
             if ((KSZ * NS) & 1) {   // the next chunk expects its first fragments in buffer 0
@@ -1160,7 +1175,9 @@ hipError_t fast_launch(bool bf16, int geom, int kci, int upw, dim3 grid, size_t 
 // units per wavefront (145 KB) and wide64 for three.  Against the general kernel, which computes every LDS address of its
 // inner loop, us per layer: 27x27 96->256 on 64 streams 182 -> 96, on 16 streams 71 -> 40, 56x56 128->128 on 8 streams
 // 85 -> 46, and no smaller one measured was slower, so every such layer with whole 64-byte rows comes here.  fp32 stays on
-// the general kernel (bound by the MFMA stream there, and its two half sums round less).
+// the general kernel (bound by the MFMA stream there, and its two half sums round less).  The sums of a stage on their own
+// (SHORT) cost 3 to 6 % of a layer (27x27 96->256 on 64 streams, whole layer in bf16: 66.0 -> 68.4 us); what the fp32 sums lose
+// where they cancel, rms: general kernel 8.9e-5, one chain 1.7e-4, this 4.4e-5.
 hipError_t fast_launch5(int geom, int upw, dim3 grid, size_t lds, hipStream_t st, const ConvParams& P) {
     typedef __hip_bfloat16 B;
     if (geom == 1) return upw == 1 ? fast_launch_one<B, 32, 1, 4, 2, 4, 5>(grid, lds, st, P) : fast_launch_one<B, 32, 2, 4, 2, 4, 5>(grid, lds, st, P);

@@ -515,6 +515,32 @@ def test_5x5_conv_kernel_shapes(oracle, case, cached):
         assert (np.abs(got[i].astype(np.float64) - want) <= 2.0 ** -7 * np.abs(want) + 1e-5 * np.abs(want).max()).all(), (case, i)
 
 
+@pytest.mark.parametrize("cin,cout,tuning", [(128, 128, (1, 8, 1, 0)), (128, 64, (2, 12, 1, 0)), (192, 128, (1, 3, 1, 0))])
+def test_5x5_sums_are_rounded_once_per_stage(cin, cout, tuning):
+    """Inputs whose second half of channels repeats the first with negated weights: the exact output is zero and the stored
+    value is what the fp32 sums lost.  Expected: every stage (5 taps x 32 channels) rounds its own running sum five times and
+    the total once, each by at most 2^-24 / sqrt(3) of the sum (rms); half as much again is allowed.  One chain over all of K
+    rounds the total at every tap: at least sqrt(5) of that, measured 3.2."""
+    H, W, p = 22, 30, 2
+    print(f"[5x5 sums] cin={cin} cout={cout} tuning={tuning}", flush=True)
+    rng = np.random.default_rng(cin + cout)
+    x = _to_dev(np.abs(rng.standard_normal((1, H, W, cin // 2))).astype(np.float32), True)
+    w = _to_dev(np.abs(rng.standard_normal((cout, 5, 5, cin // 2))).astype(np.float32), True)
+    x, w = torch.cat([x, x], 3).contiguous(), torch.cat([w, -w], 3).contiguous()
+    binding.dc_conv_tuning(*tuning)
+    try:
+        got = binding.dc_cached_conv_layer(_layer(cin, cout, 5, 1, p, False), x, w, None)
+    finally:
+        binding.dc_conv_tuning()
+    xd, wd = x[0, H // 2 - 2:H // 2 + 3, W // 2 - 2:W // 2 + 3].double().cpu().numpy(), w[0].double().cpu().numpy()
+    taps = (xd * wd).reshape(5, 5, cin // 32, 32).sum(-1)                      # [ky][kx][chunk]
+    run = np.cumsum(taps.sum(1).T.reshape(-1))                                # after every stage: [chunk][ky]
+    in_stage = np.cumsum(taps, axis=1)
+    rms = 2.0 ** -24 / np.sqrt(3.0) * np.sqrt((run ** 2).sum() + (in_stage ** 2).sum())
+    inner = got[0, 2:-2, 2:-2].double().cpu().numpy()
+    assert np.sqrt((inner ** 2).mean()) <= 1.5 * rms, np.sqrt((inner ** 2).mean()) / rms
+
+
 @pytest.mark.parametrize("bf16", [False, True])
 @pytest.mark.parametrize("H,W", [(4, 4), (2, 3), (9, 4), (5, 1), (1, 7), (4, 13)])
 @pytest.mark.parametrize("cin,cout,k,tuning", [(0, 64, 3, None), (64, 64, 3, None), (64, 64, 3, (3, 4, 1, 1)), (64, 128, 1, None), (128, 128, 5, None)])
