@@ -322,7 +322,8 @@ struct Overlap {
     hipStream_t work[2] = {nullptr, nullptr};         // further stages
     hipStream_t record = nullptr;                     // graphs are recorded here (made for the first one)
     hipEvent_t match_done = nullptr;                  // mask and motion of the current frame are in host memory
-    hipEvent_t plan_done = nullptr;                   // no pipeline, planned on the GPU: the frame's plan is complete
+    hipEvent_t plan_done = nullptr;                   // planned on the GPU, no pipeline or a look-ahead to come: the frame's plan is complete
+    bool looks_ahead = false, planned = false;        // dc_prefetch_match is in use; plan_done is the last frame's
     hipEvent_t upload_done[2] = {nullptr, nullptr};   // plan upload from staging half 0 / 1 has completed
     bool pending[2] = {false, false};
     int parity = 0;

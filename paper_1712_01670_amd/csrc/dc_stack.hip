@@ -1333,18 +1333,20 @@ int StackCall::run() {
 
     // ---- matching and planning ----
     hipStream_t head = devplan && ov && !pipe ? ov->aux : stage_st[0];
+    // A look-ahead match, taken or not, writes the match buffers and reads the caller's frames on aux: a frame that does not
+    // start there comes after it, a full one too (the next cached frame matches on the stream that it starts on).  The
+    // other stages, the caller's stream and the later frames follow from this one; planned on the host, the host waits.
+    if (pf.valid && (devplan || !cached) && head != ov->aux) DC_TRY_HIP(wait(head, ov->match_done));
     if (devplan) {
         rc = prepare_device_plan();
         if (rc) return rc;
         // (the match buffers are shared by consecutive frames: their matching and planning follow one another on one stream)
-        const bool ahead = prefetched();
-        if (ov && pf.valid && head != ov->aux) DC_TRY_HIP(wait(head, ov->match_done));
-        if (!ahead) {
+        if (!prefetched()) {
             rc = launch_match(head);
             if (rc) return rc;
         }
         if (P.torus && opt->origins_dev_out) *opt->origins_dev_out = pd.origin;
-        if (ov) ov->head = head;
+        if (ov) { ov->head = head; ov->planned = false; }
     } else if (cached) {
         rc = plan_on_host();
         if (rc) return rc;
@@ -1408,6 +1410,9 @@ int StackCall::run() {
         if (head != stage_st[0]) {
             DC_TRY_HIP(hipEventRecord(ov->plan_done, head));
             DC_TRY_HIP(wait(stage_st[0], ov->plan_done));
+        } else if (ov && ov->looks_ahead && head != ov->aux) {
+            DC_TRY_HIP(hipEventRecord(ov->plan_done, head));
+            ov->planned = true;
         }
     }
     for (int s = 0; s < k; ++s) {
@@ -1511,8 +1516,10 @@ int32_t dc_prefetch_match(void* overlap, const uint8_t* frames_next, const uint8
     }
     if (ov->head && ov->head != ov->aux) {     // the current frame's planning on the GPU still reads the match buffers
         const FrameRecord& last = ov->ring[(ov->frame_no + kFramesInFlight - 1) % kFramesInFlight];
-        if (last.valid) DC_TRY_HIP(hipStreamWaitEvent(ov->aux, last.done[0], 0));
+        if (ov->planned) DC_TRY_HIP(hipStreamWaitEvent(ov->aux, ov->plan_done, 0));
+        else if (last.valid) DC_TRY_HIP(hipStreamWaitEvent(ov->aux, last.done[0], 0));      // (planned in a graph)
     }
+    ov->looks_ahead = true;
     int rc = dc_match_blocks_opt(frames_next, frames_cur, n_streams, H, W, C, block, radius, match_options, max_block_ssd,
                                  mv, best_ssd, global_mv, n_pass, block_mask, ov->aux);
     if (rc) return rc;

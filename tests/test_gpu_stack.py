@@ -865,6 +865,48 @@ def test_lookahead_matching_without_synchronisation():
             assert torch.equal(x, y)
 
 
+@pytest.mark.parametrize("net,size", [("tiny", 64), ("vgg", 96), ("vgg", 320)])
+def test_lookahead_planned_on_the_gpu_is_dropped_by_a_full_frame(net, size):
+    """Look-ahead matches of frames planned on the GPU, taken, guessed wrong and dropped by a full frame that comes in between
+    (the next cached frame writes the same match buffers and must come after the dropped match): stacks of one stage, which
+    match on the caller's stream, and of several, no synchronisation between the steps of a run.  Same masks, motion and
+    tensors as without look-ahead (fp32; a split K may be grouped differently: K <= 4608 products, sqrt(K) 2^-24 a layer)."""
+    H = W = size
+    layers = synth.tiny_net() if net == "tiny" else synth.vgg16()[:17]
+    block = 8 if net == "tiny" else 16
+    ws, bs = synth.he_weights(layers, 3, bias_scale=0.05, input_shape=(H, W, 3))
+    T = 10
+    video = torch.from_numpy(synth.panning_video(86, n_frames=T, H=H, W=W, fg=((24, 24), (16, 32)))).to(DEV)
+    frames = [video[t:t + 1].contiguous() for t in range(T)]
+    torch.cuda.synchronize()
+    finals = {}
+    for look in (False, True):
+        print(f"[lookahead, GPU plan] {net} {size} {look}", flush=True)
+        runner = binding.StackRunner(layers, ws, bs, 1, H, W, 3, block=block, radius=block, dtype=binding.DC_F32, device_plan=True,
+                                     exact_masks=True)
+        kept = []
+        for stop in (2, 3, 4, 6, T, T, T):
+            runner.reset()
+            for t in range(stop):
+                nxt = frames[t + 1] if look and t + 1 < T else None
+                if look and t == 4:
+                    nxt = frames[0]                                  # a wrong guess
+                force = t in (3, 7)                                  # a full frame drops the match of the step before it
+                tensors = runner.step(frames[t], force_full=force, next_frames=nxt)
+            runner.reset()                                           # the last match was for a frame that never comes
+            runner.step(frames[0])
+            tensors = runner.step(frames[1])
+            torch.cuda.synchronize()
+            kept.append([x.clone() for x in tensors[1:]] + [runner.mask.clone(), runner.gmv.clone(), runner.mv.clone()])
+        finals[look] = kept
+        del runner
+    for f, (a, b) in enumerate(zip(finals[True], finals[False])):
+        assert all(torch.equal(x, y) for x, y in zip(a[-3:], b[-3:])), f
+        assert int(a[-3].sum()) > 0
+        for i, (x, y) in enumerate(zip(a[:-3], b[:-3])):
+            assert _max_rel(x, y) <= 3e-4, (f, i)
+
+
 def _max_rel(a, b):
     a, b = a.float(), b.float()
     return float((a - b).abs().max() / b.abs().max().clamp_min(1e-30))
