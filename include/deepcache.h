@@ -248,6 +248,28 @@ int32_t dc_overlap_destroy(void* overlap);
 int32_t dc_overlap_pipeline(void* overlap, int32_t frames_in_flight /* 1 or 2 */);
 
 /*
+ * What the pipeline of a handle does, for tests and for finding out what a stack runs as.  Frames planned on the GPU
+ * whose launches take the host longer than the GPU takes per frame are recorded as HIP graphs and replayed; whether
+ * that is so is measured.  dc_overlap_replay decides instead: 0 never, 1 always, -1 measured (the default).  Frames
+ * that cannot be replayed (planned on the host, with a profile, with lists or origins read back) are launched as ever.
+ * Results do not depend on it but for the grouping of split sums: launch shapes follow the lengths of the lists as
+ * the last frames had them, a recorded frame's those at its recording.  Errors: DC_ERR_NULL_PTR, DC_ERR_INVALID_ARG.
+ */
+typedef struct dc_overlap_counters {
+    int64_t frames;           /* frames run through the handle */
+    int64_t replayed;         /* of them from graphs */
+    int64_t recorded;         /* recordings (a frame's graphs each) */
+    int64_t dropped;          /* recordings given up because the lists' lengths have moved away */
+    int64_t evicted;          /* recordings given up for others (a stack keeps 16) */
+    int64_t failed;           /* recordings that failed: the stack is launched kernel by kernel from then on */
+    int64_t recuts;           /* times the layers were cut into stages anew */
+    int32_t stages;           /* stages of the last frame (1: no pipeline, or a short stack) */
+    int32_t reserved;
+} dc_overlap_counters;
+int32_t dc_overlap_replay(void* overlap, int32_t mode);
+int32_t dc_overlap_stats(const void* overlap, dc_overlap_counters* counters);
+
+/*
  * Overrides the launch heuristics of the 3x3 stride-1 GEMM kernels for the whole process (tests and
  * experiments; results do not depend on it beyond fp32 summation order): wavefront arrangement
  * (0: 64 channels per workgroup; bf16 only: 1: 128 channels, 2: 64 channels in two blocks per wavefront,

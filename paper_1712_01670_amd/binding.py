@@ -67,6 +67,11 @@ class StackStats(C.Structure):
                 ("profile", C.c_void_p)]
 
 
+class OverlapCounters(C.Structure):
+    _fields_ = [(n, C.c_int64) for n in ("frames", "replayed", "recorded", "dropped", "evicted", "failed", "recuts")] + \
+               [("stages", C.c_int32), ("reserved", C.c_int32)]
+
+
 _lib = None
 
 
@@ -86,6 +91,8 @@ def lib():
         L.dc_overlap_create.argtypes = [C.POINTER(vp)]
         L.dc_overlap_destroy.argtypes = [vp]
         L.dc_overlap_pipeline.argtypes = [vp, i32]
+        L.dc_overlap_replay.argtypes = [vp, i32]
+        L.dc_overlap_stats.argtypes = [vp, C.POINTER(OverlapCounters)]
         L.dc_prefetch_match.argtypes = [vp, vp, vp, i32, i32, i32, i32, i32, i32, u32, vp, vp, vp, vp, vp, vp, vp, sz]
         L.dc_conv_tuning.argtypes = [i32, i32, i32, i32]
         L.dc_conv_kernel_name.argtypes = [i32, C.c_char_p, sz]
@@ -561,6 +568,16 @@ class StackRunner:
                 self.overlap = None
         except Exception:
             pass
+
+    def set_replay(self, mode):
+        """Frames from recorded graphs: 0 never, 1 always, -1 as measured (the default)."""
+        _check("dc_overlap_replay", lib().dc_overlap_replay(self.overlap, int(mode)))
+
+    def overlap_counters(self):
+        """What the pipeline has done so far (frames, replayed, recorded, ..., stages of the last frame)."""
+        c = OverlapCounters()
+        _check("dc_overlap_stats", lib().dc_overlap_stats(self.overlap, C.byref(c)))
+        return c
 
     def reset(self):
         """Drop the cache (scene cut): the next frame is computed in full."""

@@ -1200,13 +1200,8 @@ struct FastChoice { int g, ks, kci; double cost; int geom; };
 
 // Overrides of the launch model (dc_conv_tuning: tests and experiments): arrangement, units per workgroup,
 // K split, channel chunk index; -1 = chosen by the model.  Process-wide; readers take a snapshot under the mutex.
-struct Tuning { int v[4]; };
 std::mutex g_tune_mutex;
-Tuning g_tune_shared{{-1, -1, -1, -1}};
-Tuning tuning_snapshot() {
-    std::lock_guard<std::mutex> g(g_tune_mutex);
-    return g_tune_shared;
-}
+ConvTuning g_tune_shared{{-1, -1, -1, -1}};
 
 // Cycle model of one launch.  A workgroup spends its stages (the longer of the MFMA time and the time to
 // bring the stage's bytes into LDS) plus fixed costs per stage and per workgroup (decode, address set-up,
@@ -1323,9 +1318,13 @@ void conv_fast_kernel_name(int id, char* buf, size_t n) {
     snprintf(buf, n, "conv_fast_kernel<%s, 3, %d, %d, 2, 4, 1>", bf16 ? "__hip_bfloat16" : "float", (bf16 ? 32 : 16) << kci, upw);
 }
 
+ConvTuning conv_tuning() {
+    std::lock_guard<std::mutex> guard(g_tune_mutex);
+    return g_tune_shared;
+}
 void conv_set_tuning(int geom, int g, int ks, int kci) {
     std::lock_guard<std::mutex> guard(g_tune_mutex);
-    g_tune_shared = Tuning{{geom >= 0 ? geom : -1, g > 0 ? g : -1, ks > 0 ? ks : -1, kci >= 0 ? kci : -1}};
+    g_tune_shared = ConvTuning{{geom >= 0 ? geom : -1, g > 0 ? g : -1, ks > 0 ? ks : -1, kci >= 0 ? kci : -1}};
 }
 
 size_t packed_weights_bytes(int k, int s, int cin, int cout, int dtype) {
@@ -1379,7 +1378,7 @@ bool launch_conv_fast(const ConvLaunch& c, long n_cap, long n_units, hipStream_t
     const int* const n_dev = c.tiles ? c.n_tiles_dev : nullptr;
     constexpr bool enabled = true;
     constexpr int g_stem_wgs = 256;      // persistent workgroups of the 7x7 / 11x11 first-layer kernels
-    const Tuning tune = tuning_snapshot();
+    const ConvTuning tune = conv_tuning();
     const int* g_tune = tune.v;
     const size_t esz = dtype_size(c.dtype);
     const bool torus = c.in_origin || c.out_origin;     // only the first-layer kernels (output) and the 3x3 GEMM kernel take origins

@@ -115,7 +115,9 @@ size_t packed_weights_bytes(int k, int s, int cin, int cout, int dtype);
 hipError_t launch_pack_weights(const void* w, void* packed, int cin, int cout, int dtype, hipStream_t st);
 void conv_kernel_name(int id, char* buf, size_t n);
 void conv_fast_kernel_name(int id, char* buf, size_t n);
+struct ConvTuning { int v[4]; };             // dc_conv_tuning's arguments, -1: chosen by the model
 void conv_set_tuning(int geom, int g, int ks, int kci);
+ConvTuning conv_tuning();
 hipError_t launch_conv(const ConvLaunch& c, hipStream_t st);
 
 hipError_t launch_shifted_copy(const RectDev* rects_dev, int n_rects, int max_rect_w, int max_rect_h,
@@ -332,6 +334,8 @@ struct Overlap {
     uint64_t frame_no = 0;
     hipStream_t head = nullptr;                       // stream of the last frame's matching and planning on the GPU
     std::vector<StackPlan*> plans;                    // most recently used first
+    int replay_mode = -1;                             // dc_overlap_replay
+    dc_overlap_counters counters{};
     // look-ahead matching: the arguments of a match already started for the next frame
     struct Prefetch {
         bool valid = false;

@@ -804,7 +804,9 @@ int StackCall::begin() {
                 P.timed_us[s] += ms * 1e3f;
             }
             ++P.timed_frames;
+            const int before = P.partition;
             P.calibrate(most);
+            ov->counters.recuts += P.partition != before ? 1 : 0;
         }
     }
     const int k = pipe ? P.n_stages : 1;
@@ -1239,7 +1241,8 @@ constexpr int kGraphOffShape = 8;           // consecutive frames with other lis
 // The entry for this frame's key, or nullptr if the frame cannot be replayed from a graph: everything its kernels take
 // as arguments has to be part of the key, and nothing may wait for the host or go through a copy in between.
 dc::FrameGraphs* StackCall::find_graphs() {
-    if (!pipe || !P.replay || (cached && !devplan) || prof || regions_out || P.no_graphs) return nullptr;
+    const bool wanted = ov && (ov->replay_mode < 0 ? P.replay : ov->replay_mode == 1 && opt && P.device_plan);
+    if (!pipe || !wanted || (cached && !devplan) || prof || regions_out || P.no_graphs) return nullptr;
     if (cached && (!host_alias || (P.torus && opt->origins_out))) return nullptr;
     const size_t n = n_layers;
     std::vector<uint64_t> key;
@@ -1268,7 +1271,10 @@ dc::FrameGraphs* StackCall::find_graphs() {
         size_t old = 0;
         for (size_t i = 1; i < P.graphs.size(); ++i)
             if (P.graphs[i]->last_use < P.graphs[old]->last_use) old = i;
-        if (P.graphs[old]->ready && drain(ov) != hipSuccess) return nullptr;      // (its graphs may still be running)
+        if (P.graphs[old]->ready) {
+            if (drain(ov) != hipSuccess) return nullptr;      // (its graphs may still be running)
+            ++ov->counters.evicted;
+        }
         P.graphs.erase(P.graphs.begin() + old);
     }
     P.graphs.emplace_back(new dc::FrameGraphs());
@@ -1304,6 +1310,7 @@ int StackCall::record_graphs(dc::FrameGraphs& g) {
     g.hint = unit_hint;
     if (rc) { g.drop(); (void)hipGetLastError(); }
     g.ready = rc == DC_OK;
+    ++(rc ? ov->counters.failed : ov->counters.recorded);
     return rc;
 }
 
@@ -1396,6 +1403,7 @@ int StackCall::run() {
         if (g->off_shape >= kGraphOffShape) {
             DC_TRY_HIP(drain(ov));
             g->drop();
+            ++ov->counters.dropped;
         }
     }
     const bool recorded = g && !g->ready && g->uses++ >= kGraphUses;
@@ -1440,8 +1448,12 @@ int StackCall::run() {
         rec->timed = timed;
         rec->valid = true;
         ++ov->frame_no;
+        ++ov->counters.frames;
+        ov->counters.replayed += replay ? 1 : 0;
+        ov->counters.stages = k;
     }
     if (recut) {
+        ++ov->counters.recuts;
         P.cut(P.device_plan ? kMaxStages : kMaxStages - 1);
         P.timed_frames = 0;
         std::fill(P.timed_us, P.timed_us + kMaxStages, 0.f);
@@ -1496,6 +1508,19 @@ int32_t dc_overlap_pipeline(void* overlap, int32_t frames_in_flight) {
     DC_TRY_HIP(drain(o));
     for (FrameRecord& r : o->ring) r.valid = false;
     o->pipeline = frames_in_flight == 2;
+    return DC_OK;
+}
+
+int32_t dc_overlap_replay(void* overlap, int32_t mode) {
+    if (!overlap) return DC_ERR_NULL_PTR;
+    if (mode < -1 || mode > 1) return DC_ERR_INVALID_ARG;
+    static_cast<Overlap*>(overlap)->replay_mode = mode;
+    return DC_OK;
+}
+
+int32_t dc_overlap_stats(const void* overlap, dc_overlap_counters* counters) {
+    if (!overlap || !counters) return DC_ERR_NULL_PTR;
+    *counters = static_cast<const Overlap*>(overlap)->counters;
     return DC_OK;
 }
 

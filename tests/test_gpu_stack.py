@@ -1,6 +1,7 @@
 """GPU parity of dc_run_stack (whole per-frame path) against the oracle: match results,
 reuse masks and propagated rectangles bit-exact; every tensor within 1e-4 (fp32) or
 2e-2 (bf16) of the oracle, relative to the tensor's largest magnitude."""
+import ctypes
 import threading
 
 import numpy as np
@@ -953,6 +954,100 @@ def test_long_pipelined_runs_stay_with_the_plain_path(net, plan):
         assert torch.equal(a[-1], b[-1]) and torch.equal(a[-2], b[-2]), f
         for i, (x, y) in enumerate(zip(a[:-2], b[:-2])):
             assert _max_rel(x, y) <= 3e-4, (f, i)
+
+
+def _replay_run(layers, ws, bs, frames, block, bf16, mode, order, before=None, **kw):
+    """A runner whose frames are replayed from graphs always (1), never (0) or that has no handle (None), over `order`
+    (frame index, or None: drop the cache); clones of the last frame's tensors, the mask and the motion after every None."""
+    H, W = frames[0].shape[1:3]
+    runner = binding.StackRunner(layers, ws, bs, frames[0].shape[0], H, W, 3, block=block, radius=block,
+                                 dtype=binding.DC_BF16 if bf16 else binding.DC_F32, device_plan=True, exact_masks=True,
+                                 overlap=mode is not None, **kw)
+    if mode is not None:
+        runner.set_replay(mode)
+    kept, tensors = [], None
+    for j, t in enumerate(order):
+        if before is not None:
+            before(j, runner)
+        if t is not None:
+            tensors = runner.step(frames[t])
+            continue
+        last = [runner.read_tensor(i, tensors) if (not runner.torus or runner.layers[i - 1]["type"] == synth.CONV) else tensors[i]
+                for i in range(1, len(layers) + 1)]
+        torch.cuda.synchronize()
+        kept.append([x.clone() for x in last] + [runner.mask.clone(), runner.gmv.clone()])
+        runner.reset()
+    counters = runner.overlap_counters() if mode is not None else None
+    return kept, counters, list(runner._kid)
+
+
+@pytest.mark.parametrize("net,size,kw", [("vgg16", 224, dict(torus=True)), ("vgg16", 96, {}), ("darknet19", 96, dict(torus=True)),
+                                         ("darknet19", 224, {})])
+def test_replayed_frames_are_the_launched_ones(net, size, kw):
+    """Frames replayed from recorded graphs, frames launched kernel by kernel and frames without a handle: every tensor bit
+    for bit, several replays of every graph, full frames and cached ones, other work of the program and synchronisations in
+    between.  (The launch shapes are fixed: units per workgroup and no split of K.)"""
+    print(f"[replay] {net} {size} {kw}", flush=True)
+    layers = synth.resolve_global_pooling(synth.vgg16()[:18] if net == "vgg16" else synth.darknet19()[:19], size, size, 3)
+    ws, bs = synth.he_weights(layers, 3, bias_scale=0.05, input_shape=(size, size, 3))
+    T = 10
+    video = torch.from_numpy(synth.panning_video(87, n_frames=T, H=size, W=size, fg=((24, 24), (16, 32)))).to(DEV)
+    frames = [video[t:t + 1].contiguous() for t in range(T)]
+    torch.cuda.synchronize()
+    order = (list(range(T)) + [None]) * 4 + [0, 1, 2, None, 0, None] + (list(range(T)) + list(range(T - 1, -1, -1)) + [None]) * 2
+    binding.dc_conv_tuning(0, 4, 1, 0)
+    try:
+        runs = {mode: _replay_run(layers, ws, bs, frames, 16, False, mode, order, **kw) for mode in (1, 0, None)}
+    finally:
+        binding.dc_conv_tuning()
+    c = runs[1][1]
+    steps = sum(t is not None for t in order)
+    assert c.frames == steps and c.failed == 0 and c.recorded >= 4 and c.replayed >= steps // 3, [(n, getattr(c, n)) for n, _ in c._fields_]
+    assert runs[0][1].replayed == runs[0][1].recorded == 0
+    if size == 224:
+        assert c.stages > 1
+    assert int(runs[0][0][0][-2].sum()) > 0
+    for other in (0, None):
+        for f, (a, b) in enumerate(zip(runs[1][0], runs[other][0])):
+            for i, (x, y) in enumerate(zip(a, b)):
+                assert torch.equal(x, y), (other, f, i)
+
+
+def test_recordings_are_dropped_and_evicted():
+    """A recording whose lists have become much longer is given up and made anew, and the seventeenth recording of a stack
+    drives the least recently used one out: same tensors as without replay all the while."""
+    layers = synth.vgg16()[:10]
+    ws, bs = synth.he_weights(layers, 3, bias_scale=0.05, input_shape=(96, 96, 3))
+    rng = np.random.default_rng(9)
+    still = rng.integers(0, 256, (1, 96, 96, 3), np.uint8)
+    noise = [rng.integers(0, 256, (1, 96, 96, 3), np.uint8) for _ in range(4)]
+    part = [still.copy() for _ in range(4)]
+    for k, p in enumerate(part):
+        p[0, 8 * k:8 * k + 24, 30:60] = noise[k][0, :24, :30]            # a moving object over a still picture
+    frames = [torch.from_numpy(v).to(DEV) for v in part + noise]
+    torch.cuda.synchronize()
+    order = [j % 4 for j in range(60)] + [None] + [4 + j % 4 for j in range(90)] + [j % 4 for j in range(20)] + [None] + \
+            [j % 4 for j in range(7 * 16)] + [None]
+    results = {}
+    copies = [[torch.from_numpy(b).to(DEV) if b is not None else None for b in bs] for _ in range(7)]     # the same values elsewhere: other keys
+    torch.cuda.synchronize()
+    tail = len(order) - 7 * 16 - 1
+
+    def before(j, runner):
+        if j >= tail and (j - tail) % 16 == 0 and order[j] is not None:
+            runner._bp = (ctypes.c_void_p * len(layers))(*[None if b is None else b.data_ptr() for b in copies[(j - tail) // 16]])
+    for mode in (1, 0):
+        binding.dc_conv_tuning(0, 4, 1, 0)
+        try:
+            results[mode] = _replay_run(layers, ws, bs, frames, 16, False, mode, order, before=before)
+        finally:
+            binding.dc_conv_tuning()
+    c = results[1][1]
+    print("[dropped, evicted]", [(n, getattr(c, n)) for n, _ in c._fields_], flush=True)
+    assert c.failed == 0 and c.dropped >= 1 and c.evicted >= 1 and c.replayed > 20
+    for f, (a, b) in enumerate(zip(results[1][0], results[0][0])):
+        for i, (x, y) in enumerate(zip(a, b)):
+            assert torch.equal(x, y), (f, i)
 
 
 def test_one_handle_for_two_stacks_and_two_caller_streams():
