@@ -1260,6 +1260,7 @@ dc::FrameGraphs* StackCall::find_graphs() {
                               static_cast<const void*>(block_mask), static_cast<const void*>(gmv)})
             key.push_back(reinterpret_cast<uint64_t>(v));
     key.push_back((uint64_t)P.partition << 32 | (cached ? 1 : 0) | (opt->extend_borders ? 2 : 0));
+    for (int v : conv_tuning().v) key.push_back((uint64_t)(int64_t)v);
     uint64_t h = 0x9e3779b97f4a7c15ull;
     for (uint64_t v : key) { h = (h ^ v) * 0xff51afd7ed558ccdull; h ^= h >> 32; }
     for (auto& g : P.graphs)

@@ -1013,6 +1013,33 @@ def test_replayed_frames_are_the_launched_ones(net, size, kw):
                 assert torch.equal(x, y), (other, f, i)
 
 
+def test_replayed_frames_follow_a_change_of_the_launch_shapes():
+    """dc_conv_tuning holds for replayed frames too: a graph recorded before the change is not replayed after it (the kernels
+    of the layers are reported as they are launched), and the one recorded before is replayed again afterwards."""
+    layers = synth.vgg16()[:10]
+    ws, bs = synth.he_weights(layers, 3, bias_scale=0.05, input_shape=(96, 96, 3))
+    video = torch.from_numpy(synth.panning_video(88, n_frames=8, H=96, W=96, fg=((24, 24), (16, 32)))).to(DEV)
+    frames = [video[t:t + 1].contiguous() for t in range(8)]
+    torch.cuda.synchronize()
+    ids, seen = {}, []
+
+    def before(j, runner):
+        if j % 40 == 0:
+            binding.dc_conv_tuning(*((1, 4, 1, 0) if j // 40 % 2 == 0 else (2, 4, 1, 0)))
+        if j % 40 == 39:
+            seen.append(runner.overlap_counters().replayed)
+            ids[j // 40] = list(runner._kid)
+    order = list(range(8)) * 20
+    try:
+        _replay_run(layers, ws, bs, frames, 16, True, 1, order, before=before)
+    finally:
+        binding.dc_conv_tuning()
+    names = [[binding.conv_kernel_name(v) for v in ids[k] if v >= 0] for k in range(4)]
+    print("[replay tuning]", names[0][-1], names[1][-1], seen, flush=True)
+    assert names[0] != names[1] and names[0] == names[2] and names[1] == names[3]
+    assert all(b > a for a, b in zip([0] + seen, seen))
+
+
 def test_recordings_are_dropped_and_evicted():
     """A recording whose lists have become much longer is given up and made anew, and the seventeenth recording of a stack
     drives the least recently used one out: same tensors as without replay all the while."""
