@@ -1236,7 +1236,8 @@ int StackCall::emit_stage(int s, hipStream_t st) {
 
 constexpr size_t kMaxFrameGraphs = 16;       // keys kept per stack
 constexpr int kGraphUses = 2;               // frames of a key that are launched kernel by kernel before it is recorded
-constexpr int kGraphOffShape = 8;           // consecutive frames with other list lengths before a graph is recorded anew
+constexpr int kGraphOffShape = 8;           // consecutive frames with other list lengths before a graph is recorded anew:
+constexpr int kGraphOffUnits = 16;          // a layer's differs by more than a quarter and this many units (the launch of a few is as good as any)
 
 // The entry for this frame's key, or nullptr if the frame cannot be replayed from a graph: everything its kernels take
 // as arguments has to be part of the key, and nothing may wait for the host or go through a copy in between.
@@ -1393,14 +1394,13 @@ int StackCall::run() {
                 break;
             }
     dc::FrameGraphs* g = find_graphs();
-    if (g && g->ready && cached) {      // a graph is kept while the lists are about as long as when it was recorded
-        long apart = 0, most = 1;
+    if (g && g->ready && cached) {      // a graph is kept while every layer's list is about as long as when it was recorded
+        bool off = false;
         for (size_t c = 0; c < unit_hint.size(); ++c) {
             const long a = std::max(unit_hint[c], 0l), b = std::max(g->hint[c], 0l);
-            apart += std::abs(a - b);
-            most += std::max(a, b);
+            off = off || std::abs(a - b) * 4 > std::max(a, b) + 4 * kGraphOffUnits;
         }
-        g->off_shape = apart * 4 > most ? g->off_shape + 1 : 0;
+        g->off_shape = off ? g->off_shape + 1 : 0;
         if (g->off_shape >= kGraphOffShape) {
             DC_TRY_HIP(drain(ov));
             g->drop();

@@ -1077,6 +1077,32 @@ def test_recordings_are_dropped_and_evicted():
             assert torch.equal(x, y), (f, i)
 
 
+def test_a_recording_is_dropped_for_one_layer_alone():
+    """Two layers that are always computed in full hold most of the units; the lists of the others grow from a few units to
+    everything.  Their launches are not kept for that reason (in the sum over the layers it is less than a quarter)."""
+    layers = synth.vgg16()[:10]
+    ws, bs = synth.he_weights(layers, 3, bias_scale=0.05, input_shape=(96, 96, 3))
+    rng = np.random.default_rng(10)
+    still = rng.integers(0, 256, (1, 96, 96, 3), np.uint8)
+    part = [still.copy() for _ in range(4)]
+    for k, p in enumerate(part):
+        p[0, 8 * k:8 * k + 8, 30:40] = rng.integers(0, 256, (8, 10, 3), np.uint8)
+    frames = [torch.from_numpy(v).to(DEV) for v in part + [rng.integers(0, 256, (1, 96, 96, 3), np.uint8) for _ in range(4)]]
+    torch.cuda.synchronize()
+    order = [j % 4 for j in range(60)] + [4 + j % 4 for j in range(90)] + [None]
+    flags = np.array([1, 1] + [0] * (len(layers) - 2), np.uint8)
+    binding.dc_conv_tuning(0, 4, 1, 0)
+    try:
+        results = {mode: _replay_run(layers, ws, bs, frames, 16, False, mode, order, no_reuse=flags) for mode in (1, 0)}
+    finally:
+        binding.dc_conv_tuning()
+    c = results[1][1]
+    print("[dropped for one layer]", [(n, getattr(c, n)) for n, _ in c._fields_], flush=True)
+    assert c.failed == 0 and c.dropped >= 1 and c.recorded > c.dropped
+    for x, y in zip(results[1][0][0], results[0][0][0]):
+        assert torch.equal(x, y)
+
+
 def test_one_handle_for_two_stacks_and_two_caller_streams():
     """A handle that is handed from one stack to another and called on changing streams orders every frame behind the
     earlier ones: same tensors as with a handle of their own.  (Stages of different stacks use the same streams, and the
