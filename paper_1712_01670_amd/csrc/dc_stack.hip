@@ -11,6 +11,7 @@
 #include <new>
 
 #include "dc_internal.h"
+#include "dc_replay.h"
 
 using namespace dc;
 
@@ -366,20 +367,8 @@ struct dc::StackPlan {
     float timed_us[kMaxStages] = {};
     std::vector<std::unique_ptr<dc::FrameGraphs>> graphs;
     bool no_graphs = false;                 // recording failed once
-    // Replaying pays while issuing a frame kernel by kernel takes the host longer than the GPU takes per frame: the first is
-    // measured on frames that are issued that way, with what the caller spends between two calls, the second is the
-    // distance of consecutive frames' ends (a frame bound by the host shows the two about equal).
-    bool replay = false;
-    float host_us = 0.f, between_us = 0.f, period_us = 0.f;   // running means (0: nothing measured yet)
+    ReplayRule replay;
     std::chrono::steady_clock::time_point left;               // end of the last call
-    int gaps = 0;                           // consecutive frame distances that were no measure of the GPU (a pause in between)
-    void measured(float& mean, float us) { mean = mean > 0.f ? mean + 0.125f * (us - mean) : us; }
-    void measured_period(float us) {
-        if (period_us > 0.f && us > 2.f * period_us && ++gaps < 8) return;
-        gaps = 0;
-        measured(period_us, us);
-    }
-    void decide() { replay = host_us > 0.f && period_us > 0.f && host_us + between_us > (replay ? 1.f : 0.97f) * period_us; }
     int stage_of(int layer) const {
         int s = 0;
         while (s + 1 < n_stages && layer >= first[s + 1]) ++s;
@@ -700,6 +689,14 @@ struct StackCall {
     Overlap::Prefetch pf;
 
     bool pipe = false, devplan = false, inplace = false;
+    bool gpu_idle = false;                   // the frames before this one were not all still running
+    float blocked_us = 0.f;                  // this call's waits so far
+    struct Blocked {                         // adds its own life to them
+        StackCall& c;
+        const std::chrono::steady_clock::time_point from = std::chrono::steady_clock::now();
+        explicit Blocked(StackCall& call) : c(call) {}
+        ~Blocked() { c.blocked_us += std::chrono::duration<float, std::micro>(std::chrono::steady_clock::now() - from).count(); }
+    };
     int area = 0;                            // plan area of this frame
     hipStream_t stage_st[kMaxStages] = {};
     unsigned char *plan_dev = nullptr, *scratch = nullptr;
@@ -797,6 +794,7 @@ int StackCall::begin() {
     if (pipe && P.recuts_left > 0) {
         FrameRecord& old = ov->ring[ov->frame_no % kFramesInFlight];
         if (old.valid && old.timed && old.plan == &P && old.partition == P.partition) {
+            const Blocked b(*this);
             DC_TRY_HIP(hipEventSynchronize(old.done[old.n_stages - 1]));      // (the first few frames only)
             for (int s = 0; s < old.n_stages; ++s) {
                 float ms = 0.f;
@@ -836,10 +834,10 @@ int StackCall::begin() {
     hipStream_t head = devplan && !pipe ? ov->aux : stage_st[0];
     if (rec.valid) DC_TRY_HIP(wait(head, rec.done[rec.n_stages - 1]));
     const FrameRecord& next = ov->ring[(area + 1) % kFramesInFlight];
-    if (pipe && rec.valid && next.valid && rec.plan == &P && next.plan == &P && hipEventQuery(next.done[next.n_stages - 1]) == hipSuccess) {
+    if (pipe && rec.valid && next.valid && rec.plan == &P && next.plan == &P) {
+        gpu_idle = hipEventQuery(next.done[next.n_stages - 1]) == hipSuccess;
         float ms = 0.f;
-        if (hipEventElapsedTime(&ms, rec.done[rec.n_stages - 1], next.done[next.n_stages - 1]) == hipSuccess) P.measured_period(ms * 1e3f);
-        P.decide();
+        if (gpu_idle && hipEventElapsedTime(&ms, rec.done[rec.n_stages - 1], next.done[next.n_stages - 1]) == hipSuccess) P.replay.period(ms * 1e3f);
     }
     const FrameRecord& prev = ov->ring[(area + kFramesInFlight - 1) % kFramesInFlight];
     if (prev.valid && (prev.plan != &P || prev.partition != P.partition || prev.n_stages != k || prev.caller != caller)) {
@@ -861,6 +859,7 @@ int StackCall::prepare_device_plan() {
     // The layer tables travel with every frame (a few KB): what the device workspace holds from earlier calls is never
     // trusted.  The staging copy is rewritten only when it differs, and then nothing may still be reading it.
     if (std::memcmp(tables_host, P.tables.data(), dl.table_bytes) != 0) {
+        const Blocked b(*this);
         if (ov) {
             DC_TRY_HIP(hipStreamSynchronize(ov->aux));
             for (hipStream_t w : ov->work) DC_TRY_HIP(hipStreamSynchronize(w));
@@ -1242,7 +1241,7 @@ constexpr int kGraphOffUnits = 16;          // a layer's differs by more than a 
 // The entry for this frame's key, or nullptr if the frame cannot be replayed from a graph: everything its kernels take
 // as arguments has to be part of the key, and nothing may wait for the host or go through a copy in between.
 dc::FrameGraphs* StackCall::find_graphs() {
-    const bool wanted = ov && (ov->replay_mode < 0 ? P.replay : ov->replay_mode == 1 && opt && P.device_plan);
+    const bool wanted = ov && (ov->replay_mode < 0 ? P.replay.on && !P.replay.refresh() : ov->replay_mode == 1 && opt && P.device_plan);
     if (!pipe || !wanted || (cached && !devplan) || prof || regions_out || P.no_graphs) return nullptr;
     if (cached && (!host_alias || (P.torus && opt->origins_out))) return nullptr;
     const size_t n = n_layers;
@@ -1274,6 +1273,7 @@ dc::FrameGraphs* StackCall::find_graphs() {
         for (size_t i = 1; i < P.graphs.size(); ++i)
             if (P.graphs[i]->last_use < P.graphs[old]->last_use) old = i;
         if (P.graphs[old]->ready) {
+            const Blocked b(*this);
             if (drain(ov) != hipSuccess) return nullptr;      // (its graphs may still be running)
             ++ov->counters.evicted;
         }
@@ -1402,6 +1402,7 @@ int StackCall::run() {
         }
         g->off_shape = off ? g->off_shape + 1 : 0;
         if (g->off_shape >= kGraphOffShape) {
+            const Blocked b(*this);
             DC_TRY_HIP(drain(ov));
             g->drop();
             ++ov->counters.dropped;
@@ -1434,12 +1435,12 @@ int StackCall::run() {
         if (rc) return rc;
         if (rec) DC_TRY_HIP(hipEventRecord(rec->done[s], stage_st[s]));
     }
-    if (pipe && P.device_plan) {
+    if (pipe && (devplan || (!cached && P.device_plan))) {
         const auto t_end = std::chrono::steady_clock::now();
         auto us = [](auto a, auto b) { return std::chrono::duration<float, std::micro>(b - a).count(); };
-        if (!replay && !recorded) P.measured(P.host_us, us(t_start, t_end));
-        const float between = us(P.left, t_start);
-        if (between < 50.f) P.measured(P.between_us, between);
+        if (replay) P.replay.replayed();
+        else if (!recorded && !timed) P.replay.issued(us(t_start, t_end) - blocked_us, gpu_idle || P.replay.refresh());
+        P.replay.between(us(P.left, t_start));
         P.left = t_end;
     }
     if (replay && local.layer_kernel_id) std::copy(g->kernel_id.begin(), g->kernel_id.end(), local.layer_kernel_id);

@@ -4,6 +4,7 @@ declares, rejects bad arguments before touching the GPU, and its host region log
 import ctypes as C
 import os
 import re
+import subprocess
 
 import numpy as np
 import pytest
@@ -319,3 +320,62 @@ def test_reuse_sweep_generator_hits_its_target_ratio(oracle):
     # across the cut nothing matches
     v = synth.reuse_sweep_video(4003, 0.75, n_frames=8, cut_at=4)
     assert oracle.match_blocks(v[4], v[3], 16, 16, synth.max_block_ssd(16))["mask"].sum() == 0
+
+
+def test_replay_rule(tmp_path):
+    """The rule that decides about recorded graphs: on for a frame bound by the host, off for one bound by the GPU, whatever
+    the first calls took; measured again while frames are replayed, and undone when the host has become the faster side."""
+    source = tmp_path / "rule.cpp"
+    source.write_text(r"""
+#include "dc_replay.h"
+#include <cstdio>
+using dc::ReplayRule;
+static int fail(const char* what) { std::puts(what); return 1; }
+int main() {
+    {   // bound by the GPU: 1000 us a frame, 300 us to issue one; the first calls take long, and calls on full queues do
+        ReplayRule r;
+        for (int f = 0; f < 200; ++f) {
+            r.issued(f < ReplayRule::kFirstFrames ? 20000.f : f % 10 < 3 ? 300.f : 1000.f, f % 10 < 3);
+            r.between(2.f);
+            if (f > 3) r.period(1000.f);
+            if (r.on) return fail("bound by the GPU");
+        }
+    }
+    {   // nothing measured on the host: off
+        ReplayRule r;
+        for (int f = 0; f < 50; ++f) { r.issued(900.f, false); r.period(800.f); }
+        if (r.on) return fail("nothing measured");
+    }
+    {   // bound by the host, then the caller's machine gets faster: on, refreshed, off
+        ReplayRule r;
+        int on_at = -1, refreshes = 0, off_at = -1;
+        for (int f = 0; f < 2000; ++f) {
+            const bool fast = f >= 400, again = r.refresh();
+            refreshes += again;
+            if (r.on && !again) r.replayed();
+            else r.issued(fast ? 100.f : 300.f, !r.on || again);
+            r.period(r.on ? 200.f : fast ? 200.f : 300.f);
+            if (r.on && on_at < 0) on_at = f;
+            if (!r.on && on_at >= 0 && off_at < 0) off_at = f;
+        }
+        if (on_at < 0 || on_at > 8) return fail("bound by the host: late");
+        if (off_at < 400) return fail("undone too early or never");
+        if (refreshes < 2) return fail("no refresh");
+        if (r.on) return fail("back on");
+    }
+    {   // pauses between frames are no measure of the GPU, a new pace is
+        ReplayRule r;
+        for (int f = 0; f < 10; ++f) r.period(100.f);
+        r.period(5000.f);
+        if (r.period_us > 101.f) return fail("pause");
+        for (int f = 0; f < 60; ++f) r.period(400.f);
+        if (r.period_us < 390.f) return fail("pace");
+    }
+    return 0;
+}
+""")
+    exe = tmp_path / "rule"
+    csrc = os.path.join(os.path.dirname(os.path.abspath(binding.__file__)), "csrc")
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-I", csrc, str(source), "-o", str(exe)], check=True)
+    out = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert out.returncode == 0, out.stdout
