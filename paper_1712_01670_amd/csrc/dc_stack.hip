@@ -500,6 +500,9 @@ int make_plan(StackPlan& P, const dc_layer* layers, int n_layers, int n_streams,
     P.may_in_place = may_in_place;
     device_plan_layout(layers, n_layers, P.hs, P.ws, n_streams, max_rects, P.dl, P.no_reuse.empty() ? nullptr : P.no_reuse.data());
     P.dl_fits_host = P.dl.ok && P.dl.table_bytes <= kDevHostRegion - 3 * kDevHostSlot;
+    // Asked for and possible (the kernels hold the blocks of a frame in 64 rows of 64 bits); otherwise the host plans, and the
+    // stages are laid out for that: aux is left to the matching, which the host waits for.
+    P.device_plan = P.device_plan && P.dl_fits_host && H / block >= 1 && W / block >= 1 && H / block <= 64 && W / block <= 64;
     if (P.dl.ok) {
         P.tables.assign(P.dl.table_bytes, 0);
         std::memcpy(P.tables.data(), P.dl.layers.data(), P.dl.layers.size() * sizeof(PlanLayerDev));
@@ -821,7 +824,7 @@ int StackCall::begin() {
         plan_dev = ws_dev + (size_t)area * area_bytes;
         scratch = ws_dev + plans_all / 256 * 256;
     }
-    devplan = cached && P.device_plan && gh() >= 1 && gw() >= 1 && gh() <= 64 && gw() <= 64 && P.dl_fits_host &&
+    devplan = cached && P.device_plan &&
               align_up(P.dl.table_bytes, 256) + P.dl.frame_bytes <= area_bytes && ws_host_bytes >= kDevHostRegion + 256;
     if (P.torus && cached && !devplan) return DC_ERR_UNSUPPORTED;      // a torus frame is planned on the GPU or not at all
     if (!ov) return DC_OK;

@@ -1103,6 +1103,35 @@ def test_a_recording_is_dropped_for_one_layer_alone():
         assert torch.equal(x, y)
 
 
+def test_frames_of_more_blocks_than_the_gpu_plans_run_as_host_planned():
+    """A frame of more than 64 blocks per row is planned on the host whatever device_plan says: same tensors bit for bit as
+    without the option, and the same pipeline: no stage of layers on the stream of the matching, which the host waits for."""
+    H, W, T = 96, 16 * 66, 9
+    layers = synth.vgg16()
+    ws, bs = synth.he_weights(layers, 3, bias_scale=0.05, input_shape=(H, W, 3))
+    video = torch.from_numpy(synth.panning_video(89, n_frames=T, H=H, W=W, fg=((24, 24), (32, 160)))).to(DEV)
+    frames = [video[t:t + 1].contiguous() for t in range(T)]
+    torch.cuda.synchronize()
+    results = {}
+    for dp in (False, True):
+        print(f"[66 blocks] device_plan={dp}", flush=True)
+        runner = binding.StackRunner(layers, ws, bs, 1, H, W, 3, block=16, radius=8, dtype=binding.DC_F32, expiry=6, device_plan=dp,
+                                     exact_masks=dp)
+        kept = []
+        for t in range(T):
+            tensors = runner.step(frames[t])
+            if t in (2, T - 1):
+                torch.cuda.synchronize()
+                assert runner.stats.n_reusable_blocks > 0
+                kept.append([x.clone() for x in tensors[1:]] + [runner.mask.clone()])
+        results[dp] = kept, runner.overlap_counters().stages
+        del runner
+    assert results[True][1] == results[False][1] <= 3, (results[True][1], results[False][1])
+    for a, b in zip(results[True][0], results[False][0]):
+        for i, (x, y) in enumerate(zip(a, b)):
+            assert torch.equal(x, y), i
+
+
 def test_one_handle_for_two_stacks_and_two_caller_streams():
     """A handle that is handed from one stack to another and called on changing streams orders every frame behind the
     earlier ones: same tensors as with a handle of their own.  (Stages of different stacks use the same streams, and the
