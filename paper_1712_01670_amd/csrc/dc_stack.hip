@@ -390,6 +390,7 @@ struct dc::StackPlan {
         for (int i = first[s]; i < first[s + 1]; ++i) us += layer_us[i];
         return us;
     }
+    float period(float longest_us, int k) const;      // of a frame in k stages
     void calibrate(int max_stages);
 };
 
@@ -473,7 +474,10 @@ float layer_cost(const StackPlan& P, int i) {
         const bool gemm = plain_square(l) && ((l.k == 3 && l.s == 1) || l.k == 1);
         us = 5.0 + (gemm ? 0.0 : 0.8 * g.kh * g.kw) + g.kh * g.kw * l.cin * l.cout * esz / 0.8e6 * std::min(1.0, 400.0 / out_px) + std::max(bytes / 3.5e6, flops / ((P.dtype == DC_BF16 ? 0.9e9 : 0.1e9) * (gemm ? 1.0 : 0.25)));
     } else if (l.type == DC_FC) {
-        us = 8.0 + (double)P.hs[l.in0] * P.ws[l.in0] * P.cs[l.in0] * l.cout * esz * (1.0 + n / 6.0) / 4e6;
+        const double row = (double)P.hs[l.in0] * P.ws[l.in0] * P.cs[l.in0] * esz;
+        // the weights from memory, or a wavefront's walk along its neuron's row (a whole one for one stream, a sixteenth
+        // for several): few neurons on long rows are that chain of loads
+        us = 8.0 + std::max(row * l.cout * (1.0 + n / 40.0) / 4e6, n < 2.0 ? row / 1024.0 * 0.35 : row / 2048.0 * (0.85 + 0.035 * n));
     } else if (l.type == DC_LRN) {
         us = 3.0 + bytes / 1e6;
     }
@@ -548,12 +552,16 @@ int make_plan(StackPlan& P, const dc_layer* layers, int n_layers, int n_streams,
 }  // namespace
 
 // Cuts the layers into at most max_stages stages of about equal time such that no tensor with a single buffer is
-// written in one stage and read in a later one (the writer's next frame would have to wait for the reader).  A stage
-// costs the host a cross-stream wait (8-12 us) per frame, and planned on the host a frame waits for its matching anyway, so
-// short stages are not worth having.
+// written in one stage and read in a later one (the writer's next frame would have to wait for the reader).
+// A frame takes as long as its longest stage or as the host needs for it: graphs, events and cross-stream waits of a stage cost
+// the host about 30 us (Dave on one fp32 stream, us per frame with 1 to 4 stages: 95, 80, 117, 133; VGG-16 224x224 bf16: 200, 140,
+// 135, 147; ResNet-50: 515, 320, 257, 212), so a stage has to shorten what is the longer of the two by a tenth.  Planned on the
+// host, a frame waits for its matching anyway and stages under 80 us are not worth having (VGG-16 224x224: 167, 169, 200;
+// ResNet-50: 284 with two, 361 with three).
+constexpr float kStageHostUs = 30.f;
+float StackPlan::period(float longest_us, int k) const { return device_plan ? std::max(longest_us, kStageHostUs * k) : longest_us; }
 void StackPlan::cut(int max_stages) {
     const int n = (int)layers.size();
-    const float stage_us_min = device_plan ? 40.f : 80.f;
     std::vector<char> allowed(n, 1);       // allowed[i]: a stage may start with layer i
     for (int t = 0; t <= n; ++t)
         if (single[t])
@@ -561,8 +569,8 @@ void StackPlan::cut(int max_stages) {
     const float head = device_plan ? head_us : 0.f;
     float total = head;
     for (float v : layer_us) total += v;
-    int k = (int)(total / stage_us_min);
-    k = k < 1 ? 1 : (k > max_stages ? max_stages : k);
+    int k = device_plan ? max_stages : (int)(total / 80.f);
+    k = std::min({std::max(k, 1), max_stages, n});
     // best[s][i]: smallest possible longest stage when layers 0 .. i - 1 form s stages
     std::vector<float> sum(n + 1, head);
     for (int i = 0; i < n; ++i) sum[i + 1] = sum[i] + layer_us[i];
@@ -576,7 +584,7 @@ void StackPlan::cut(int max_stages) {
                 const float v = std::max(best[s - 1][j], sum[i] - sum[j]);
                 if (v < best[s][i]) { best[s][i] = v; from[s][i] = j; }
             }
-    while (k > 1 && best[k][n] > 0.9f * best[k - 1][n]) --k;                // a stage that shortens nothing
+    while (k > 1 && period(best[k][n], k) > 0.9f * period(best[k - 1][n], k - 1)) --k;      // a stage that shortens nothing
     n_stages = k;
     first[k] = n;
     for (int s = k, i = n; s > 1; --s) { i = from[s][i]; first[s - 1] = i; }
@@ -605,7 +613,7 @@ void StackPlan::calibrate(int max_stages) {
     std::copy(first, first + kMaxStages + 1, old_first);
     std::vector<int> old_crossing = crossing;
     cut(max_stages);
-    if (longest() < 0.93f * now) {
+    if (period(longest(), n_stages) < 0.93f * period(now, old_stages)) {
         --recuts_left;
     } else {                                // as good as it gets
         recuts_left = 0;

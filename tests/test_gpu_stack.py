@@ -1132,6 +1132,28 @@ def test_frames_of_more_blocks_than_the_gpu_plans_run_as_host_planned():
             assert torch.equal(x, y), i
 
 
+def test_short_stacks_are_cut_into_few_stages():
+    """A stage costs the host about 30 us per frame: a stack of under 150 us on the GPU is not cut into four (it was, and
+    ran slower than without stages), a longer one is."""
+    stages = {}
+    for net, H, W in (("dave", 66, 200), ("resnet50", 224, 224)):
+        layers = synth.resolve_global_pooling(synth.dave_orig() if net == "dave" else synth.resnet50_trunk(), H, W, 3)
+        ws, bs = synth.he_weights(layers, 3, residual_scale=0.5, input_shape=(H, W, 3))
+        video = torch.from_numpy(synth.panning_video(90, n_frames=8, H=H, W=W, fg=((16, 16),))).to(DEV)
+        frames = [video[t:t + 1].contiguous() for t in range(8)]
+        torch.cuda.synchronize()
+        runner = binding.StackRunner(layers, ws, bs, 1, H, W, 3, block=16, radius=16, dtype=binding.DC_F32, device_plan=True, exact_masks=True)
+        for t in range(48):
+            if t % 8 == 0:
+                runner.reset()
+            runner.step(frames[t % 8])
+        torch.cuda.synchronize()
+        stages[net] = runner.overlap_counters().stages
+        del runner
+    print("[stages]", stages, flush=True)
+    assert stages["dave"] <= 3 and stages["resnet50"] == 4
+
+
 def test_one_handle_for_two_stacks_and_two_caller_streams():
     """A handle that is handed from one stack to another and called on changing streams orders every frame behind the
     earlier ones: same tensors as with a handle of their own.  (Stages of different stacks use the same streams, and the
