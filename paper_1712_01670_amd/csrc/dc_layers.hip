@@ -382,86 +382,93 @@ struct Vec16 {
     }
 };
 
-// Max or average pooling, CV vectors per pixel.  grid.y walks the (stream, output row) pairs, grid.x the Wout * CV vectors of a
-// row, so the only division per vector is one of 32 bits.  The loads of a group of kPoolGroup window columns go out together: a
-// window is otherwise a chain of memory latencies (7x7 over 7x7x1024, 16 bf16 streams: one load at a time 19.0 us).
+// Position of vector i of an output map of Wout * CV vectors a row (the divisors' reciprocals: fast_div_any).
+struct PoolMap {
+    int Hin, Win, CV, Hout, Wout;
+    uint32_t cv_magic, wout_magic, groups_magic;
+    unsigned out_vecs;                    // of a stream
+    int groups;                           // workgroups of a stream's map
+};
+// The launch's workgroups in the order in which the eight XCDs (workgroup i runs on XCD i % 8) each have a contiguous run of
+// them: windows of neighbouring rows share input rows, and each XCD has an L2 of its own.
+__device__ __forceinline__ int pool_group() { return (int)(blockIdx.x % 8 * (gridDim.x / 8) + blockIdx.x / 8); }     // (the grid is a multiple of eight)
+__device__ __forceinline__ void pool_pixel(const PoolMap& m, unsigned i, int& y, int& x, int& cv) {
+    const int pix = fast_div_any((int)i, m.cv_magic, m.CV);
+    cv = (int)i - pix * m.CV;
+    y = fast_div_any(pix, m.wout_magic, m.Wout);
+    x = pix - y * m.Wout;
+}
+
+// Max or average pooling, CV vectors per pixel: a thread per vector of a stream's output map, counted in 32 bits.  Bound by memory,
+// and what it reads twice has to come from L2: in launch order, rows spread over the XCDs, 3x3 stride 2 over 112x112x64, 64
+// streams, took 55.8 us in fp32 and 29.9 in bf16 (average; maximum 53.7 and 26.7), now 35.0 and 25.4 (33.5 and 18.4).  The loads of
+// a group of kPoolGroup window columns go out together: a window is otherwise a chain of memory latencies (7x7 over 7x7x1024,
+// 16 bf16 streams: one load at a time 19.0 us).
 constexpr int kPoolGroup = 4;
 template <typename T, bool AVG>
-__global__ __launch_bounds__(kThreads) void pool_vec_kernel(const uint4* __restrict__ in, uint4* __restrict__ out,
-                                                            unsigned n_rows, int Hin, int Win, int CV, int Hout, int Wout,
-                                                            int k, int s, int p) {
+__global__ __launch_bounds__(kThreads) void pool_vec_kernel(const uint4* __restrict__ in, uint4* __restrict__ out, int n_streams,
+                                                            PoolMap m, int k, int s, int p) {
     constexpr int VE = Vec16<T>::VE;
-    const unsigned row_vecs = (unsigned)Wout * (unsigned)CV;
-    for (unsigned row = blockIdx.y; row < n_rows; row += gridDim.y) {
-        const unsigned stream = row / (unsigned)Hout;
-        const int y = (int)(row - stream * (unsigned)Hout);
-        const int y0 = max(y * s - p, 0), y1 = min(y * s - p + k, Hin);
-        const uint4* const map = in + (size_t)stream * Hin * Win * CV;
-        uint4* const orow = out + (size_t)row * row_vecs;
-        for (unsigned i = blockIdx.x * kThreads + threadIdx.x; i < row_vecs; i += gridDim.x * kThreads) {
-            const int x = (int)(i / (unsigned)CV), cv = (int)(i - (unsigned)x * (unsigned)CV);
-            const int x0 = max(x * s - p, 0), x1 = min(x * s - p + k, Win);
-            float acc[VE];
+    const int group = pool_group(), stream = fast_div_any(group, m.groups_magic, m.groups);
+    const unsigned i = (unsigned)(group - stream * m.groups) * kThreads + threadIdx.x;
+    if (stream >= n_streams || i >= m.out_vecs) return;
+    const uint4* const map = in + (size_t)stream * m.Hin * m.Win * m.CV;
+    int y, x, cv;
+    pool_pixel(m, i, y, x, cv);
+    const int y0 = max(y * s - p, 0), y1 = min(y * s - p + k, m.Hin), x0 = max(x * s - p, 0), x1 = min(x * s - p + k, m.Win);
+    float acc[VE];
 #pragma unroll
-            for (int e = 0; e < VE; ++e) acc[e] = AVG ? 0.f : -INFINITY;
-            for (int iy = y0; iy < y1; ++iy) {
-                const uint4* const line = map + (size_t)iy * Win * CV + cv;
-                for (int ix = x0; ix < x1; ix += kPoolGroup) {
-                    float f[kPoolGroup][VE];
+    for (int e = 0; e < VE; ++e) acc[e] = AVG ? 0.f : -INFINITY;
+    for (int iy = y0; iy < y1; ++iy) {
+        const uint4* const line = map + (size_t)iy * m.Win * m.CV + cv;
+        for (int ix = x0; ix < x1; ix += kPoolGroup) {
+            float f[kPoolGroup][VE];
 #pragma unroll
-                    for (int d = 0; d < kPoolGroup; ++d) Vec16<T>::load(line + (size_t)min(ix + d, x1 - 1) * CV, f[d]);   // past the end: the last one again, not used
+            for (int d = 0; d < kPoolGroup; ++d) Vec16<T>::load(line + (size_t)min(ix + d, x1 - 1) * m.CV, f[d]);   // past the end: the last one again, not used
 #pragma unroll
-                    for (int d = 0; d < kPoolGroup; ++d)
-                        if (ix + d < x1) {
+            for (int d = 0; d < kPoolGroup; ++d)
+                if (ix + d < x1) {
 #pragma unroll
-                            for (int e = 0; e < VE; ++e) acc[e] = AVG ? acc[e] + f[d][e] : fmaxf(acc[e], f[d][e]);
-                        }
+                    for (int e = 0; e < VE; ++e) acc[e] = AVG ? acc[e] + f[d][e] : fmaxf(acc[e], f[d][e]);
                 }
-            }
-            if (AVG) {
-                const int cnt = (y1 - y0) * (x1 - x0);
-#pragma unroll
-                for (int e = 0; e < VE; ++e) acc[e] = cnt > 0 ? acc[e] / (float)cnt : 0.f;
-            }
-            Vec16<T>::store(orow + i, acc);
         }
     }
+    if (AVG) {
+        const int cnt = (y1 - y0) * (x1 - x0);
+#pragma unroll
+        for (int e = 0; e < VE; ++e) acc[e] = cnt > 0 ? acc[e] / (float)cnt : 0.f;
+    }
+    Vec16<T>::store(out + (size_t)stream * m.out_vecs + i, acc);
 }
 
 // Max-pooling over 3x3 windows that all reach into the map (padding below 3), in the manner of pool_vec_kernel with the nine
 // loads of a window in flight together.  A tap outside the map reads the nearest one of the window's own inside it, which a
-// maximum does not see.  55x55x96 stride 1, 64 bf16 streams: 39.0 us with three 64-bit divisions per vector and a load at a
-// time, 24.3 now; 27x27x256: 24.8 -> 15.6.
+// maximum does not see.  55x55x96 stride 1, 64 bf16 streams: 38.7 us with three 64-bit divisions per vector and a load at a
+// time, 20.4 now; 27x27x256: 25.1 -> 13.6.
 template <typename T>
-__global__ __launch_bounds__(kThreads) void maxpool3x3_vec_kernel(const uint4* __restrict__ in, uint4* __restrict__ out,
-                                                                  unsigned n_rows, int Hin, int Win, int CV, int Hout, int Wout,
-                                                                  int s, int p) {
+__global__ __launch_bounds__(kThreads) void maxpool3x3_vec_kernel(const uint4* __restrict__ in, uint4* __restrict__ out, int n_streams,
+                                                                  PoolMap m, int s, int p) {
     constexpr int VE = Vec16<T>::VE;
-    const unsigned row_vecs = (unsigned)Wout * (unsigned)CV;
-    for (unsigned row = blockIdx.y; row < n_rows; row += gridDim.y) {
-        const unsigned stream = row / (unsigned)Hout;
-        const int y = (int)(row - stream * (unsigned)Hout);
-        const uint4* const map = in + (size_t)stream * Hin * Win * CV;
-        size_t line[3];
+    const int group = pool_group(), stream = fast_div_any(group, m.groups_magic, m.groups);
+    const unsigned i = (unsigned)(group - stream * m.groups) * kThreads + threadIdx.x;
+    if (stream >= n_streams || i >= m.out_vecs) return;
+    const uint4* const map = in + (size_t)stream * m.Hin * m.Win * m.CV;
+    int y, x, cv;
+    pool_pixel(m, i, y, x, cv);
+    float f[9][VE];
 #pragma unroll
-        for (int d = 0; d < 3; ++d) line[d] = (size_t)min(max(y * s - p + d, 0), Hin - 1) * Win;
-        uint4* const orow = out + (size_t)row * row_vecs;
-        for (unsigned i = blockIdx.x * kThreads + threadIdx.x; i < row_vecs; i += gridDim.x * kThreads) {
-            const int x = (int)(i / (unsigned)CV), cv = (int)(i - (unsigned)x * (unsigned)CV);
-            float f[9][VE];
-#pragma unroll
-            for (int t = 0; t < 9; ++t)
-                Vec16<T>::load(map + (line[t / 3] + min(max(x * s - p + t % 3, 0), Win - 1)) * CV + cv, f[t]);
-            float acc[VE];
-#pragma unroll
-            for (int e = 0; e < VE; ++e) acc[e] = -INFINITY;
-#pragma unroll
-            for (int t = 0; t < 9; ++t)
-#pragma unroll
-                for (int e = 0; e < VE; ++e) acc[e] = fmaxf(acc[e], f[t][e]);
-            Vec16<T>::store(orow + i, acc);
-        }
+    for (int t = 0; t < 9; ++t) {
+        const size_t line = (size_t)min(max(y * s - p + t / 3, 0), m.Hin - 1) * m.Win;
+        Vec16<T>::load(map + (line + min(max(x * s - p + t % 3, 0), m.Win - 1)) * m.CV + cv, f[t]);
     }
+    float acc[VE];
+#pragma unroll
+    for (int e = 0; e < VE; ++e) acc[e] = -INFINITY;
+#pragma unroll
+    for (int t = 0; t < 9; ++t)
+#pragma unroll
+        for (int e = 0; e < VE; ++e) acc[e] = fmaxf(acc[e], f[t][e]);
+    Vec16<T>::store(out + (size_t)stream * m.out_vecs + i, acc);
 }
 
 // The pooling of the VGG- and Darknet-style stacks, 2x2 windows with stride 2 and no padding: every window lies
@@ -824,7 +831,7 @@ hipError_t launch_pool(const void* in, void* out, int n_streams, int Hin, int Wi
     const size_t n = (size_t)n_streams * Hout * Wout * C;
     if (n == 0) return hipSuccess;
     if ((C * dtype_size(dtype)) % 16 == 0 && reinterpret_cast<uintptr_t>(in) % 16 == 0 && reinterpret_cast<uintptr_t>(out) % 16 == 0 &&
-        (size_t)Wout * C < 0x7fffffffull) {
+        (size_t)Hout * Wout * (C * dtype_size(dtype) / 16) < 0x7fffffffull) {
         const int cv = (int)(C * dtype_size(dtype) / 16);
         const size_t nv = (size_t)n_streams * Hout * Wout * cv;
         if (!AVG && k == 2 && s == 2 && p == 0 && (size_t)n_streams * Hout <= 65535 && (size_t)Hin * Win * cv < 0x7fffffffull) {
@@ -837,24 +844,24 @@ hipError_t launch_pool(const void* in, void* out, int n_streams, int Hin, int Wi
                                    Win, cv, Hout, Wout);
             return hipGetLastError();
         }
-        // (stream, row) pairs are counted in 32 bits: larger batches go out in several launches of whole streams
-        const int per_launch = (int)std::min<size_t>((size_t)n_streams, std::max<size_t>(1, 0x7fffffffu / (size_t)Hout));
-        const size_t in_map = (size_t)Hin * Win * cv, out_map = (size_t)Hout * Wout * cv;
+        auto magic = [](int d) { return (uint32_t)((0x100000000ull + (uint64_t)d - 1) / (uint64_t)d); };     // (fast_div_any)
+        const unsigned vecs = (unsigned)((size_t)Hout * Wout * cv);
+        const int groups = (int)((vecs + kThreads - 1) / kThreads);
+        const PoolMap m{Hin, Win, cv, Hout, Wout, magic(cv), magic(Wout), magic(groups), vecs, groups};
+        // a launch has less than 2^32 threads: larger batches go out in several, of whole streams
+        const int per_launch = std::max(1, (1 << 23) / groups);
         for (int s0 = 0; s0 < n_streams; s0 += per_launch) {
-            const unsigned rows = (unsigned)std::min(per_launch, n_streams - s0) * (unsigned)Hout;
-            const size_t gx = ((size_t)Wout * cv + kThreads - 1) / kThreads;
-            const dim3 grid((unsigned)std::min<size_t>(gx, 65535), std::min(rows, 65535u));
-            const uint4* const ip = (const uint4*)in + (size_t)s0 * in_map;
-            uint4* const op = (uint4*)out + (size_t)s0 * out_map;
+            const int ns = std::min(per_launch, n_streams - s0);
+            const dim3 grid((unsigned)(((size_t)ns * groups + 7) / 8 * 8));
+            const uint4* const ip = (const uint4*)in + (size_t)s0 * Hin * Win * cv;
+            uint4* const op = (uint4*)out + (size_t)s0 * vecs;
             if (!AVG && k == 3 && p < 3) {
-                if (dtype == DC_BF16)
-                    hipLaunchKernelGGL(maxpool3x3_vec_kernel<__hip_bfloat16>, grid, dim3(kThreads), 0, st, ip, op, rows, Hin, Win, cv, Hout, Wout, s, p);
-                else
-                    hipLaunchKernelGGL(maxpool3x3_vec_kernel<float>, grid, dim3(kThreads), 0, st, ip, op, rows, Hin, Win, cv, Hout, Wout, s, p);
+                if (dtype == DC_BF16) hipLaunchKernelGGL(maxpool3x3_vec_kernel<__hip_bfloat16>, grid, dim3(kThreads), 0, st, ip, op, ns, m, s, p);
+                else hipLaunchKernelGGL(maxpool3x3_vec_kernel<float>, grid, dim3(kThreads), 0, st, ip, op, ns, m, s, p);
             } else if (dtype == DC_BF16) {
-                hipLaunchKernelGGL((pool_vec_kernel<__hip_bfloat16, AVG>), grid, dim3(kThreads), 0, st, ip, op, rows, Hin, Win, cv, Hout, Wout, k, s, p);
+                hipLaunchKernelGGL((pool_vec_kernel<__hip_bfloat16, AVG>), grid, dim3(kThreads), 0, st, ip, op, ns, m, k, s, p);
             } else {
-                hipLaunchKernelGGL((pool_vec_kernel<float, AVG>), grid, dim3(kThreads), 0, st, ip, op, rows, Hin, Win, cv, Hout, Wout, k, s, p);
+                hipLaunchKernelGGL((pool_vec_kernel<float, AVG>), grid, dim3(kThreads), 0, st, ip, op, ns, m, k, s, p);
             }
         }
         return hipGetLastError();

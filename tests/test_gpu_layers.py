@@ -751,3 +751,19 @@ def test_raster_positions_of_a_large_batch(oracle):
         for s in (0, n - 1):
             want = oracle.conv_cached(x[s], w, None, 3, 1, 1, True, bf16=True)
             assert _rel_err(got[s].float().cpu().numpy(), want) <= 2e-2, (cin, s)
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("H,W,ch,k,s,p,n", [(33, 41, 48, 3, 1, 1, 5), (40, 24, 64, 3, 2, 1, 7), (17, 19, 8, 3, 2, 0, 9), (30, 30, 96, 2, 1, 0, 3),
+                                             (9, 9, 16, 9, 1, 0, 11), (64, 64, 32, 3, 1, 2, 1)])
+def test_pooling_workgroups_cover_every_stream(oracle, H, W, ch, k, s, p, n, bf16):
+    """Workgroups dealt to the XCDs in runs: numbers of them that are no multiple of eight, maps of one and of many workgroups,
+    a partial last one per stream."""
+    print(f"[pool groups] {H}x{W}x{ch} k={k} s={s} p={p} n={n} bf16={bf16}", flush=True)
+    x = (np.random.default_rng(H + ch).standard_normal((n, H, W, ch)) * 4).astype(np.float32)
+    if bf16:
+        x = oracle.round_bf16(x)
+    got_max, got_avg = (_to_np(f(_to_dev(x, bf16), k, s, p)) for f in (binding.dc_maxpool_layer, binding.dc_avgpool_layer))
+    for i in range(n):
+        assert np.array_equal(got_max[i], oracle.maxpool(x[i], k, s, p)), i
+        assert _rel_err(got_avg[i], oracle.avgpool(x[i], k, s, p, bf16=bf16)) <= (2e-2 if bf16 else 1e-4), i
