@@ -238,9 +238,12 @@ __global__ __launch_bounds__(kThreads) void fc_kernel(const T* __restrict__ x, c
     const int o = blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
     const int s0 = blockIdx.y * NS;
     if (o >= cout) return;                        // whole wavefronts leave
-    float acc[NS];
+    constexpr int NA = NS > 1 ? VE : 1;           // sums per stream
+    float acc[NS][NA];
 #pragma unroll
-    for (int s = 0; s < NS; ++s) acc[s] = 0.f;
+    for (int s = 0; s < NS; ++s)
+#pragma unroll
+        for (int a = 0; a < NA; ++a) acc[s][a] = 0.f;
     for (size_t k = (size_t)lane * VE; k < K; k += 64 * VE) {
         float wf[VE];
         fc_load<T, VE>(w + (size_t)o * K + k, wf);
@@ -250,14 +253,18 @@ __global__ __launch_bounds__(kThreads) void fc_kernel(const T* __restrict__ x, c
                 float xf[VE];
                 fc_load<T, VE>(x + (size_t)(s0 + s) * K + k, xf);
 #pragma unroll
-                for (int e = 0; e < VE; ++e) acc[s] = fmaf(wf[e], xf[e], acc[s]);
+                for (int e = 0; e < VE; ++e) acc[s][e % NA] = fmaf(wf[e], xf[e], acc[s][e % NA]);
             }
         }
     }
     const float b = bias ? bias[o] : 0.f;
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
-        float v = wave_sum_f32(acc[s]) + b;
+#pragma unroll
+        for (int a = NA / 2; a >= 1; a >>= 1)
+#pragma unroll
+            for (int i = 0; i < a; ++i) acc[s][i] += acc[s][i + a];
+        float v = wave_sum_f32(acc[s][0]) + b;
         if (relu) v = v > 0.f ? v : 0.f;
         if (lane == 0 && s0 + s < n_streams) out[(size_t)(s0 + s) * cout + o] = from_float<T>(v);
     }
@@ -1024,15 +1031,13 @@ hipError_t fc_launch(const void* x, const void* w, const float* bias, void* out,
     constexpr int WPB = kThreads / 64;
     const unsigned gx = (unsigned)((cout + WPB - 1) / WPB);
     // streams per pass over the weights: the partial sums of a pass live in registers
-    if (n_streams == 1) {
+    if (n_streams == 1)
         hipLaunchKernelGGL((fc_kernel<T, 1, VE>), dim3(gx, 1), dim3(kThreads), 0, st, xp, wp, bias, op, n_streams, K, cout, relu);
-    } else if constexpr (VE == 1) {   // rows that are not whole vectors
-        if (n_streams <= 4)
-            hipLaunchKernelGGL((fc_kernel<T, 4, 1>), dim3(gx, 1), dim3(kThreads), 0, st, xp, wp, bias, op, n_streams, K, cout, relu);
-        else
-            hipLaunchKernelGGL((fc_kernel<T, 16, 1>), dim3(gx, (unsigned)((n_streams + 15) / 16)), dim3(kThreads), 0, st, xp, wp, bias,
-                               op, n_streams, K, cout, relu);
-    }
+    else if (n_streams <= 4 || VE > 1)
+        hipLaunchKernelGGL((fc_kernel<T, 4, VE>), dim3(gx, (unsigned)((n_streams + 3) / 4)), dim3(kThreads), 0, st, xp, wp, bias, op, n_streams, K, cout, relu);
+    else              // rows that are not whole vectors
+        hipLaunchKernelGGL((fc_kernel<T, VE == 1 ? 16 : 4, VE>), dim3(gx, (unsigned)((n_streams + 15) / 16)), dim3(kThreads), 0, st, xp, wp, bias,
+                           op, n_streams, K, cout, relu);
     return hipGetLastError();
 }
 
@@ -1050,6 +1055,13 @@ hipError_t fc_vec(const void* x, const void* w, const float* bias, void* out, in
                   hipStream_t st) {
     // one stream: a wavefront per neuron leaves no MFMA column idle and streams the weights as fast (12.8 us; two streams 22.6 against 13.7)
     if (n_streams == 1) return fc_launch<T, 16 / sizeof(T)>(x, w, bias, out, n_streams, K, cout, relu, st);
+    // fp32, few streams, few neurons: a workgroup of 16 neurons streams what one CU can, a wavefront per neuron spreads the rows
+    // over four times as many (us, 16 neurons -> one: two streams 9216 -> 256 22.9 -> 13.5, 4096 -> 1000 11.5 -> 11.5, 1152 -> 100
+    // 4.8 -> 4.1, but 50176 -> 512 117 -> 123; three 4096 -> 256 11.7 -> 8.9, but -> 1000 11.8 -> 14.9; four 9216 -> 256 24.7 -> 20.9,
+    // but 1152 -> 100 5.0 -> 5.3).  With a sum per element of a vector its error against 64 bits is no larger (1.13e-7 against
+    // 1.18e-7) for rows from 1024 to 32768.
+    if (sizeof(T) == 4 && n_streams <= 4 && (long)n_streams * cout <= 2048 && K * cout <= (8u << 20) && K >= (n_streams < 4 ? 1024u : 4096u) && K <= 32768)
+        return fc_launch<T, 16 / sizeof(T)>(x, w, bias, out, n_streams, K, cout, relu, st);
     if (n_streams <= 16) return fc_mfma_launch<T, 1>(x, w, bias, out, n_streams, K, cout, relu, st);
     if (n_streams <= 32) return fc_mfma_launch<T, 2>(x, w, bias, out, n_streams, K, cout, relu, st);
     return fc_mfma_launch<T, 4>(x, w, bias, out, n_streams, K, cout, relu, st);

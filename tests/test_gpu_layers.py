@@ -767,3 +767,22 @@ def test_pooling_workgroups_cover_every_stream(oracle, H, W, ch, k, s, p, n, bf1
     for i in range(n):
         assert np.array_equal(got_max[i], oracle.maxpool(x[i], k, s, p)), i
         assert _rel_err(got_avg[i], oracle.avgpool(x[i], k, s, p, bf16=bf16)) <= (2e-2 if bf16 else 1e-4), i
+
+
+@pytest.mark.parametrize("n,K,cout", [(2, 1024, 100), (2, 9216, 256), (3, 4096, 255), (4, 4096, 512), (4, 4100, 3), (2, 4096, 1024), (2, 1028, 1)])
+def test_fc_few_fp32_streams_and_neurons(n, K, cout):
+    """A wavefront per neuron for two to four fp32 streams: against 64 bits.  A lane adds K / 256 products to each of its four
+    sums, each rounded once, then eight levels of pairs, the bias: rms error at most 2^-24 / sqrt(3) sqrt(K / 256 + 10) of the root of the sum
+    of the squared products, by which the result is compared; five of those for the largest of n cout values."""
+    print(f"[fc few] n={n} K={K} cout={cout}", flush=True)
+    rng = np.random.default_rng(K + cout)
+    x = np.maximum(rng.standard_normal((n, 1, 1, K)), 0).astype(np.float32)
+    w = rng.standard_normal((cout, K)).astype(np.float32)
+    b = rng.standard_normal(cout).astype(np.float32)
+    got = _to_np(binding.dc_fc_layer(_to_dev(x, False), _to_dev(w, False), torch.from_numpy(b).to(DEV), False)).reshape(n, cout)
+    xd, wd = x.reshape(n, K).astype(np.float64), w.astype(np.float64)
+    want = xd @ wd.T + b
+    scale = np.sqrt((xd ** 2) @ (wd ** 2).T) + np.abs(want)
+    err = (got - want) / scale
+    bound = 2.0 ** -24 / np.sqrt(3.0) * np.sqrt(K / 256 + 10)
+    assert np.sqrt((err ** 2).mean()) <= bound and np.abs(err).max() <= 5 * bound, (np.sqrt((err ** 2).mean()) / bound, np.abs(err).max() / bound)
