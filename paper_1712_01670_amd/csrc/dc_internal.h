@@ -309,6 +309,7 @@ struct StackPlan;                          // what dc_run_stack derives from a s
 struct FrameRecord {
     hipEvent_t done[kMaxStages] = {};      // that stage of the frame has finished
     hipEvent_t start[kMaxStages] = {};     // (timed frames) its first kernel may start
+    hipEvent_t read[kMaxStages] = {};      // (StackPlan::tight) its first layer has read what the stage before wrote last
     bool valid = false, timed = false;
     const StackPlan* plan = nullptr;
     int partition = 0;                     // StackPlan::partition of the frame

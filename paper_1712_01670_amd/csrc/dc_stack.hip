@@ -357,6 +357,7 @@ struct dc::StackPlan {
     // the cut into stages (see dc_internal.h): stage s is layers first[s] .. first[s + 1] - 1
     int partition = 0, n_stages = 1;
     int first[kMaxStages + 1] = {};
+    bool tight[kMaxStages] = {};            // the cut before stage s crosses a tensor with a single buffer
     std::vector<float> layer_us;            // rough time of every layer, and of the matching and planning before them
     float head_us = 0.f;
     std::vector<char> single;               // tensors whose buffer is the same for consecutive frames: no cut may cross them
@@ -552,7 +553,10 @@ int make_plan(StackPlan& P, const dc_layer* layers, int n_layers, int n_streams,
 }  // namespace
 
 // Cuts the layers into at most max_stages stages of about equal time such that no tensor with a single buffer is
-// written in one stage and read in a later one (the writer's next frame would have to wait for the reader).
+// written in one stage and read in a later one (the writer's next frame would have to wait for the reader).  Where poolings
+// lie on the torus too, no other cut is left: there a stage may start with the only reader of the tensor that the stage before
+// it writes last, and the next frame's writer waits for that one layer (an event and a wait per frame, no graphs; VGG-16
+// 224x224 on one fp32 stream 384 us per frame in one stage, 259 so; 64 bf16 streams 1787 and 1620).
 // A frame takes as long as its longest stage or as the host needs for it: graphs, events and cross-stream waits of a stage cost
 // the host about 30 us (Dave on one fp32 stream, us per frame with 1 to 4 stages: 95, 80, 117, 133; VGG-16 224x224 bf16: 200, 140,
 // 135, 147; ResNet-50: 515, 320, 257, 212), so a stage has to shorten what is the longer of the two by a tenth.  Planned on the
@@ -565,7 +569,8 @@ void StackPlan::cut(int max_stages) {
     std::vector<char> allowed(n, 1);       // allowed[i]: a stage may start with layer i
     for (int t = 0; t <= n; ++t)
         if (single[t])
-            for (int i = t; i <= last_reader[t]; ++i) allowed[i] = 0;       // the writer is layer t - 1
+            for (int i = t; i <= last_reader[t]; ++i)                       // the writer is layer t - 1
+                allowed[i] = pool_torus && i == t && last_reader[t] == t && allowed[i] == 1 ? 2 : 0;
     const float head = device_plan ? head_us : 0.f;
     float total = head;
     for (float v : layer_us) total += v;
@@ -589,9 +594,10 @@ void StackPlan::cut(int max_stages) {
     first[k] = n;
     for (int s = k, i = n; s > 1; --s) { i = from[s][i]; first[s - 1] = i; }
     first[0] = 0;
+    for (int s = 0; s < kMaxStages; ++s) tight[s] = s > 0 && s < k && allowed[first[s]] == 2;
     crossing.clear();
     for (int t = 0; t <= n; ++t)
-        if (last_reader[t] >= 0 && stage_of(last_reader[t]) > writer_stage(t)) crossing.push_back(t);
+        if (last_reader[t] >= 0 && stage_of(last_reader[t]) > writer_stage(t) && !(single[t] && tight[stage_of(last_reader[t])])) crossing.push_back(t);
     ++partition;
 }
 
@@ -611,6 +617,8 @@ void StackPlan::calibrate(int max_stages) {
     const int old_stages = n_stages, old_partition = partition;
     int old_first[kMaxStages + 1];
     std::copy(first, first + kMaxStages + 1, old_first);
+    bool old_tight[kMaxStages];
+    std::copy(tight, tight + kMaxStages, old_tight);
     std::vector<int> old_crossing = crossing;
     cut(max_stages);
     if (period(longest(), n_stages) < 0.93f * period(now, old_stages)) {
@@ -619,6 +627,7 @@ void StackPlan::calibrate(int max_stages) {
         recuts_left = 0;
         n_stages = old_stages; partition = old_partition;
         std::copy(old_first, old_first + kMaxStages + 1, first);
+        std::copy(old_tight, old_tight + kMaxStages, tight);
         crossing.swap(old_crossing);
     }
 }
@@ -840,6 +849,7 @@ int StackCall::begin() {
     for (int s = 0; s < k; ++s) {
         if (!rec.done[s]) DC_TRY_HIP(hipEventCreate(&rec.done[s]));
         if (!rec.start[s]) DC_TRY_HIP(hipEventCreate(&rec.start[s]));
+        if (P.tight[s] && !rec.read[s]) DC_TRY_HIP(hipEventCreateWithFlags(&rec.read[s], hipEventDisableTiming));
     }
     // the plan area's (and the record's) last frame has to be over
     hipStream_t head = devplan && !pipe ? ov->aux : stage_st[0];
@@ -1240,7 +1250,16 @@ int StackCall::emit_layer(int i, hipStream_t st) {
 int StackCall::emit_stage(int s, hipStream_t st) {
     int rc = emit_copies(s, st);
     const int end = pipe ? P.first[s + 1] : n_layers;
-    for (int i = pipe ? P.first[s] : 0; i < end && !rc; ++i) rc = emit_layer(i, st);
+    for (int i = pipe ? P.first[s] : 0; i < end && !rc; ++i) {
+        if (pipe && i + 1 == end && s + 1 < P.n_stages && P.tight[s + 1]) {
+            // the last frame's next stage has to have read the tensor that this layer writes (with another cut its end
+            // has been waited for)
+            const FrameRecord& last = ov->ring[(area + kFramesInFlight - 1) % kFramesInFlight];
+            if (last.valid && last.plan == &P && last.partition == P.partition) DC_TRY_HIP(wait(st, last.read[s + 1]));
+        }
+        rc = emit_layer(i, st);
+        if (pipe && i == P.first[s] && P.tight[s] && !rc) DC_TRY_HIP(hipEventRecord(ov->ring[area].read[s], st));
+    }
     return rc;
 }
 
@@ -1254,6 +1273,8 @@ constexpr int kGraphOffUnits = 16;          // a layer's differs by more than a 
 dc::FrameGraphs* StackCall::find_graphs() {
     const bool wanted = ov && (ov->replay_mode < 0 ? P.replay.on && !P.replay.refresh() : ov->replay_mode == 1 && opt && P.device_plan);
     if (!pipe || !wanted || (cached && !devplan) || prof || regions_out || P.no_graphs) return nullptr;
+    for (bool tight : P.tight)      // (a wait in the middle of a stage)
+        if (tight) return nullptr;
     if (cached && (!host_alias || (P.torus && opt->origins_out))) return nullptr;
     const size_t n = n_layers;
     std::vector<uint64_t> key;
@@ -1505,6 +1526,7 @@ int32_t dc_overlap_destroy(void* overlap) {
         for (int s = 0; s < kMaxStages; ++s) {
             if (r.done[s]) (void)hipEventDestroy(r.done[s]);
             if (r.start[s]) (void)hipEventDestroy(r.start[s]);
+            if (r.read[s]) (void)hipEventDestroy(r.read[s]);
         }
     if (o->match_done) (void)hipEventDestroy(o->match_done);
     if (o->plan_done) (void)hipEventDestroy(o->plan_done);

@@ -966,14 +966,14 @@ def _replay_run(layers, ws, bs, frames, block, bf16, mode, order, before=None, *
     if mode is not None:
         runner.set_replay(mode)
     kept, tensors = [], None
+    on_torus = [runner.torus and (L["type"] == synth.CONV or (runner.cache_pool_add and L["type"] == synth.MAXPOOL)) for L in runner.layers]
     for j, t in enumerate(order):
         if before is not None:
             before(j, runner)
         if t is not None:
             tensors = runner.step(frames[t])
             continue
-        last = [runner.read_tensor(i, tensors) if (not runner.torus or runner.layers[i - 1]["type"] == synth.CONV) else tensors[i]
-                for i in range(1, len(layers) + 1)]
+        last = [runner.read_tensor(i, tensors) if on_torus[i - 1] else tensors[i] for i in range(1, len(layers) + 1)]
         torch.cuda.synchronize()
         kept.append([x.clone() for x in last] + [runner.mask.clone(), runner.gmv.clone()])
         runner.reset()
@@ -1152,6 +1152,32 @@ def test_short_stacks_are_cut_into_few_stages():
         del runner
     print("[stages]", stages, flush=True)
     assert stages["dave"] <= 3 and stages["resnet50"] == 4
+
+
+@pytest.mark.parametrize("net,size,streams", [("vgg16", 224, 1), ("vgg16", 160, 3), ("darknet19", 224, 2)])
+def test_stages_across_tensors_with_a_single_buffer(net, size, streams):
+    """Convolutions and poolings on the torus: every tensor is one buffer, and a stage starts with the only reader of what the
+    stage before it wrote; the next frame's writer waits for that reader.  Several stages, no synchronisation between the frames
+    of a run: every tensor bit for bit that of the path without a handle (fixed launch shapes)."""
+    print(f"[tight stages] {net} {size} x{streams}", flush=True)
+    layers = synth.vgg16()[:18] if net == "vgg16" else synth.darknet19()[:17]
+    ws, bs = synth.he_weights(layers, 3, bias_scale=0.05, input_shape=(size, size, 3))
+    T = 10
+    videos = [synth.panning_video(91 + s, n_frames=T, H=size, W=size, fg=((24, 24), (16, 32))) for s in range(streams)]
+    frames = [torch.from_numpy(np.stack([v[t] for v in videos])).to(DEV) for t in range(T)]
+    torch.cuda.synchronize()
+    order = (list(range(T)) + [None]) * 3 + [0, 1, 2, 3, None] + (list(range(T)) + list(range(T - 1, -1, -1)) + [None]) * 2
+    binding.dc_conv_tuning(0, 4, 1, 0)
+    try:
+        runs = {mode: _replay_run(layers, ws, bs, frames, 16, False, mode, order, torus=True, cache_pool_add=True) for mode in (1, None)}
+    finally:
+        binding.dc_conv_tuning()
+    c = runs[1][1]
+    assert c.stages > 1 and c.replayed == c.recorded == 0, [(n, getattr(c, n)) for n, _ in c._fields_]
+    assert int(runs[1][0][0][-2].sum()) > 0
+    for f, (a, b) in enumerate(zip(runs[1][0], runs[None][0])):
+        for i, (x, y) in enumerate(zip(a, b)):
+            assert torch.equal(x, y), (f, i)
 
 
 def test_one_handle_for_two_stacks_and_two_caller_streams():
