@@ -223,7 +223,15 @@ int32_t dc_probe_mfma_rate(int32_t lds_reads, void* scratch_dev, size_t scratch_
  *    alternate between two buffers: its writer waits for the readers of the frame that last used
  *    the buffer.  Synchronising the caller's stream yields the frame's results.  In this mode the
  *    inputs (frames, weights) must be complete in memory when the call is made, and the caller's
- *    own streams must be done with the tensors handed over.
+ *    own streams must be done with the tensors handed over: a call's first stages start at once,
+ *    while the caller's stream may still be at earlier frames, so work queued there in order
+ *    reads a tensor of the first stages safely only if no later call has been given its buffer
+ *    (the outputs of the last stage, the stack's output among them, are written on the caller's
+ *    stream itself).  What the caller queues on its stream behind a frame stands in front of the
+ *    next frame's last stage; if it is long, the stack is cut with a shorter last stage (planned
+ *    on the GPU, from the first frames), and a stream of its own that waits for the frame keeps it
+ *    out of the way altogether.
+ *    The device workspace holds four plan areas and four scratch areas of 32 MiB each.
  * Callers that may not create streams simply pass no handle.
  */
 int32_t dc_overlap_create(void** overlap);
@@ -264,7 +272,7 @@ typedef struct dc_overlap_counters {
     int64_t failed;           /* recordings that failed: the stack is launched kernel by kernel from then on */
     int64_t recuts;           /* times the layers were cut into stages anew */
     int32_t stages;           /* stages of the last frame (1: no pipeline, or a short stack) */
-    int32_t reserved;
+    int32_t last_layers;      /* layers of its last stage, which runs on the caller's stream */
 } dc_overlap_counters;
 int32_t dc_overlap_replay(void* overlap, int32_t mode);
 int32_t dc_overlap_stats(const void* overlap, dc_overlap_counters* counters);

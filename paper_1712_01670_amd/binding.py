@@ -69,7 +69,7 @@ class StackStats(C.Structure):
 
 class OverlapCounters(C.Structure):
     _fields_ = [(n, C.c_int64) for n in ("frames", "replayed", "recorded", "dropped", "evicted", "failed", "recuts")] + \
-               [("stages", C.c_int32), ("reserved", C.c_int32)]
+               [("stages", C.c_int32), ("last_layers", C.c_int32)]
 
 
 _lib = None
@@ -589,7 +589,8 @@ class StackRunner:
         """frames: uint8 cuda tensor [n][H][W][C], resident (its producer has completed: the library reads it on
         streams of its own) and contiguous; it is kept by reference as the next step's previous frame, so the
         caller must not overwrite it before that step has run.  Returns the list of this frame's tensors, valid
-        once the current stream is synchronised.  next_frames: the tensor the next step will be called with, if
+        once the current stream is synchronised, until the next step but one (on a torus: the next step) is issued:
+        with a pipeline its first stages do not wait for what the current stream still has to do.  next_frames: the tensor the next step will be called with, if
         the caller has it already (a decoder one frame ahead): its matching is started at the end of this step
         (dc_prefetch_match), so the next step does not wait for it; mv / mask then belong to that frame."""
         assert frames.is_cuda and frames.dtype == torch.uint8 and frames.is_contiguous()

@@ -310,7 +310,8 @@ struct FrameRecord {
     hipEvent_t done[kMaxStages] = {};      // that stage of the frame has finished
     hipEvent_t start[kMaxStages] = {};     // (timed frames) its first kernel may start
     hipEvent_t read[kMaxStages] = {};      // (StackPlan::tight) its first layer has read what the stage before wrote last
-    bool valid = false, timed = false;
+    hipEvent_t after = nullptr;            // (timed frames) the caller's own work behind it has finished
+    bool valid = false, timed = false, tail = false;      // tail: `after` is recorded
     const StackPlan* plan = nullptr;
     int partition = 0;                     // StackPlan::partition of the frame
     int n_stages = 0;

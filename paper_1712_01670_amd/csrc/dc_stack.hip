@@ -360,12 +360,15 @@ struct dc::StackPlan {
     bool tight[kMaxStages] = {};            // the cut before stage s crosses a tensor with a single buffer
     std::vector<float> layer_us;            // rough time of every layer, and of the matching and planning before them
     float head_us = 0.f;
+    float tail_us = 0.f;                    // what the caller queues behind a frame on its own stream, the last stage's
     std::vector<char> single;               // tensors whose buffer is the same for consecutive frames: no cut may cross them
     std::vector<int> crossing;              // tensors that a later stage than their writer's reads
     // The layers' times are rough: the first frames after a cut are timed stage by stage, the times of a stage's layers are
     // scaled to what it took, and the layers are cut again if that promises a shorter longest stage.
     int recuts_left = 3, timed_frames = 0;
     float timed_us[kMaxStages] = {};
+    int timed_tails = 0;
+    float timed_tail_us = 0.f;
     std::vector<std::unique_ptr<dc::FrameGraphs>> graphs;
     bool no_graphs = false;                 // recording failed once
     ReplayRule replay;
@@ -387,7 +390,7 @@ struct dc::StackPlan {
         return most;
     }
     float stage_us(int s) const {
-        float us = s == 0 && device_plan ? head_us : 0.f;
+        float us = (s == 0 && device_plan ? head_us : 0.f) + (s + 1 == n_stages ? tail_us : 0.f);
         for (int i = first[s]; i < first[s + 1]; ++i) us += layer_us[i];
         return us;
     }
@@ -554,7 +557,8 @@ int make_plan(StackPlan& P, const dc_layer* layers, int n_layers, int n_streams,
 
 // Cuts the layers into at most max_stages stages of about equal time such that no tensor with a single buffer is
 // written in one stage and read in a later one (the writer's next frame would have to wait for the reader).  Where poolings
-// lie on the torus too, no other cut is left: there a stage may start with the only reader of the tensor that the stage before
+// lie on the torus too, no other cut is left, and where the caller's stream is busy with the caller's own work, the last stage
+// should be short: there a stage may start with the only reader of the tensor that the stage before
 // it writes last, and the next frame's writer waits for that one layer (an event and a wait per frame, no graphs; VGG-16
 // 224x224 on one fp32 stream 384 us per frame in one stage, 259 so; 64 bf16 streams 1787 and 1620).
 // A frame takes as long as its longest stage or as the host needs for it: graphs, events and cross-stream waits of a stage cost
@@ -570,7 +574,7 @@ void StackPlan::cut(int max_stages) {
     for (int t = 0; t <= n; ++t)
         if (single[t])
             for (int i = t; i <= last_reader[t]; ++i)                       // the writer is layer t - 1
-                allowed[i] = pool_torus && i == t && last_reader[t] == t && allowed[i] == 1 ? 2 : 0;
+                allowed[i] = (pool_torus || tail_us > 0.f) && i == t && last_reader[t] == t && allowed[i] == 1 ? 2 : 0;
     const float head = device_plan ? head_us : 0.f;
     float total = head;
     for (float v : layer_us) total += v;
@@ -589,7 +593,15 @@ void StackPlan::cut(int max_stages) {
                 const float v = std::max(best[s - 1][j], sum[i] - sum[j]);
                 if (v < best[s][i]) { best[s][i] = v; from[s][i] = j; }
             }
-    while (k > 1 && period(best[k][n], k) > 0.9f * period(best[k - 1][n], k - 1)) --k;      // a stage that shortens nothing
+    // the last stage shares the caller's stream with what the caller does there
+    std::vector<float> whole(k + 1, 1e30f);
+    whole[1] = sum[n] + tail_us;
+    for (int s = 2; s <= k; ++s)
+        for (int j = s - 2; j < n; ++j) {
+            const float v = allowed[j] ? std::max(best[s - 1][j], sum[n] - sum[j] + tail_us) : 1e30f;
+            if (v < whole[s]) { whole[s] = v; from[s][n] = j; }
+        }
+    while (k > 1 && period(whole[k], k) > 0.9f * period(whole[k - 1], k - 1)) --k;          // a stage that shortens nothing
     n_stages = k;
     first[k] = n;
     for (int s = k, i = n; s > 1; --s) { i = from[s][i]; first[s - 1] = i; }
@@ -605,14 +617,19 @@ void StackPlan::cut(int max_stages) {
 constexpr int kTimedFrames = 4;
 void StackPlan::calibrate(int max_stages) {
     if (timed_frames < kTimedFrames) return;
+    const float new_tail = timed_tails ? timed_tail_us / timed_tails : 0.f;
     float now = 0.f;
     for (int s = 0; s < n_stages; ++s) {
-        const float took = timed_us[s] / timed_frames, ratio = took / std::max(stage_us(s), 1.f);
+        const bool last = s + 1 == n_stages;
+        const float took = timed_us[s] / timed_frames, ratio = took / std::max(stage_us(s) - (last ? tail_us : 0.f), 1.f);
         for (int i = first[s]; i < first[s + 1]; ++i) layer_us[i] *= ratio;
         if (s == 0 && device_plan) head_us *= ratio;
-        now = std::max(now, took);
+        now = std::max(now, took + (last && new_tail > 20.f ? new_tail : 0.f));
         timed_us[s] = 0.f;
     }
+    tail_us = new_tail > 20.f ? new_tail : 0.f;      // (the two events alone are some microseconds apart)
+    timed_tails = 0;
+    timed_tail_us = 0.f;
     timed_frames = 0;
     const int old_stages = n_stages, old_partition = partition;
     int old_first[kMaxStages + 1];
@@ -807,6 +824,14 @@ int StackCall::check() {
 // the streams do not.
 int StackCall::begin() {
     pipe = ov && ov->pipeline;
+    if (pipe) {     // the end of what the caller has queued behind the last frame: known to the GPU while that frame still runs
+        FrameRecord& last = ov->ring[(ov->frame_no + kFramesInFlight - 1) % kFramesInFlight];
+        if (last.valid && last.timed && !last.tail && last.plan == &P && last.caller == caller && hipEventQuery(last.done[last.n_stages - 1]) == hipErrorNotReady) {
+            if (!last.after) DC_TRY_HIP(hipEventCreate(&last.after));
+            DC_TRY_HIP(hipEventRecord(last.after, caller));
+            last.tail = true;
+        }
+    }
     // With a pipeline and planning on the GPU, matching and planning head stage 0; planned on the host they run on aux,
     // because the host waits for them.
     const int most = P.device_plan ? kMaxStages : kMaxStages - 1;
@@ -816,10 +841,16 @@ int StackCall::begin() {
         if (old.valid && old.timed && old.plan == &P && old.partition == P.partition) {
             const Blocked b(*this);
             DC_TRY_HIP(hipEventSynchronize(old.done[old.n_stages - 1]));      // (the first few frames only)
+            float ms = 0.f;
             for (int s = 0; s < old.n_stages; ++s) {
-                float ms = 0.f;
                 DC_TRY_HIP(hipEventElapsedTime(&ms, old.start[s], old.done[s]));
                 P.timed_us[s] += ms * 1e3f;
+            }
+            if (old.tail) {
+                DC_TRY_HIP(hipEventSynchronize(old.after));
+                DC_TRY_HIP(hipEventElapsedTime(&ms, old.done[old.n_stages - 1], old.after));
+                P.timed_tail_us += ms * 1e3f;
+                ++P.timed_tails;
             }
             ++P.timed_frames;
             const int before = P.partition;
@@ -1480,11 +1511,13 @@ int StackCall::run() {
         rec->plan = &P; rec->partition = P.partition; rec->n_stages = k; rec->caller = caller;
         rec->bufs.assign(eff.begin(), eff.end());
         rec->timed = timed;
+        rec->tail = false;
         rec->valid = true;
         ++ov->frame_no;
         ++ov->counters.frames;
         ov->counters.replayed += replay ? 1 : 0;
         ov->counters.stages = k;
+        ov->counters.last_layers = pipe ? P.first[k] - P.first[k - 1] : n_layers;
     }
     if (recut) {
         ++ov->counters.recuts;
@@ -1528,6 +1561,8 @@ int32_t dc_overlap_destroy(void* overlap) {
             if (r.start[s]) (void)hipEventDestroy(r.start[s]);
             if (r.read[s]) (void)hipEventDestroy(r.read[s]);
         }
+    for (FrameRecord& r : o->ring)
+        if (r.after) (void)hipEventDestroy(r.after);
     if (o->match_done) (void)hipEventDestroy(o->match_done);
     if (o->plan_done) (void)hipEventDestroy(o->plan_done);
     if (o->record) (void)hipStreamDestroy(o->record);

@@ -1180,6 +1180,39 @@ def test_stages_across_tensors_with_a_single_buffer(net, size, streams):
             assert torch.equal(x, y), (f, i)
 
 
+def test_the_callers_own_work_shortens_the_last_stage():
+    """The last stage shares the caller's stream with what the caller queues there behind every frame: with much of it (16
+    passes over 64 MiB) the last stage is cut shorter than without, and the tensors are the same bit for bit."""
+    layers = synth.vgg16()
+    ws, bs = synth.he_weights(layers, 3, bias_scale=0.05, input_shape=(224, 224, 3))
+    video = torch.from_numpy(synth.panning_video(94, n_frames=8, H=224, W=224, fg=((24, 24), (16, 32)))).to(DEV)
+    frames = [video[t:t + 1].contiguous() for t in range(8)]
+    work = torch.zeros(64 << 20, dtype=torch.uint8, device=DEV)
+    torch.cuda.synchronize()
+    results = {}
+    binding.dc_conv_tuning(0, 4, 1, 0)
+    try:
+        for passes in (0, 16):
+            runner = binding.StackRunner(layers, ws, bs, 1, 224, 224, 3, block=16, radius=16, dtype=binding.DC_F32, device_plan=True,
+                                         exact_masks=True, torus=True)
+            for t in range(48):
+                if t % 8 == 0:
+                    runner.reset()
+                tensors = runner.step(frames[t % 8])
+                for _ in range(passes if t < 47 else 0):
+                    work.add_(1)
+            last = [runner.read_tensor(i + 1, tensors) for i, L in enumerate(layers) if L["type"] == synth.CONV]
+            torch.cuda.synchronize()
+            results[passes] = runner.overlap_counters(), [x.clone() for x in last] + [tensors[-1].clone(), runner.mask.clone()]
+            del runner
+    finally:
+        binding.dc_conv_tuning()
+    print("[last stage]", {k: (v[0].stages, v[0].last_layers) for k, v in results.items()}, flush=True)
+    assert results[16][0].last_layers < results[0][0].last_layers
+    for i, (x, y) in enumerate(zip(results[0][1], results[16][1])):
+        assert torch.equal(x, y), i
+
+
 def test_one_handle_for_two_stacks_and_two_caller_streams():
     """A handle that is handed from one stack to another and called on changing streams orders every frame behind the
     earlier ones: same tensors as with a handle of their own.  (Stages of different stacks use the same streams, and the
