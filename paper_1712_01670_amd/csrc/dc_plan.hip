@@ -450,7 +450,9 @@ __device__ __forceinline__ void erode_stream(uint32_t* maps, const int* ops, int
         const uint32_t* in = maps + DC_OP(src0);
         auto each = [&](auto word) {
             for (int i = first; i < words; i += stride) {
-                const int y = wpr == 1 ? i : (int)__umulhi((uint32_t)i, magic), x0 = (i - y * wpr) * 32;
+                int y = wpr == 1 ? i : (int)__umulhi((uint32_t)i, magic);
+                if (!IN_LDS && y * wpr > i) --y;      // (one too large at most, on maps of 2^32 words times words per row)
+                const int x0 = (i - y * wpr) * 32;
                 const unsigned bits = word(i, y, x0);
                 maps[dst + i] = y >= row_lo && y < row_hi ? bits & column_range(x0, col_lo, col_hi) : 0u;
             }

@@ -66,3 +66,31 @@ def test_large_frame_maps_built_in_the_workspace(oracle):
     """A frame whose bitmaps (more than 128 KB per stream) do not fit the workgroup's LDS: the same maps, built in the
     workspace instead."""
     _check(oracle, _mixed_stack()[:6], 1000, 1100, 4, 16, 2, 30, density=0.9, max_motion=20)
+
+
+def test_rows_of_a_map_of_ten_million_words():
+    """One 3x3 layer on a 24864 x 12720 map (777 words a row): from row 12650 on the row of a word is not the product with the
+    rounded reciprocal.  Everything matched, no motion: every pixel but the border's is reusable."""
+    import ctypes as C
+    H, W, block = 12720, 24864, 16
+    wpr = W // 32
+    magic = -(-2 ** 32 // wpr)
+    assert ((12700 * wpr - 1) * magic) >> 32 == 12700                  # (the product is one row too far there)
+    layers = [dict(type=synth.CONV, k=3, s=1, p=1, cin=4, cout=4, relu=1, in0=0, in1=-1)]
+    Lc, words, wsb, offs = binding.layers_to_c(layers), C.c_size_t(), C.c_size_t(), (C.c_int64 * 2)()
+    assert binding.lib().dc_propagate_masks_size(Lc, 1, H, W, 4, C.byref(words), offs, C.byref(wsb)) == 0
+    mask = torch.ones((1, H // block, W // block), dtype=torch.uint8, device=DEV)
+    gmv = torch.zeros((1, 2), dtype=torch.int32, device=DEV)
+    bitmaps = torch.zeros(words.value, dtype=torch.int32, device=DEV)
+    dxy = torch.zeros(4, dtype=torch.int32, device=DEV)
+    ws = torch.zeros(wsb.value + 256, dtype=torch.uint8, device=DEV)
+    print("[masks] 777 words x 12720 rows", flush=True)
+    assert binding.lib().dc_propagate_masks(Lc, 1, 1, H, W, 4, block, binding._ptr(mask), binding._ptr(gmv), 0, binding._ptr(bitmaps),
+                                            binding._ptr(dxy), binding._ptr(ws), ws.numel(), binding._stream()) == 0
+    torch.cuda.synchronize()
+    got = bitmaps[offs[1]:offs[1] + H * wpr].reshape(H, wpr)
+    want = torch.full((H, wpr), -1, dtype=torch.int32, device=DEV)
+    want[:, 0] = -2
+    want[:, -1] = 0x7fffffff
+    want[0] = want[-1] = 0
+    assert torch.equal(got, want)
