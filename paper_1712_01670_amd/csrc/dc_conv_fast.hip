@@ -1284,6 +1284,7 @@ FastChoice choose_fast(const ConvLaunch& c, long n_units, long n_cap, size_t scr
 
 // Ids 64.. name the instantiations of this file: 64 + ((bf16 * 2 + kci) * 8 + UPW - 1), 96.. the first-layer kernel,
 // 110.. the wide arrangement.
+bool conv_5x5_kernel_built(int id) { return id >= 132 && (id - 132) / 8 < kNumGeom && fast_built(5, true, (id - 132) / 8, 0, (id - 132) % 8 + 1); }
 void conv_fast_kernel_name(int id, char* buf, size_t n) {
     if (id == 126) { snprintf(buf, n, "conv_regw_kernel<2, 2, false>"); return; }
     if (id == 130) { snprintf(buf, n, "conv_regw_kernel<2, 2, true>"); return; }      // tensors on a torus
@@ -1293,7 +1294,7 @@ void conv_fast_kernel_name(int id, char* buf, size_t n) {
         return;
     }
     if (id >= 132) {  // 132 + arrangement * 8 + UPW - 1: 5x5 layers
-        const Geom& G = kGeom[(id - 132) / 8 % kNumGeom];
+        const Geom& G = kGeom[(id - 132) / 8];
         snprintf(buf, n, "conv_fast_kernel<__hip_bfloat16, 5, 32, %d, %d, %d, %d>", (id - 132) % 8 + 1, G.wm, G.wn, G.nbw);
         return;
     }

@@ -379,3 +379,17 @@ int main() {
     subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-I", csrc, str(source), "-o", str(exe)], check=True)
     out = subprocess.run([str(exe)], capture_output=True, text=True)
     assert out.returncode == 0, out.stdout
+
+
+def test_kernel_names_of_the_5x5_layers():
+    """Ids from 132 on: a name for the five instantiations that exist, an error for every other id."""
+    built = {}
+    for kid in range(132, 400):
+        buf = C.create_string_buffer(160)
+        rc = binding.lib().dc_conv_kernel_name(kid, buf, 160)
+        assert rc in (0, -1), (kid, rc)
+        if rc == 0:
+            built[kid] = buf.value.decode()
+    assert sorted(built) == [140, 141, 148, 149, 150]
+    assert built[141] == "conv_fast_kernel<__hip_bfloat16, 5, 32, 2, 4, 2, 4>" and built[150] == "conv_fast_kernel<__hip_bfloat16, 5, 32, 3, 4, 2, 2>"
+    assert binding.lib().dc_conv_kernel_name(131, C.create_string_buffer(160), 160) == -1
