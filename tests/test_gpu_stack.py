@@ -741,10 +741,9 @@ def test_overlap_modes_give_identical_tensors(net, size, bf16):
 
 
 def test_pipelined_frames_with_irregular_buffer_alternation():
-    """With two frames in flight the library skips the cross-stream wait for a tensor whose buffer is the one its
-    work stream used last and not the previous frame's, and records no event for it; a caller that then reuses the
-    previous frame's buffer after all must still get the same tensors (the library waits for the whole previous
-    frame instead).  The runner's choice of the set for the tensors that are not conv outputs is overridden
+    """The writer of a tensor that crosses from one stage to the next waits for the readers of the frame that last used its
+    buffer, and a tensor that turns out to have the same buffer in consecutive frames is kept inside one stage; a caller that
+    alternates the buffers irregularly must still get the same tensors.  The runner's choice of the set for the tensors that are not conv outputs is overridden
     frame by frame with a pattern that holds every transition; frames are issued without synchronisation."""
     H = W = 96
     layers = synth.vgg16()
@@ -915,9 +914,9 @@ def _max_rel(a, b):
 
 @pytest.mark.parametrize("net,plan", [("vgg", dict(torus=True)), ("googlenet", {}), ("resnet", dict(cache_pool_add=True))])
 def test_long_pipelined_runs_stay_with_the_plain_path(net, plan):
-    """Pipelined frames planned on the GPU over a run long enough for the stages to be cut anew from measured times and
-    for frames to be replayed from graphs: the tensors of the last frame of runs that end at different places are those
-    of the plain path (one stream, no handle), which takes neither.  fp32; the lists' lengths are known to the launches
+    """Pipelined frames planned on the GPU over a run long enough for the stages to be cut anew from measured times, launched
+    or replayed as measured and replayed throughout: the tensors of the last frame of runs that end at different places are
+    those of the plain path (one stream, no handle), which takes neither.  fp32; the lists' lengths are known to the launches
     with different delays, so partial sums of a split K may be added in another grouping: K <= 4608 products, relative
     error of a sum up to sqrt(K) 2^-24 per layer, over at most 60 layers below 3e-4."""
     H = W = 96
@@ -933,10 +932,12 @@ def test_long_pipelined_runs_stay_with_the_plain_path(net, plan):
     frames = [video[t:t + 1].contiguous() for t in range(T)]
     torch.cuda.synchronize()
     finals = {}
-    for mode, kw in (("pipeline", dict(overlap=True, pipeline=True)), ("plain", dict(overlap=False))):
+    for mode, kw in (("pipeline", dict(overlap=True, pipeline=True)), ("replayed", dict(overlap=True, pipeline=True)), ("plain", dict(overlap=False))):
         print(f"[long run] {net} {mode}", flush=True)
         runner = binding.StackRunner(layers, ws, bs, 1, H, W, 3, block=16, radius=16, dtype=binding.DC_F32, expiry=6,
                                      device_plan=True, exact_masks=True, want_origins=False, **plan, **kw)
+        if mode == "replayed":
+            runner.set_replay(1)
         kept = []
         for stop in (5, 61, 90, 11):
             runner.reset()
@@ -949,11 +950,15 @@ def test_long_pipelined_runs_stay_with_the_plain_path(net, plan):
             torch.cuda.synchronize()
             kept.append([x.clone() for x in last] + [runner.mask.clone(), runner.gmv.clone()])
         finals[mode] = kept
+        if mode == "replayed":
+            c = runner.overlap_counters()
+            assert c.failed == 0 and c.replayed > c.frames // 3, [(n, getattr(c, n)) for n, _ in c._fields_]
         del runner
-    for f, (a, b) in enumerate(zip(finals["pipeline"], finals["plain"])):
-        assert torch.equal(a[-1], b[-1]) and torch.equal(a[-2], b[-2]), f
-        for i, (x, y) in enumerate(zip(a[:-2], b[:-2])):
-            assert _max_rel(x, y) <= 3e-4, (f, i)
+    for mode in ("pipeline", "replayed"):
+        for f, (a, b) in enumerate(zip(finals[mode], finals["plain"])):
+            assert torch.equal(a[-1], b[-1]) and torch.equal(a[-2], b[-2]), (mode, f)
+            for i, (x, y) in enumerate(zip(a[:-2], b[:-2])):
+                assert _max_rel(x, y) <= 3e-4, (mode, f, i)
 
 
 def _replay_run(layers, ws, bs, frames, block, bf16, mode, order, before=None, **kw):
@@ -1269,11 +1274,14 @@ def test_two_threads_with_a_stack_each():
             with torch.cuda.stream(torch.cuda.Stream()):
                 runner = binding.StackRunner(layers, ws, bs, 1, H, W, 3, block=16, radius=16, dtype=binding.DC_F32, expiry=6,
                                              device_plan=True, exact_masks=True)
+                runner.set_replay(1)
                 for t in range(10 * T):
                     if t % T == 0:
                         runner.reset()
                     tensors = runner.step(mine[t % T])
                 torch.cuda.current_stream().synchronize()
+                c = runner.overlap_counters()
+                assert c.failed == 0 and c.recorded >= 4 and c.replayed > 10, [(n, getattr(c, n)) for n, _ in c._fields_]
                 results[key] = [x.clone() for x in tensors[1:]] + [runner.mask.clone(), runner.gmv.clone()]
                 torch.cuda.current_stream().synchronize()
         except Exception as e:                       # noqa: BLE001 (reported by the main thread)
