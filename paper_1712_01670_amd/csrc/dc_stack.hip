@@ -481,7 +481,7 @@ float layer_cost(const StackPlan& P, int i) {
         const double row = (double)P.hs[l.in0] * P.ws[l.in0] * P.cs[l.in0] * esz;
         // the weights from memory, or a wavefront's walk along its neuron's row (a whole one for one stream, a sixteenth
         // for several): few neurons on long rows are that chain of loads
-        us = 8.0 + std::max(row * l.cout * (1.0 + n / 40.0) / 4e6, n < 2.0 ? row / 1024.0 * 0.35 : row / 2048.0 * (0.85 + 0.035 * n));
+        us = 8.0 + std::max(row * l.cout * (1.0 + n / 6.0) / 4e6, n < 2.0 ? row / 1024.0 * 0.35 : row / 2048.0 * (0.85 + 0.035 * n));
     } else if (l.type == DC_LRN) {
         us = 3.0 + bytes / 1e6;
     }
