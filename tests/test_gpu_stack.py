@@ -670,9 +670,10 @@ def test_border_case_planned_on_the_gpu(oracle):
 
 @pytest.mark.parametrize("n_streams,bf16", [(1, False), (3, True)])
 def test_frames_planned_on_the_gpu_without_any_wait(oracle, n_streams, bf16):
-    """Frames planned on the GPU, two in flight, issued back to back: the host never waits for a frame (no regions
-    are asked for), expiry and a scene cut included; every tensor of every frame is cloned on the caller's stream and
-    compared with the oracle at the end, and the work counters of the last frame are read once everything is done."""
+    """Frames planned on the GPU, two in flight: the host never waits for the frame that it has just issued (no regions are asked
+    for), expiry and a scene cut included; every tensor of every frame is cloned on the caller's stream, before the step that
+    is given its buffer again, and compared with the oracle at the end, and the work counters of the last frame are read once
+    everything is done."""
     layers = synth.vgg16()[:10]
     T, H, W = 9, 96, 96
     videos = np.stack([synth.panning_video(6100 + s, n_frames=T, H=H, W=W, fg=((24, 24),), margin=32) for s in range(n_streams)])
@@ -682,11 +683,15 @@ def test_frames_planned_on_the_gpu_without_any_wait(oracle, n_streams, bf16):
     refs = [oracle.Stream(layers, ws, bs, H, W, 3, block=16, radius=8, bf16=bf16, expiry=4) for _ in range(n_streams)]
     dv = torch.from_numpy(np.ascontiguousarray(videos.transpose(1, 0, 2, 3, 4))).to(DEV)
     torch.cuda.synchronize()
-    kept = []
+    kept, cloned = [], []
     for t in range(T):
         if t == 6:
             r.reset()
+        if t >= 2:
+            cloned[t - 2].synchronize()          # this step's first stage may overwrite that frame's tensors at once
         kept.append([x.clone() for x in r.step(dv[t])])
+        cloned.append(torch.cuda.Event())
+        cloned[t].record()
     torch.cuda.synchronize()
     tol = 2e-2 if bf16 else 1e-4
     last_blocks = 0
