@@ -557,8 +557,8 @@ int make_plan(StackPlan& P, const dc_layer* layers, int n_layers, int n_streams,
 
 // Cuts the layers into at most max_stages stages of about equal time such that no tensor with a single buffer is
 // written in one stage and read in a later one (the writer's next frame would have to wait for the reader).  Where poolings
-// lie on the torus too, no other cut is left, and where the caller's stream is busy with the caller's own work, the last stage
-// should be short: there a stage may start with the only reader of the tensor that the stage before
+// lie on the torus too, no other cut is left, and where the caller's stream is busy with the caller's own work for long, the last
+// stage should be short: there a stage may start with the only reader of the tensor that the stage before
 // it writes last, and the next frame's writer waits for that one layer (an event and a wait per frame, no graphs; VGG-16
 // 224x224 on one fp32 stream 384 us per frame in one stage, 259 so; 64 bf16 streams 1787 and 1620).
 // A frame takes as long as its longest stage or as the host needs for it: graphs, events and cross-stream waits of a stage cost
@@ -567,6 +567,8 @@ int make_plan(StackPlan& P, const dc_layer* layers, int n_layers, int n_streams,
 // host, a frame waits for its matching anyway and stages under 80 us are not worth having (VGG-16 224x224: 167, 169, 200;
 // ResNet-50: 284 with two, 361 with three).
 constexpr float kStageHostUs = 30.f;
+constexpr float kTightTailUs = 100.f;      // the caller's work from which such a cut pays for the graphs that the stack gives up with it (VGG-16
+                                           // 224x224 on one bf16 stream, us per frame without -> with it: 20 us of work 141 -> 181, 70 us 196 -> 190, 140 us 286 -> 226)
 float StackPlan::period(float longest_us, int k) const { return device_plan ? std::max(longest_us, kStageHostUs * k) : longest_us; }
 void StackPlan::cut(int max_stages) {
     const int n = (int)layers.size();
@@ -574,7 +576,7 @@ void StackPlan::cut(int max_stages) {
     for (int t = 0; t <= n; ++t)
         if (single[t])
             for (int i = t; i <= last_reader[t]; ++i)                       // the writer is layer t - 1
-                allowed[i] = (pool_torus || tail_us > 0.f) && i == t && last_reader[t] == t && allowed[i] == 1 ? 2 : 0;
+                allowed[i] = (pool_torus || tail_us > kTightTailUs) && i == t && last_reader[t] == t && allowed[i] == 1 ? 2 : 0;
     const float head = device_plan ? head_us : 0.f;
     float total = head;
     for (float v : layer_us) total += v;
