@@ -125,3 +125,33 @@ def test_retest_sample_shapes(oracle, H, W, C, B, R):
     ssd = np.sort(np.concatenate([oracle.match_blocks(cur[s], prev[s], B, R, 0)["best_ssd"].ravel() for s in range(2)]))
     for thr in {int(ssd[len(ssd) // 2]), int(ssd[-1]), int(ssd[len(ssd) // 4])}:      # a block exactly at the limit each time
         _compare(oracle, cur, prev, B, R, thr, "retest")
+
+
+# Three channels and a range of the block edge have a kernel of their own: the last row and column of candidates take another
+# way than the rest, the vector is the last tie-break, the window is fetched in pieces that may straddle an end of the frame,
+# and rows start at any byte.
+@pytest.mark.parametrize("H,W,B,k", [(16, 16, 16, 1), (8, 8, 8, 1), (48, 48, 16, 1), (49, 51, 16, 1), (65, 83, 16, 2), (24, 24, 8, 1), (27, 41, 8, 1),
+                                     (40, 53, 8, 3), (17, 331, 16, 1), (130, 19, 16, 1)])
+def test_range_of_the_block_edge(oracle, H, W, B, k):
+    dev = torch.device("cuda:0")
+    rng = np.random.default_rng(H * W + B)
+    prev = rng.integers(0, 256, (H, W, 3)).astype(np.uint8)
+    pairs = [(np.roll(prev, (-sy, -sx), axis=(0, 1)), prev)                      # the vector (sx, sy) wherever it stays in the frame
+             for sy, sx in [(B, B), (B, -B), (-B, B), (-B, -B), (B, 3), (-2, B), (B, B - 1), (B - 1, B), (0, 0)]]
+    dots = (rng.random((2, H, W, 1)) < 0.004) * np.full(3, 90)                   # nearly flat: most candidates of a block are equal
+    pairs += [(dots[0].astype(np.uint8), dots[1].astype(np.uint8)), (np.full_like(prev, 255), np.zeros_like(prev))]
+    y, x = np.mgrid[0:H, 0:W]
+    for wave in (y, x, x + y):                                                    # equal minima B / 2 to either side
+        stripes = (np.cos(2 * np.pi * wave / B) * 100 + 128).astype(np.uint8)[..., None].repeat(3, 2)
+        pairs.append((255 - stripes, stripes))
+    cur = np.ascontiguousarray(np.stack([c for c, _ in pairs]))
+    prv = np.ascontiguousarray(np.stack([p for _, p in pairs]))
+    out = binding.dc_match_blocks_opt(torch.from_numpy(cur).to(dev), torch.from_numpy(prv).to(dev), B, B, 1000,
+                                      method=binding.DC_MATCH_EXHAUSTIVE, k_skip=k)
+    torch.cuda.synchronize()
+    got = {key: v.cpu().numpy() for key, v in out.items()}
+    for s in range(len(pairs)):
+        want = oracle.match_blocks(cur[s], prv[s], B, B, 1000, k_skip=k)
+        assert np.array_equal(got["best_ssd"][s].view(np.uint32), want["best_ssd"]), s
+        assert np.array_equal(got["mv"][s], want["mv"]), s
+        assert got["gmv"][s].tolist() == want["gmv"].tolist() and np.array_equal(got["mask"][s], want["mask"]), s
