@@ -214,7 +214,7 @@ int32_t dc_conv_tuning(int32_t arrangement, int32_t units_per_workgroup, int32_t
 
 int32_t dc_conv_kernel_name(int32_t kernel_id, char* buf, size_t n) {
     if (!buf) return DC_ERR_NULL_PTR;
-    if (n < 2 || kernel_id < 0 || kernel_id == 131 || (kernel_id > 131 && !conv_5x5_kernel_built(kernel_id))) return DC_ERR_INVALID_ARG;
+    if (n < 2 || kernel_id < 0 || kernel_id == 131 || (kernel_id > 131 && !conv_kernel_built(kernel_id))) return DC_ERR_INVALID_ARG;
     conv_kernel_name(kernel_id, buf, n);
     return DC_OK;
 }

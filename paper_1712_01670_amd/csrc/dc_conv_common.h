@@ -120,6 +120,10 @@ __device__ __forceinline__ V keep_scalar(V v) {
     return v;
 }
 
+// Barrier of a workgroup for LDS alone.  __syncthreads() also waits until no load of the wavefront is outstanding, which
+// ends every prefetch that is meant to travel across it.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 // Activation fused into a convolution's epilogue: 1 = ReLU, 2 = leaky ReLU with slope 0.1 (Darknet-style stacks).
 __device__ __forceinline__ float activate(float v, int mode) {
     return mode == 2 ? (v > 0.f ? v : 0.1f * v) : fmaxf(v, 0.f);

@@ -855,7 +855,7 @@ __global__ __launch_bounds__(WM * 128) void conv_pw_kernel(ConvParams P) {
         if (ahead >= 2) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
         else if (ahead == 1) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
         else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();                            // chunk c is in LDS; everyone is done with chunk c - 1
+        lds_barrier();                              // chunk c is in LDS; everyone is done with chunk c - 1
         if (c + D < n_ch) issue(chunk_of(c + D), (c + D) % NSTG);
         const unsigned char* sb = ring + (c % NSTG) * STAGE;
 #pragma unroll
@@ -908,6 +908,166 @@ __global__ __launch_bounds__(WM * 128) void conv_pw_kernel(ConvParams P) {
                 F::store4(px + j * 4, v0);
                 F::store4(px + j * 4 + 4, v1);
             }
+        }
+    }
+}
+
+constexpr int kPwSplit = 4;           // wavefronts that share a tile's K
+constexpr int kPwSplitId = 400;       // kernel ids: + 2 (units - 1) + bf16
+
+// ---- 1x1 convolutions of few units and a deep K ---------------------------------------------------
+// With few (unit group, channel tile) pairs the ring above leaves most CUs idle and the others with a step of 0.4 us per 128
+// bytes of K (what one CU fetches, not how far ahead: eight stages instead of four change nothing).  Here the WK wavefronts of a workgroup split K among themselves and
+// each fetches the fragments of its part straight into registers, so every operand byte of the tile is loaded once, all
+// loads of a part are in flight together and nothing waits for another wavefront before the partial tiles are added
+// through LDS (in the order of the wavefronts).  Wavefront w takes the 128-byte pieces w, w + WK, ... of every row.
+// Channel order within a wavefront's blocks, strides, tails and tensors on a torus as in the kernel above.
+template <typename T, int U, int NB, int WK>
+__global__ __launch_bounds__(WK * 64) void conv_pw_split_kernel(ConvParams P) {
+    typedef Frag<T> F;
+    typedef typename F::vec vec;
+    constexpr int ES = (int)sizeof(T), RB = 128, GPC = 2, NT = NB * 16;
+    constexpr int ITEMS = U * NB / 2;                      // (unit, pair of channel blocks): what a lane stores at once
+    static_assert(NB % 2 == 0, "eight channels a store");
+    __shared__ __align__(16) floatx4 red[WK][U * NB][64];
+
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l16 = lane & 15, q = lane >> 4;
+    const int n_units = unit_count(P);
+    const int n_wg_tiles = (n_units + U - 1) / U * P.R, tiles_per_xcd = (n_wg_tiles + 7) >> 3;
+    const int t = (int)(blockIdx.x & 7) * tiles_per_xcd + (int)(blockIdx.x >> 3);
+    if ((int)(blockIdx.x >> 3) >= tiles_per_xcd || t >= n_wg_tiles) return;    // the whole workgroup, before any barrier
+    const int ug = t / P.R, ntile = t - ug * P.R;
+    const int n0 = ntile * NT;
+    const int CinES = P.Cin * ES;
+    const __amdgpu_buffer_rsrc_t in_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(P.in), 0, P.in_bytes, kBufferFlags);
+    const __amdgpu_buffer_rsrc_t w_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(P.w), 0, P.w_bytes, kBufferFlags);
+
+    uint32_t wgo[NB];
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+        const int ch = n0 + (l16 >> 2) * (4 * NB) + 4 * j + (l16 & 3);
+        wgo[j] = ch < P.Cout ? (uint32_t)(ch * CinES) : kOob;
+    }
+    struct Pieces { vec w[GPC][NB], x[GPC][U]; };
+    uint32_t pgo[U];
+    // offsets beyond a row's end, a missing pixel or channel: all beyond the tensor, the load returns zeros (both out of
+    // range wrap to the start of the tensor and meet sums that are not stored)
+    auto k_offset = [&](int chunk, int g) { const int kb = chunk * RB + g * 64 + q * 16; return kb < CinES ? (uint32_t)kb : kOob; };
+    auto load_w = [&](Pieces& f, int chunk) {
+#pragma unroll
+        for (int g = 0; g < GPC; ++g) {
+            const uint32_t ko = k_offset(chunk, g);
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+                const uint32_t off = wgo[j] + ko;
+                f.w[g][j] = __builtin_bit_cast(vec, __builtin_amdgcn_raw_buffer_load_b128(w_rsrc, off, 0, 0));
+            }
+        }
+    };
+    auto load_x = [&](Pieces& f, int chunk) {
+#pragma unroll
+        for (int g = 0; g < GPC; ++g) {
+            const uint32_t ko = k_offset(chunk, g);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint32_t off = pgo[u] + ko;
+                f.x[g][u] = __builtin_bit_cast(vec, __builtin_amdgcn_raw_buffer_load_b128(in_rsrc, off, 0, 0));
+            }
+        }
+    };
+    floatx4 acc[U][NB];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int j = 0; j < NB; ++j) acc[u][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    auto mma = [&](const Pieces& f) {
+#pragma unroll
+        for (int g = 0; g < GPC; ++g)
+#pragma unroll
+            for (int e = 0; e < F::NE; ++e)
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int j = 0; j < NB; ++j) F::mma1(f.w[g][j], f.x[g][u], acc[u][j], e);
+    };
+
+    Pieces a, b;
+    const int n_ch = P.n_chunks;
+    if (wave < n_ch) load_w(a, wave);                      // on their way while the units are looked up
+    // unit u: place of the lane's pixel in the output (element offset; -1: not stored) and in the input
+    int dst[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int at = ug * U + u;
+        int stream = 0, uy = 0, ux = 0, mixed = 0xffff;
+        if (at < n_units) {
+            if (P.units) {
+                const TileDev td = P.units[at];
+                stream = td.stream; uy = td.ty; ux = td.tx; mixed = td.reuse_mask;
+            } else {
+                stream = fast_div_any(at, P.npix_magic, P.units_x * P.units_y);
+                const int r = at - stream * (P.units_x * P.units_y);
+                uy = fast_div(r, P.pw_magic); ux = r - uy * P.units_x; mixed = 0;
+            }
+        }
+        const int y = uy * 4 + (l16 >> 2), x = ux * 4 + (l16 & 3);
+        const bool ok = at < n_units && y < P.Hout && x < P.Wout;
+        int iy = y * P.s, ix = x * P.s, oy = y, ox = x;
+        if (P.in_origin || P.out_origin) {                 // tensors on a torus (stride 1 only: the launcher sees to it)
+            const size_t og = (size_t)stream * P.origin_stride;
+            if (P.in_origin && ok) { ix = torus_wrap(x, P.in_origin[og], P.Win); iy = torus_wrap(y, P.in_origin[og + 1], P.Hin); }
+            if (P.out_origin && ok) { ox = torus_wrap(x, P.out_origin[og], P.Wout); oy = torus_wrap(y, P.out_origin[og + 1], P.Hout); }
+        }
+        pgo[u] = ok ? (uint32_t)(((stream * P.Hin + iy) * P.Win + ix) * CinES) : kOob;
+        dst[u] = ok && !((mixed >> l16) & 1) ? ((stream * P.Hout + oy) * P.Wout + ox) * P.Cout : -1;
+    }
+    if (wave < n_ch) {
+        load_x(a, wave);
+        for (int c = wave;;) {
+            if (c + WK < n_ch) { load_w(b, c + WK); load_x(b, c + WK); }
+            mma(a);
+            c += WK;
+            if (c >= n_ch) break;
+            if (c + WK < n_ch) { load_w(a, c + WK); load_x(a, c + WK); }
+            mma(b);
+            c += WK;
+            if (c >= n_ch) break;
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int j = 0; j < NB; ++j) red[wave][u * NB + j][lane] = acc[u][j];
+    __syncthreads();
+    const int parts = n_ch < WK ? n_ch : WK;
+#pragma unroll
+    for (int i0 = 0; i0 < ITEMS; i0 += WK) {
+        const int item = i0 + wave;
+        if (item >= ITEMS) break;
+        const int u = item / (NB / 2), j = item % (NB / 2) * 2;
+        const int co = n0 + q * (4 * NB) + 4 * j;
+        int at = dst[0];
+#pragma unroll
+        for (int v = 1; v < U; ++v) at = u == v ? dst[v] : at;
+        if (co >= P.Cout || at < 0) continue;
+        floatx4 v0 = red[0][u * NB + j][lane], v1 = red[0][u * NB + j + 1][lane];
+#pragma unroll
+        for (int w = 1; w < WK; ++w)
+            if (w < parts) { v0 += red[w][u * NB + j][lane]; v1 += red[w][u * NB + j + 1][lane]; }
+        if (P.bias) { v0 += *reinterpret_cast<const floatx4*>(P.bias + co); v1 += *reinterpret_cast<const floatx4*>(P.bias + co + 4); }
+        if (P.relu) { activate4(v0, P.relu); activate4(v1, P.relu); }
+        T* const px = reinterpret_cast<T*>(P.out) + at + co;
+        if constexpr (sizeof(T) == 2) {
+            uintx4 w4;
+            w4[0] = (uint32_t)F::bits(v0[0]) | ((uint32_t)F::bits(v0[1]) << 16);
+            w4[1] = (uint32_t)F::bits(v0[2]) | ((uint32_t)F::bits(v0[3]) << 16);
+            w4[2] = (uint32_t)F::bits(v1[0]) | ((uint32_t)F::bits(v1[1]) << 16);
+            w4[3] = (uint32_t)F::bits(v1[2]) | ((uint32_t)F::bits(v1[3]) << 16);
+            *reinterpret_cast<uintx4*>(px) = w4;
+        } else {
+            F::store4(px, v0);
+            F::store4(px + 4, v1);
         }
     }
 }
@@ -1284,13 +1444,17 @@ FastChoice choose_fast(const ConvLaunch& c, long n_units, long n_cap, size_t scr
 
 // Ids 64.. name the instantiations of this file: 64 + ((bf16 * 2 + kci) * 8 + UPW - 1), 96.. the first-layer kernel,
 // 110.. the wide arrangement.
-bool conv_5x5_kernel_built(int id) { return id >= 132 && (id - 132) / 8 < kNumGeom && fast_built(5, true, (id - 132) / 8, 0, (id - 132) % 8 + 1); }
+bool conv_kernel_built(int id) { return id >= kPwSplitId ? id < kPwSplitId + 4 : id >= 132 && (id - 132) / 8 < kNumGeom && fast_built(5, true, (id - 132) / 8, 0, (id - 132) % 8 + 1); }
 void conv_fast_kernel_name(int id, char* buf, size_t n) {
     if (id == 126) { snprintf(buf, n, "conv_regw_kernel<2, 2, false>"); return; }
     if (id == 130) { snprintf(buf, n, "conv_regw_kernel<2, 2, true>"); return; }      // tensors on a torus
     if (id == 129) { snprintf(buf, n, "conv_fast_kernel<__hip_bfloat16, 3, 32, 3, 6, 2, 4>"); return; }     // the tall arrangement
     if (id == 127 || id == 128 || id == 108 || id == 109) {      // 108 + bf16 (64 x 64 tile), 127 + bf16 (128 x 128): conv_pw_kernel (1x1)
         snprintf(buf, n, "conv_pw_kernel<%s, %d>", id == 109 || id == 128 ? "__hip_bfloat16" : "float", id >= 127 ? 4 : 2);
+        return;
+    }
+    if (id >= kPwSplitId) {
+        snprintf(buf, n, "conv_pw_split_kernel<%s, %d, 2, %d>", (id - kPwSplitId) % 2 ? "__hip_bfloat16" : "float", (id - kPwSplitId) / 2 + 1, kPwSplit);
         return;
     }
     if (id >= 132) {  // 132 + arrangement * 8 + UPW - 1: 5x5 layers
@@ -1369,9 +1533,31 @@ hipError_t pw_launch_n(dim3 grid, size_t lds, hipStream_t st, const ConvParams& 
     hipLaunchKernelGGL((conv_pw_kernel<T, WM>), grid, dim3(WM * 128), lds, st, P);
     return hipGetLastError();
 }
+// units: 1, 2 (split K, 32 channels), 4 (64 channels), 8 (128 channels)
 template <typename T>
-hipError_t pw_launch(int wm, dim3 grid, size_t lds, hipStream_t st, const ConvParams& P) {
-    return wm == 4 ? pw_launch_n<T, 4>(grid, lds, st, P) : pw_launch_n<T, 2>(grid, lds, st, P);
+hipError_t pw_launch(int units, dim3 grid, size_t lds, hipStream_t st, const ConvParams& P) {
+    if (units == 8) return pw_launch_n<T, 4>(grid, lds, st, P);
+    if (units == 4) return pw_launch_n<T, 2>(grid, lds, st, P);
+    if (units == 2) hipLaunchKernelGGL((conv_pw_split_kernel<T, 2, 2, kPwSplit>), grid, dim3(kPwSplit * 64), 0, st, P);
+    else hipLaunchKernelGGL((conv_pw_split_kernel<T, 1, 2, kPwSplit>), grid, dim3(kPwSplit * 64), 0, st, P);
+    return hipGetLastError();
+}
+// Units per workgroup of a 1x1 layer.  us per launch, one launch after another with the caches emptied in between, bf16:
+//   one unit, K split (t1 = workgroups that it makes): 14x14 1024->256 one stream 6.2 (four units: 9.1, 11.4 with the barrier
+//   that ended the prefetch), 7x7 2048->512 one to four streams 8.4 - 8.7 (13.5), 28x28 512->128 4.9 (6.7); with 512 workgroups it
+//   is even (14x14 1024->256 four streams 9.1, 9.0) and two units take 7.7; with 1024 the ring wins (13.8 against 9.1).  fp32 is
+//   bound by its MFMAs there, so four wavefronts on a tile pay up to 512 workgroups of two units (14x14 1024->256 eight streams
+//   19.4 against 27.1).
+//   128 x 128 tiles need three workgroups of the smaller ones per CU: 28x28 512->128 32 streams (784 small tiles) 11.4 against
+//   14.1, 14x14 256->1024 16 streams (1024) 9.4 against 11.1, but 14x14 1024->256 32 streams (512) 14.6 against 12.1.  fp32:
+//   only where K is deep (14x14 1024->512 32 streams, 1024 tiles: 75.7 against 81.1; 56x56 256->128, 6272 tiles: 96 against 79).
+int pw_units(const ConvLaunch& c, long n_units, int n_chunks, int forced) {
+    if (forced == 1 || forced == 2 || forced == 4 || forced == 8) return forced;
+    const bool bf16 = c.dtype == DC_BF16;
+    const long r32 = (c.Cout + 31) / 32, small_tiles = (n_units + 3) / 4 * ((c.Cout + 63) / 64);
+    if (n_units * r32 <= 256) return 1;
+    if ((n_units + 1) / 2 * r32 <= (bf16 ? 256 : 512)) return 2;
+    return c.Cout >= 128 && (bf16 ? small_tiles >= 768 : small_tiles >= 1024 && n_chunks >= 32) ? 8 : 4;
 }
 bool launch_conv_fast(const ConvLaunch& c, long n_cap, long n_units, hipStream_t st, hipError_t* err) {
     // below, n_units is the length the launch is tuned for and n_cap the length it must cover; they differ only
@@ -1422,13 +1608,12 @@ bool launch_conv_fast(const ConvLaunch& c, long n_cap, long n_units, hipStream_t
         reinterpret_cast<uintptr_t>(c.out) % 16 == 0 && (!c.bias || reinterpret_cast<uintptr_t>(c.bias) % 16 == 0)) {
         constexpr bool pw_enabled = true;
         const int units_y = (c.Hout + 3) / 4, units_x = (c.Wout + 3) / 4;
-        // Tile: 4 units x 64 channels; with enough of those to give every CU several, 8 units x 128 channels
-        const long small_tiles = (n_units + 3) / 4 * ((c.Cout + 63) / 64);
-        const int wm = g_tune[1] == 8 ? 4 : (g_tune[1] == 4 ? 2 : (small_tiles >= 4096 && c.Cout >= 128 ? 4 : 2));
-        const int g_units = 2 * wm, nt = 32 * wm;
+        const int kc = (int)(128 / esz), n_chunks = (c.Cin + kc - 1) / kc;
+        const int g_units = pw_units(c, n_units, n_chunks, g_tune[1]), nt = g_units == 8 ? 128 : g_units == 4 ? 64 : 32;
+        const int threads = g_units >= 4 ? g_units * 64 : kPwSplit * 64;
         const long R = (c.Cout + nt - 1) / nt, tiles = (n_cap + g_units - 1) / g_units * R;
         if (pw_enabled && (double)c.n_streams * c.Hout * c.Wout * c.Cout < 2147483648.0 &&
-            tiles + 8 < 2147483647L / (wm * 128)) {
+            tiles + 8 < 2147483647L / threads) {
             ConvParams P{};
             P.in = c.in; P.w = c.w; P.bias = c.bias; P.out = c.out;
             P.Hin = c.Hin; P.Win = c.Win; P.Cin = c.Cin; P.Hout = c.Hout; P.Wout = c.Wout; P.Cout = c.Cout;
@@ -1439,19 +1624,19 @@ bool launch_conv_fast(const ConvLaunch& c, long n_cap, long n_units, hipStream_t
             P.pw_magic = (uint32_t)((0x100000000ull + (uint64_t)units_x - 1) / (uint64_t)units_x);
             P.in_bytes = (uint32_t)((size_t)c.n_streams * c.Hin * c.Win * c.Cin * esz);
             P.w_bytes = (uint32_t)((size_t)c.Cout * c.Cin * esz);
-            const int kc = (int)(128 / esz);
-            P.n_chunks = (c.Cin + kc - 1) / kc;
+            P.n_chunks = n_chunks;
             P.in_origin = c.in_origin; P.out_origin = c.out_origin; P.origin_stride = c.origin_stride;
             P.R = (int)R;
             P.n_wg_tiles = (int)tiles;
             P.tiles_per_xcd = (int)((tiles + 7) / 8);
             // Every kernel starts with cold caches, so a workgroup's walk over K is a chain of long-latency loads:
             // up to four chunks are in flight per workgroup, and several workgroups share a CU.
-            const int stages = P.n_chunks < 4 ? P.n_chunks : 4;
-            const size_t lds = kHeaderBytes + (size_t)stages * (size_t)(wm * 8192);
-            if (c.kernel_id) *c.kernel_id = (wm == 4 ? 127 : 108) + (c.dtype == DC_BF16 ? 1 : 0);
-            *err = c.dtype == DC_BF16 ? pw_launch<__hip_bfloat16>(wm, dim3((unsigned)(8 * P.tiles_per_xcd)), lds, st, P)
-                                      : pw_launch<float>(wm, dim3((unsigned)(8 * P.tiles_per_xcd)), lds, st, P);
+            const int stages = n_chunks < 4 ? n_chunks : 4;
+            const size_t lds = kHeaderBytes + (size_t)stages * (size_t)(g_units * 4096);      // (of the kernels with a ring)
+            const int bf16 = c.dtype == DC_BF16 ? 1 : 0;
+            if (c.kernel_id) *c.kernel_id = (g_units == 8 ? 127 : g_units == 4 ? 108 : kPwSplitId + 2 * (g_units - 1)) + bf16;
+            const dim3 grid((unsigned)(8 * P.tiles_per_xcd));
+            *err = bf16 ? pw_launch<__hip_bfloat16>(g_units, grid, lds, st, P) : pw_launch<float>(g_units, grid, lds, st, P);
             return true;
         }
     }

@@ -115,7 +115,7 @@ size_t packed_weights_bytes(int k, int s, int cin, int cout, int dtype);
 hipError_t launch_pack_weights(const void* w, void* packed, int cin, int cout, int dtype, hipStream_t st);
 void conv_kernel_name(int id, char* buf, size_t n);
 void conv_fast_kernel_name(int id, char* buf, size_t n);
-bool conv_5x5_kernel_built(int id);        // ids from 132
+bool conv_kernel_built(int id);        // ids from 132 on
 struct ConvTuning { int v[4]; };             // dc_conv_tuning's arguments, -1: chosen by the model
 void conv_set_tuning(int geom, int g, int ks, int kci);
 ConvTuning conv_tuning();

@@ -620,6 +620,16 @@ def test_pointwise_kernel(oracle, case, pw_tile, bf16, cached):
         assert _rel_err(got[i], want) <= (2e-2 if bf16 else 1e-4), (case, i)
 
 
+# The kernel whose four wavefronts split K in pieces of 128 bytes: fewer pieces than wavefronts, a last piece that is not whole,
+# more than two pieces per wavefront, channels that end inside a 32-channel tile, a last workgroup with one unit of two.
+@pytest.mark.parametrize("cached", [False, True])
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("pw_tile", [1, 2], indirect=True)
+@pytest.mark.parametrize("case", PW_CASES + [(7, 7, 1096, 40, 1), (15, 13, 840, 8, 2), (8, 5, 192, 264, 1)])
+def test_pointwise_kernel_with_split_k(oracle, case, pw_tile, bf16, cached):
+    test_pointwise_kernel(oracle, case, pw_tile, bf16, cached)
+
+
 @pytest.mark.parametrize("bf16", [False, True])
 @pytest.mark.parametrize("case", [(20, 24, 4, 32, 3, 1, 1), (20, 24, 64, 64, 3, 1, 1), (20, 24, 64, 128, 1, 1, 0), (21, 25, 32, 48, 5, 2, 2),
                                   (21, 25, 6, 10, 3, 1, 1), (12, 12, 512, 64, 3, 1, 1)])

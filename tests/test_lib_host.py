@@ -393,3 +393,9 @@ def test_kernel_names_of_the_5x5_layers():
     assert sorted(built) == [140, 141, 148, 149, 150]
     assert built[141] == "conv_fast_kernel<__hip_bfloat16, 5, 32, 2, 4, 2, 4>" and built[150] == "conv_fast_kernel<__hip_bfloat16, 5, 32, 3, 4, 2, 2>"
     assert binding.lib().dc_conv_kernel_name(131, C.create_string_buffer(160), 160) == -1
+
+
+def test_kernel_names_of_the_split_1x1_layers():
+    assert [binding.conv_kernel_name(400 + i) for i in range(4)] == [
+        f"conv_pw_split_kernel<{t}, {u}, 2, 4>" for u in (1, 2) for t in ("float", "__hip_bfloat16")]
+    assert binding.lib().dc_conv_kernel_name(404, C.create_string_buffer(160), 160) == -1
