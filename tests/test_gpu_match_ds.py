@@ -93,6 +93,18 @@ def test_darknet_geometry_many_streams(oracle):
     _compare(oracle, cur, prev, 16, 16, synth.max_block_ssd(16), "416x416, 3 streams", ks=(1, 2))
 
 
+# Blocks of whole dwords are compared a dword at a time: 1 to 4 dwords per lane, all lanes with one or a part of them, windows of one
+# and of several 16-byte pieces per row, pieces over both ends of the frame, frames too small for a piece, rows at any byte.
+@pytest.mark.parametrize("H,W,C,B,R", [(4, 4, 1, 4, 4), (2, 2, 2, 2, 1), (3, 3, 2, 2, 2), (19, 23, 4, 8, 6), (41, 37, 3, 12, 9), (35, 33, 2, 14, 3),
+                                       (33, 49, 4, 16, 5), (48, 51, 3, 16, 16), (16, 16, 3, 16, 16), (70, 61, 1, 32, 20), (40, 90, 3, 16, 30),
+                                       (25, 31, 4, 4, 0)])
+def test_blocks_of_whole_dwords(oracle, H, W, C, B, R):
+    rng = np.random.default_rng(H * W + R)
+    prev = np.stack([synth._box_blur5(rng.integers(0, 256, (H, W, C)).astype(np.uint8)) for _ in range(3)])
+    cur = np.stack([np.roll(prev[0], (R // 2, -R // 3), axis=(0, 1)), rng.integers(0, 256, (H, W, C)).astype(np.uint8), 255 - prev[2]])
+    _compare(oracle, cur, prev, B, R, 40 * B * B * C, f"dwords {H}x{W}x{C}")
+
+
 def test_argument_checks():
     dev = torch.device("cuda:0")
     f = torch.zeros((1, 32, 32, 3), dtype=torch.uint8, device=dev)
