@@ -8,6 +8,8 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import threading
+import types
 
 import numpy as np
 import torch
@@ -147,9 +149,7 @@ def _ptr(t):
 def layers_to_c(layers):
     arr = (Layer * len(layers))()
     for i, L in enumerate(layers):
-        for f, ct in Layer._fields_:
-            v = L[f] if f in L else synth.LAYER_DEFAULTS[f]
-            setattr(arr[i], f, float(v) if ct is C.c_float else int(v))
+        arr[i] = Layer(*[(float if ct is C.c_float else int)(L[f] if f in L else synth.LAYER_DEFAULTS[f]) for f, ct in Layer._fields_])
     return arr
 
 
@@ -224,6 +224,27 @@ def _alloc_regions(n, cap):
     return regs, store
 
 
+# Regions as a record array: one assignment per field instead of one per entry
+_REGIONS_DTYPE = np.dtype([("rects", np.uint64)] + [(f, np.int32) for f, _ in Regions._fields_[1:]], align=True)
+assert _REGIONS_DTYPE.itemsize == C.sizeof(Regions)
+
+
+def _regions_to_c(regions):
+    """(dc_regions array, the rectangles it points to, longest list) of a list of (rects [m][4], (dx, dy)); both arrays have to
+    live as long as the call."""
+    lists = [np.asarray(r, np.int32).reshape(-1, 4) for r, _ in regions]
+    counts = [len(r) for r in lists]
+    cap = max(1, max(counts))
+    store = np.zeros((len(lists), cap, 4), np.int32)
+    for i, r in enumerate(lists):
+        store[i, :len(r)] = r
+    regs = np.zeros(len(lists), _REGIONS_DTYPE)
+    regs["rects"] = store.ctypes.data + np.arange(len(lists), dtype=np.uint64) * (16 * cap)
+    regs["capacity"], regs["n"] = cap, counts
+    regs["dx"], regs["dy"] = [int(d[0]) for _, d in regions], [int(d[1]) for _, d in regions]
+    return regs, store, cap
+
+
 def _regions_to_py(r):
     n = min(r.n, r.capacity)
     rects = np.array([[r.rects[i].x, r.rects[i].y, r.rects[i].w, r.rects[i].h] for i in range(n)],
@@ -242,26 +263,44 @@ def dc_propagate_regions(layers, H, W, block, block_mask, mx, my, cap=1024, exte
     return [_regions_to_py(regs[t]) for t in range(len(layers) + 1)]
 
 
-class _Workspace:
-    """Device + pinned host scratch, grown on demand and kept per device."""
+class _Workspaces:
+    """Device + pinned host scratch of single-layer calls, grown on demand.  Two sets take turns, so that the host prepares a
+    call while the GPU still works on the one before; a set belongs to one call from take() to give() (threads), and its
+    event, recorded behind the call's work, has passed before it is used again (streams)."""
+    KEPT = 2
 
     def __init__(self):
-        self.dev = None
-        self.host = None
-        self.busy = None   # event recorded after the last call that read the host staging
+        self.lock = threading.Lock()
+        self.free = []
+        self.made = 0
 
-    def get(self, dev_bytes, host_bytes, device):
-        if self.busy is not None:
-            self.busy.synchronize()   # the previous upload must have left the staging buffer
-            self.busy = None
-        if self.dev is None or self.dev.numel() < dev_bytes or self.dev.device != device:
-            self.dev = torch.empty(max(int(dev_bytes), 256), dtype=torch.uint8, device=device)
-        if self.host is None or self.host.numel() < host_bytes:
-            self.host = torch.empty(max(int(host_bytes), 256), dtype=torch.uint8, pin_memory=True)
-        return self.dev, self.host
+    def take(self, dev_bytes, host_bytes, device):
+        with self.lock:
+            if self.made < self.KEPT or not self.free:
+                self.made += 1
+                ws = types.SimpleNamespace(dev=None, host=None, event=None)
+            else:
+                ws = self.free.pop(0)
+        if ws.event is not None:
+            ws.event.synchronize()
+        if ws.dev is None or ws.dev.numel() < dev_bytes or ws.dev.device != device:
+            ws.dev = torch.empty(max(int(dev_bytes), 256), dtype=torch.uint8, device=device)
+            ws.event = torch.cuda.Event()
+        if ws.host is None or ws.host.numel() < host_bytes:
+            ws.host = torch.empty(max(int(host_bytes), 256), dtype=torch.uint8, pin_memory=True)
+        return ws
+
+    def give(self, ws):
+        ws.event.record()
+        with self.lock:
+            if len(self.free) < self.KEPT:
+                self.free.append(ws)
+                return
+            self.made -= 1
+        ws.event.synchronize()          # more calls at once than sets are kept: this one's memory goes back
 
 
-_conv_ws = _Workspace()
+_conv_ws = _Workspaces()
 
 
 def dc_pack_conv_weights(layer, weights):
@@ -293,25 +332,20 @@ def dc_cached_conv_layer(layer, x, weights, bias, cache_prev=None, regions=None,
         out = torch.empty((n, Ho, Wo, layer["cout"]), dtype=x.dtype, device=x.device)
     Lc = layers_to_c([layer])
     regs = None
-    keep = None
     max_rects = 1
     if regions is not None:
         assert len(regions) == n
-        max_rects = max(1, max(len(r[0]) for r in regions))
-        regs, keep = _alloc_regions(n, max_rects)
-        for i, (rects, dxy) in enumerate(regions):
-            regs[i].n = len(rects)
-            regs[i].dx, regs[i].dy = int(dxy[0]), int(dxy[1])
-            for j, r in enumerate(rects):
-                keep[i][j] = Rect(*[int(v) for v in r])
+        regs, store, max_rects = _regions_to_c(regions)
     db, hb = C.c_size_t(), C.c_size_t()
     _check("dc_conv_workspace_bytes", lib().dc_conv_workspace_bytes(Lc, n, Hin, Win, max_rects, C.byref(db), C.byref(hb)))
-    wd, wh = _conv_ws.get(db.value, hb.value, x.device)
-    _check("dc_cached_conv_layer", lib().dc_cached_conv_layer(
-        Lc, _ptr(x), _ptr(weights), _ptr(packed), _ptr(bias), _ptr(cache_prev), _ptr(out), n, Hin, Win, regs, dtype,
-        _ptr(wd), wd.numel(), C.c_void_p(wh.data_ptr()), wh.numel(), _stream()))
-    _conv_ws.busy = torch.cuda.Event()
-    _conv_ws.busy.record()
+    ws = _conv_ws.take(db.value, hb.value, x.device)
+    try:
+        _check("dc_cached_conv_layer", lib().dc_cached_conv_layer(
+            Lc, _ptr(x), _ptr(weights), _ptr(packed), _ptr(bias), _ptr(cache_prev), _ptr(out), n, Hin, Win,
+            None if regs is None else regs.ctypes.data, dtype, _ptr(ws.dev), ws.dev.numel(), C.c_void_p(ws.host.data_ptr()),
+            ws.host.numel(), _stream()))
+    finally:
+        _conv_ws.give(ws)
     return out
 
 

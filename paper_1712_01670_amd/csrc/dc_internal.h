@@ -366,6 +366,8 @@ struct PlanAddr {
     size_t bytes;
 };
 PlanAddr pack_plan(const LayerPlan& plan, unsigned char* host, unsigned char* dev);
+const unsigned char* device_alias(void* host);
+hipError_t upload_plans(void* dst_dev, const unsigned char* src_host, size_t bytes, void* ws_host, hipStream_t st);
 struct Bracket {   // records a profile slot around a launch when a profile is attached
     Profile* p; int slot; hipStream_t st;
     Bracket(Profile* p_, int slot_, hipStream_t st_) : p(p_), slot(slot_), st(st_) {

@@ -49,36 +49,6 @@ hipError_t spin_wait(hipEvent_t e) {
     }
 }
 
-// Small plans (one or a few streams) go from the pinned staging buffer to the device with a kernel that reads
-// the host memory through its device address: a launch costs the host a few microseconds where an asynchronous
-// copy on an idle stream measured 25.  Large plans (64 streams: megabytes) are faster through the copy engine,
-// and pageable staging memory has no device address.
-__global__ void __launch_bounds__(256) upload_kernel(const uint4* __restrict__ src, uint4* __restrict__ dst, size_t n_vec) {
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_vec; i += (size_t)gridDim.x * blockDim.x)
-        dst[i] = src[i];
-}
-
-// Device address of a host buffer: nullptr if it is not pinned.  Asked on every call: a caller may free a
-// pinned buffer and pass pageable memory at the same address later.
-const unsigned char* device_alias(void* host) {
-    void* d = nullptr;
-    if (hipHostGetDevicePointer(&d, host, 0) != hipSuccess) { d = nullptr; (void)hipGetLastError(); }
-    return static_cast<const unsigned char*>(d);
-}
-
-hipError_t upload_plans(void* dst_dev, const unsigned char* src_host, size_t bytes, void* ws_host, hipStream_t st) {
-    if (bytes > 256 * 1024) return hipMemcpyAsync(dst_dev, src_host, bytes, hipMemcpyHostToDevice, st);
-    const unsigned char* alias = device_alias(ws_host);
-    if (!alias || bytes % 16 || reinterpret_cast<uintptr_t>(dst_dev) % 16 || reinterpret_cast<uintptr_t>(src_host) % 16)
-        return hipMemcpyAsync(dst_dev, src_host, bytes, hipMemcpyHostToDevice, st);
-    const unsigned char* src = alias + (src_host - static_cast<const unsigned char*>(ws_host));
-    const size_t n_vec = bytes / 16;
-    const unsigned grid = (unsigned)std::min<size_t>((n_vec + 255) / 256, 1024);
-    hipLaunchKernelGGL(upload_kernel, dim3(grid), dim3(256), 0, st, reinterpret_cast<const uint4*>(src),
-                       static_cast<uint4*>(dst_dev), n_vec);
-    return hipGetLastError();
-}
-
 // ---- planning on the GPU: layout of the tables and of one frame's plan in the device workspace ----
 constexpr size_t kDevHostRegion = 64 * 1024;    // tail of the host workspace: header, two counter slots, table staging
 constexpr size_t kDevHostSlot = 4096;

@@ -796,3 +796,61 @@ def test_fc_few_fp32_streams_and_neurons(n, K, cout):
     err = (got - want) / scale
     bound = 2.0 ** -24 / np.sqrt(3.0) * np.sqrt(K / 256 + 10)
     assert np.sqrt((err ** 2).mean()) <= bound and np.abs(err).max() <= 5 * bound, (np.sqrt((err ** 2).mean()) / bound, np.abs(err).max() / bound)
+
+
+# Single-layer calls take turns on two workspaces; the plan travels with the copies in one launch while those take at most 32
+# rectangles of whole 16-byte vectors.  Calls one behind the other, and from two threads on streams of their own, against calls that
+# are waited for: 32 rectangles, 33, channel runs that are no whole vectors, no rectangle at all.
+@pytest.mark.parametrize("per_stream,cout,bf16", [(8, 64, True), (8, 64, False), (11, 64, True), (8, 20, True), (0, 64, True)])
+def test_single_layer_calls_without_a_wait_in_between(per_stream, cout, bf16):
+    import threading
+    n, H, W, cin = 4, 24, 28, 32
+    dt = torch.bfloat16 if bf16 else torch.float32
+    gen = torch.Generator(DEV)
+    gen.manual_seed(per_stream + cout)
+    w = torch.randn((cout, 3, 3, cin), generator=gen, device=DEV).to(dt) * 0.1
+    layer = _layer(cin, cout, 3, 1, 1, True)
+    rng = np.random.default_rng(7)
+    calls = []
+    for c in range(10):
+        regions = []
+        for s in range(n - 1):
+            rects = [[1 + 2 * j, 1 + int(rng.integers(0, 4)), 2, int(rng.integers(1, 16))] for j in range(per_stream)]
+            regions.append((np.array(rects, np.int32).reshape(-1, 4), (int(rng.integers(-1, 2)), int(rng.integers(-1, 2)))))
+        regions.append((np.array([[2, 3, 9, 11]] * (1 if per_stream == 11 else 0), np.int32).reshape(-1, 4), (1, 0)))
+        if per_stream == 8:
+            regions[-1] = (np.array([[3 * j, 0, 3, 24] for j in range(8)], np.int32), (0, 0))
+        x = torch.randn((n, H, W, cin), generator=gen, device=DEV).to(dt)
+        prev = torch.randn((n, H, W, cout), generator=gen, device=DEV).to(dt)
+        calls.append((x, prev, regions))
+    torch.cuda.synchronize()
+
+    def run(i):
+        x, prev, regions = calls[i]
+        return binding.dc_cached_conv_layer(layer, x, w, None, prev, regions)
+    want = []
+    for i in range(10):
+        want.append(run(i))
+        torch.cuda.synchronize()
+        x, prev, regions = calls[i]
+        for s, (rects, (dx, dy)) in enumerate(regions):
+            for rx, ry, rw, rh in rects.tolist():
+                assert torch.equal(want[i][s, ry:ry + rh, rx:rx + rw], prev[s, ry + dy:ry + dy + rh, rx + dx:rx + dx + rw])
+    got = [run(i) for i in range(10)]
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(got, want))
+    bad = []
+
+    def worker():
+        st = torch.cuda.Stream()
+        with torch.cuda.stream(st):
+            res = [run(i) for i in range(10)]
+            st.synchronize()
+        bad.extend(i for i in range(10) if not torch.equal(res[i], want[i]))
+    threads = [threading.Thread(target=worker) for _ in range(3)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    assert not bad and len(binding._conv_ws.free) <= binding._conv_ws.KEPT
