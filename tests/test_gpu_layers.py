@@ -630,6 +630,53 @@ def test_pointwise_kernel_with_split_k(oracle, case, pw_tile, bf16, cached):
     test_pointwise_kernel(oracle, case, pw_tile, bf16, cached)
 
 
+# 3x3 layers of at most 256 (unit, 16 or 32 channels) pairs, whose eight wavefronts split K in runs of (64 bytes of channels,
+# kernel row): fewer such items than wavefronts, rows that end inside a piece, an uneven split, channels that end inside a
+# tile, windows without padding and with stride 2, the last size that takes 16 channels and the first that takes 32 (bf16).
+SPLIT_CASES = [  # (streams, H, W, cin, cout, s, p)
+    (2, 5, 9, 8, 8, 1, 1),
+    (1, 13, 11, 40, 24, 2, 1),
+    (3, 8, 6, 96, 72, 1, 0),
+    (2, 7, 7, 512, 128, 1, 1),
+    (1, 16, 16, 256, 256, 1, 1),       # 16 units x 16: the most with 16 channels
+    (1, 17, 13, 256, 264, 1, 1),       # 20 units x 17: 32 channels in bf16
+    (4, 14, 14, 64, 264, 2, 1),        # 16 units x 17
+    (2, 9, 10, 24, 136, 2, 2),
+]
+
+
+@pytest.mark.parametrize("cached", [False, True])
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("case", SPLIT_CASES)
+def test_3x3_kernel_with_split_k(oracle, case, bf16, cached):
+    """Tolerance: both sides sum at least in fp32 (9 cin terms: below 1e-5 of the map); bf16 results are rounded, 2^-8 each."""
+    n, H, W, cin, cout, s, p = case
+    print(f"[split 3x3] case={case} bf16={bf16} cached={cached}", flush=True)
+    rng = np.random.default_rng(sum(case) + 11)
+    Ho, Wo = (H + 2 * p - 3) // s + 1, (W + 2 * p - 3) // s + 1
+    x = rng.standard_normal((n, H, W, cin)).astype(np.float32)
+    w = (rng.standard_normal((cout, 3, 3, cin)) * np.sqrt(2.0 / (cin * 9))).astype(np.float32)
+    b = (rng.standard_normal(cout) * 0.1).astype(np.float32)
+    cache = rng.standard_normal((n, Ho, Wo, cout)).astype(np.float32)
+    if bf16:
+        x, w, cache = oracle.round_bf16(x), oracle.round_bf16(w), oracle.round_bf16(cache)
+    regions = [_random_regions(rng, oracle, Ho, Wo) for _ in range(n)] if cached else None
+    layer, wd = _layer(cin, cout, 3, s, p, True), _to_dev(w, bf16)
+    run = lambda weights, packed: _to_np(binding.dc_cached_conv_layer(
+        layer, _to_dev(x, bf16), weights, torch.from_numpy(b).to(DEV), cache_prev=_to_dev(cache, bf16) if cached else None,
+        regions=regions, packed=packed))
+    got, packed = run(wd, None), binding.dc_pack_conv_weights(layer, wd)
+    if packed is not None:
+        assert np.array_equal(got, run(torch.zeros_like(wd), packed)), "packed weights must not change a bit"
+    for i in range(n):
+        mask = oracle.rasterize(regions[i][0], Ho, Wo) if cached else np.zeros((Ho, Wo), np.uint8)
+        want = oracle.conv_cached(x[i], w, b, 3, s, p, True, cache_prev=cache[i], mask=mask, bf16=bf16,
+                                  dxy=regions[i][1] if cached else (0, 0))
+        m = mask.astype(bool)
+        assert np.array_equal(got[i][m], want[m])
+        assert _rel_err(got[i], want) <= (1e-2 if bf16 else 1e-5), (case, i)
+
+
 @pytest.mark.parametrize("bf16", [False, True])
 @pytest.mark.parametrize("case", [(20, 24, 4, 32, 3, 1, 1), (20, 24, 64, 64, 3, 1, 1), (20, 24, 64, 128, 1, 1, 0), (21, 25, 32, 48, 5, 2, 2),
                                   (21, 25, 6, 10, 3, 1, 1), (12, 12, 512, 64, 3, 1, 1)])

@@ -399,3 +399,10 @@ def test_kernel_names_of_the_split_1x1_layers():
     assert [binding.conv_kernel_name(400 + i) for i in range(4)] == [
         f"conv_pw_split_kernel<{t}, {u}, 2, 4>" for u in (1, 2) for t in ("float", "__hip_bfloat16")]
     assert binding.lib().dc_conv_kernel_name(404, C.create_string_buffer(160), 160) == -1
+
+
+def test_kernel_names_of_the_split_3x3_layers():
+    assert [binding.conv_kernel_name(410 + i) for i in range(3)] == [
+        "conv_split_kernel<float, 1>", "conv_split_kernel<__hip_bfloat16, 1>", "conv_split_kernel<__hip_bfloat16, 2>"]
+    for kid in (409, 413):
+        assert binding.lib().dc_conv_kernel_name(kid, C.create_string_buffer(160), 160) == -1
