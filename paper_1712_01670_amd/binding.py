@@ -232,12 +232,17 @@ assert _REGIONS_DTYPE.itemsize == C.sizeof(Regions)
 def _regions_to_c(regions):
     """(dc_regions array, the rectangles it points to, longest list) of a list of (rects [m][4], (dx, dy)); both arrays have to
     live as long as the call."""
-    lists = [np.asarray(r, np.int32).reshape(-1, 4) for r, _ in regions]
+    lists = [r for r, _ in regions]
     counts = [len(r) for r in lists]
     cap = max(1, max(counts))
     store = np.zeros((len(lists), cap, 4), np.int32)
     for i, r in enumerate(lists):
-        store[i, :len(r)] = r
+        if isinstance(r, np.ndarray) and r.ndim == 2 and r.shape[1] == 4 and r.dtype.kind in "iu":
+            store[i, :len(r)] = r
+            continue
+        for j, q in enumerate(r):                # anything that yields numbers: lists, tensors (also on the GPU), floats
+            x, y, w, h = (int(v) for v in q)
+            store[i, j] = x, y, w, h
     regs = np.zeros(len(lists), _REGIONS_DTYPE)
     regs["rects"] = store.ctypes.data + np.arange(len(lists), dtype=np.uint64) * (16 * cap)
     regs["capacity"], regs["n"] = cap, counts

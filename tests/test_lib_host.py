@@ -8,6 +8,7 @@ import subprocess
 
 import numpy as np
 import pytest
+import torch
 
 from paper_1712_01670_amd import binding, synth
 
@@ -406,3 +407,20 @@ def test_kernel_names_of_the_split_3x3_layers():
         "conv_split_kernel<float, 1>", "conv_split_kernel<__hip_bfloat16, 1>", "conv_split_kernel<__hip_bfloat16, 2>"]
     for kid in (409, 413):
         assert binding.lib().dc_conv_kernel_name(kid, C.create_string_buffer(160), 160) == -1
+
+
+def test_regions_of_a_single_layer_call_in_every_form():
+    """Rectangles as arrays, lists, tensors or floats fill the C structures alike; what is no rectangle is refused."""
+    want = [[1, 2, 3, 4], [5, 6, 7, 8]]
+    forms = [np.array(want, np.int32), np.array(want, np.int64), np.array(want, np.float32), want, [tuple(r) for r in want],
+             torch.tensor(want), list(torch.tensor(want)), np.array(want, np.int32)[::-1][::-1]]
+    regs, store, cap = binding._regions_to_c([(f, (np.int64(3), -2)) for f in forms] + [([], (0, 0)), (np.zeros((0, 4), np.int32), (0, 0))])
+    assert cap == 2
+    c = C.cast(regs.ctypes.data, C.POINTER(binding.Regions))
+    for i in range(len(forms)):
+        assert (c[i].n, c[i].dx, c[i].dy, c[i].capacity) == (2, 3, -2, 2)
+        assert [[c[i].rects[j].x, c[i].rects[j].y, c[i].rects[j].w, c[i].rects[j].h] for j in range(2)] == want
+    assert c[len(forms)].n == c[len(forms) + 1].n == 0
+    for bad in ([1, 2, 3, 4], np.arange(4), np.arange(8), [[1, 2, 3, 4, 5]], np.array([[1, 2, 3, np.nan]])):
+        with pytest.raises((TypeError, ValueError)):
+            binding._regions_to_c([(bad, (0, 0))])
