@@ -355,6 +355,133 @@ __global__ __launch_bounds__(kFcWaves * 64) void fc_mfma_kernel(const T* __restr
     out[(size_t)s * cout + o] = from_float<T>(v);
 }
 
+// Four vectors of every lane, transposed within quads of lanes: vector t of lane b becomes vector b of lane t.
+template <int CTRL, typename V>
+__device__ __forceinline__ void quad_swap(V& lo, V& hi, bool upper) {
+    const uintx4 l = __builtin_bit_cast(uintx4, lo), h = __builtin_bit_cast(uintx4, hi);
+    uintx4 nl, nh;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const uint32_t from_hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)h[e], CTRL, 0xf, 0xf, true);
+        const uint32_t from_lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)l[e], CTRL, 0xf, 0xf, true);
+        nl[e] = upper ? from_hi : l[e];
+        nh[e] = upper ? h[e] : from_lo;
+    }
+    lo = __builtin_bit_cast(V, nl);
+    hi = __builtin_bit_cast(V, nh);
+}
+template <typename V>
+__device__ __forceinline__ void quad_transpose(V (&v)[4], int lane) {
+    quad_swap<0xb1>(v[0], v[1], lane & 1);        // lanes 1 apart
+    quad_swap<0xb1>(v[2], v[3], lane & 1);
+    quad_swap<0x4e>(v[0], v[2], lane & 2);        // lanes 2 apart
+    quad_swap<0x4e>(v[1], v[3], lane & 2);
+}
+
+// The same GEMM for long rows.  Loaded as a fragment, a row per lane, 16 neighbouring lanes ask for 16 bytes of 16 rows: a look-up
+// in the CU's cache for every 16 bytes, and 16 bytes per clock is what a CU took in (asking further ahead changed nothing).
+// Here four lanes fetch 64 bytes of a row together, for four rows in turn, and exchange the vectors within the quad.  The
+// wavefronts deal the 256-byte chunks of K; K is summed in sixteen parts as above, two of them by each of eight wavefronts
+// where the registers hold no more.
+// us per call, the kernel above -> this: bf16 9216 -> 4096 64 streams 43.1 -> 24.7 (34 bytes a clock into a CU), 32 streams 26.9
+// -> 17.0, 16 streams 19.2 -> 14.2 (75 MB of weights: 14), 4096 -> 1000 64 streams 19.8 -> 11.3; fp32, whose MFMAs and
+// exchanges now take turns, 9216 -> 4096 64 streams 95.4 -> 80.5, 16 streams 41.3 -> 34.7.  Error of the fp32 sums against 64 bits 1.15e-7
+// -> 1.06e-7 (9216), 7.45e-8 -> 7.40e-8 (2048).
+constexpr int kFcParts = 16;                      // parts of K, summed apart
+template <typename T, int NB, int WAVES>
+__global__ __launch_bounds__(WAVES * 64) void fc_quad_kernel(const T* __restrict__ x, const T* __restrict__ w,
+                                                             const float* __restrict__ bias, T* __restrict__ out,
+                                                             int n_streams, size_t K, int cout, int relu) {
+    typedef Frag<T> F;
+    typedef typename F::vec vec;
+    constexpr int VE = F::VE;
+    constexpr int CH = 16 * VE;                   // elements of a chunk: four K groups of four vectors
+    constexpr int PH = kFcParts / WAVES;          // parts of a wavefront, by the parity of the round
+    static_assert(PH == 1 || PH == 2, "");
+    __shared__ float red[kFcParts][NB * 256];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l16 = lane & 15, q = lane >> 4;
+    const int o0 = blockIdx.x * 16, s0 = blockIdx.y * (NB * 16);
+    // the quad's four rows; rows past the end repeat the tile's first one (not stored)
+    const T *wrow[4], *xrow[NB][4];
+    const size_t first = (size_t)(l16 & 12) * K;
+    const T* const w0 = w + (size_t)o0 * K;
+    const T* const x0 = x + (size_t)s0 * K;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        wrow[t] = o0 + (l16 & 12) + t < cout ? w0 + t * K + first : w0;
+#pragma unroll
+        for (int j = 0; j < NB; ++j) xrow[j][t] = s0 + j * 16 + (l16 & 12) + t < n_streams ? x0 + (j * 16 + t) * K + first : x0;
+    }
+    floatx4 acc[PH][NB];
+#pragma unroll
+    for (int h = 0; h < PH; ++h)
+#pragma unroll
+        for (int j = 0; j < NB; ++j) acc[h][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    // K is a multiple of VE: a vector lies inside its row or past the row's end (then the last one is fetched)
+    auto fetch = [&](vec (&v)[4], const T* const (&row)[4], size_t k) {
+        const size_t want = k + (size_t)(q * 4 + (lane & 3)) * VE, at = want < K ? want : K - VE;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) v[t] = *reinterpret_cast<const vec*>(row[t] + at);
+    };
+    auto arrange = [&](vec (&v)[4], size_t k) {   // vector t of a lane: elements k + (4 q + t) VE of row l16, zeros past the end
+        quad_transpose(v, lane);
+        if (k + CH > K)
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                if (k + (size_t)(q * 4 + t) * VE >= K) v[t] = vec{};
+    };
+    // the chunk's inputs (from L2) are loaded when it is multiplied, its weights (from memory) one chunk ahead
+    constexpr size_t kStep = (size_t)WAVES * CH;
+    vec wa[4], wb[4];
+    if ((size_t)wave * CH < K) fetch(wa, wrow, (size_t)wave * CH);
+    auto round = [&](floatx4 (&sums)[NB], vec (&wc)[4], vec (&wn)[4], size_t k) {
+        vec xv[NB][4];
+#pragma unroll
+        for (int j = 0; j < NB; ++j) fetch(xv[j], xrow[j], k);
+        if (k + kStep < K) fetch(wn, wrow, k + kStep);
+        arrange(wc, k);
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+            arrange(xv[j], k);
+            floatx4 part[4];       // the sums of a K group alone, then added to the total: short chains of roundings
+#pragma unroll
+            for (int t = 0; t < 4; ++t) part[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int e = 0; e < F::NE; ++e)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) F::mma1(wc[t], xv[j][t], part[t], e);
+            sums[j] += (part[0] + part[1]) + (part[2] + part[3]);
+        }
+    };
+    for (size_t k = (size_t)wave * CH; k < K; k += 2 * kStep) {
+        round(acc[0], wa, wb, k);
+        if (k + kStep >= K) break;
+        round(acc[PH - 1], wb, wa, k + kStep);
+    }
+#pragma unroll
+    for (int h = 0; h < PH; ++h)
+#pragma unroll
+        for (int j = 0; j < NB; ++j)              // register r of a lane: neuron 4 q + r, stream 16 j + l16
+            *reinterpret_cast<floatx4*>(&red[h * WAVES + wave][(j * 16 + l16) * 16 + q * 4]) = acc[h][j];
+    __syncthreads();
+    for (int i = tid; i < NB * 256; i += WAVES * 64) {
+        const int o = o0 + (i & 15), s = s0 + (i >> 4);
+        if (o >= cout || s >= n_streams) continue;
+        float sum[kFcParts];
+#pragma unroll
+        for (int p = 0; p < kFcParts; ++p) sum[p] = red[p][i];
+#pragma unroll
+        for (int d = kFcParts / 2; d >= 1; d >>= 1)
+#pragma unroll
+            for (int p = 0; p < d; ++p) sum[p] += sum[p + d];
+        float v = sum[0];
+        if (bias) v += bias[o];
+        if (relu) v = v > 0.f ? v : 0.f;
+        out[(size_t)s * cout + o] = from_float<T>(v);
+    }
+}
+
 // ---- 16-byte vector forms: one thread per (pixel, vector of 4 fp32 / 8 bf16 channels) --------------------------
 template <typename T>
 struct Vec16 {
@@ -1041,12 +1168,21 @@ hipError_t fc_launch(const void* x, const void* w, const float* bias, void* out,
     return hipGetLastError();
 }
 
+// Rows of 1536 elements on are worth the exchanges (us, fragments as loaded -> quads): bf16 1536 -> 100 64 streams 8.8 -> 6.3,
+// 16 streams 4.5 -> 3.3; fp32 16.3 -> 14.6, 7.3 -> 5.3; below, bf16 1032 -> 72 24 streams 3.3 -> 4.0, fp32 1152 -> 100 33
+// streams 11.0 -> 11.9.  Few streams wait for the weights alone (bf16 4096 -> 4096 three streams 8.5 -> 9.0,
+// 2048 -> 256 five 4.4 -> 3.5; fp32 9216 -> 4096 five streams 31.6 -> 32.9, nine 33.8 -> 33.7).
 template <typename T, int NB>
 hipError_t fc_mfma_launch(const void* x, const void* w, const float* bias, void* out, int n_streams, size_t K, int cout, int relu,
                           hipStream_t st) {
     const dim3 grid((unsigned)((cout + 15) / 16), (unsigned)((n_streams + NB * 16 - 1) / (NB * 16)));
-    hipLaunchKernelGGL((fc_mfma_kernel<T, NB>), grid, dim3(kFcWaves * 64), 0, st, (const T*)x, (const T*)w, bias, (T*)out, n_streams, K,
-                       cout, relu);
+    constexpr int WAVES = NB == 4 || (NB == 2 && sizeof(T) == 4) ? 8 : 16;      // as many as their registers allow
+    if (K >= 1536 && n_streams > (sizeof(T) == 2 ? 4 : 8))
+        hipLaunchKernelGGL((fc_quad_kernel<T, NB, WAVES>), grid, dim3(WAVES * 64), 0, st, (const T*)x, (const T*)w, bias, (T*)out, n_streams,
+                           K, cout, relu);
+    else
+        hipLaunchKernelGGL((fc_mfma_kernel<T, NB>), grid, dim3(kFcWaves * 64), 0, st, (const T*)x, (const T*)w, bias, (T*)out, n_streams, K,
+                           cout, relu);
     return hipGetLastError();
 }
 

@@ -424,6 +424,30 @@ def test_fully_connected_layer_on_the_matrix_cores(oracle, n, K, cout, bf16):
 
 
 @pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("n", [7, 20, 64])
+def test_fully_connected_rounds_and_the_rows_end(n, bf16):
+    """One to five rounds of the wavefronts, ending on a chunk, a vector short of it and a vector behind it.  Whole numbers of
+    few bits, so every sum is exact.  Vectors behind a row's end repeat its last one and must not count: an infinity there
+    belongs to its stream and to neurons with a weight of their own sign alone."""
+    print(f"[fc rounds] n={n} bf16={bf16}", flush=True)
+    rng = np.random.default_rng(n)
+    ve, cout = (8 if bf16 else 4), 18
+    step = (8 if n > 32 or (n > 16 and not bf16) else 16) * 16 * ve
+    for rounds in range(1, 6):
+        for K in (rounds * step - ve, rounds * step, rounds * step + ve, (rounds - 1) * step + 16 * ve):
+            x = rng.integers(-1, 2, (n, 1, 1, K)).astype(np.float32)
+            w = rng.integers(-1, 2, (cout, K)).astype(np.float32)
+            w[:, -1] = np.where(w[:, -1] == 0, 1, w[:, -1])
+            want = x.reshape(n, K) @ w.T
+            if bf16:
+                want = torch.from_numpy(want).bfloat16().float().numpy()
+            x[n // 2, 0, 0, -1] = np.inf
+            want[n // 2] = np.where(w[:, -1] > 0, np.inf, -np.inf)
+            got = _to_np(binding.dc_fc_layer(_to_dev(x, bf16), _to_dev(w, bf16), None, False)).reshape(n, cout)
+            assert np.array_equal(got, want), K
+
+
+@pytest.mark.parametrize("bf16", [False, True])
 @pytest.mark.parametrize("H,W,ch,k,s,p", [(13, 17, 24, 3, 1, 1), (14, 9, 8, 3, 2, 0), (5, 6, 520, 3, 2, 2), (1, 1, 8, 3, 1, 1), (2, 7, 2056, 3, 3, 2),
                                           (7, 7, 1024, 7, 1, 0), (9, 5, 16, 5, 1, 2), (8, 11, 8, 4, 3, 1), (11, 12, 40, 9, 2, 4)])
 def test_pooling_windows(oracle, H, W, ch, k, s, p, bf16):
