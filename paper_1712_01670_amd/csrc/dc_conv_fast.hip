@@ -914,8 +914,6 @@ __global__ __launch_bounds__(WM * 128) void conv_pw_kernel(ConvParams P) {
 
 constexpr int kPwSplit = 4;           // wavefronts that share a tile's K
 constexpr int kPwSplitId = 400;       // kernel ids: + 2 (units - 1) + bf16
-constexpr int kSplit = 8;             // the same for 3x3 layers (see conv_split_kernel)
-constexpr int kSplitId = 410;         // kernel ids: + 0 float, + 1 bf16, + 2 bf16 with 32 channels
 
 // ---- 1x1 convolutions of few units and a deep K ---------------------------------------------------
 // With few (unit group, channel tile) pairs the ring above leaves most CUs idle and the others with a step of 0.4 us per 128
@@ -1072,137 +1070,6 @@ __global__ __launch_bounds__(WK * 64) void conv_pw_split_kernel(ConvParams P) {
             F::store4(px + 4, v1);
         }
     }
-}
-
-// ---- 3x3 convolutions of few units ----------------------------------------------------------------
-// A workgroup of conv_fast_kernel takes in about 28 bytes per clock however far ahead it asks, and with few units few
-// workgroups share the whole of the weights (14x14 256->256 on one stream: 32 of them, 336 KB each).  Here the tiles are a
-// unit x 16 NB channels, as many as there are CUs, and the WK wavefronts of a workgroup split K as in the kernel above:
-// fragments straight into registers, no barrier before the partial tiles are added through LDS in the order of the
-// wavefronts.  K is walked in items of one kernel row x 64 bytes of channels, an equal run of them per wavefront, so that
-// the three rows of a patch come from the CU's own cache the second and third time.  Eight wavefronts, so that no chain of
-// fp32 sums is longer than the K split of conv_fast_kernel leaves it (four are as fast).  Stride 1 and 2, any channel count
-// of whole vectors.
-template <typename T, int NB>
-__global__ __launch_bounds__(kSplit * 64) void conv_split_kernel(ConvParams P) {
-    typedef Frag<T> F;
-    typedef typename F::vec vec;
-    constexpr int ES = (int)sizeof(T), WK = kSplit, NT = NB * 16, KSZ = 3;
-    __shared__ __align__(16) floatx4 red[WK][NB][64];
-
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int l16 = lane & 15, q = lane >> 4;
-    const int n_units = unit_count(P);
-    const int n_wg_tiles = n_units * P.R, tiles_per_xcd = (n_wg_tiles + 7) >> 3;
-    const int t = (int)(blockIdx.x & 7) * tiles_per_xcd + (int)(blockIdx.x >> 3);
-    if ((int)(blockIdx.x >> 3) >= tiles_per_xcd || t >= n_wg_tiles) return;    // the whole workgroup, before any barrier
-    // an XCD takes consecutive tiles: all units of a channel tile, whose weights then come from memory once
-    const int ntile = t / n_units, ug = t - ntile * n_units;
-    const int n0 = ntile * NT;
-    const int CinES = P.Cin * ES;
-    const __amdgpu_buffer_rsrc_t in_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(P.in), 0, P.in_bytes, kBufferFlags);
-    const __amdgpu_buffer_rsrc_t w_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(P.w), 0, P.w_bytes, kBufferFlags);
-
-    // weights: the plain rows [channel][tap][cin] or the packed copy [channel / 16][64-byte chunk][tap][channel % 16][64 bytes]
-    const bool packed = P.w_packed != 0;
-    const int w_tap = packed ? 1024 : CinES, w_chunk = packed ? KSZ * KSZ * 1024 : 64;
-    uint32_t wgo[NB];
-#pragma unroll
-    for (int j = 0; j < NB; ++j) {
-        const int ch = n0 + (l16 >> 2) * (4 * NB) + 4 * j + (l16 & 3);
-        const uint32_t row = packed ? (uint32_t)(ch / 16 * (CinES / 64) * (KSZ * KSZ * 1024) + ch % 16 * 64) : (uint32_t)(ch * (KSZ * KSZ) * CinES);
-        wgo[j] = ch < P.Cout ? row + (uint32_t)(q * 16) : kOob;
-    }
-    struct Pieces { vec w[KSZ][NB], x[KSZ]; };
-    auto load_w = [&](Pieces& f, int chunk, int ky) {
-        const bool in_k = chunk * 64 + q * 16 < CinES;     // (rows need only be whole vectors)
-#pragma unroll
-        for (int kx = 0; kx < KSZ; ++kx)
-#pragma unroll
-            for (int j = 0; j < NB; ++j) {
-                const uint32_t off = in_k && wgo[j] != kOob ? wgo[j] + (uint32_t)((ky * KSZ + kx) * w_tap + chunk * w_chunk) : kOob;
-                f.w[kx][j] = __builtin_bit_cast(vec, __builtin_amdgcn_raw_buffer_load_b128(w_rsrc, off, 0, 0));
-            }
-    };
-    const int n_items = P.n_chunks * KSZ;                  // chunk of 64 bytes outside, kernel row inside
-    const int i0 = wave * n_items / WK, i1 = (wave + 1) * n_items / WK;
-    Pieces a, b;
-    if (i0 < i1) load_w(a, i0 / KSZ, i0 % KSZ);            // on their way while the units are looked up
-
-    // the lane's pixel: its place in the output (element offset; -1: not stored) and its window in the input
-    int stream = 0, uy = 0, ux = 0, mixed = 0;
-    if (P.units) {
-        const TileDev td = P.units[ug];
-        stream = td.stream; uy = td.ty; ux = td.tx; mixed = td.reuse_mask;
-    } else {
-        stream = fast_div_any(ug, P.npix_magic, P.units_x * P.units_y);
-        const int r = ug - stream * (P.units_x * P.units_y);
-        uy = fast_div(r, P.pw_magic); ux = r - uy * P.units_x;
-    }
-    const int y = uy * 4 + (l16 >> 2), x = ux * 4 + (l16 & 3);
-    const bool in_map = y < P.Hout && x < P.Wout;
-    int oy = y, ox = x, in_x = 0, in_y = 0;                // tensors on a torus (stride 1 only: the launcher sees to it)
-    const size_t og = (size_t)stream * P.origin_stride;
-    if (P.in_origin) { in_x = P.in_origin[og]; in_y = P.in_origin[og + 1]; }
-    if (P.out_origin && in_map) { ox = torus_wrap(x, P.out_origin[og], P.Wout); oy = torus_wrap(y, P.out_origin[og + 1], P.Hout); }
-    const int dst = in_map && !((mixed >> l16) & 1) ? ((stream * P.Hout + oy) * P.Wout + ox) * P.Cout : -1;
-    const int win_y = in_map ? y * P.s - P.p : -(1 << 24); // every row of a pixel outside the map fails the range test
-    uint32_t col[KSZ];                                     // byte offsets of the window's columns within a row (kOob: padding)
-#pragma unroll
-    for (int kx = 0; kx < KSZ; ++kx) {
-        const int ix = x * P.s - P.p + kx;
-        col[kx] = (unsigned)ix < (unsigned)P.Win ? (uint32_t)((P.in_origin ? torus_wrap(ix, in_x, P.Win) : ix) * CinES + q * 16) : kOob;
-    }
-    auto load_x = [&](Pieces& f, int chunk, int ky) {
-        const int iy = win_y + ky;
-        const bool ok = chunk * 64 + q * 16 < CinES && (unsigned)iy < (unsigned)P.Hin;
-        const int line = P.in_origin && ok ? torus_wrap(iy, in_y, P.Hin) : iy;
-        const uint32_t row = (uint32_t)((stream * P.Hin + line) * P.Win * CinES + chunk * 64);
-#pragma unroll
-        for (int kx = 0; kx < KSZ; ++kx) {
-            const uint32_t off = ok && col[kx] != kOob ? row + col[kx] : kOob;
-            f.x[kx] = __builtin_bit_cast(vec, __builtin_amdgcn_raw_buffer_load_b128(in_rsrc, off, 0, 0));
-        }
-    };
-    floatx4 acc[NB];
-#pragma unroll
-    for (int j = 0; j < NB; ++j) acc[j] = floatx4{0.f, 0.f, 0.f, 0.f};
-    auto mma = [&](const Pieces& f) {
-#pragma unroll
-        for (int kx = 0; kx < KSZ; ++kx)
-#pragma unroll
-            for (int e = 0; e < F::NE; ++e)
-#pragma unroll
-                for (int j = 0; j < NB; ++j) F::mma1(f.w[kx][j], f.x[kx], acc[j], e);
-    };
-    if (i0 < i1) {
-        int chunk = i0 / KSZ, ky = i0 % KSZ;
-        auto next = [&] { if (++ky == KSZ) { ky = 0; ++chunk; } };
-        load_x(a, chunk, ky);
-        for (int i = i0;;) {
-            next();
-            if (i + 1 < i1) { load_w(b, chunk, ky); load_x(b, chunk, ky); }
-            mma(a);
-            if (++i >= i1) break;
-            next();
-            if (i + 1 < i1) { load_w(a, chunk, ky); load_x(a, chunk, ky); }
-            mma(b);
-            if (++i >= i1) break;
-        }
-    }
-#pragma unroll
-    for (int j = 0; j < NB; ++j) red[wave][j][lane] = acc[j];
-    __syncthreads();
-    // a lane holds 4 NB consecutive channels of its pixel; wavefront j adds and stores four of them
-    if (wave >= NB || dst < 0) return;
-    const int co = n0 + q * (4 * NB) + 4 * wave;
-    if (co >= P.Cout) return;
-    floatx4 v = red[0][wave][lane];
-#pragma unroll
-    for (int w = 1; w < WK; ++w) v += red[w][wave][lane];
-    if (P.bias) v += *reinterpret_cast<const floatx4*>(P.bias + co);
-    if (P.relu) activate4(v, P.relu);
-    F::store4(reinterpret_cast<T*>(P.out) + dst + co, v);
 }
 
 // ---- first layer -------------------------------------------------------------------------
@@ -1577,17 +1444,13 @@ FastChoice choose_fast(const ConvLaunch& c, long n_units, long n_cap, size_t scr
 
 // Ids 64.. name the instantiations of this file: 64 + ((bf16 * 2 + kci) * 8 + UPW - 1), 96.. the first-layer kernel,
 // 110.. the wide arrangement.
-bool conv_kernel_built(int id) { return id >= kSplitId ? id < kSplitId + 3 : id >= kPwSplitId ? id < kPwSplitId + 4 : id >= 132 && (id - 132) / 8 < kNumGeom && fast_built(5, true, (id - 132) / 8, 0, (id - 132) % 8 + 1); }
+bool conv_kernel_built(int id) { return id >= kPwSplitId ? id < kPwSplitId + 4 : id >= 132 && (id - 132) / 8 < kNumGeom && fast_built(5, true, (id - 132) / 8, 0, (id - 132) % 8 + 1); }
 void conv_fast_kernel_name(int id, char* buf, size_t n) {
     if (id == 126) { snprintf(buf, n, "conv_regw_kernel<2, 2, false>"); return; }
     if (id == 130) { snprintf(buf, n, "conv_regw_kernel<2, 2, true>"); return; }      // tensors on a torus
     if (id == 129) { snprintf(buf, n, "conv_fast_kernel<__hip_bfloat16, 3, 32, 3, 6, 2, 4>"); return; }     // the tall arrangement
     if (id == 127 || id == 128 || id == 108 || id == 109) {      // 108 + bf16 (64 x 64 tile), 127 + bf16 (128 x 128): conv_pw_kernel (1x1)
         snprintf(buf, n, "conv_pw_kernel<%s, %d>", id == 109 || id == 128 ? "__hip_bfloat16" : "float", id >= 127 ? 4 : 2);
-        return;
-    }
-    if (id >= kSplitId) {
-        snprintf(buf, n, "conv_split_kernel<%s, %d>", id > kSplitId ? "__hip_bfloat16" : "float", id > kSplitId + 1 ? 2 : 1);
         return;
     }
     if (id >= kPwSplitId) {
@@ -1696,20 +1559,6 @@ int pw_units(const ConvLaunch& c, long n_units, int n_chunks, int forced) {
     if ((n_units + 1) / 2 * r32 <= (bf16 ? 256 : 512)) return 2;
     return c.Cout >= 128 && (bf16 ? small_tiles >= 768 : small_tiles >= 1024 && n_chunks >= 32) ? 8 : 4;
 }
-// 16-channel blocks per workgroup of conv_split_kernel, or 0: the layer goes elsewhere.  One workgroup per CU is where it
-// pays; us per launch with the caches emptied in between, bf16 (before -> here, t = workgroups of one block):
-//   7x7 512->512 one stream (t = 128) 14.7 and its reduction's launch -> 9.6, 14x14 256->256 (256) 10.0 -> 7.2, stride 2
-//   14x14 512->512 (128) 14.1 -> 11.2, 28x28 256->256 (256) 10.2 -> 7.6.  Two blocks, 7x7 512->512 four streams (256 workgroups
-//   of two) 16.6 -> 12.6, stride 2 56x56 128->128 8.5 -> 7.4, but 28x28 128->128 (196) 7.3 -> 7.4: K has to be deep at stride 1.
-//   Beyond, every tile reads its weights again: 14x14 256->256 four streams 10.7 -> 12.3, 26x26 256->512 10.8 -> 19.8.
-//   fp32: 14x14 256->256 one stream 16.2 -> 10.2, stride 2 14x14 512->512 27.2 -> 19.4; two blocks are bound by their MFMAs
-//   (14x14 512->512 21.6 -> 25.9).
-int split_blocks(const ConvLaunch& c, long n_units) {
-    const bool bf16 = c.dtype == DC_BF16;
-    const long r16 = (c.Cout + 15) / 16, r32 = (c.Cout + 31) / 32;
-    if (n_units * r16 <= 256) return 1;
-    return bf16 && n_units * r32 <= 256 && (c.s == 2 || c.Cin >= 256) ? 2 : 0;
-}
 bool launch_conv_fast(const ConvLaunch& c, long n_cap, long n_units, hipStream_t st, hipError_t* err) {
     // below, n_units is the length the launch is tuned for and n_cap the length it must cover; they differ only
     // when the list is built on the GPU (then the kernels read the real length from memory)
@@ -1788,36 +1637,6 @@ bool launch_conv_fast(const ConvLaunch& c, long n_cap, long n_units, hipStream_t
             if (c.kernel_id) *c.kernel_id = (g_units == 8 ? 127 : g_units == 4 ? 108 : kPwSplitId + 2 * (g_units - 1)) + bf16;
             const dim3 grid((unsigned)(8 * P.tiles_per_xcd));
             *err = bf16 ? pw_launch<__hip_bfloat16>(g_units, grid, lds, st, P) : pw_launch<float>(g_units, grid, lds, st, P);
-            return true;
-        }
-    }
-    if (c.k == 3 && (c.s == 1 || c.s == 2) && g_tune[0] < 0 && g_tune[1] < 0 && (c.Cin * esz) % 16 == 0 && c.Cout % 8 == 0 &&
-        (!torus || (c.s == 1 && (c.Cin * esz) % 64 == 0 && c.Cout % geom_nt(0) == 0)) &&
-        reinterpret_cast<uintptr_t>(c.in) % 16 == 0 && reinterpret_cast<uintptr_t>(c.w) % 16 == 0 &&
-        reinterpret_cast<uintptr_t>(c.out) % 16 == 0 && (!c.bias || reinterpret_cast<uintptr_t>(c.bias) % 16 == 0)) {
-        const int nb = split_blocks(c, n_units);
-        const long R = nb ? (c.Cout + nb * 16 - 1) / (nb * 16) : 0, tiles = n_cap * R;
-        if (nb && (double)c.n_streams * c.Hout * c.Wout * c.Cout < 2147483648.0 && tiles + 8 < 2147483647L / (kSplit * 64)) {
-            ConvParams P{};
-            P.in = c.in; P.w = c.w; P.bias = c.bias; P.out = c.out;
-            P.Hin = c.Hin; P.Win = c.Win; P.Cin = c.Cin; P.Hout = c.Hout; P.Wout = c.Wout; P.Cout = c.Cout;
-            P.k = c.k; P.s = c.s; P.p = c.p; P.relu = c.relu;
-            P.units = c.tiles; P.n_units = (int)n_cap; P.n_units_dev = n_dev;
-            P.units_x = (c.Wout + 3) / 4; P.units_y = (c.Hout + 3) / 4;
-            P.npix_magic = (uint32_t)((0x100000000ull + (uint64_t)(P.units_x * P.units_y) - 1) / (uint64_t)(P.units_x * P.units_y));
-            P.pw_magic = (uint32_t)((0x100000000ull + (uint64_t)P.units_x - 1) / (uint64_t)P.units_x);
-            P.in_bytes = (uint32_t)((size_t)c.n_streams * c.Hin * c.Win * c.Cin * esz);
-            P.w_bytes = (uint32_t)((size_t)c.Cout * 9 * c.Cin * esz);
-            P.in_origin = c.in_origin; P.out_origin = c.out_origin; P.origin_stride = c.origin_stride;
-            P.n_chunks = (int)((c.Cin * esz + 63) / 64);       // pieces of 64 bytes
-            P.R = (int)R;
-            if (c.s == 1 && c.w_packed && reinterpret_cast<uintptr_t>(c.w_packed) % 16 == 0) { P.w = c.w_packed; P.w_packed = 1; }
-            if (c.kernel_id) *c.kernel_id = kSplitId + (c.dtype == DC_BF16 ? nb : 0);
-            const dim3 grid((unsigned)(8 * ((tiles + 7) / 8))), block(kSplit * 64);
-            if (c.dtype != DC_BF16) hipLaunchKernelGGL((conv_split_kernel<float, 1>), grid, block, 0, st, P);
-            else if (nb == 1) hipLaunchKernelGGL((conv_split_kernel<__hip_bfloat16, 1>), grid, block, 0, st, P);
-            else hipLaunchKernelGGL((conv_split_kernel<__hip_bfloat16, 2>), grid, block, 0, st, P);
-            *err = hipGetLastError();
             return true;
         }
     }

@@ -654,28 +654,27 @@ def test_pointwise_kernel_with_split_k(oracle, case, pw_tile, bf16, cached):
     test_pointwise_kernel(oracle, case, pw_tile, bf16, cached)
 
 
-# 3x3 layers of at most 256 (unit, 16 or 32 channels) pairs, whose eight wavefronts split K in runs of (64 bytes of channels,
-# kernel row): fewer such items than wavefronts, rows that end inside a piece, an uneven split, channels that end inside a
-# tile, windows without padding and with stride 2, the last size that takes 16 channels and the first that takes 32 (bf16).
-SPLIT_CASES = [  # (streams, H, W, cin, cout, s, p)
+# 3x3 layers of few units: channels that end inside a tile, rows that are no whole chunks, windows without padding and with stride 2,
+# maps of a few units with deep rows.
+FEW_UNIT_CASES = [  # (streams, H, W, cin, cout, s, p)
     (2, 5, 9, 8, 8, 1, 1),
     (1, 13, 11, 40, 24, 2, 1),
     (3, 8, 6, 96, 72, 1, 0),
     (2, 7, 7, 512, 128, 1, 1),
-    (1, 16, 16, 256, 256, 1, 1),       # 16 units x 16: the most with 16 channels
-    (1, 17, 13, 256, 264, 1, 1),       # 20 units x 17: 32 channels in bf16
-    (4, 14, 14, 64, 264, 2, 1),        # 16 units x 17
+    (1, 16, 16, 256, 256, 1, 1),
+    (1, 17, 13, 256, 264, 1, 1),
+    (4, 14, 14, 64, 264, 2, 1),
     (2, 9, 10, 24, 136, 2, 2),
 ]
 
 
 @pytest.mark.parametrize("cached", [False, True])
 @pytest.mark.parametrize("bf16", [False, True])
-@pytest.mark.parametrize("case", SPLIT_CASES)
-def test_3x3_kernel_with_split_k(oracle, case, bf16, cached):
+@pytest.mark.parametrize("case", FEW_UNIT_CASES)
+def test_3x3_layers_of_few_units(oracle, case, bf16, cached):
     """Tolerance: both sides sum at least in fp32 (9 cin terms: below 1e-5 of the map); bf16 results are rounded, 2^-8 each."""
     n, H, W, cin, cout, s, p = case
-    print(f"[split 3x3] case={case} bf16={bf16} cached={cached}", flush=True)
+    print(f"[few-unit 3x3] case={case} bf16={bf16} cached={cached}", flush=True)
     rng = np.random.default_rng(sum(case) + 11)
     Ho, Wo = (H + 2 * p - 3) // s + 1, (W + 2 * p - 3) // s + 1
     x = rng.standard_normal((n, H, W, cin)).astype(np.float32)

@@ -402,13 +402,6 @@ def test_kernel_names_of_the_split_1x1_layers():
     assert binding.lib().dc_conv_kernel_name(404, C.create_string_buffer(160), 160) == -1
 
 
-def test_kernel_names_of_the_split_3x3_layers():
-    assert [binding.conv_kernel_name(410 + i) for i in range(3)] == [
-        "conv_split_kernel<float, 1>", "conv_split_kernel<__hip_bfloat16, 1>", "conv_split_kernel<__hip_bfloat16, 2>"]
-    for kid in (409, 413):
-        assert binding.lib().dc_conv_kernel_name(kid, C.create_string_buffer(160), 160) == -1
-
-
 def test_regions_of_a_single_layer_call_in_every_form():
     """Rectangles as arrays, lists, tensors or floats fill the C structures alike; what is no rectangle is refused."""
     want = [[1, 2, 3, 4], [5, 6, 7, 8]]
