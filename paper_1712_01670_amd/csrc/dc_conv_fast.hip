@@ -1552,7 +1552,7 @@ hipError_t pw_launch(int units, dim3 grid, size_t lds, hipStream_t st, const Con
 //   14.1, 14x14 256->1024 16 streams (1024) 9.4 against 11.1, but 14x14 1024->256 32 streams (512) 14.6 against 12.1.  fp32:
 //   only where K is deep (14x14 1024->512 32 streams, 1024 tiles: 75.7 against 81.1; 56x56 256->128, 6272 tiles: 96 against 79).
 int pw_units(const ConvLaunch& c, long n_units, int n_chunks, int forced) {
-    if (forced == 1 || forced == 2 || forced == 4 || forced == 8) return forced;
+    if (forced == 4 || forced == 8) return forced;
     const bool bf16 = c.dtype == DC_BF16;
     const long r32 = (c.Cout + 31) / 32, small_tiles = (n_units + 3) / 4 * ((c.Cout + 63) / 64);
     if (n_units * r32 <= 256) return 1;

@@ -644,14 +644,32 @@ def test_pointwise_kernel(oracle, case, pw_tile, bf16, cached):
         assert _rel_err(got[i], want) <= (2e-2 if bf16 else 1e-4), (case, i)
 
 
-# The kernel whose four wavefronts split K in pieces of 128 bytes: fewer pieces than wavefronts, a last piece that is not whole,
-# more than two pieces per wavefront, channels that end inside a 32-channel tile, a last workgroup with one unit of two.
+# The kernel whose four wavefronts split K in pieces of 128 bytes, which takes layers of few units: fewer pieces than wavefronts, a last
+# piece that is not whole, more than two pieces per wavefront, channels that end inside a 32-channel tile; from (14, 14, 256, 200) on
+# some with two units per workgroup, the last ones with one unit in the last.
 @pytest.mark.parametrize("cached", [False, True])
 @pytest.mark.parametrize("bf16", [False, True])
-@pytest.mark.parametrize("pw_tile", [1, 2], indirect=True)
-@pytest.mark.parametrize("case", PW_CASES + [(7, 7, 1096, 40, 1), (15, 13, 840, 8, 2), (8, 5, 192, 264, 1)])
-def test_pointwise_kernel_with_split_k(oracle, case, pw_tile, bf16, cached):
-    test_pointwise_kernel(oracle, case, pw_tile, bf16, cached)
+@pytest.mark.parametrize("case", PW_CASES + [(7, 7, 1096, 40, 1), (15, 13, 840, 8, 2), (8, 5, 192, 264, 1), (12, 12, 840, 328, 1), (9, 9, 40, 1000, 1)])
+def test_pointwise_kernel_with_split_k(oracle, case, bf16, cached):
+    test_pointwise_kernel(oracle, case, None, bf16, cached)
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+def test_tuning_values_of_3x3_layers_leave_1x1_layers_alone(bf16):
+    """Units per workgroup that the 1x1 kernel has no tile for are ignored: the same bits, whatever another layer is tuned to."""
+    gen = torch.Generator(DEV)
+    gen.manual_seed(4)
+    dt = torch.bfloat16 if bf16 else torch.float32
+    x = torch.randn((4, 56, 56, 256), generator=gen, device=DEV).to(dt)
+    w = torch.randn((256, 1, 1, 256), generator=gen, device=DEV).to(dt)
+    run = lambda: binding.dc_cached_conv_layer(_layer(256, 256, 1, 1, 0, True), x, w, None)
+    want = run()
+    for units in (1, 2, 3, 5, 18):
+        binding.dc_conv_tuning(units_per_workgroup=units)
+        try:
+            assert torch.equal(run(), want), units
+        finally:
+            binding.dc_conv_tuning()
 
 
 # 3x3 layers of few units: channels that end inside a tile, rows that are no whole chunks, windows without padding and with stride 2,
