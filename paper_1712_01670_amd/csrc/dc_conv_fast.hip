@@ -913,17 +913,23 @@ __global__ __launch_bounds__(WM * 128) void conv_pw_kernel(ConvParams P) {
 }
 
 constexpr int kPwSplit = 4;           // wavefronts that share a tile's K
-constexpr int kPwSplitId = 400;       // kernel ids: + 2 (units - 1) + bf16
+constexpr int kPwSplitId = 400;       // kernel ids: + units - 1
 
-// ---- 1x1 convolutions of few units and a deep K ---------------------------------------------------
-// With few (unit group, channel tile) pairs the ring above leaves most CUs idle and the others with a step of 0.4 us per 128
-// bytes of K (what one CU fetches, not how far ahead: eight stages instead of four change nothing).  Here the WK wavefronts of a workgroup split K among themselves and
-// each fetches the fragments of its part straight into registers, so every operand byte of the tile is loaded once, all
-// loads of a part are in flight together and nothing waits for another wavefront before the partial tiles are added
+// ---- fp32 1x1 convolutions of few units -----------------------------------------------------------
+// With few (unit group, channel tile) pairs the ring above leaves most CUs idle and the others with a serial walk over K, bound by
+// the fp32 MFMAs of a lone workgroup and by what one CU fetches.  Here the WK wavefronts of a workgroup split K among
+// themselves and each fetches the fragments of its part straight into registers, so every operand byte of the tile is loaded
+// once, all loads of a part are in flight together and nothing waits for another wavefront before the partial tiles are added
 // through LDS (in the order of the wavefronts).  Wavefront w takes the 128-byte pieces w, w + WK, ... of every row.
 // Channel order within a wavefront's blocks, strides, tails and tensors on a torus as in the kernel above.
-template <typename T, int U, int NB, int WK>
+// us a call between two events with the caches emptied before, ring -> this: 14x14 1024->256 one stream 31.7 -> 15.6, 28x28
+// 512->128 21.3 -> 13.0, 7x7 2048->512 53.0 -> 20.3, 56x56 64->256 12.4 -> 13.1.  Error of the sums against 64 bits, same
+// layers: 3.99e-7 -> 2.06e-7, 2.84e-7 -> 1.51e-7, 5.76e-7 -> 2.90e-7, 1.03e-7 -> 0.79e-7.
+// (In bf16, whose MFMAs are sixteen times as fast, the ring's workgroups wait for memory alone and whole stacks gained nothing:
+// Darknet-19 416x416 on one stream took 1577 us a clip of ten frames with this kernel and 1467 without.)
+template <int U, int NB, int WK>
 __global__ __launch_bounds__(WK * 64) void conv_pw_split_kernel(ConvParams P) {
+    typedef float T;
     typedef Frag<T> F;
     typedef typename F::vec vec;
     constexpr int ES = (int)sizeof(T), RB = 128, GPC = 2, NT = NB * 16;
@@ -1058,17 +1064,8 @@ __global__ __launch_bounds__(WK * 64) void conv_pw_split_kernel(ConvParams P) {
         if (P.bias) { v0 += *reinterpret_cast<const floatx4*>(P.bias + co); v1 += *reinterpret_cast<const floatx4*>(P.bias + co + 4); }
         if (P.relu) { activate4(v0, P.relu); activate4(v1, P.relu); }
         T* const px = reinterpret_cast<T*>(P.out) + at + co;
-        if constexpr (sizeof(T) == 2) {
-            uintx4 w4;
-            w4[0] = (uint32_t)F::bits(v0[0]) | ((uint32_t)F::bits(v0[1]) << 16);
-            w4[1] = (uint32_t)F::bits(v0[2]) | ((uint32_t)F::bits(v0[3]) << 16);
-            w4[2] = (uint32_t)F::bits(v1[0]) | ((uint32_t)F::bits(v1[1]) << 16);
-            w4[3] = (uint32_t)F::bits(v1[2]) | ((uint32_t)F::bits(v1[3]) << 16);
-            *reinterpret_cast<uintx4*>(px) = w4;
-        } else {
-            F::store4(px, v0);
-            F::store4(px + 4, v1);
-        }
+        F::store4(px, v0);
+        F::store4(px + 4, v1);
     }
 }
 
@@ -1444,7 +1441,7 @@ FastChoice choose_fast(const ConvLaunch& c, long n_units, long n_cap, size_t scr
 
 // Ids 64.. name the instantiations of this file: 64 + ((bf16 * 2 + kci) * 8 + UPW - 1), 96.. the first-layer kernel,
 // 110.. the wide arrangement.
-bool conv_kernel_built(int id) { return id >= kPwSplitId ? id < kPwSplitId + 4 : id >= 132 && (id - 132) / 8 < kNumGeom && fast_built(5, true, (id - 132) / 8, 0, (id - 132) % 8 + 1); }
+bool conv_kernel_built(int id) { return id >= kPwSplitId ? id < kPwSplitId + 2 : id >= 132 && (id - 132) / 8 < kNumGeom && fast_built(5, true, (id - 132) / 8, 0, (id - 132) % 8 + 1); }
 void conv_fast_kernel_name(int id, char* buf, size_t n) {
     if (id == 126) { snprintf(buf, n, "conv_regw_kernel<2, 2, false>"); return; }
     if (id == 130) { snprintf(buf, n, "conv_regw_kernel<2, 2, true>"); return; }      // tensors on a torus
@@ -1454,7 +1451,7 @@ void conv_fast_kernel_name(int id, char* buf, size_t n) {
         return;
     }
     if (id >= kPwSplitId) {
-        snprintf(buf, n, "conv_pw_split_kernel<%s, %d, 2, %d>", (id - kPwSplitId) % 2 ? "__hip_bfloat16" : "float", (id - kPwSplitId) / 2 + 1, kPwSplit);
+        snprintf(buf, n, "conv_pw_split_kernel<%d, 2, %d>", id - kPwSplitId + 1, kPwSplit);
         return;
     }
     if (id >= 132) {  // 132 + arrangement * 8 + UPW - 1: 5x5 layers
@@ -1533,31 +1530,34 @@ hipError_t pw_launch_n(dim3 grid, size_t lds, hipStream_t st, const ConvParams& 
     hipLaunchKernelGGL((conv_pw_kernel<T, WM>), grid, dim3(WM * 128), lds, st, P);
     return hipGetLastError();
 }
-// units: 1, 2 (split K, 32 channels), 4 (64 channels), 8 (128 channels)
+// units: 1, 2 (fp32: split K, 32 channels), 4 (64 channels), 8 (128 channels)
 template <typename T>
 hipError_t pw_launch(int units, dim3 grid, size_t lds, hipStream_t st, const ConvParams& P) {
     if (units == 8) return pw_launch_n<T, 4>(grid, lds, st, P);
     if (units == 4) return pw_launch_n<T, 2>(grid, lds, st, P);
-    if (units == 2) hipLaunchKernelGGL((conv_pw_split_kernel<T, 2, 2, kPwSplit>), grid, dim3(kPwSplit * 64), 0, st, P);
-    else hipLaunchKernelGGL((conv_pw_split_kernel<T, 1, 2, kPwSplit>), grid, dim3(kPwSplit * 64), 0, st, P);
-    return hipGetLastError();
+    if constexpr (sizeof(T) == 4) {
+        if (units == 2) hipLaunchKernelGGL((conv_pw_split_kernel<2, 2, kPwSplit>), grid, dim3(kPwSplit * 64), 0, st, P);
+        else hipLaunchKernelGGL((conv_pw_split_kernel<1, 2, kPwSplit>), grid, dim3(kPwSplit * 64), 0, st, P);
+        return hipGetLastError();
+    }
+    return hipErrorInvalidValue;
 }
-// Units per workgroup of a 1x1 layer.  us per launch, one launch after another with the caches emptied in between, bf16:
-//   one unit, K split (t1 = workgroups that it makes): 14x14 1024->256 one stream 6.2 (four units: 9.1, 11.4 with the barrier
-//   that ended the prefetch), 7x7 2048->512 one to four streams 8.4 - 8.7 (13.5), 28x28 512->128 4.9 (6.7); with 512 workgroups it
-//   is even (14x14 1024->256 four streams 9.1, 9.0) and two units take 7.7; with 1024 the ring wins (13.8 against 9.1).  fp32 is
-//   bound by its MFMAs there, so four wavefronts on a tile pay up to 512 workgroups of two units (14x14 1024->256 eight streams
-//   19.4 against 27.1).
-//   128 x 128 tiles need three workgroups of the smaller ones per CU: 28x28 512->128 32 streams (784 small tiles) 11.4 against
-//   14.1, 14x14 256->1024 16 streams (1024) 9.4 against 11.1, but 14x14 1024->256 32 streams (512) 14.6 against 12.1.  fp32:
-//   only where K is deep (14x14 1024->512 32 streams, 1024 tiles: 75.7 against 81.1; 56x56 256->128, 6272 tiles: 96 against 79).
-int pw_units(const ConvLaunch& c, long n_units, int n_chunks, int forced) {
+// Units per workgroup of a 1x1 layer.
+//   fp32: the kernel that splits K adds in another order than the ring, so the length that decides between them is the longest
+//   the list can be, not the one an earlier frame had: a frame's bits do not depend on counters that may have arrived or not,
+//   and the grid, which covers that length, has at most 512 workgroups.  One unit per workgroup while that makes one per CU
+//   (us as above, one unit, two, ring: 14x14 1024->256 one stream 15.6, 18.2, 31.7), two up to two workgroups per CU (13x13
+//   1024->512 two streams 21.0, 18.8, 32.0); four wavefronts per tile hide each other's MFMAs there.
+//   128 x 128 tiles need every CU to hold several workgroups; 4096 of the smaller ones (measured in bf16: 2 % of a ResNet-50
+//   frame on 64 streams).  fp32: only where K is deep as well (us, 64 x 64 -> 128 x 128: 14x14 1024->2048 32 streams 312 -> 296,
+//   but 56x56 256->128 92 -> 107, 64->256 64 streams 108 -> 118).
+int pw_units(const ConvLaunch& c, long n_cap, long n_units, int n_chunks, int forced) {
     if (forced == 4 || forced == 8) return forced;
     const bool bf16 = c.dtype == DC_BF16;
     const long r32 = (c.Cout + 31) / 32, small_tiles = (n_units + 3) / 4 * ((c.Cout + 63) / 64);
-    if (n_units * r32 <= 256) return 1;
-    if ((n_units + 1) / 2 * r32 <= (bf16 ? 256 : 512)) return 2;
-    return c.Cout >= 128 && (bf16 ? small_tiles >= 768 : small_tiles >= 1024 && n_chunks >= 32) ? 8 : 4;
+    if (!bf16 && n_cap * r32 <= 256) return 1;
+    if (!bf16 && (n_cap + 1) / 2 * r32 <= 512) return 2;
+    return small_tiles >= 4096 && c.Cout >= 128 && (bf16 || n_chunks >= 32) ? 8 : 4;
 }
 bool launch_conv_fast(const ConvLaunch& c, long n_cap, long n_units, hipStream_t st, hipError_t* err) {
     // below, n_units is the length the launch is tuned for and n_cap the length it must cover; they differ only
@@ -1609,7 +1609,7 @@ bool launch_conv_fast(const ConvLaunch& c, long n_cap, long n_units, hipStream_t
         constexpr bool pw_enabled = true;
         const int units_y = (c.Hout + 3) / 4, units_x = (c.Wout + 3) / 4;
         const int kc = (int)(128 / esz), n_chunks = (c.Cin + kc - 1) / kc;
-        const int g_units = pw_units(c, n_units, n_chunks, g_tune[1]), nt = g_units == 8 ? 128 : g_units == 4 ? 64 : 32;
+        const int g_units = pw_units(c, n_cap, n_units, n_chunks, g_tune[1]), nt = g_units == 8 ? 128 : g_units == 4 ? 64 : 32;
         const int threads = g_units >= 4 ? g_units * 64 : kPwSplit * 64;
         const long R = (c.Cout + nt - 1) / nt, tiles = (n_cap + g_units - 1) / g_units * R;
         if (pw_enabled && (double)c.n_streams * c.Hout * c.Wout * c.Cout < 2147483648.0 &&
@@ -1634,7 +1634,7 @@ bool launch_conv_fast(const ConvLaunch& c, long n_cap, long n_units, hipStream_t
             const int stages = n_chunks < 4 ? n_chunks : 4;
             const size_t lds = kHeaderBytes + (size_t)stages * (size_t)(g_units * 4096);      // (of the kernels with a ring)
             const int bf16 = c.dtype == DC_BF16 ? 1 : 0;
-            if (c.kernel_id) *c.kernel_id = (g_units == 8 ? 127 : g_units == 4 ? 108 : kPwSplitId + 2 * (g_units - 1)) + bf16;
+            if (c.kernel_id) *c.kernel_id = (g_units == 8 ? 127 : g_units == 4 ? 108 : kPwSplitId + g_units - 1) + (g_units >= 4 ? bf16 : 0);
             const dim3 grid((unsigned)(8 * P.tiles_per_xcd));
             *err = bf16 ? pw_launch<__hip_bfloat16>(g_units, grid, lds, st, P) : pw_launch<float>(g_units, grid, lds, st, P);
             return true;

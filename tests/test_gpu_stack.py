@@ -1310,7 +1310,8 @@ def test_two_threads_with_a_stack_each():
 
 # Counters of earlier frames tune the launches of a frame planned on the GPU, and they are there or not as it happens.  Some rules
 # that follow them change the order of sums (a split K, the channel chunk); these layers keep to one order over the lengths here.
-_HINTED = {"3x3": [(64, 3, 1, 1), (32, 3, 1, 1), (64, 3, 1, 1)]}      # [(cout, k, s, p)]
+_HINTED = {"3x3": [(64, 3, 1, 1), (32, 3, 1, 1), (64, 3, 1, 1)],      # [(cout, k, s, p)]
+           "1x1": [(64, 3, 1, 1), (256, 1, 1, 0), (128, 1, 1, 0), (512, 1, 1, 0), (64, 1, 1, 0)]}
 
 
 @pytest.mark.parametrize("bf16", [False, True])
@@ -1347,3 +1348,20 @@ def test_outputs_do_not_depend_on_the_counters_of_earlier_frames(name, bf16):
         for t in range(T):
             for i in range(len(layers) + 1):
                 assert torch.equal(clip[t][i], clips[0][t][i]), (name, t, i)
+
+
+@pytest.mark.parametrize("cout,kernel", [(32, "conv_pw_split_kernel<1, 2, 4>"), (40, "conv_pw_split_kernel<2, 2, 4>"),
+                                         (128, "conv_pw_split_kernel<2, 2, 4>"), (136, "conv_pw_kernel<float, 2>")])
+def test_kernel_of_a_1x1_layer_follows_the_size_of_its_map(cout, kernel):
+    """256 units: at most 256 tiles of one unit x 32 channels, at most 512 of two, or the ring, in full frames and in quiet ones."""
+    print(f"[1x1 rule] cout={cout}", flush=True)
+    layers = [dict(type=synth.CONV, k=1, s=1, p=0, cin=3, cout=cout, relu=1, in0=0, in1=-1)]
+    ws, bs = synth.he_weights(layers, 5, bias_scale=0.05, input_shape=(64, 64, 3))
+    frame = torch.from_numpy(np.random.default_rng(1).integers(0, 256, (1, 64, 64, 3)).astype(np.uint8)).to(DEV)
+    for dtype, want in ((binding.DC_F32, kernel), (binding.DC_BF16, "conv_pw_kernel<__hip_bfloat16, 2>")):
+        runner = binding.StackRunner(layers, ws, bs, 1, 64, 64, 3, block=8, radius=8, dtype=dtype, expiry=4, device_plan=True, exact_masks=True)
+        for t in range(4):
+            runner.step(frame)
+            torch.cuda.synchronize()
+            assert runner.last_full == (t == 0)
+            assert binding.conv_kernel_name(runner.layer_stats()["kernel_id"][0]) == want, t
