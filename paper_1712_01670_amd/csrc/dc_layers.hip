@@ -377,28 +377,52 @@ __device__ __forceinline__ void quad_transpose(V (&v)[4], int lane) {
     quad_swap<0x4e>(v[0], v[2], lane & 2);        // lanes 2 apart
     quad_swap<0x4e>(v[1], v[3], lane & 2);
 }
+// The same across the four rows of 16 lanes: vector t of a lane in row q becomes vector q of its lane in row t.
+template <bool FAR, typename V>
+__device__ __forceinline__ void row_swap(V& lo, V& hi) {      // rows 1 (FAR: 2) apart: lo's upper ones and hi's lower ones change places
+    uintx4 l = __builtin_bit_cast(uintx4, lo), h = __builtin_bit_cast(uintx4, hi);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const auto r = FAR ? __builtin_amdgcn_permlane32_swap(l[e], h[e], false, false) : __builtin_amdgcn_permlane16_swap(l[e], h[e], false, false);
+        l[e] = r[0];
+        h[e] = r[1];
+    }
+    lo = __builtin_bit_cast(V, l);
+    hi = __builtin_bit_cast(V, h);
+}
+template <typename V>
+__device__ __forceinline__ void row_transpose(V (&v)[4]) {
+    row_swap<false>(v[0], v[1]);
+    row_swap<false>(v[2], v[3]);
+    row_swap<true>(v[0], v[2]);
+    row_swap<true>(v[1], v[3]);
+}
 
-// The same GEMM for long rows.  Loaded as a fragment, a row per lane, 16 neighbouring lanes ask for 16 bytes of 16 rows: a look-up
-// in the CU's cache for every 16 bytes, and 16 bytes per clock is what a CU took in (asking further ahead changed nothing).
-// Here four lanes fetch 64 bytes of a row together, for four rows in turn, and exchange the vectors within the quad.  The
-// wavefronts deal the 256-byte chunks of K; K is summed in sixteen parts as above, two of them by each of eight wavefronts
-// where the registers hold no more.
-// us per call, the kernel above -> this: bf16 9216 -> 4096 64 streams 43.1 -> 24.7 (34 bytes a clock into a CU), 32 streams 26.9
-// -> 17.0, 16 streams 19.2 -> 14.2 (75 MB of weights: 14), 4096 -> 1000 64 streams 19.8 -> 11.3; fp32, whose MFMAs and
-// exchanges now take turns, 9216 -> 4096 64 streams 95.4 -> 80.5, 16 streams 41.3 -> 34.7.  Error of the fp32 sums against 64 bits 1.15e-7
-// -> 1.06e-7 (9216), 7.45e-8 -> 7.40e-8 (2048).
-constexpr int kFcParts = 16;                      // parts of K, summed apart
-template <typename T, int NB, int WAVES>
-__global__ __launch_bounds__(WAVES * 64) void fc_quad_kernel(const T* __restrict__ x, const T* __restrict__ w,
-                                                             const float* __restrict__ bias, T* __restrict__ out,
-                                                             int n_streams, size_t K, int cout, int relu) {
+// The same GEMM for long rows.  Loaded as a fragment, a row per lane, 16 neighbouring lanes ask for 16 bytes of 16 rows: a
+// look-up in the CU's cache for every 16 bytes, and 16 bytes per clock is what a CU took in (asking further ahead changed nothing).
+// Here four lanes fetch 64 bytes of a row together, for four rows in turn, and exchange the vectors within the quad.  A wavefront
+// takes 256 bytes of K at a time.
+// bf16: a second exchange, between the rows of 16 lanes, puts every vector where the kernel above has it.  The chunk is then the
+// 128-byte chunks of two wavefronts above, their sums stay apart, and the outputs are the same bit for bit.  us per call, the
+// kernel above -> this (-> with the sums of the four vectors as they come, other bits in the last place): 9216 -> 4096 64 streams
+// 43.0 -> 28.6 (25.3), 4096 -> 1000 64 streams 19.9 -> 13.3 (11.5), 16 streams 9.3 -> 6.9 (5.6), 2048 -> 512 32 streams 7.4 -> 5.7 (4.6).
+// fp32, whose MFMAs and exchanges take turns, would lose to the second exchange what the first one gains (9216 -> 4096 64 streams
+// 94.0 -> 91.2): a part of K is every sixteenth chunk there, and the vectors are summed as they come.  9216 -> 4096 64 streams
+// 94.0 -> 80.5, 4096 -> 1000 16 streams 16.6 -> 12.1, 2048 -> 512 32 streams 13.1 -> 10.9.  Its error against 64 bits over K from 1536 to
+// 9216 and 9 to 64 streams is 0.93 to 1.03 of the kernel's above (1.15e-7 -> 1.06e-7 for 9216, 7.5e-8 for 2048).
+template <typename T, int NB>
+constexpr int fc_quad_waves() { return sizeof(T) == 2 || NB > 1 ? kFcWaves / 2 : kFcWaves; }      // (fp32: as many as its registers allow)
+template <typename T, int NB>
+__global__ __launch_bounds__((fc_quad_waves<T, NB>()) * 64) void fc_quad_kernel(const T* __restrict__ x, const T* __restrict__ w,
+                                                                                const float* __restrict__ bias, T* __restrict__ out,
+                                                                                int n_streams, size_t K, int cout, int relu) {
     typedef Frag<T> F;
     typedef typename F::vec vec;
-    constexpr int VE = F::VE;
+    constexpr int VE = F::VE, WAVES = fc_quad_waves<T, NB>(), PH = kFcWaves / WAVES;      // PH: parts of a wavefront
     constexpr int CH = 16 * VE;                   // elements of a chunk: four K groups of four vectors
-    constexpr int PH = kFcParts / WAVES;          // parts of a wavefront, by the parity of the round
-    static_assert(PH == 1 || PH == 2, "");
-    __shared__ float red[kFcParts][NB * 256];
+    constexpr bool SAME = sizeof(T) == 2;         // the order of the kernel above
+    constexpr int AHEAD = SAME && NB == 1 ? 2 : 1;        // chunks of weights on their way behind the one in work
+    __shared__ float red[kFcWaves][NB * 256];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, q = lane >> 4;
     const int o0 = blockIdx.x * 16, s0 = blockIdx.y * (NB * 16);
@@ -424,22 +448,26 @@ __global__ __launch_bounds__(WAVES * 64) void fc_quad_kernel(const T* __restrict
 #pragma unroll
         for (int t = 0; t < 4; ++t) v[t] = *reinterpret_cast<const vec*>(row[t] + at);
     };
-    auto arrange = [&](vec (&v)[4], size_t k) {   // vector t of a lane: elements k + (4 q + t) VE of row l16, zeros past the end
+    // vector t of a lane: elements k + (4 t + q) VE (fp32: k + (4 q + t) VE) of row l16, zeros past the end
+    auto arrange = [&](vec (&v)[4], size_t k) {
         quad_transpose(v, lane);
+        if constexpr (SAME) row_transpose(v);
         if (k + CH > K)
 #pragma unroll
             for (int t = 0; t < 4; ++t)
-                if (k + (size_t)(q * 4 + t) * VE >= K) v[t] = vec{};
+                if (k + (size_t)(SAME ? t * 4 + q : q * 4 + t) * VE >= K) v[t] = vec{};
     };
-    // the chunk's inputs (from L2) are loaded when it is multiplied, its weights (from memory) one chunk ahead
+    // the chunk's inputs (from L2) are loaded when it is multiplied, its weights (from memory) before
     constexpr size_t kStep = (size_t)WAVES * CH;
-    vec wa[4], wb[4];
-    if ((size_t)wave * CH < K) fetch(wa, wrow, (size_t)wave * CH);
-    auto round = [&](floatx4 (&sums)[NB], vec (&wc)[4], vec (&wn)[4], size_t k) {
+    vec wv[AHEAD + 1][4];
+#pragma unroll
+    for (int d = 0; d < AHEAD; ++d)
+        if (wave * CH + d * kStep < K) fetch(wv[d], wrow, wave * CH + d * kStep);
+    auto round = [&](floatx4 (&sums)[NB], vec (&wc)[4], vec (&wn)[4], size_t k) {      // sums: of fp32
         vec xv[NB][4];
 #pragma unroll
         for (int j = 0; j < NB; ++j) fetch(xv[j], xrow[j], k);
-        if (k + kStep < K) fetch(wn, wrow, k + kStep);
+        if (k + AHEAD * kStep < K) fetch(wn, wrow, k + AHEAD * kStep);
         arrange(wc, k);
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
@@ -451,28 +479,37 @@ __global__ __launch_bounds__(WAVES * 64) void fc_quad_kernel(const T* __restrict
             for (int e = 0; e < F::NE; ++e)
 #pragma unroll
                 for (int t = 0; t < 4; ++t) F::mma1(wc[t], xv[j][t], part[t], e);
-            sums[j] += (part[0] + part[1]) + (part[2] + part[3]);
+            if constexpr (SAME) {
+                acc[0][j] += part[0] + part[1];
+                acc[1][j] += part[2] + part[3];
+            } else {
+                sums[j] += (part[0] + part[1]) + (part[2] + part[3]);
+            }
         }
     };
-    for (size_t k = (size_t)wave * CH; k < K; k += 2 * kStep) {
-        round(acc[0], wa, wb, k);
+    for (size_t k = (size_t)wave * CH; k < K; k += (AHEAD + 1) * kStep) {
+        round(acc[0], wv[0], wv[AHEAD], k);
         if (k + kStep >= K) break;
-        round(acc[PH - 1], wb, wa, k + kStep);
+        round(acc[PH - 1], wv[1], wv[0], k + kStep);
+        if constexpr (AHEAD == 2) {
+            if (k + 2 * kStep >= K) break;
+            round(acc[0], wv[2], wv[1], k + 2 * kStep);
+        }
     }
 #pragma unroll
     for (int h = 0; h < PH; ++h)
 #pragma unroll
         for (int j = 0; j < NB; ++j)              // register r of a lane: neuron 4 q + r, stream 16 j + l16
-            *reinterpret_cast<floatx4*>(&red[h * WAVES + wave][(j * 16 + l16) * 16 + q * 4]) = acc[h][j];
+            *reinterpret_cast<floatx4*>(&red[SAME ? 2 * wave + h : h * WAVES + wave][(j * 16 + l16) * 16 + q * 4]) = acc[h][j];
     __syncthreads();
     for (int i = tid; i < NB * 256; i += WAVES * 64) {
         const int o = o0 + (i & 15), s = s0 + (i >> 4);
         if (o >= cout || s >= n_streams) continue;
-        float sum[kFcParts];
+        float sum[kFcWaves];
 #pragma unroll
-        for (int p = 0; p < kFcParts; ++p) sum[p] = red[p][i];
+        for (int p = 0; p < kFcWaves; ++p) sum[p] = red[p][i];
 #pragma unroll
-        for (int d = kFcParts / 2; d >= 1; d >>= 1)
+        for (int d = kFcWaves / 2; d >= 1; d >>= 1)
 #pragma unroll
             for (int p = 0; p < d; ++p) sum[p] += sum[p + d];
         float v = sum[0];
@@ -1168,17 +1205,16 @@ hipError_t fc_launch(const void* x, const void* w, const float* bias, void* out,
     return hipGetLastError();
 }
 
-// Rows of 1536 elements on are worth the exchanges (us, fragments as loaded -> quads): bf16 1536 -> 100 64 streams 8.8 -> 6.3,
-// 16 streams 4.5 -> 3.3; fp32 16.3 -> 14.6, 7.3 -> 5.3; below, bf16 1032 -> 72 24 streams 3.3 -> 4.0, fp32 1152 -> 100 33
-// streams 11.0 -> 11.9.  Few streams wait for the weights alone (bf16 4096 -> 4096 three streams 8.5 -> 9.0,
-// 2048 -> 256 five 4.4 -> 3.5; fp32 9216 -> 4096 five streams 31.6 -> 32.9, nine 33.8 -> 33.7).
+// Rows of 1536 elements on are worth the exchanges (us, fragments as loaded -> quads): bf16 1536 -> 100 64 streams 8.7 -> 7.0,
+// 16 streams 4.5 -> 3.7; fp32 16.3 -> 14.6, 7.2 -> 5.3; below (measured with one exchange), bf16 1032 -> 72 24 streams 3.3 -> 4.0, fp32
+// 1152 -> 100 33 streams 11.0 -> 11.9.  Few streams wait for the weights alone: bf16 9216 -> 4096 five streams 14.6 -> 15.7, nine 16.1 -> 16.0;
+// fp32 five 31.6 -> 32.9, nine 33.7 -> 33.7.
 template <typename T, int NB>
 hipError_t fc_mfma_launch(const void* x, const void* w, const float* bias, void* out, int n_streams, size_t K, int cout, int relu,
                           hipStream_t st) {
     const dim3 grid((unsigned)((cout + 15) / 16), (unsigned)((n_streams + NB * 16 - 1) / (NB * 16)));
-    constexpr int WAVES = NB == 4 || (NB == 2 && sizeof(T) == 4) ? 8 : 16;      // as many as their registers allow
-    if (K >= 1536 && n_streams > (sizeof(T) == 2 ? 4 : 8))
-        hipLaunchKernelGGL((fc_quad_kernel<T, NB, WAVES>), grid, dim3(WAVES * 64), 0, st, (const T*)x, (const T*)w, bias, (T*)out, n_streams,
+    if (K >= 1536 && n_streams > 8)
+        hipLaunchKernelGGL((fc_quad_kernel<T, NB>), grid, dim3(fc_quad_waves<T, NB>() * 64), 0, st, (const T*)x, (const T*)w, bias, (T*)out, n_streams,
                            K, cout, relu);
     else
         hipLaunchKernelGGL((fc_mfma_kernel<T, NB>), grid, dim3(kFcWaves * 64), 0, st, (const T*)x, (const T*)w, bias, (T*)out, n_streams, K,

@@ -424,7 +424,7 @@ def test_fully_connected_layer_on_the_matrix_cores(oracle, n, K, cout, bf16):
 
 
 @pytest.mark.parametrize("bf16", [False, True])
-@pytest.mark.parametrize("n", [7, 20, 64])
+@pytest.mark.parametrize("n", [9, 20, 64])
 def test_fully_connected_rounds_and_the_rows_end(n, bf16):
     """One to five rounds of the wavefronts, ending on a chunk, a vector short of it and a vector behind it.  Whole numbers of
     few bits, so every sum is exact.  Vectors behind a row's end repeat its last one and must not count: an infinity there
@@ -432,7 +432,7 @@ def test_fully_connected_rounds_and_the_rows_end(n, bf16):
     print(f"[fc rounds] n={n} bf16={bf16}", flush=True)
     rng = np.random.default_rng(n)
     ve, cout = (8 if bf16 else 4), 18
-    step = (8 if n > 32 or (n > 16 and not bf16) else 16) * 16 * ve
+    step = (8 if bf16 or n > 16 else 16) * 16 * ve
     for rounds in range(1, 6):
         for K in (rounds * step - ve, rounds * step, rounds * step + ve, (rounds - 1) * step + 16 * ve):
             x = rng.integers(-1, 2, (n, 1, 1, K)).astype(np.float32)
@@ -445,6 +445,20 @@ def test_fully_connected_rounds_and_the_rows_end(n, bf16):
             want[n // 2] = np.where(w[:, -1] > 0, np.inf, -np.inf)
             got = _to_np(binding.dc_fc_layer(_to_dev(x, bf16), _to_dev(w, bf16), None, False)).reshape(n, cout)
             assert np.array_equal(got, want), K
+
+
+@pytest.mark.parametrize("K", [1536, 1544, 2040, 2176, 4096, 9208, 9216])
+def test_bf16_fully_connected_outputs_do_not_depend_on_the_number_of_streams(K):
+    """Four streams take another kernel than nine and more, whose wavefronts fetch K in other pieces: the sums are the same bit for bit."""
+    print(f"[fc order] K={K}", flush=True)
+    gen = torch.Generator(DEV)
+    gen.manual_seed(K)
+    x = torch.randn((70, 1, 1, K), generator=gen, device=DEV).bfloat16()
+    w = (torch.randn((37, K), generator=gen, device=DEV) * K ** -0.5).bfloat16()
+    b = torch.randn(37, generator=gen, device=DEV) * 0.1
+    want = torch.cat([binding.dc_fc_layer(x[s:s + 4].contiguous(), w, b, False) for s in range(0, 68, 4)])
+    for n in (9, 16, 17, 32, 33, 64, 68):
+        assert torch.equal(binding.dc_fc_layer(x[:n].contiguous(), w, b, False), want[:n]), n
 
 
 @pytest.mark.parametrize("bf16", [False, True])
