@@ -581,7 +581,8 @@ def test_5x5_sums_are_rounded_once_per_stage(cin, cout, tuning):
 
 @pytest.mark.parametrize("bf16", [False, True])
 @pytest.mark.parametrize("H,W", [(4, 4), (2, 3), (9, 4), (5, 1), (1, 7), (4, 13)])
-@pytest.mark.parametrize("cin,cout,k,tuning", [(0, 64, 3, None), (64, 64, 3, None), (64, 64, 3, (3, 4, 1, 1)), (64, 128, 1, None), (128, 128, 5, None)])
+@pytest.mark.parametrize("cin,cout,k,tuning", [(0, 64, 3, None), (64, 64, 3, None), (64, 64, 3, (3, 4, 1, 1)), (64, 128, 1, None), (128, 128, 5, None),
+                                               (64, 64, 3, (0, 2, 1, 0)), (64, 64, 3, (0, 1, 2, 0)), (64, 128, 1, (-1, 4, -1, -1)), (64, 128, 1, (-1, 8, -1, -1))])
 def test_conv_on_maps_of_one_unit_column(oracle, cin, cout, k, tuning, H, W, bf16):
     """Maps of a single 4x4 unit, unit column or unit row, several streams, in full: every pixel of every stream is written."""
     cin = cin or (8 if bf16 else 4)                   # (a pixel of one 16-byte vector: the first-layer kernel)
@@ -733,22 +734,29 @@ def test_3x3_layers_of_few_units(oracle, case, bf16, cached):
 
 
 @pytest.mark.parametrize("bf16", [False, True])
-@pytest.mark.parametrize("case", [(20, 24, 4, 32, 3, 1, 1), (20, 24, 64, 64, 3, 1, 1), (20, 24, 64, 128, 1, 1, 0), (21, 25, 32, 48, 5, 2, 2),
-                                  (21, 25, 6, 10, 3, 1, 1), (12, 12, 512, 64, 3, 1, 1)])
-def test_leaky_relu_in_every_conv_kernel(oracle, case, bf16):
-    """relu = 2 (leaky, slope 0.1) in the epilogue of the first-layer, 3x3, 1x1, general, element-load and split-K
-    kernels."""
+@pytest.mark.parametrize("case,tuning", [((20, 24, 4, 32, 3, 1, 1), None), ((20, 24, 64, 64, 3, 1, 1), None), ((20, 24, 64, 128, 1, 1, 0), None),
+                                         ((21, 25, 32, 48, 5, 2, 2), None), ((21, 25, 6, 10, 3, 1, 1), None), ((12, 12, 512, 64, 3, 1, 1), None),
+                                         ((20, 24, 64, 64, 3, 1, 1), (0, 2, 1, 0)), ((12, 12, 512, 64, 3, 1, 1), (0, 2, 4, 0)),
+                                         ((20, 24, 64, 128, 1, 1, 0), (-1, 4, -1, -1)), ((20, 24, 64, 128, 1, 1, 0), (-1, 8, -1, -1))])
+def test_leaky_relu_in_every_conv_kernel(oracle, case, tuning, bf16):
+    """relu = 2 (leaky, slope 0.1) in the epilogue of the first-layer, 3x3, 1x1 (fp32: split K as well), general, element-load and
+    split-K kernels; the tuned cases name the 3x3 kernel, its split of K with the reduction, and the 1x1 ring's two tiles."""
     H, W, cin, cout, k, s, p = case
     if bf16 and cin == 4:
         cin = 8
-    print(f"[leaky] case={case} bf16={bf16}", flush=True)
+    print(f"[leaky] case={case} tuning={tuning} bf16={bf16}", flush=True)
     rng = np.random.default_rng(sum(case) + 1)
     x = rng.standard_normal((2, H, W, cin)).astype(np.float32)
     w = (rng.standard_normal((cout, k, k, cin)) * np.sqrt(2.0 / (cin * k * k))).astype(np.float32)
     b = (rng.standard_normal(cout) * 0.1).astype(np.float32)
     if bf16:
         x, w = oracle.round_bf16(x), oracle.round_bf16(w)
-    got = _to_np(binding.dc_cached_conv_layer(_layer(cin, cout, k, s, p, 2), _to_dev(x, bf16), _to_dev(w, bf16), torch.from_numpy(b).to(DEV)))
+    if tuning:
+        binding.dc_conv_tuning(*tuning)
+    try:
+        got = _to_np(binding.dc_cached_conv_layer(_layer(cin, cout, k, s, p, 2), _to_dev(x, bf16), _to_dev(w, bf16), torch.from_numpy(b).to(DEV)))
+    finally:
+        binding.dc_conv_tuning()
     for i in range(2):
         want = oracle.conv_cached(x[i], w, b, k, s, p, 2, bf16=bf16)
         assert (want < 0).any()
@@ -901,7 +909,7 @@ def test_fc_few_fp32_streams_and_neurons(n, K, cout):
 
 
 # Single-layer calls take turns on two workspaces; the plan travels with the copies in one launch while those take at most 32
-# rectangles of whole 16-byte vectors.  Calls one behind the other, and from two threads on streams of their own, against calls that
+# rectangles of whole 16-byte vectors.  Calls one behind the other, and from three threads on streams of their own, against calls that
 # are waited for: 32 rectangles, 33, channel runs that are no whole vectors, no rectangle at all.
 @pytest.mark.parametrize("per_stream,cout,bf16", [(8, 64, True), (8, 64, False), (11, 64, True), (8, 20, True), (0, 64, True)])
 def test_single_layer_calls_without_a_wait_in_between(per_stream, cout, bf16):

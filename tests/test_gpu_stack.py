@@ -997,7 +997,18 @@ def test_replayed_frames_are_the_launched_ones(net, size, kw):
     """Frames replayed from recorded graphs, frames launched kernel by kernel and frames without a handle: every tensor bit
     for bit, several replays of every graph, full frames and cached ones, other work of the program and synchronisations in
     between.  (The launch shapes are fixed: units per workgroup and no split of K.)"""
-    print(f"[replay] {net} {size} {kw}", flush=True)
+    _check_replays(net, size, kw, 4)
+
+
+@pytest.mark.parametrize("net,size,kw", [("darknet19", 96, dict(torus=True)), ("darknet19", 224, {})])
+def test_replayed_frames_with_1x1_layers_that_split_k(net, size, kw):
+    """The same with two units per workgroup: no tile of the 1x1 layers, which choose their kernel by the size of their maps."""
+    kernels = {binding.conv_kernel_name(k) for k in _check_replays(net, size, kw, 2) if k >= 0}
+    assert any(k.startswith("conv_pw_split_kernel") for k in kernels), kernels
+
+
+def _check_replays(net, size, kw, units):
+    print(f"[replay] {net} {size} {kw} {units}", flush=True)
     layers = synth.resolve_global_pooling(synth.vgg16()[:18] if net == "vgg16" else synth.darknet19()[:19], size, size, 3)
     ws, bs = synth.he_weights(layers, 3, bias_scale=0.05, input_shape=(size, size, 3))
     T = 10
@@ -1005,7 +1016,7 @@ def test_replayed_frames_are_the_launched_ones(net, size, kw):
     frames = [video[t:t + 1].contiguous() for t in range(T)]
     torch.cuda.synchronize()
     order = (list(range(T)) + [None]) * 4 + [0, 1, 2, None, 0, None] + (list(range(T)) + list(range(T - 1, -1, -1)) + [None]) * 2
-    binding.dc_conv_tuning(0, 4, 1, 0)
+    binding.dc_conv_tuning(0, units, 1, 0)
     try:
         runs = {mode: _replay_run(layers, ws, bs, frames, 16, False, mode, order, **kw) for mode in (1, 0, None)}
     finally:
@@ -1021,6 +1032,7 @@ def test_replayed_frames_are_the_launched_ones(net, size, kw):
         for f, (a, b) in enumerate(zip(runs[1][0], runs[other][0])):
             for i, (x, y) in enumerate(zip(a, b)):
                 assert torch.equal(x, y), (other, f, i)
+    return runs[0][2]
 
 
 def test_replayed_frames_follow_a_change_of_the_launch_shapes():
