@@ -338,8 +338,8 @@ struct dc::StackPlan {
     static constexpr int kTimedFrames = 4;
     int recuts_left = 3, timed_frames = 0;
     float timed_us[kMaxStages][kTimedFrames] = {};
-    int timed_tails = 0;
-    float timed_tail_us = 0.f;
+    int timed_tails = 0;                    // the caller's work is known behind frames that still ran at the next call
+    float timed_tail_us[kTimedFrames] = {};
     std::vector<std::unique_ptr<dc::FrameGraphs>> graphs;
     bool no_graphs = false;                 // recording failed once
     ReplayRule replay;
@@ -588,10 +588,12 @@ void StackPlan::cut(int max_stages) {
 
 // After kTimedFrames timed frames: scales the layers' times by what their stages took and cuts again if that pays.  A stage's
 // time is the second shortest of the four: the first use of a kernel or a pause of the host between its launches is in one of
-// them now and then (9 ms against 100 us: by the mean, Darknet-19 on one stream ended in stages of 66, 14 and 190 us).
+// them now and then (9 ms against 100 us: by the mean, Darknet-19 on one stream ended in stages of 66, 14 and 190 us).  The
+// caller's work is taken by the same rule, the shorter of two where no more are known: a single long wait in it is not the rule.
 void StackPlan::calibrate(int max_stages) {
     if (timed_frames < kTimedFrames) return;
-    const float new_tail = timed_tails ? timed_tail_us / timed_tails : 0.f;
+    std::sort(timed_tail_us, timed_tail_us + timed_tails);
+    const float new_tail = timed_tails ? timed_tail_us[timed_tails > 2 ? 1 : 0] : 0.f;
     float now = 0.f;
     for (int s = 0; s < n_stages; ++s) {
         const bool last = s + 1 == n_stages;
@@ -603,7 +605,6 @@ void StackPlan::calibrate(int max_stages) {
     }
     tail_us = new_tail > 20.f ? new_tail : 0.f;      // (the two events alone are some microseconds apart)
     timed_tails = 0;
-    timed_tail_us = 0.f;
     timed_frames = 0;
     const int old_stages = n_stages, old_partition = partition;
     int old_first[kMaxStages + 1];
@@ -823,8 +824,7 @@ int StackCall::begin() {
             if (old.tail) {
                 DC_TRY_HIP(hipEventSynchronize(old.after));
                 DC_TRY_HIP(hipEventElapsedTime(&ms, old.done[old.n_stages - 1], old.after));
-                P.timed_tail_us += ms * 1e3f;
-                ++P.timed_tails;
+                P.timed_tail_us[P.timed_tails++] = ms * 1e3f;
             }
             ++P.timed_frames;
             const int before = P.partition;
@@ -1496,7 +1496,7 @@ int StackCall::run() {
     if (recut) {
         ++ov->counters.recuts;
         P.cut(P.device_plan ? kMaxStages : kMaxStages - 1);
-        P.timed_frames = 0;
+        P.timed_frames = P.timed_tails = 0;
     }
     return DC_OK;
 }

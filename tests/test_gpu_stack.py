@@ -1235,6 +1235,31 @@ def test_the_callers_own_work_shortens_the_last_stage():
         assert torch.equal(x, y), i
 
 
+def test_one_long_wait_in_the_callers_work_does_not_decide_the_cut():
+    """Of the four frames that are timed after a cut one has 10 ms of the caller's work behind it, the others none: the layers are
+    cut anew from the times of their stages as without it."""
+    layers = synth.resolve_global_pooling(synth.dave_orig(), 66, 200, 3)
+    ws, bs = synth.he_weights(layers, 3, bias_scale=0.05, input_shape=(66, 200, 3))
+    video = torch.from_numpy(np.stack([synth.panning_video(94 + s, n_frames=8, H=66, W=200, fg=((24, 24), (16, 32))) for s in range(16)], 1)).to(DEV)
+    frames = [video[t].contiguous() for t in range(8)]
+    torch.cuda.synchronize()
+    cuts = {}
+    for wait in (False, True, False):
+        runner = binding.StackRunner(layers, ws, bs, 16, 66, 200, 3, block=16, radius=16, dtype=binding.DC_BF16, device_plan=True, exact_masks=True)
+        for t in range(40):
+            if t % 8 == 0:
+                runner.reset()
+            runner.step(frames[t % 8])
+            if t == 0 or (wait and t == 1):                # (behind the first, full frame: the timed ones still run at the next call)
+                torch.cuda._sleep(24_000_000)
+        torch.cuda.synchronize()
+        c = runner.overlap_counters()
+        print(f"[one wait] {wait}: {c.recuts} recuts, {c.stages} stages, {c.last_layers} layers in the last", flush=True)
+        cuts.setdefault(wait, []).append(c.recuts)
+        del runner
+    assert cuts[True][0] >= 1 or 0 in cuts[False], cuts     # (the first cut could be as good as it gets on another host)
+
+
 def test_one_handle_for_two_stacks_and_two_caller_streams():
     """A handle that is handed from one stack to another and called on changing streams orders every frame behind the
     earlier ones: same tensors as with a handle of their own.  (Stages of different stacks use the same streams, and the
