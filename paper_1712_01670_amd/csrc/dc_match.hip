@@ -8,6 +8,7 @@
 // (ssd, |dx|+|dy|, dy, dx) is packed in 64 bits and reduced with wavefront shuffles.
 // Kernel 2 (motion + re-test): every workgroup recomputes the stream's mean motion
 // from the per-block results (a few hundred values) and re-tests its own block.
+#include <algorithm>
 #include <cstdlib>
 #include <type_traits>
 
@@ -1218,6 +1219,7 @@ hipError_t launch_match(const uint8_t* cur, const uint8_t* prev, int n_streams, 
                         int B, int R, int k_skip, uint32_t max_ssd, int16_t* mv, uint32_t* best_ssd,
                         int32_t* gmv, int32_t* n_pass, uint8_t* mask, hipStream_t st) {
     const int gh = H / B, gw = W / B;
+    k_skip = std::min(k_skip, std::max(gw, gh));           // beyond, the first block alone is searched either way (and sums overflow)
     const int rows = B + 2 * R;
     const bool aligned = ((reinterpret_cast<uintptr_t>(prev) & 3) == 0) && ((W * C) % 4 == 0);
     dim3 grid(((gw + k_skip - 1) / k_skip) * ((gh + k_skip - 1) / k_skip), n_streams);   // the searched blocks
@@ -1294,6 +1296,7 @@ hipError_t launch_match_diamond(const uint8_t* cur, const uint8_t* prev, int n_s
                                 int R, int k_skip, uint32_t max_ssd, int16_t* mv, uint32_t* best_ssd, int32_t* gmv,
                                 int32_t* n_pass, uint8_t* mask, hipStream_t st) {
     const int gh = H / B, gw = W / B;
+    k_skip = std::min(k_skip, std::max(gw, gh));           // as above
     const unsigned long long nvec = (2ull * R + 1) * (2ull * R + 1);
     const int cap = (int)(nvec < 0x7fffffffull ? nvec : 0x7fffffffull);
     auto magic = [](int d) { return (uint32_t)((0x100000000ull + (uint64_t)d - 1) / (uint64_t)d); };

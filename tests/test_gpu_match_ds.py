@@ -105,6 +105,25 @@ def test_blocks_of_whole_dwords(oracle, H, W, C, B, R):
     _compare(oracle, cur, prev, B, R, 40 * B * B * C, f"dwords {H}x{W}x{C}")
 
 
+@pytest.mark.parametrize("H,W,B,R", [(64, 16, 16, 16), (16, 64, 16, 16), (49, 35, 8, 8), (64, 16, 16, 5), (20, 45, 5, 4), (8, 8, 8, 8)])
+def test_k_skip_beyond_the_grid(oracle, H, W, B, R):
+    """Any k from the longer side of the block grid on searches the first block alone, up to the largest that the argument holds."""
+    print(f"[k-skip] {H}x{W} B={B} R={R}", flush=True)
+    rng = np.random.default_rng(H + W)
+    prev = synth._box_blur5(rng.integers(0, 256, (H, W, 3)).astype(np.uint8))[None]
+    cur = np.roll(prev, (1, 2), axis=(1, 2))
+    dev = torch.device("cuda:0")
+    k0 = max(H // B, W // B)
+    for method, ref in ((binding.DC_MATCH_EXHAUSTIVE, oracle.match_blocks), (binding.DC_MATCH_DIAMOND, oracle.match_blocks_ds)):
+        want = ref(cur[0], prev[0], B, R, 1000, k_skip=k0)
+        for k in (k0, k0 + 1, 2 ** 31 - 1 - k0, 2 ** 31 - 1):
+            out = binding.dc_match_blocks_opt(torch.from_numpy(cur).to(dev), torch.from_numpy(prev).to(dev), B, R, 1000, method=method, k_skip=k)
+            torch.cuda.synchronize()
+            got = {key: v.cpu().numpy() for key, v in out.items()}
+            assert np.array_equal(got["best_ssd"][0].view(np.uint32), want["best_ssd"]) and np.array_equal(got["mv"][0], want["mv"]), (method, k)
+            assert got["gmv"][0].tolist() == want["gmv"].tolist() and np.array_equal(got["mask"][0], want["mask"]), (method, k)
+
+
 def test_argument_checks():
     dev = torch.device("cuda:0")
     f = torch.zeros((1, 32, 32, 3), dtype=torch.uint8, device=dev)
