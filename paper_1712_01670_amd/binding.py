@@ -286,13 +286,18 @@ class _Workspaces:
                 ws = types.SimpleNamespace(dev=None, host=None, event=None)
             else:
                 ws = self.free.pop(0)
-        if ws.event is not None:
-            ws.event.synchronize()
-        if ws.dev is None or ws.dev.numel() < dev_bytes or ws.dev.device != device:
-            ws.dev = torch.empty(max(int(dev_bytes), 256), dtype=torch.uint8, device=device)
-            ws.event = torch.cuda.Event()
-        if ws.host is None or ws.host.numel() < host_bytes:
-            ws.host = torch.empty(max(int(host_bytes), 256), dtype=torch.uint8, pin_memory=True)
+        try:
+            if ws.event is not None:
+                ws.event.synchronize()
+            if ws.dev is None or ws.dev.numel() < dev_bytes or ws.dev.device != device:
+                ws.dev = torch.empty(max(int(dev_bytes), 256), dtype=torch.uint8, device=device)
+                ws.event = torch.cuda.Event()
+            if ws.host is None or ws.host.numel() < host_bytes:
+                ws.host = torch.empty(max(int(host_bytes), 256), dtype=torch.uint8, pin_memory=True)
+        except BaseException:
+            with self.lock:              # (out of memory: the set is gone, a later call makes another)
+                self.made -= 1
+            raise
         return ws
 
     def give(self, ws):

@@ -416,3 +416,34 @@ def test_regions_of_a_single_layer_call_in_every_form():
     for bad in ([1, 2, 3, 4], np.arange(4), np.arange(8), [[1, 2, 3, 4, 5]], np.array([[1, 2, 3, np.nan]])):
         with pytest.raises((TypeError, ValueError)):
             binding._regions_to_c([(bad, (0, 0))])
+
+
+def test_a_workspace_that_cannot_be_made_does_not_count_as_one(monkeypatch):
+    """Out of memory while a set grows: the set is dropped, and calls take turns on as many sets as before once there is memory again."""
+    class Event:
+        def synchronize(self): pass
+        def record(self): pass
+    empty, fail = torch.empty, []
+
+    def allocate(n, dtype, **kw):
+        if fail:
+            raise torch.OutOfMemoryError("planted")
+        return empty(n, dtype=dtype)
+    monkeypatch.setattr(binding.torch, "empty", allocate)
+    monkeypatch.setattr(binding.torch.cuda, "Event", Event)
+    pool, cpu = binding._Workspaces(), torch.device("cpu")
+    held = [pool.take(1000, 1000, cpu) for _ in range(2)]
+    for ws in held:
+        pool.give(ws)
+    fail.append(1)
+    for _ in range(5):
+        with pytest.raises(torch.OutOfMemoryError):
+            pool.take(5000, 1000, cpu)
+    fail.clear()
+    assert pool.made == len(pool.free)
+    first = pool.take(5000, 1000, cpu)
+    pool.give(first)
+    second = pool.take(5000, 1000, cpu)
+    assert second is not first                   # two in turn again
+    pool.give(second)
+    assert pool.made == len(pool.free) == pool.KEPT == 2
