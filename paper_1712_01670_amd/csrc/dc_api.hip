@@ -68,6 +68,9 @@ hipError_t upload_plans(void* dst_dev, const unsigned char* src_host, size_t byt
 // arguments instead of waiting for the upload.  Row y < n of the grid copies rectangle y, the last one uploads.  A single 3x3
 // 256->256 layer on 8 streams of 56x56 (plan 16 KB, 16 rectangles): copy engine, copies, convolution 57 us a call; upload
 // kernel with two workspaces in turn 38; this 36, what the host needs.
+// 32 rectangles are 1 KiB of arguments: two for each of 16 streams.  More take the upload and the copies in two launches, which
+// costs 2 to 3 us (28x28 64->64, 33 and 64 rectangles 34.7 and 37.8 us a call; with room for 96 here 32.4 and 34.7, and 32
+// rectangles 33.4 against 33.1); 4 KiB is what a launch takes in arguments.
 constexpr int kCopyArgRects = 32;
 struct CopyArgs {
     const uint4 *src, *prev;

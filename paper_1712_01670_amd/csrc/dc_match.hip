@@ -1238,7 +1238,8 @@ hipError_t launch_match(const uint8_t* cur, const uint8_t* prev, int n_streams, 
         const int nd = 2 * R + 1;
         const int need = 3 + C * (16 * nt - 1) + 64 * ksteps + 4, real = 3 + rows * C + 4;
         const int wsm = (int)align_up((size_t)(need > real ? need : real), 16);
-        // the instantiations below that know the block shape take their row sums from the window bytes: no per-pixel sums
+        // the instantiations below that know the block shape take their row sums from the window bytes: no per-pixel sums (they
+        // serve the ranges from 17 to 23 and 9 to 15; those of the block edge have gone above)
         const bool fused = (nt == 3 && B == 16 && C == 3) || (nt == 2 && B == 8 && C == 3);
         const size_t dead = (size_t)rows * wsm + (size_t)B * 64 * ksteps + (size_t)((fused ? 0 : rows * rows) + rows * nd) * 4;
         const size_t ldsm = dead + 16 + (size_t)(3 * kMfmaWaves + nd * nd) * 4;
