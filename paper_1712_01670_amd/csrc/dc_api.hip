@@ -289,7 +289,7 @@ int32_t dc_probe_mfma_rate(int32_t lds_reads, void* scratch_dev, size_t scratch_
 }
 
 int32_t dc_conv_tuning(int32_t arrangement, int32_t units_per_workgroup, int32_t k_split, int32_t chunk_index) {
-    if (arrangement > 4 || units_per_workgroup > 18 || chunk_index > 1) return DC_ERR_INVALID_ARG;
+    if (arrangement > 5 || units_per_workgroup > 18 || chunk_index > 1) return DC_ERR_INVALID_ARG;
     conv_set_tuning(arrangement, units_per_workgroup, k_split, chunk_index);
     return DC_OK;
 }

@@ -1,7 +1,8 @@
 // Cache-aware convolution (Section 5 "Reuse", steps 2-3), the kernels for the common layer shape: 3x3 taps,
-// stride 1.  Three kernels share this file:
+// stride 1.  Four kernels share this file:
 //   conv_fast_kernel   channel counts that are whole 64-byte rows, 64 or 128 output channels per workgroup (5x5 taps
 //                      as well, in bf16);
+//   conv_deep_kernel   bf16, 3x3, many units: weights from L2 into registers (see there);
 //   conv_regw_kernel   64 input channels in bf16 and many units: persistent, weights in registers (see there);
 //   conv_first_kernel  input pixels of one 16-byte vector (the padded first layer), nothing staged (see there).
 //
@@ -389,6 +390,202 @@ __global__ __launch_bounds__(WM* WN * 64) void conv_fast_kernel(ConvParams P) {
         float* px = part + (size_t)(ug * P.g_rt + g) * 16 * P.Cout;
 #pragma unroll
         for (int j = 0; j < NBW; ++j) *reinterpret_cast<floatx4*>(px + j * 16) = acc[u][j];
+    }
+}
+
+// ---- 3x3, bf16, tiles of 128 or 256 output channels: a wavefront's weights come straight from L2 ----------------
+// conv_fast_kernel stages the weights of a kernel row in LDS, where four wavefronts read each fragment: 7 or 8 LDS reads
+// for 12 or 16 MFMAs, a barrier per kernel row, and one workgroup per CU, whose wavefronts reach every barrier together
+// (matrix pipes busy in 0.54 of a CU's cycles).  Here a wavefront holds all units of its workgroup against 64 channels of
+// its own, so that a weight fragment has one reader and needs no LDS: it is loaded into registers two taps ahead.  Only
+// the patches go through LDS (double-buffered, one barrier per 32 channels = nine taps), a fragment of them feeds four
+// MFMAs, and two workgroups of four wavefronts (four of two) share a CU out of step: pipes busy in 0.72 of the cycles.
+//   workgroup = UPW units x 64 NW channels; wavefront = UPW units x 64 channels (128 accumulator registers for 8 units)
+// 56x56 256->256 on 64 streams: 214 -> 175 us (1.35 PFLOP/s issued), 28x28 512->512 199 -> 186, 112x112 128->128 254 -> 222.
+// What bounds it now: power (the clock falls to 1.85 GHz) and the look-ups of the weight fragments in the CU's cache, two
+// per four lanes in the packed layout (rows of 64 bytes); without any weight loads the first of these takes 153 us, and
+// without the LDS reads or the patch loads as long as with them.  Through an LDS ring of each wavefront's own the weights
+// took longer (183, 189, 265 us).  The sums are taken in the order of conv_fast_kernel with chunks of 32 channels and no
+// split of K: the same bits.
+//
+// The MFMA as one instruction on a tied accumulator: left to the compiler, a third of them write to other registers than
+// they read, and 8 units do not fit.  The compiler does not see an MFMA then, so the wait states before other
+// instructions touch the registers are written out where that happens.
+__device__ __forceinline__ void mfma_in_place(const bf16x8& a, const bf16x8& b, floatx4& c) {
+    asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
+}
+template <int NW, int UPW>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void conv_deep_kernel(ConvParams P) {
+    typedef __hip_bfloat16 T;
+    typedef Frag<T> F;
+    typedef F::vec vec;
+    constexpr int NBW = 4, NT = NW * NBW * 16, RB = 64, PW = 6, PR = PW * PW;     // channels of a workgroup; a patch row: 32 channels
+    constexpr int P_INSTR = (UPW * PR + 15) / 16, NPI = (P_INSTR + NW - 1) / NW, PBYTES = P_INSTR * 1024;
+    constexpr int NQ = (UPW + 1) / 2;               // steps of a tap: two units each, whose fragments are read together
+    static_assert(UPW >= 2 && UPW <= 8 && NPI <= 10, "fits the registers; patch loads end four taps before the barrier");
+
+    extern __shared__ __align__(16) unsigned char smem[];
+    const FastHeader<8> H(smem);                    // (its tables are aligned for even numbers)
+    unsigned char* const patch0 = smem + kHeaderBytes;
+    const int tid = threadIdx.x;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l16 = lane & 15, q = lane >> 4;
+
+    int ug, ntile;
+    decode_workgroup(P.R, ug, ntile);
+    const int n_units = unit_count(P);
+    if (ug * P.g_rt >= n_units) return;             // the whole workgroup, before any barrier
+    const int n0 = ntile * NT + wave * 64;          // first channel of this wavefront
+    const __amdgpu_buffer_rsrc_t in_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        reinterpret_cast<void*>(keep_scalar(reinterpret_cast<uintptr_t>(P.in))), 0, keep_scalar(P.in_bytes), kBufferFlags);
+    const __amdgpu_buffer_rsrc_t w_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        reinterpret_cast<void*>(keep_scalar(reinterpret_cast<uintptr_t>(P.w))), 0, keep_scalar(P.w_bytes), kBufferFlags);
+    const int CinES = P.Cin * 2;
+    const int n_ch = keep_scalar(P.n_chunks);
+
+    // Weights: row l16 of MFMA block j carries channel (l16 / 4) * 16 + 4 j + l16 % 4 of the wavefront's 64, so that a
+    // lane ends with 16 consecutive channels of a pixel and stores them in 16-byte pieces.
+    const bool packed = P.w_packed != 0;
+    const int ts = keep_scalar(packed ? 1024 : CinES);               // byte distance of two taps, chunks, blocks
+    const int cs = keep_scalar(packed ? 9 * 1024 : RB);
+    const int js = keep_scalar(packed ? 4 * 64 : 4 * 9 * CinES);
+    const int wch = n0 + (l16 >> 2) * 16 + (l16 & 3);
+    const uint32_t wlane = packed ? (uint32_t)(wch / 16 * (n_ch * 9) * 1024 + wch % 16 * 64 + q * 16)
+                                  : (uint32_t)(wch * 9 * CinES + q * 16);
+    vec w[3][NBW];
+    auto load_w = [&](int slot, int soff) {
+#pragma unroll
+        for (int j = 0; j < NBW; ++j) {
+            const int so = soff + j * js;
+            w[slot][j] = __builtin_bit_cast(vec, __builtin_amdgcn_raw_buffer_load_b128(w_rsrc, wlane, so, 0));
+        }
+    };
+    int wo = 0;                                     // of the current chunk's first tap
+    load_w(0, wo);                                  // they travel while the unit table is decoded
+    load_w(1, wo + ts);
+
+    decode_units_fast<8, NW * 64, 2>(P, H, ug, tid, n_units);
+
+    // patch loads: 16 rows of 64 bytes each, dealt to the wavefronts in turn.  A patch is 36 rows without gaps; chunk c
+    // (16 bytes) of the row at (py, px) sits at position c ^ 2 (py % 2): no bank conflicts for any tap.
+    uint32_t pgo[NPI];
+    const int lrow = lane >> 2, lpos = lane & 3;
+#pragma unroll
+    for (int i = 0; i < NPI; ++i) {
+        const int row = (wave + i * NW) * 16 + lrow, unit0 = row / PR, r = row - unit0 * PR;
+        const int py = r / PW, px = r - py * PW;
+        const int unit = unit0 < UPW ? unit0 : UPW - 1;
+        const int4 uq = H.uq[unit];
+        const int c16 = (lpos ^ (py % 2 * 2)) << 4;
+        const bool ok = unit0 < UPW && (unsigned)(uq.y + py) < (unsigned)P.Hin && (unsigned)(uq.z + px) < (unsigned)P.Win;
+        uint32_t off = (uint32_t)(uq.x + (py * P.Win + px) * CinES + c16);
+        if (P.in_origin && ok) {                    // the input lies on a torus: the patch may cross its seams
+            const int4 og = H.uorg[unit];
+            const int iy = torus_wrap(uq.y + py, og.y, P.Hin), ix = torus_wrap(uq.z + px, og.x, P.Win);
+            off = (uint32_t)(((H.ustream[unit] * P.Hin + iy) * P.Win + ix) * CinES + c16);
+        }
+        pgo[i] = ok ? off : kOob;
+    }
+    auto issue_p1 = [&](int i, int so, int pbuf) {
+        unsigned char* dst = patch0 + pbuf * PBYTES + (wave + i * NW) * 1024;
+        const uint32_t off = pgo[i];
+        if ((i + 1) * NW <= P_INSTR || wave + i * NW < P_INSTR)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(in_rsrc, (__attribute__((address_space(3))) void*)dst, 16, off, so, 0, 0);
+    };
+
+    int paddr[6];                                   // kernel rows 0 and 1; row 2 is row 0 two lines further down
+#pragma unroll
+    for (int t = 0; t < 6; ++t) {
+        const int py = (l16 >> 2) + t / 3, px = (l16 & 3) + t % 3;
+        paddr[t] = (py * PW + px) * RB + ((q ^ (py % 2 * 2)) << 4);
+    }
+    vec x[2][2];
+    auto read_x = [&](int pbuf, int t, int h, int b) {     // step h of tap t
+        const int ky = t / 3, kx = t % 3;
+        const unsigned char* xp = patch0 + pbuf * PBYTES + paddr[ky % 2 * 3 + kx] + (ky / 2) * (2 * PW * RB);
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+            if (h * 2 + u < UPW) x[b][u] = *reinterpret_cast<const vec*>(xp + (h * 2 + u) * (PR * RB));
+    };
+    floatx4 acc[UPW][NBW];
+#pragma unroll
+    for (int u = 0; u < UPW; ++u)
+#pragma unroll
+        for (int j = 0; j < NBW; ++j) acc[u][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    auto mma = [&](int h, int b, int slot) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+            if (h * 2 + u < UPW)
+#pragma unroll
+                for (int j = 0; j < NBW; ++j) mfma_in_place(w[slot][j], x[b][u], acc[h * 2 + u][j]);
+    };
+
+#pragma unroll
+    for (int i = 0; i < NPI; ++i) issue_p1(i, 0, 0);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    lds_barrier();
+    read_x(0, 0, 0, 0);
+    asm volatile("s_nop 4");                        // (the accumulators were cleared)
+    for (int c = 0; c < n_ch; ++c) {
+        const int pbuf = c & 1;
+        const bool more = c + 1 < n_ch;
+#pragma unroll
+        for (int t = 0; t < 9; ++t) {
+            // (the last chunk's loads beyond its taps fetch weights that nothing uses, or zeros from outside the tensor)
+            load_w((t + 2) % 3, t + 2 < 9 ? wo + (t + 2) * ts : wo + cs + (t - 7) * ts);
+#pragma unroll
+            for (int i = 2 * t; i < 2 * t + 2 && i < NPI; ++i)
+                if (more) issue_p1(i, (c + 1) * RB, pbuf ^ 1);
+#pragma unroll
+            for (int h = 0; h < NQ; ++h) {
+                const int b = (t * NQ + h) & 1;
+                if (h + 1 < NQ) read_x(pbuf, t, h + 1, b ^ 1);
+                else if (t < 8) read_x(pbuf, t + 1, 0, b ^ 1);
+                else if (more) {
+                    // This wavefront's share of the next patches has landed: at least sixteen weight loads were issued
+                    // after them.  Behind the barrier all shares have, and nobody reads the current buffer any more.
+                    asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+                    lds_barrier();
+                    read_x(pbuf ^ 1, 0, 0, b ^ 1);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                mma(h, b, t % 3);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        if ((9 * NQ) & 1) { x[0][0] = x[1][0]; x[0][1] = x[1][1]; asm volatile("s_nop 4"); }   // the next chunk expects its first fragments in buffer 0
+        wo += cs;
+    }
+
+#pragma unroll
+    for (int u = 0; u < UPW; ++u)       // the sums are read by other than MFMAs from here on
+        asm volatile("s_nop 15\n\ts_nop 4" : "+v"(acc[u][0]), "+v"(acc[u][1]), "+v"(acc[u][2]), "+v"(acc[u][3]));
+    const int chan = n0 + 16 * q;
+    floatx4 bias[NBW];
+#pragma unroll
+    for (int j = 0; j < NBW; ++j)
+        bias[j] = P.bias ? *reinterpret_cast<const floatx4*>(P.bias + chan + j * 4) : floatx4{0.f, 0.f, 0.f, 0.f};
+    T* const out = reinterpret_cast<T*>(P.out) + ((l16 >> 2) * P.Wout + (l16 & 3)) * P.Cout + chan;
+    const bool relu = P.relu != 0;
+#pragma unroll
+    for (int u = 0; u < UPW; ++u) {
+        if (H.skip[u * 16 + l16]) continue;
+        T* px = out + H.uq[u].w;
+        if (P.out_origin) {                         // the output lies on a torus: the unit may cross its seams
+            const int4 og = H.uorg[u];
+            const int y = torus_wrap(H.uq[u].y + P.p + (l16 >> 2), og.w, P.Hout), xo = torus_wrap(H.uq[u].z + P.p + (l16 & 3), og.z, P.Wout);
+            px = reinterpret_cast<T*>(P.out) + ((H.ustream[u] * P.Hout + y) * P.Wout + xo) * P.Cout + chan;
+        }
+        uint32_t v[2 * NBW];
+#pragma unroll
+        for (int j = 0; j < NBW; ++j) {
+            floatx4 sum = acc[u][j] + bias[j];
+            if (relu) activate4(sum, P.relu);
+            v[2 * j] = (uint32_t)F::bits(sum[0]) | ((uint32_t)F::bits(sum[1]) << 16);
+            v[2 * j + 1] = (uint32_t)F::bits(sum[2]) | ((uint32_t)F::bits(sum[3]) << 16);
+        }
+        *reinterpret_cast<uintx4*>(px) = uintx4{v[0], v[1], v[2], v[3]};
+        *reinterpret_cast<uintx4*>(px + 8) = uintx4{v[4], v[5], v[6], v[7]};
     }
 }
 
@@ -1353,12 +1550,40 @@ size_t fast_lds_bytes(int k, int geom, int kci, int upw) {
     return kHeaderBytes + 2 * (size_t)(kGeom[geom].wm * upw * (3 + k) * 8 / rpi) * 1024 + 2 * (size_t)(k * geom_nt(geom) / rpi) * 1024;
 }
 
-struct FastChoice { int g, ks, kci; double cost; int geom; };
+struct FastChoice { int g, ks, kci; double cost; int geom; };      // geom kDeep: conv_deep_kernel, ks its wavefronts
 
 // Overrides of the launch model (dc_conv_tuning: tests and experiments): arrangement, units per workgroup,
 // K split, channel chunk index; -1 = chosen by the model.  Process-wide; readers take a snapshot under the mutex.
 std::mutex g_tune_mutex;
 ConvTuning g_tune_shared{{-1, -1, -1, -1}};
+
+// conv_deep_kernel: 256 channels per workgroup, 128 where the layer's channels are no multiple of 256.
+constexpr int kDeep = 4, kDeepMinUnits = 6, kDeepMaxUnits = 8;
+constexpr int kDeepId = 416;          // kernel ids: + units - 1, + 8 for two wavefronts
+inline size_t deep_lds_bytes(int g) { return kHeaderBytes + 2 * (size_t)((g * 36 + 15) / 16) * 1024; }
+template <int NW>
+hipError_t deep_launch(int g, dim3 grid, hipStream_t st, const ConvParams& P) {
+    if (g == 8) hipLaunchKernelGGL((conv_deep_kernel<NW, 8>), grid, dim3(NW * 64), deep_lds_bytes(8), st, P);
+    else if (g == 7) hipLaunchKernelGGL((conv_deep_kernel<NW, 7>), grid, dim3(NW * 64), deep_lds_bytes(7), st, P);
+    else hipLaunchKernelGGL((conv_deep_kernel<NW, 6>), grid, dim3(NW * 64), deep_lds_bytes(6), st, P);
+    return hipGetLastError();
+}
+// Cost of a launch in the unit of the model below (about 0.5 ns).  A CU holds two workgroups of four wavefronts (four of two);
+// a pair of them takes the longer of its MFMAs and its weight fragments' cache look-ups (two per four lanes), a lone one
+// more than half of a pair.  Measured, us, conv_fast_kernel's best -> units per workgroup 6 / 7 / 8: 56x56 256->256 64 streams
+// 214 -> 212 / 175 / 181, 16 streams 60 -> 68 / 51 / 54; 28x28 512->512 64 streams 199 -> 219 / 186 / 221, 16 streams
+// 60 -> 83 / 55 / 60; 112x112 128->128 64 streams 254 -> 233 / 222 / 223; launches of less than one workgroup per CU
+// lose (13x13 512->1024 16 streams 34 -> 41 / 45 / 50), and so do few workgroups of two wavefronts (13x13 384->384 64
+// streams 40 -> 49 / 56 / 65), hence the least number of those.
+double deep_cost(const ConvLaunch& c, long n_units, int g) {
+    const int nw = c.Cout % 256 ? 2 : 4, n_ch = c.Cin / 32;
+    const long wgs = (n_units + g - 1) / g * (c.Cout / (64 * nw));
+    if (nw == 2 && wgs < 2048) return 1e300;
+    const double m = 576.0 * g * n_ch, look = 2 * 4608.0 * 1.08 * n_ch;
+    const double pair = (2.6 * m > look ? 2.6 * m : look) + (nw == 2 ? 20000 : 10000), lone = 1.45 * m + 7000;
+    const long per_cu = nw == 2 ? (wgs + 511) / 512 : (wgs + 255) / 256;
+    return (per_cu / 2) * pair + (per_cu % 2) * lone;
+}
 
 // Cycle model of one launch.  A workgroup spends its stages (the longer of the MFMA time and the time to
 // bring the stage's bytes into LDS) plus fixed costs per stage and per workgroup (decode, address set-up,
@@ -1441,13 +1666,20 @@ FastChoice choose_fast(const ConvLaunch& c, long n_units, long n_cap, size_t scr
 
 // Ids 64.. name the instantiations of this file: 64 + ((bf16 * 2 + kci) * 8 + UPW - 1), 96.. the first-layer kernel,
 // 110.. the wide arrangement.
-bool conv_kernel_built(int id) { return id >= kPwSplitId ? id < kPwSplitId + 2 : id >= 132 && (id - 132) / 8 < kNumGeom && fast_built(5, true, (id - 132) / 8, 0, (id - 132) % 8 + 1); }
+bool conv_kernel_built(int id) {
+    if (id >= kDeepId) return id < kDeepId + 16 && id % 8 + 1 >= kDeepMinUnits;
+    return id >= kPwSplitId ? id < kPwSplitId + 2 : id >= 132 && (id - 132) / 8 < kNumGeom && fast_built(5, true, (id - 132) / 8, 0, (id - 132) % 8 + 1);
+}
 void conv_fast_kernel_name(int id, char* buf, size_t n) {
     if (id == 126) { snprintf(buf, n, "conv_regw_kernel<2, 2, false>"); return; }
     if (id == 130) { snprintf(buf, n, "conv_regw_kernel<2, 2, true>"); return; }      // tensors on a torus
     if (id == 129) { snprintf(buf, n, "conv_fast_kernel<__hip_bfloat16, 3, 32, 3, 6, 2, 4>"); return; }     // the tall arrangement
     if (id == 127 || id == 128 || id == 108 || id == 109) {      // 108 + bf16 (64 x 64 tile), 127 + bf16 (128 x 128): conv_pw_kernel (1x1)
         snprintf(buf, n, "conv_pw_kernel<%s, %d>", id == 109 || id == 128 ? "__hip_bfloat16" : "float", id >= 127 ? 4 : 2);
+        return;
+    }
+    if (id >= kDeepId) {
+        snprintf(buf, n, "conv_deep_kernel<%d, %d>", id < kDeepId + 8 ? 4 : 2, id % 8 + 1);
         return;
     }
     if (id >= kPwSplitId) {
@@ -1673,23 +1905,32 @@ bool launch_conv_fast(const ConvLaunch& c, long n_cap, long n_units, hipStream_t
     if (scratch > kConvScratchBytes) scratch = kConvScratchBytes;
     // The model costs about 2 us per call on the host; the same layers come back every frame with the same or a
     // recently seen unit count, so its answers are kept in a small direct-mapped table.
-    struct Memo { int dtype, k, cin, cout, tune[4]; long n_units, n_cap; size_t scratch; FastChoice ch; bool used; };
+    struct Memo { int dtype, k, cin, cout, tune[4]; bool packed; long n_units, n_cap; size_t scratch; FastChoice ch; bool used; };
     static Memo memo[256];
     static std::mutex memo_mutex;
+    const bool packed = c.w_packed && reinterpret_cast<uintptr_t>(c.w_packed) % 16 == 0;
+    const bool deep_shape = c.dtype == DC_BF16 && c.k == 3 && c.Cout % 128 == 0;
     FastChoice ch;
     {
         std::lock_guard<std::mutex> guard(memo_mutex);
         Memo& slot = memo[((unsigned long)n_units * 2654435761ul + (unsigned)c.Cin * 40503u + (unsigned)c.Cout * 97u + (unsigned)c.dtype + (unsigned)c.k * 31u) % 256];
-        if (slot.used && slot.dtype == c.dtype && slot.k == c.k && slot.cin == c.Cin && slot.cout == c.Cout && slot.n_units == n_units && slot.n_cap == n_cap &&
+        if (slot.used && slot.dtype == c.dtype && slot.k == c.k && slot.packed == packed && slot.cin == c.Cin && slot.cout == c.Cout && slot.n_units == n_units && slot.n_cap == n_cap &&
             slot.scratch == scratch && slot.tune[0] == g_tune[0] && slot.tune[1] == g_tune[1] && slot.tune[2] == g_tune[2] &&
             slot.tune[3] == g_tune[3]) {
             ch = slot.ch;
         } else {
             ch = choose_fast(c, n_units, n_cap, scratch, g_tune[0] == 4 ? 3 : g_tune[0]);    // tuning 3 names another kernel
-            slot = Memo{c.dtype, c.k, c.Cin, c.Cout, {g_tune[0], g_tune[1], g_tune[2], g_tune[3]}, n_units, n_cap, scratch, ch, true};
+            if (deep_shape && packed && g_tune[0] < 0 && g_tune[1] < 0 && g_tune[2] < 0 && g_tune[3] < 0)
+                for (int g = kDeepMaxUnits; g >= kDeepMinUnits; --g) {
+                    const double cost = deep_cost(c, n_units, g);
+                    if (cost < ch.cost) ch = FastChoice{g, c.Cout % 256 ? 2 : 4, 0, cost, kDeep};
+                }
+            if (deep_shape && g_tune[0] == 5)
+                ch = FastChoice{std::min(std::max(g_tune[1], kDeepMinUnits), kDeepMaxUnits), c.Cout % 256 || g_tune[2] == 2 ? 2 : 4, 0, 0, kDeep};
+            slot = Memo{c.dtype, c.k, c.Cin, c.Cout, {g_tune[0], g_tune[1], g_tune[2], g_tune[3]}, packed, n_units, n_cap, scratch, ch, true};
         }
     }
-    if (g_tune[1] > 0 && ch.g > 0) {    // forced shape within the arrangement the model picked
+    if (g_tune[1] > 0 && ch.g > 0 && ch.geom != kDeep) {    // forced shape within the arrangement the model picked
         const int f_g = g_tune[1], f_ks = g_tune[2], f_kci = g_tune[3] < 0 ? ch.kci : g_tune[3];
         const Geom& G = kGeom[ch.geom];
         const int kc = (c.dtype == DC_BF16 ? 32 : 16) << f_kci;
@@ -1704,7 +1945,9 @@ bool launch_conv_fast(const ConvLaunch& c, long n_cap, long n_units, hipStream_t
         }
     }
     if (ch.g < 1) return false;
-    const int upw = (ch.g + kGeom[ch.geom].wm - 1) / kGeom[ch.geom].wm;
+    const bool deep = ch.geom == kDeep;
+    const int nt = deep ? 64 * ch.ks : geom_nt(ch.geom), ks = deep ? 1 : ch.ks;
+    const int upw = deep ? ch.g : (ch.g + kGeom[ch.geom].wm - 1) / kGeom[ch.geom].wm;
     const int kc = (c.dtype == DC_BF16 ? 32 : 16) << ch.kci;
     const int units_y = (c.Hout + 3) / 4, units_x = (c.Wout + 3) / 4;
 
@@ -1722,21 +1965,25 @@ bool launch_conv_fast(const ConvLaunch& c, long n_cap, long n_units, hipStream_t
     P.w_bytes = (uint32_t)((size_t)c.Cout * c.k * c.k * c.Cin * esz);
     P.out_vec = 1;
     P.n_chunks = c.Cin / kc;
-    P.R = c.Cout / geom_nt(ch.geom);
-    P.ks = ch.ks;
-    P.chunks_per_split = (P.n_chunks + ch.ks - 1) / ch.ks;
-    P.partial = ch.ks > 1 ? static_cast<float*>(c.scratch) : nullptr;
+    P.R = c.Cout / nt;
+    P.ks = ks;
+    P.chunks_per_split = (P.n_chunks + ks - 1) / ks;
+    P.partial = ks > 1 ? static_cast<float*>(c.scratch) : nullptr;
     P.in_origin = c.in_origin; P.out_origin = c.out_origin; P.origin_stride = c.origin_stride;
-    if (c.k == 3 && c.w_packed && reinterpret_cast<uintptr_t>(c.w_packed) % 16 == 0) { P.w = c.w_packed; P.w_packed = 1; }
+    if (c.k == 3 && packed) { P.w = c.w_packed; P.w_packed = 1; }
 
-    if (c.kernel_id) *c.kernel_id = c.k == 5 ? 132 + ch.geom * 8 + upw - 1 : ch.geom == 3 ? 129 : ch.geom ? 110 + (ch.geom - 1) * 8 + ch.kci * 4 + upw - 1 : 64 + ((c.dtype == DC_BF16 ? 2 : 0) + ch.kci) * 8 + upw - 1;
+    if (c.kernel_id) *c.kernel_id = deep ? kDeepId + (ch.ks == 2 ? 8 : 0) + ch.g - 1 : c.k == 5 ? 132 + ch.geom * 8 + upw - 1 : ch.geom == 3 ? 129 : ch.geom ? 110 + (ch.geom - 1) * 8 + ch.kci * 4 + upw - 1 : 64 + ((c.dtype == DC_BF16 ? 2 : 0) + ch.kci) * 8 + upw - 1;
     const long groups = (n_cap + ch.g - 1) / ch.g;
     const long wgx = groups * P.R;
-    if (wgx > 2147483647L || ch.ks > 65535) { *err = hipErrorInvalidValue; return true; }
-    const dim3 grid((unsigned)wgx, (unsigned)ch.ks);
+    if (wgx > 2147483647L || ks > 65535) { *err = hipErrorInvalidValue; return true; }
+    const dim3 grid((unsigned)wgx, (unsigned)ks);
+    if (deep) {
+        *err = ch.ks == 2 ? deep_launch<2>(ch.g, grid, st, P) : deep_launch<4>(ch.g, grid, st, P);
+        return true;
+    }
     const size_t lds = fast_lds_bytes(c.k, ch.geom, ch.kci, upw);
     *err = c.k == 5 ? fast_launch5(ch.geom, upw, grid, lds, st, P) : fast_launch(c.dtype == DC_BF16, ch.geom, ch.kci, upw, grid, lds, st, P);
-    if (*err != hipSuccess || ch.ks == 1) return true;
+    if (*err != hipSuccess || ks == 1) return true;
     const size_t total = (size_t)n_cap * 16 * (c.Cout / 4);
     if (c.dtype == DC_BF16)
         hipLaunchKernelGGL(conv_split_reduce_kernel<__hip_bfloat16>, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, P);

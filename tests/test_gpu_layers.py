@@ -964,3 +964,47 @@ def test_single_layer_calls_without_a_wait_in_between(per_stream, cout, bf16):
         t.join()
     torch.cuda.synchronize()
     assert not bad and len(binding._conv_ws.free) <= binding._conv_ws.KEPT
+
+
+# The bf16 kernel whose weights go straight to registers (arrangement 5; a K split of 2 selects its 128-channel workgroups):
+# 6 to 8 units per workgroup, a last workgroup that is not full, one channel chunk (first and last at once), two and more,
+# ragged maps, both widths of a workgroup.
+DEEP_CASES = [
+    (22, 30, 32, 256, (5, 8, -1, -1)), (22, 30, 64, 256, (5, 7, -1, -1)), (13, 17, 96, 256, (5, 6, -1, -1)),
+    (14, 14, 128, 512, (5, 8, 2, -1)), (37, 41, 32, 128, (5, 7, -1, -1)), (5, 3, 160, 384, (5, 6, -1, -1)),
+    (45, 61, 64, 128, (5, 8, -1, -1)),
+]
+
+
+@pytest.mark.parametrize("cached", [False, True])
+@pytest.mark.parametrize("case", DEEP_CASES)
+def test_deep_conv_kernel_shapes(oracle, case, cached):
+    if cached and case[1] < 8:
+        pytest.skip("the rectangles of the cached case need a wider map")
+    test_fast_conv_kernel_shapes(oracle, case, True, cached)
+
+
+def test_deep_conv_kernel_bits_and_borders():
+    """The same sums in the same order as the kernel it stands in for (chunks of 32 channels, K not split), leaky and no
+    activation, no bias, infinities in the padding's neighbours and a NaN: the same bits."""
+    n, H, W, cin, cout = 3, 23, 21, 96, 256
+    g = torch.Generator(DEV)
+    g.manual_seed(5)
+    x = torch.randn((n, H, W, cin), generator=g, device=DEV).bfloat16()
+    x[0, 0, 0, 5], x[1, H - 1, W - 1, 7], x[2, 4, 4, 0] = float("inf"), float("-inf"), float("nan")
+    w = (torch.randn((cout, 3, 3, cin), generator=g, device=DEV) * 0.05).bfloat16()
+    b = torch.randn(cout, generator=g, device=DEV)
+    for relu, bias in ((0, b), (1, b), (2, None)):
+        layer = dict(_layer(cin, cout, 3, 1, 1, True), relu=relu)
+        wp = binding.dc_pack_conv_weights(layer, w)
+        out = {}
+        for tuning in ((1, 8, 1, 0), (5, 8, -1, -1), (5, 7, -1, -1), (5, 6, 2, -1)):
+            print(f"[deep bits] relu={relu} {tuning}", flush=True)
+            binding.dc_conv_tuning(*tuning)
+            try:
+                out[tuning] = binding.dc_cached_conv_layer(layer, x, w, bias, packed=wp).view(torch.int16)
+            finally:
+                binding.dc_conv_tuning()
+        base = out.pop((1, 8, 1, 0))
+        for tuning, got in out.items():
+            assert torch.equal(got, base), tuning

@@ -1402,3 +1402,21 @@ def test_kernel_of_a_1x1_layer_follows_the_size_of_its_map(cout, kernel):
             torch.cuda.synchronize()
             assert runner.last_full == (t == 0)
             assert binding.conv_kernel_name(runner.layer_stats()["kernel_id"][0]) == want, t
+
+
+@pytest.mark.parametrize("units,width", [(8, -1), (7, 2)])
+def test_torus_through_the_kernel_with_weights_in_registers(oracle, units, width):
+    """Tensors on a torus, lists built on the GPU, through the bf16 kernel whose weights go straight to registers."""
+    video = np.stack([synth.panning_video(7100 + s, n_frames=5, H=96, W=96, fg=((24, 24),), margin=32) for s in range(3)])
+    layers = [dict(type=synth.CONV, k=3, s=1, p=1, cin=3, cout=64, relu=1, in0=0, in1=-1),
+              dict(type=synth.CONV, k=3, s=1, p=1, cin=64, cout=256, relu=1, in0=1, in1=-1),
+              dict(type=synth.CONV, k=3, s=1, p=1, cin=256, cout=128, relu=1, in0=2, in1=-1),
+              dict(type=synth.CONV, k=3, s=1, p=1, cin=128, cout=256, relu=1, in0=3, in1=-1)]
+    binding.dc_conv_tuning(5, units, width)
+    try:
+        runner, reuse = _run_one(oracle, layers, video, 16, 16, True, device_plan=True, exact_masks=True, torus=True, resets=(3,),
+                                 bias_scale=0.02)
+        names = [binding.conv_kernel_name(k) for k in runner.layer_stats()["kernel_id"][1:]]
+    finally:
+        binding.dc_conv_tuning()
+    assert names == [f"conv_deep_kernel<{2 if width == 2 or c == 128 else 4}, {units}>" for c in (256, 128, 256)] and max(reuse) > 0.3

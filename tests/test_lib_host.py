@@ -447,3 +447,15 @@ def test_a_workspace_that_cannot_be_made_does_not_count_as_one(monkeypatch):
     assert second is not first                   # two in turn again
     pool.give(second)
     assert pool.made == len(pool.free) == pool.KEPT == 2
+
+
+def test_kernel_names_of_the_kernel_with_weights_in_registers():
+    """Ids from 416 on: four or two wavefronts, 6 to 8 units; every other id is an error."""
+    built = {}
+    for kid in range(402, 448):
+        buf = C.create_string_buffer(160)
+        rc = binding.lib().dc_conv_kernel_name(kid, buf, 160)
+        assert rc in (0, -1), (kid, rc)
+        if rc == 0:
+            built[kid] = buf.value.decode()
+    assert built == {416 + (8 if nw == 2 else 0) + g - 1: f"conv_deep_kernel<{nw}, {g}>" for nw in (4, 2) for g in (6, 7, 8)}
