@@ -1438,6 +1438,179 @@ __global__ __launch_bounds__(256) void conv_stem_kernel(ConvParams P) { conv_fir
 template <typename T>
 __global__ __launch_bounds__(256) void conv_stem11_kernel(ConvParams P) { conv_first_body<T, 1, 11, 4, 1>(P); }
 
+// ---- bf16 stems whose input pixels hold at most four channels ---------------------------------------------------
+// Tensor 0 of a stack has eight channels per pixel (one 16-byte vector), of which a frame fills three or four; the rest are
+// exact zeros.  The kernels above multiply all eight (11x11: 33 MFMAs per unit and 16 channels, 7x7: 14), and every block
+// of 16 or 32 channels fetches every input vector again: AlexNet's first layer loads 33 KiB per unit and block.  Here the
+// unit's patch is brought into LDS once, four channels a pixel, for all channels of the workgroup: a fragment of eight
+// elements is two taps, K is 17 groups (7x7: 7), and a wavefront keeps the weights of 16 NB channels in registers.
+//   workgroup = NU units at a time, NWC wavefronts of 16 NB channels each per unit; persistent, walks the unit list
+//   K groups  = kernel rows of PPR tap pairs: 4 pairs (7x7) are one group; 6 pairs (11x11): rows in twos, group 0 and 1 the
+//               first four pairs of each, group 2 the other two pairs of both; the last row alone takes two groups
+// LDS rows are RS bytes apart, chosen so that the four rows a read touches fall into different banks.
+// Channels four to seven of the weights meet zeros and are not read.
+// 227x227 11x11 -> 96 on 64 streams: 91.4 -> 28.1 us (37 MB out and 53 MB in: 18 at the copy's rate), 224x224 7x7 -> 64 on 16
+// streams 23.1 -> 16.0.  What bounds it now: a step's chain of load, LDS write, barrier and reads at two workgroups per CU.
+template <int K, int S, int NB, int NWC, int NU>
+__global__ __launch_bounds__(NWC * NU * 64) void conv_stem4_kernel(ConvParams P) {
+    typedef __hip_bfloat16 T;
+    typedef Frag<T> F;
+    typedef F::vec vec;
+    constexpr int PPR = (K + 1) / 2, PH = 3 * S + K, PWX = 3 * S + 2 * PPR, RS = K == 11 ? 224 : 160;
+    constexpr int NG = PPR == 4 ? K : K / 2 * 3 + 2;
+    constexpr int GT = NWC * 64, NPT = (PH * PWX + GT - 1) / GT, PATCH = PH * RS;
+    static_assert((PPR == 4 || (PPR == 6 && K % 2)) && PWX * 8 <= RS, "shape");
+
+    __shared__ __align__(16) unsigned char smem[NU * 2 * PATCH];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l16 = lane & 15, q = lane >> 4;
+    const int wave_u = wave / NWC, wave_c = wave % NWC;
+    const int n0 = ((int)blockIdx.y * NWC + wave_c) * (NB * 16);
+    const __amdgpu_buffer_rsrc_t in_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(P.in), 0, P.in_bytes, kBufferFlags);
+    const __amdgpu_buffer_rsrc_t w_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(P.w), 0, P.w_bytes, kBufferFlags);
+
+    // group g, quarter q: kernel row and tap pair
+    auto row_of = [&](int g) { return PPR == 4 ? g : g < NG - 2 ? g / 3 * 2 + (g % 3 == 2 ? q >> 1 : g % 3) : K - 1; };
+    auto pair_of = [&](int g) { return PPR == 4 ? q : g < NG - 2 ? (g % 3 == 2 ? 4 + (q & 1) : q) : g == NG - 2 ? q : 4 + q; };
+    vec wv[NG][NB];
+#pragma unroll
+    for (int g = 0; g < NG; ++g)
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+            // row l16 of block j: channel (l16 / 4) * 4 NB + 4 j + l16 % 4, so that a lane ends with 4 NB consecutive ones
+            const int co = n0 + (l16 >> 2) * (4 * NB) + j * 4 + (l16 & 3);
+            uintx4 v;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int tap = 2 * pair_of(g) + h;
+                const uint32_t off = tap < K ? (uint32_t)((co * (K * K) + row_of(g) * K + tap) * 16) : kOob;
+                const uintx2 d = __builtin_bit_cast(uintx2, __builtin_amdgcn_raw_buffer_load_b64(w_rsrc, off, 0, 0));
+                v[2 * h] = d[0]; v[2 * h + 1] = d[1];
+            }
+            wv[g][j] = __builtin_bit_cast(vec, v);
+        }
+    const int chan = n0 + 4 * NB * q;
+    floatx4 bias[NB];
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+        bias[j] = P.bias ? *reinterpret_cast<const floatx4*>(P.bias + chan + j * 4) : floatx4{0.f, 0.f, 0.f, 0.f};
+    const bool relu = P.relu != 0;
+
+    // the pixels of a patch that this thread brings: row and column in the patch, byte offset in LDS
+    const int gt = wave_c * 64 + lane;
+    int ppy[NPT], ppx[NPT];
+#pragma unroll
+    for (int i = 0; i < NPT; ++i) {
+        const int at = gt + i * GT;
+        ppy[i] = at / PWX;
+        ppx[i] = at - ppy[i] * PWX;
+    }
+    const int n_units = unit_count(P), per = P.units_x * P.units_y;
+    struct UnitPos { int stream, uy, ux, mixed; };     // mixed == -1: no such unit
+    auto locate = [&](int u) {
+        UnitPos r{0, 0, 0, -1};
+        if (u >= n_units) return r;
+        if (P.units) {
+            const TileDev t = P.units[u];
+            r.stream = t.stream; r.uy = t.ty; r.ux = t.tx; r.mixed = t.reuse_mask & 0xffff;
+        } else {
+            r.stream = fast_div_any(u, P.npix_magic, per);
+            const int rem = u - r.stream * per;
+            r.uy = fast_div(rem, P.pw_magic); r.ux = rem - r.uy * P.units_x;
+            r.mixed = 0;
+        }
+        return r;
+    };
+    uintx2 px[NPT];
+    auto load_px = [&](const UnitPos& pos) {
+        const int y0 = pos.uy * (4 * S) - P.p, x0 = pos.ux * (4 * S) - P.p;
+#pragma unroll
+        for (int i = 0; i < NPT; ++i) {
+            const int iy = y0 + ppy[i], ix = x0 + ppx[i];
+            const bool ok = pos.mixed >= 0 && (unsigned)iy < (unsigned)P.Hin && (unsigned)ix < (unsigned)P.Win;
+            const uint32_t off = ok ? (uint32_t)(((pos.stream * P.Hin + iy) * P.Win + ix) * 16) : kOob;
+            px[i] = __builtin_bit_cast(uintx2, __builtin_amdgcn_raw_buffer_load_b64(in_rsrc, off, 0, 0));
+        }
+    };
+    // read side: quarter q reads pair q of a row, or (group 2 of two rows) pair 4 + q % 2 of row q / 2
+    const int xaddr = (l16 >> 2) * (S * RS) + (l16 & 3) * (S * 8) + q * 16;
+    const int xaddr3 = (l16 >> 2) * (S * RS) + (l16 & 3) * (S * 8) + (4 + (q & 1)) * 16, xaddr2 = xaddr3 + (q >> 1) * RS;
+
+    const int step = (int)gridDim.x * NU, first = (int)blockIdx.x * NU;
+    if (first >= n_units) return;                      // the whole workgroup, before any barrier
+    int u = first + wave_u;
+    UnitPos pos = locate(u), pos_next = locate(u + step);
+    load_px(pos);
+    int buf = 0;
+    for (int base = first;; base += step, buf ^= 1) {
+        unsigned char* const patch = smem + (wave_u * 2 + buf) * PATCH;
+#pragma unroll
+        for (int i = 0; i < NPT; ++i)
+            if ((i + 1) * GT <= PH * PWX || gt + i * GT < PH * PWX) *reinterpret_cast<uintx2*>(patch + ppy[i] * RS + ppx[i] * 8) = px[i];
+        if constexpr (NWC > 1) lds_barrier();      // the patch is in LDS; nobody reads the other buffer any more
+        const bool more = base + step < n_units;
+        UnitPos after{0, 0, 0, -1};
+        if (more) {
+            load_px(pos_next);
+            after = locate(u + 2 * step);
+        }
+        floatx4 acc[NB];
+#pragma unroll
+        for (int j = 0; j < NB; ++j) acc[j] = bias[j];
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            const unsigned char* xp = patch;
+            if (PPR == 4) xp += xaddr + g * RS;
+            else if (g < NG - 2) xp += g % 3 == 2 ? xaddr2 + g / 3 * 2 * RS : xaddr + (g / 3 * 2 + g % 3) * RS;
+            else xp += (g == NG - 2 ? xaddr : xaddr3) + (K - 1) * RS;   // (the weights of the last group's quarters 2 and 3 are zero)
+            const vec x = *reinterpret_cast<const vec*>(xp);
+#pragma unroll
+            for (int j = 0; j < NB; ++j) F::mma1(wv[g][j], x, acc[j], 0);
+        }
+        const int y = pos.uy * 4 + (l16 >> 2), x = pos.ux * 4 + (l16 & 3);
+        if (pos.mixed >= 0 && y < P.Hout && x < P.Wout && !((pos.mixed >> l16) & 1)) {      // a reusable pixel holds the cached value
+            int yo = y, xo = x;
+            if (P.out_origin) {
+                xo = torus_wrap(x, P.out_origin[(size_t)pos.stream * P.origin_stride], P.Wout);
+                yo = torus_wrap(y, P.out_origin[(size_t)pos.stream * P.origin_stride + 1], P.Hout);
+            }
+            T* out = reinterpret_cast<T*>(P.out) + ((pos.stream * P.Hout + yo) * P.Wout + xo) * P.Cout + chan;
+            uint32_t v[2 * NB];
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+                if (relu) activate4(acc[j], P.relu);
+                v[2 * j] = (uint32_t)F::bits(acc[j][0]) | ((uint32_t)F::bits(acc[j][1]) << 16);
+                v[2 * j + 1] = (uint32_t)F::bits(acc[j][2]) | ((uint32_t)F::bits(acc[j][3]) << 16);
+            }
+#pragma unroll
+            for (int j = 0; j < NB; j += 2)
+                *reinterpret_cast<uintx4*>(out + j * 4) = uintx4{v[2 * j], v[2 * j + 1], v[2 * j + 2], v[2 * j + 3]};
+        }
+        if (!more) break;
+        u += step;
+        pos = pos_next;
+        pos_next = after;
+    }
+}
+
+// Workgroups of a launch: two per CU, which is what the registers allow (11x11: 256 / 512 / 768 / 1024 of them 42 / 28 / 38 /
+// 35 us on 64 streams, 7x7 on 16 streams 18 / 16 / 19 / 21: every further one loads its weights again).
+constexpr int kStem4Wgs = 512;
+constexpr int kStem4Id = 432;         // kernel ids: 7x7, then 11x11 with 1, 2, 3 wavefronts a unit
+// Wavefronts per unit of conv_stem4_kernel, 0: not its shape.
+int stem4_waves(const ConvLaunch& c) {
+    if (c.dtype != DC_BF16 || c.c_frame < 1 || c.c_frame > 4 || c.Cin != 8) return 0;
+    if (c.k == 7 && c.s == 2) return c.Cout % 64 == 0 ? 1 : 0;
+    return c.k == 11 && c.s == 4 ? (c.Cout % 96 == 0 ? 3 : c.Cout % 64 == 0 ? 2 : c.Cout % 32 == 0 ? 1 : 0) : 0;
+}
+hipError_t stem4_launch(int k, int nwc, dim3 grid, hipStream_t st, const ConvParams& P) {
+    if (k == 7) hipLaunchKernelGGL((conv_stem4_kernel<7, 2, 4, 1, 4>), grid, dim3(256), 0, st, P);
+    else if (nwc == 3) hipLaunchKernelGGL((conv_stem4_kernel<11, 4, 2, 3, 1>), grid, dim3(192), 0, st, P);
+    else if (nwc == 2) hipLaunchKernelGGL((conv_stem4_kernel<11, 4, 2, 2, 1>), grid, dim3(128), 0, st, P);
+    else hipLaunchKernelGGL((conv_stem4_kernel<11, 4, 2, 1, 1>), grid, dim3(64), 0, st, P);
+    return hipGetLastError();
+}
+
 template <typename T>
 hipError_t first_launch(int k, int nb, dim3 grid, hipStream_t st, const ConvParams& P) {
     const size_t lds = P.out_origin ? (size_t)P.n_streams * sizeof(int2) : 0;      // the table of origins
@@ -1667,6 +1840,7 @@ FastChoice choose_fast(const ConvLaunch& c, long n_units, long n_cap, size_t scr
 // Ids 64.. name the instantiations of this file: 64 + ((bf16 * 2 + kci) * 8 + UPW - 1), 96.. the first-layer kernel,
 // 110.. the wide arrangement.
 bool conv_kernel_built(int id) {
+    if (id >= kStem4Id) return id < kStem4Id + 4;
     if (id >= kDeepId) return id < kDeepId + 16 && id % 8 + 1 >= kDeepMinUnits;
     return id >= kPwSplitId ? id < kPwSplitId + 2 : id >= 132 && (id - 132) / 8 < kNumGeom && fast_built(5, true, (id - 132) / 8, 0, (id - 132) % 8 + 1);
 }
@@ -1676,6 +1850,11 @@ void conv_fast_kernel_name(int id, char* buf, size_t n) {
     if (id == 129) { snprintf(buf, n, "conv_fast_kernel<__hip_bfloat16, 3, 32, 3, 6, 2, 4>"); return; }     // the tall arrangement
     if (id == 127 || id == 128 || id == 108 || id == 109) {      // 108 + bf16 (64 x 64 tile), 127 + bf16 (128 x 128): conv_pw_kernel (1x1)
         snprintf(buf, n, "conv_pw_kernel<%s, %d>", id == 109 || id == 128 ? "__hip_bfloat16" : "float", id >= 127 ? 4 : 2);
+        return;
+    }
+    if (id >= kStem4Id) {
+        if (id == kStem4Id) snprintf(buf, n, "conv_stem4_kernel<7, 2, 4, 1, 4>");
+        else snprintf(buf, n, "conv_stem4_kernel<11, 4, 2, %d, 1>", id - kStem4Id);
         return;
     }
     if (id >= kDeepId) {
@@ -1830,6 +2009,13 @@ bool launch_conv_fast(const ConvLaunch& c, long n_cap, long n_units, hipStream_t
                 *c.kernel_id = c.k == 11 ? 106 + (c.dtype == DC_BF16 ? 1 : 0)
                              : c.k == 7 ? 102 + (c.dtype == DC_BF16 ? 2 : 0) + (nb == 2 ? 1 : 0)
                                         : 96 + (c.dtype == DC_BF16 ? 3 : 0) + (nb == 4 ? 2 : (nb == 2 ? 1 : 0));
+            if (const int nwc = stem4_waves(c)) {
+                const int gy = c.Cout / (c.k == 7 ? 64 : 32 * nwc);
+                const long nu = c.k == 7 ? 4 : 1, wgs = std::min((n_cap + nu - 1) / nu, std::max(1L, (long)kStem4Wgs / gy));
+                if (c.kernel_id) *c.kernel_id = kStem4Id + (c.k == 7 ? 0 : nwc);
+                *err = stem4_launch(c.k, nwc, dim3((unsigned)wgs, (unsigned)gy), st, P);
+                return true;
+            }
             const dim3 grid((unsigned)wgx, (unsigned)(c.Cout / (16 * nb)));
             *err = c.dtype == DC_BF16 ? first_launch<__hip_bfloat16>(c.k, nb, grid, st, P) : first_launch<float>(c.k, nb, grid, st, P);
             return true;

@@ -87,6 +87,7 @@ struct ConvLaunch {
     const float* bias;
     void* out;
     int n_streams, Hin, Win, Cin, Hout, Wout, Cout, k, s, p, relu, dtype;
+    int c_frame = 0;                  // channels of a pixel that can be other than zero (tensor 0 of a stack: the frame's); 0: all
     int kw = 0, pw = 0, dil = 1;      // kw > 0: k rows x kw columns, paddings p / pw; dil: distance between taps
     // Tensors on a torus (optional, device): (ox, oy) of stream s at origin[s * origin_stride + 0 / 1]; nullptr: none.
     // Only the 3x3 stride-1 GEMM kernel and the first-layer kernels take them (the launch fails otherwise).
@@ -386,7 +387,7 @@ int run_conv_planned(const dc_layer& l, const void* in, const void* w, const flo
                      bool copy_done = false, void* scratch = nullptr, size_t scratch_bytes = 0,
                      const void* w_packed = nullptr, const TileDev* dev_tiles = nullptr, int dev_capacity = 0,
                      const int* dev_count = nullptr, long dev_hint = -1, const int32_t* in_origin = nullptr,
-                     const int32_t* out_origin = nullptr, int origin_stride = 0);
+                     const int32_t* out_origin = nullptr, int origin_stride = 0, int c_frame = 0);
 
 
 }  // namespace dc

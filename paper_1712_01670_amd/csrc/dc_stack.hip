@@ -1209,7 +1209,7 @@ int StackCall::emit_layer(int i, hipStream_t st) {
                                     devplan ? reinterpret_cast<const TileDev*>(pd.area + P.dl.convs[c].list_off) : nullptr,
                                     devplan ? n_streams * P.dl.convs[c].units_x * P.dl.convs[c].units_y : 0,
                                     devplan ? pd.n_units + c : nullptr, devplan ? unit_hint[c] : -1, origin_of(a), origin_of(t),
-                                    2 * (n_layers + 1));
+                                    2 * (n_layers + 1), a == 0 ? C : 0);
         }
         case DC_MAXPOOL:
             if (origin_of(a))            // its input lies on a torus, and with the cache its output too

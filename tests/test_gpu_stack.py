@@ -1420,3 +1420,19 @@ def test_torus_through_the_kernel_with_weights_in_registers(oracle, units, width
     finally:
         binding.dc_conv_tuning()
     assert names == [f"conv_deep_kernel<{2 if width == 2 or c == 128 else 4}, {units}>" for c in (256, 128, 256)] and max(reuse) > 0.3
+
+
+# Stems of bf16 stacks, whose input patch goes through LDS with four channels a pixel: 7x7 and the three widths of 11x11, frames
+# of three and four channels, more units than a launch has workgroups (the walk over the list) and fewer, ragged maps.
+@pytest.mark.parametrize("k,s,p,cout,C,n,H,W,kid", [
+    (7, 2, 3, 64, 3, 3, 224, 224, 0), (7, 2, 3, 128, 4, 1, 61, 83, 0), (7, 2, 0, 64, 3, 2, 64, 48, 0),
+    (11, 4, 0, 96, 3, 4, 227, 227, 3), (11, 4, 2, 192, 4, 1, 70, 99, 3), (11, 4, 2, 64, 3, 2, 64, 80, 2), (11, 4, 5, 32, 3, 3, 96, 64, 1)])
+def test_stems_with_four_channels_a_pixel(oracle, k, s, p, cout, C, n, H, W, kid):
+    video = np.stack([synth.panning_video(7300 + i, n_frames=3, H=H, W=W, fg=((24, 24),), margin=32) for i in range(n)])
+    if C == 4:
+        video = np.concatenate([video, video[..., :1] ^ 85], axis=-1)
+    layers = [dict(type=synth.CONV, k=k, s=s, p=p, cin=C, cout=cout, relu=1, in0=0, in1=-1)]
+    runner, reuse = _run_one(oracle, layers, video, 16, 8, True, device_plan=True, exact_masks=True, bias_scale=0.1)
+    assert max(reuse) > 0.2
+    assert binding.conv_kernel_name(runner.layer_stats()["kernel_id"][0]) == \
+        ("conv_stem4_kernel<7, 2, 4, 1, 4>" if k == 7 else f"conv_stem4_kernel<11, 4, 2, {kid}, 1>")
