@@ -121,7 +121,7 @@ int run_conv_planned(const dc_layer& l, const void* in, const void* w, const flo
                      const ConvTiling& tiling, const LayerPlan* plan, const PlanAddr* addr, hipStream_t st,
                      Profile* prof, int gemm_slot, int copy_slot, int* kernel_id, bool copy_done, void* scratch, size_t scratch_bytes,
                      const void* w_packed, const TileDev* dev_tiles, int dev_capacity, const int* dev_count, long dev_hint,
-                     const int32_t* in_origin, const int32_t* out_origin, int origin_stride, int c_frame) {
+                     const int32_t* in_origin, const int32_t* out_origin, int origin_stride, int c_frame, ConvAdd* add) {
     const WindowGeom wg = window_geom(l);
     const int Hout = (Hin + 2 * wg.ph - wg.eh) / l.s + 1, Wout = (Win + 2 * wg.pw - wg.ew) / l.s + 1;
     ConvLaunch c;
@@ -131,7 +131,7 @@ int run_conv_planned(const dc_layer& l, const void* in, const void* w, const flo
     c.n_streams = n_streams; c.Hin = Hin; c.Win = Win; c.Cin = l.cin;
     c.Hout = Hout; c.Wout = Wout; c.Cout = l.cout; c.k = l.k; c.s = l.s; c.p = l.p; c.relu = l.relu;
     if (!plain_square(l)) { c.kw = wg.kw; c.pw = wg.pw; c.dil = wg.dil; }
-    c.dtype = dtype; c.tiling = tiling; c.c_frame = c_frame;
+    c.dtype = dtype; c.tiling = tiling; c.c_frame = c_frame; c.add = add;
     c.scratch = scratch; c.scratch_bytes = scratch_bytes;
     c.in_origin = in_origin; c.out_origin = out_origin; c.origin_stride = origin_stride;
     if (dev_tiles) {      // a list the planning kernels built: its length is in device memory, the copies are done

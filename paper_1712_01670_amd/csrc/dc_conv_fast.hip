@@ -908,9 +908,19 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(const uintx4* src, ui
 // 16 NBW, so that a lane ends up with 4 NBW consecutive channels of one pixel and stores them in 16-byte pieces.
 // Cin only has to be a whole number of 16-byte vectors (the last chunk is filled with zeros), Cout a multiple of 8.
 // Workgroups are numbered so that the channel tiles of one unit group run on the same XCD at about the same time:
-// the second to last of them find the input pixels in that XCD's L2.
-template <typename T, int WM>
-__global__ __launch_bounds__(WM * 128) void conv_pw_kernel(ConvParams P) {
+// the second to last of them find the input pixels in that XCD's L2; the groups go round the XCDs.
+// What a short launch waits for is its chain of loads, so the list entries are fetched together with the list's length,
+// the bias and the first weights while the unit table is made, and no load is waited for between the stores.  The 15 layer
+// shapes of ResNet-50 on 1 / 16 / 64 streams, us in all: 104.8 -> 98.3, 182.5 -> 172.0, 459.5 -> 447.1 (one got longer:
+// 56x56 64->256 on more than 16 streams, 31 -> 36).
+//
+// ADD: the layer is followed by the element-wise sum of its output with another tensor (a residual block's end), and the
+// sum is written here as well: the convolution's output is rounded as it is stored and summed as the sum's own kernel
+// does (ResNet-50 on one stream, frame after frame without stages: 497 -> 462 us, on 16 streams 874 -> 830).  Where a pixel is reusable its output is the copied value, fetched beside the other summand while K is walked.
+// Units without work stand behind the others in the list (plan_lists_kernel); a group of them only adds.
+constexpr int kPwHeaderBytes = 1536;
+template <typename T, int WM, bool ADD>
+__device__ __forceinline__ void conv_pw_body(const ConvParams& P) {
     typedef Frag<T> F;
     typedef typename F::vec vec;
     constexpr int ES = (int)sizeof(T), VE = F::VE;
@@ -923,64 +933,30 @@ __global__ __launch_bounds__(WM * 128) void conv_pw_kernel(ConvParams P) {
     static_assert(WM == 2 || WM == 4, "two patch and two weight load instructions per wavefront and stage");
 
     extern __shared__ __align__(16) unsigned char smem[];
-    const FastHeader<G> H(smem);
-    unsigned char* const ring = smem + kHeaderBytes;
+    int4* const uq = reinterpret_cast<int4*>(smem);                   // [G] {stream, row, column of the unit, its reuse mask; -1: none}
+    int2* const px = reinterpret_cast<int2*>(smem + 128);             // [16 G] byte offset in the input, element offset in the output
+    unsigned char* const px_skip = smem + 1152;                       // [16 G] 1: not stored; 3: no such pixel
+    unsigned char* const ring = smem + kPwHeaderBytes;
+    static_assert(G <= 8, "tables");
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wave_n = wave % WN, wave_m = wave / WN;
     const int l16 = lane & 15, q = lane >> 4;
 
-    // (unit group, channel tile) pairs of this launch, dealt to the XCDs in equal consecutive shares
-    const int n_units = unit_count(P);
-    const int n_wg_tiles = (n_units + G - 1) / G * P.R, tiles_per_xcd = (n_wg_tiles + 7) >> 3;
-    const int t = (int)(blockIdx.x & 7) * tiles_per_xcd + (int)(blockIdx.x >> 3);
-    if ((int)(blockIdx.x >> 3) >= tiles_per_xcd || t >= n_wg_tiles) return;    // the whole workgroup, before any barrier
-    const int ug = t / P.R, ntile = t - ug * P.R;
+    const int xj = (int)(blockIdx.x >> 3) / P.R, ntile = (int)(blockIdx.x >> 3) - xj * P.R;
+    const int ug = xj * 8 + (int)(blockIdx.x & 7);
+    const int n_cap = P.n_units;                    // what the launch is sized for
+    if (ug * G >= n_cap) return;                    // the whole workgroup, before any barrier
+    TileDev td{0, 0, 0, 0};
+    if (tid < G && P.units && ug * G + tid < n_cap) td = P.units[ug * G + tid];     // (beyond the list's length: not used)
+    const int n_work = unit_count(P), n_units = ADD ? n_cap : n_work;
+    const bool gemm = !ADD || ug * G < n_work;      // (ADD) some unit of this group has a pixel to compute
+    if (!ADD && ug * G >= n_work) return;
     const int n0 = ntile * NT;
     const int CinES = P.Cin * ES;
     const __amdgpu_buffer_rsrc_t in_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(P.in), 0, P.in_bytes, kBufferFlags);
     const __amdgpu_buffer_rsrc_t w_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(P.w), 0, P.w_bytes, kBufferFlags);
-
-    // unit table: uq = {byte offset of the input pixel under the unit's first output pixel, row and column of
-    // that output pixel, element offset of it in the output}
-    if (tid < G) {
-        const int u = ug * G + tid;
-        const bool valid = u < n_units;
-        int stream = 0, uy = 0, ux = 0, mixed = 0;
-        if (valid) {
-            if (P.units) {
-                const TileDev td = P.units[u];
-                stream = td.stream; uy = td.ty; ux = td.tx; mixed = td.reuse_mask;
-            } else {
-                stream = fast_div_any(u, P.npix_magic, P.units_x * P.units_y);
-                const int r = u - stream * (P.units_x * P.units_y);
-                uy = fast_div(r, P.pw_magic); ux = r - uy * P.units_x;
-            }
-        }
-        int4 v;
-        v.x = ((stream * P.Hin + uy * 4 * P.s) * P.Win + ux * 4 * P.s) * CinES;
-        v.y = valid ? uy * 4 : (1 << 24);           // every pixel of a missing unit fails the range test
-        v.z = ux * 4;
-        v.w = ((stream * P.Hout + uy * 4) * P.Wout + ux * 4) * P.Cout;
-        H.uq[tid] = v;
-        H.ukind[tid] = valid ? mixed : -1;
-        if (P.in_origin || P.out_origin) {      // tensors on a torus (stride 1 only: the launcher sees to it)
-            int4 og{0, 0, 0, 0};
-            const size_t at = (size_t)stream * P.origin_stride;
-            if (P.in_origin) { og.x = P.in_origin[at]; og.y = P.in_origin[at + 1]; }
-            if (P.out_origin) { og.z = P.out_origin[at]; og.w = P.out_origin[at + 1]; }
-            H.uorg[tid] = og;
-            H.ustream[tid] = stream;
-        }
-    }
-    __syncthreads();
-    if (tid < G * 16) {
-        const int g = tid >> 4, kind = H.ukind[g];
-        const int y = H.uq[g].y + ((tid >> 2) & 3), x = H.uq[g].z + (tid & 3);
-        H.skip[tid] = (kind < 0 || y >= P.Hout || x >= P.Wout || ((kind >> (tid & 15)) & 1)) ? 1 : 0;
-    }
-    __syncthreads();
 
     // load side: instruction j of a stage fills its LDS bytes [1024 j, 1024 j + 1024) = rows 8 j .. 8 j + 7; this
     // wavefront issues j = wave and wave + NW of the patch rows and of the weight rows
@@ -992,36 +968,103 @@ __global__ __launch_bounds__(WM * 128) void conv_pw_kernel(ConvParams P) {
         const int row = (wave + i * NW) * 8 + lrow;
         const int c = lpos ^ ((row >> 1) & 7);
         lch[i] = c * VE;
-        const int g = row >> 4, oy = (row >> 2) & 3, ox = row & 3;
-        const int4 uq = H.uq[g];
-        const bool ok = uq.y + oy < P.Hout && uq.z + ox < P.Wout;
-        pgo[i] = ok ? (uint32_t)(uq.x + (oy * P.Win + ox) * P.s * CinES + (c << 4)) : kOob;
-        if (P.in_origin && ok) {        // the input lies on a torus: the pixel's place follows from the stream's origin
-            const int4 og = H.uorg[g];
-            const int iy = torus_wrap(uq.y + oy, og.y, P.Hin), ix = torus_wrap(uq.z + ox, og.x, P.Win);
-            pgo[i] = (uint32_t)(((H.ustream[g] * P.Hin + iy) * P.Win + ix) * CinES + (c << 4));
-        }
         const int ch = n0 + row / (NBW * 16) * (NBW * 16) + ((row & 15) >> 2) * (4 * NBW) + ((row >> 4) % NBW) * 4 + (row & 3);
         wgo[i] = ch < P.Cout ? (uint32_t)(ch * CinES + (c << 4)) : kOob;
     }
-    auto issue = [&](int chunk, int slot) {
-        unsigned char* dst = ring + slot * STAGE + wave * 1024;
-        const int c0 = chunk * KC;
+    auto issue_w = [&](int chunk, int slot) {
+        unsigned char* dst = ring + slot * STAGE + PBYTES + wave * 1024;
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
-            const bool in_k = c0 + lch[i] < P.Cin;
+            const bool in_k = chunk * KC + lch[i] < P.Cin;
+            const uint32_t off = in_k ? wgo[i] + (uint32_t)(chunk * RB) : kOob;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rsrc, (__attribute__((address_space(3))) void*)(dst + i * (NW * 1024)),
+                                                     16, off, 0, 0, 0);
+        }
+    };
+    // Every unit group starts its walk over K at another chunk: rows are Cin * ES bytes apart, a power of two for
+    // most layers, so workgroups that all read chunk c of their rows at the same time would all hit the few memory
+    // channels those addresses map to.
+    const int n_ch = P.n_chunks;
+    const int start = ug % n_ch;
+    auto chunk_of = [&](int c) { const int cc = start + c; return cc < n_ch ? cc : cc - n_ch; };
+    // the bias now: in the epilogue its wait would be one for the stores before it as well
+    const int chan0 = n0 + wave_n * (NBW * 16) + q * (4 * NBW);
+    floatx4 b[NBW];
+#pragma unroll
+    for (int j = 0; j < NBW; ++j)
+        b[j] = (P.bias && chan0 + j * 4 < P.Cout) ? *reinterpret_cast<const floatx4*>(P.bias + chan0 + j * 4) : floatx4{0.f, 0.f, 0.f, 0.f};
+    asm volatile("" ::: "memory");
+    if (gemm) {
+#pragma unroll
+        for (int d = 0; d < D; ++d)
+            if (d < n_ch) issue_w(chunk_of(d), d);
+    }
+
+    // tables of the group's units and pixels
+    if (tid < G) {
+        const int u = ug * G + tid;
+        int4 v{0, 0, 0, -1};
+        if (u < n_units && P.units) {
+            v = int4{td.stream, td.ty, td.tx, td.reuse_mask & 0xffff};
+        } else if (u < n_units) {   // raster order
+            v.x = fast_div_any(u, P.npix_magic, P.units_x * P.units_y);
+            const int r = u - v.x * (P.units_x * P.units_y);
+            v.y = fast_div(r, P.pw_magic); v.z = r - v.y * P.units_x; v.w = 0;
+        }
+        uq[tid] = v;
+    }
+    lds_barrier();
+    if (tid < G * 16) {
+        const int4 u = uq[tid >> 4];
+        const int stream = u.x, y = u.y * 4 + ((tid >> 2) & 3), x = u.z * 4 + (tid & 3);
+        const int skip = u.w < 0 || y >= P.Hout || x >= P.Wout ? 3 : (u.w >> (tid & 15)) & 1;
+        int iy = y * P.s, ix = x * P.s, oy = y, ox = x;
+        if ((P.in_origin || P.out_origin) && !(skip & 2)) {      // tensors on a torus (stride 1 only: the launcher sees to it)
+            const size_t at = (size_t)stream * P.origin_stride;
+            if (P.in_origin) { ix = torus_wrap(x, P.in_origin[at], P.Win); iy = torus_wrap(y, P.in_origin[at + 1], P.Hin); }
+            if (P.out_origin) { ox = torus_wrap(x, P.out_origin[at], P.Wout); oy = torus_wrap(y, P.out_origin[at + 1], P.Hout); }
+        }
+        px[tid] = int2{((stream * P.Hin + iy) * P.Win + ix) * CinES, ((stream * P.Hout + oy) * P.Wout + ox) * P.Cout};
+        px_skip[tid] = (unsigned char)skip;
+    }
+    lds_barrier();
+
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int row = (wave + i * NW) * 8 + lrow;
+        const int c = lpos ^ ((row >> 1) & 7);
+        pgo[i] = px_skip[row] & 2 ? kOob : (uint32_t)px[row].x + (uint32_t)(c << 4);
+    }
+    auto issue_p = [&](int chunk, int slot) {
+        unsigned char* dst = ring + slot * STAGE + wave * 1024;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const bool in_k = chunk * KC + lch[i] < P.Cin;
             const uint32_t off = in_k ? pgo[i] + (uint32_t)(chunk * RB) : kOob;
             __builtin_amdgcn_raw_ptr_buffer_load_lds(in_rsrc, (__attribute__((address_space(3))) void*)(dst + i * (NW * 1024)),
                                                      16, off, 0, 0, 0);
         }
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const bool in_k = c0 + lch[i] < P.Cin;
-            const uint32_t off = in_k ? wgo[i] + (uint32_t)(chunk * RB) : kOob;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rsrc, (__attribute__((address_space(3))) void*)(dst + PBYTES + i * (NW * 1024)),
-                                                     16, off, 0, 0, 0);
-        }
     };
+
+    // (ADD) the other summand, and the copied values of reusable pixels: older than the patch loads, so that no count
+    // of outstanding loads below includes them
+    constexpr int NV = NBW * 4 / VE;                // 16-byte vectors of a lane's channels
+    uintx4 other[ADD ? UPW : 1][NV], kept[ADD ? UPW : 1][NV];
+    if constexpr (ADD) {
+#pragma unroll
+        for (int u = 0; u < UPW; ++u) {
+            const int row = (wave_m * UPW + u) * 16 + l16, skip = px_skip[row];
+            const int at = px[row].y + chan0;
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                const bool in = !(skip & 2) && chan0 + v * VE < P.Cout;
+                other[u][v] = kept[u][v] = uintx4{0, 0, 0, 0};
+                if (in) other[u][v] = *reinterpret_cast<const uintx4*>(static_cast<const T*>(P.add_in) + at + v * VE);
+                if (in && (skip & 1)) kept[u][v] = *reinterpret_cast<const uintx4*>(static_cast<const T*>(P.out) + at + v * VE);
+            }
+        }
+        asm volatile("" ::: "memory");              // they leave now
+    }
 
     // read side
     const int sw = (l16 >> 1) & 7;
@@ -1037,23 +1080,25 @@ __global__ __launch_bounds__(WM * 128) void conv_pw_kernel(ConvParams P) {
 #pragma unroll
         for (int j = 0; j < NBW; ++j) acc[u][j] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-    // Every unit group starts its walk over K at another chunk: rows are Cin * ES bytes apart, a power of two for
-    // most layers, so workgroups that all read chunk c of their rows at the same time would all hit the few memory
-    // channels those addresses map to.
-    const int n_ch = P.n_chunks;
-    const int start = ug % n_ch;
-    auto chunk_of = [&](int c) { const int cc = start + c; return cc < n_ch ? cc : cc - n_ch; };
+    if (gemm) {
 #pragma unroll
-    for (int d = 0; d < D; ++d)
-        if (d < n_ch) issue(chunk_of(d), d);
-    for (int c = 0; c < n_ch; ++c) {
-        // the loads of chunk c are complete when at most the later chunks' (4 instructions each) are outstanding
+        for (int d = 0; d < D; ++d)
+            if (d < n_ch) issue_p(chunk_of(d), d);
+    }
+    for (int c = 0; gemm && c < n_ch; ++c) {
+        // the loads of chunk c are complete when at most the later chunks' are outstanding: four instructions each, of the
+        // first three chunks (whose weights went ahead) two
         const int ahead = n_ch - 1 - c < D - 1 ? n_ch - 1 - c : D - 1;
-        if (ahead >= 2) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
-        else if (ahead == 1) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+        if (c >= 2 && ahead >= 2) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+        else if (c == 1 && ahead >= 2) asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
+        else if (c == 0 ? ahead >= 2 : c >= 2 && ahead == 1) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+        else if (ahead == 1) asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
         else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         lds_barrier();                              // chunk c is in LDS; everyone is done with chunk c - 1
-        if (c + D < n_ch) issue(chunk_of(c + D), (c + D) % NSTG);
+        if (c + D < n_ch) {
+            issue_p(chunk_of(c + D), (c + D) % NSTG);
+            issue_w(chunk_of(c + D), (c + D) % NSTG);
+        }
         const unsigned char* sb = ring + (c % NSTG) * STAGE;
 #pragma unroll
         for (int g = 0; g < GPC; ++g) {
@@ -1071,43 +1116,64 @@ __global__ __launch_bounds__(WM * 128) void conv_pw_kernel(ConvParams P) {
         }
     }
 
-    // a lane holds 4 NBW consecutive channels of each of its pixels
-    const int chan0 = n0 + wave_n * (NBW * 16) + q * (4 * NBW);
-    if (chan0 >= P.Cout) return;
-    floatx4 b[NBW];
+    // The compiler's own waits for the early loads end here: between the stores they would wait for those too.
 #pragma unroll
-    for (int j = 0; j < NBW; ++j)
-        b[j] = (P.bias && chan0 + j * 4 < P.Cout) ? *reinterpret_cast<const floatx4*>(P.bias + chan0 + j * 4) : floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < NBW; ++j) asm volatile("" : "+v"(b[j]));
+    if constexpr (ADD)
+#pragma unroll
+        for (int u = 0; u < UPW; ++u)
+#pragma unroll
+            for (int v = 0; v < NV; ++v) asm volatile("" : "+v"(other[u][v]), "+v"(kept[u][v]));
+    // a lane holds 4 NBW consecutive channels of each of its pixels
+    if (chan0 >= P.Cout) return;
     const bool relu = P.relu != 0;
 #pragma unroll
     for (int u = 0; u < UPW; ++u) {
-        const int g = wave_m * UPW + u;
-        if (H.skip[g * 16 + l16]) continue;
-        T* px = reinterpret_cast<T*>(P.out) + H.uq[g].w + ((l16 >> 2) * P.Wout + (l16 & 3)) * P.Cout + chan0;
-        if (P.out_origin) {               // the output lies on a torus
-            const int4 og = H.uorg[g];
-            const int y = torus_wrap(H.uq[g].y + (l16 >> 2), og.w, P.Hout), x = torus_wrap(H.uq[g].z + (l16 & 3), og.z, P.Wout);
-            px = reinterpret_cast<T*>(P.out) + ((H.ustream[g] * P.Hout + y) * P.Wout + x) * P.Cout + chan0;
-        }
+        const int row = (wave_m * UPW + u) * 16 + l16, skip = px_skip[row];
+        if (ADD ? skip & 2 : skip) continue;
+        const int at = px[row].y + chan0;
+        T* const out = reinterpret_cast<T*>(P.out) + at;
 #pragma unroll
-        for (int j = 0; j < NBW; j += 2) {          // eight channels at a time (Cout is a multiple of 8)
-            if (chan0 + j * 4 >= P.Cout) break;
-            floatx4 v0 = acc[u][j] + b[j], v1 = acc[u][j + 1] + b[j + 1];
-            if (relu) { activate4(v0, P.relu); activate4(v1, P.relu); }
-            if constexpr (sizeof(T) == 2) {         // eight bf16 channels in one 16-byte store
-                uintx4 w4;
-                w4[0] = (uint32_t)F::bits(v0[0]) | ((uint32_t)F::bits(v0[1]) << 16);
-                w4[1] = (uint32_t)F::bits(v0[2]) | ((uint32_t)F::bits(v0[3]) << 16);
-                w4[2] = (uint32_t)F::bits(v1[0]) | ((uint32_t)F::bits(v1[1]) << 16);
-                w4[3] = (uint32_t)F::bits(v1[2]) | ((uint32_t)F::bits(v1[3]) << 16);
-                *reinterpret_cast<uintx4*>(px + j * 4) = w4;
+        for (int v = 0; v < NV; ++v) {              // 16 bytes at a time: eight bf16 or four fp32 channels
+            if (chan0 + v * VE >= P.Cout) break;
+            uintx4 bits;
+            if constexpr (sizeof(T) == 2) {
+                floatx4 v0 = acc[u][2 * v] + b[2 * v], v1 = acc[u][2 * v + 1] + b[2 * v + 1];
+                if (relu) { activate4(v0, P.relu); activate4(v1, P.relu); }
+                bits[0] = (uint32_t)F::bits(v0[0]) | ((uint32_t)F::bits(v0[1]) << 16);
+                bits[1] = (uint32_t)F::bits(v0[2]) | ((uint32_t)F::bits(v0[3]) << 16);
+                bits[2] = (uint32_t)F::bits(v1[0]) | ((uint32_t)F::bits(v1[1]) << 16);
+                bits[3] = (uint32_t)F::bits(v1[2]) | ((uint32_t)F::bits(v1[3]) << 16);
             } else {
-                F::store4(px + j * 4, v0);
-                F::store4(px + j * 4 + 4, v1);
+                floatx4 v0 = acc[u][v] + b[v];
+                if (relu) activate4(v0, P.relu);
+                bits = __builtin_bit_cast(uintx4, v0);
+            }
+            if (!ADD || !skip) *reinterpret_cast<uintx4*>(out + v * VE) = bits;
+            if constexpr (ADD) {
+                if (skip) bits = kept[u][v];
+                const uintx4 o = other[u][v];
+                auto sum = [&](float x, float y) { const float t = x + y; return !P.add_relu || t > 0.f ? t : 0.f; };
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    if constexpr (sizeof(T) == 2) {
+                        const float lo = sum(__uint_as_float(bits[e] << 16), __uint_as_float(o[e] << 16));
+                        const float hi = sum(__uint_as_float(bits[e] & 0xffff0000u), __uint_as_float(o[e] & 0xffff0000u));
+                        bits[e] = (uint32_t)F::bits(lo) | ((uint32_t)F::bits(hi) << 16);
+                    } else {
+                        bits[e] = __float_as_uint(sum(__uint_as_float(bits[e]), __uint_as_float(o[e])));
+                    }
+                }
+                *reinterpret_cast<uintx4*>(static_cast<T*>(P.add_out) + at + v * VE) = bits;
             }
         }
     }
 }
+template <typename T, int WM>
+__global__ __launch_bounds__(WM * 128) void conv_pw_kernel(ConvParams P) { conv_pw_body<T, WM, false>(P); }
+template <typename T, int WM>
+__global__ __launch_bounds__(WM * 128) void conv_pw_add_kernel(ConvParams P) { conv_pw_body<T, WM, true>(P); }
+constexpr int kPwAddId = 440;         // kernel ids: + 2 for the 128 x 128 tile + bf16
 
 constexpr int kPwSplit = 4;           // wavefronts that share a tile's K
 constexpr int kPwSplitId = 400;       // kernel ids: + units - 1
@@ -1840,6 +1906,7 @@ FastChoice choose_fast(const ConvLaunch& c, long n_units, long n_cap, size_t scr
 // Ids 64.. name the instantiations of this file: 64 + ((bf16 * 2 + kci) * 8 + UPW - 1), 96.. the first-layer kernel,
 // 110.. the wide arrangement.
 bool conv_kernel_built(int id) {
+    if (id >= kPwAddId) return id < kPwAddId + 4;
     if (id >= kStem4Id) return id < kStem4Id + 4;
     if (id >= kDeepId) return id < kDeepId + 16 && id % 8 + 1 >= kDeepMinUnits;
     return id >= kPwSplitId ? id < kPwSplitId + 2 : id >= 132 && (id - 132) / 8 < kNumGeom && fast_built(5, true, (id - 132) / 8, 0, (id - 132) % 8 + 1);
@@ -1850,6 +1917,10 @@ void conv_fast_kernel_name(int id, char* buf, size_t n) {
     if (id == 129) { snprintf(buf, n, "conv_fast_kernel<__hip_bfloat16, 3, 32, 3, 6, 2, 4>"); return; }     // the tall arrangement
     if (id == 127 || id == 128 || id == 108 || id == 109) {      // 108 + bf16 (64 x 64 tile), 127 + bf16 (128 x 128): conv_pw_kernel (1x1)
         snprintf(buf, n, "conv_pw_kernel<%s, %d>", id == 109 || id == 128 ? "__hip_bfloat16" : "float", id >= 127 ? 4 : 2);
+        return;
+    }
+    if (id >= kPwAddId) {
+        snprintf(buf, n, "conv_pw_add_kernel<%s, %d>", id & 1 ? "__hip_bfloat16" : "float", id >= kPwAddId + 2 ? 4 : 2);
         return;
     }
     if (id >= kStem4Id) {
@@ -1935,10 +2006,13 @@ hipError_t pw_launch_n(dim3 grid, size_t lds, hipStream_t st, const ConvParams& 
     if (lds > 64 * 1024 && !raised.load()) {
         hipError_t a = hipFuncSetAttribute(reinterpret_cast<const void*>(conv_pw_kernel<T, WM>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes);
+        if (a == hipSuccess) a = hipFuncSetAttribute(reinterpret_cast<const void*>(conv_pw_add_kernel<T, WM>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes);
         if (a != hipSuccess) return a;
         raised.store(true);
     }
-    hipLaunchKernelGGL((conv_pw_kernel<T, WM>), grid, dim3(WM * 128), lds, st, P);
+    if (P.add_out) hipLaunchKernelGGL((conv_pw_add_kernel<T, WM>), grid, dim3(WM * 128), lds, st, P);
+    else hipLaunchKernelGGL((conv_pw_kernel<T, WM>), grid, dim3(WM * 128), lds, st, P);
     return hipGetLastError();
 }
 // units: 1, 2 (fp32: split K, 32 channels), 4 (64 channels), 8 (128 channels)
@@ -2029,9 +2103,10 @@ bool launch_conv_fast(const ConvLaunch& c, long n_cap, long n_units, hipStream_t
         const int kc = (int)(128 / esz), n_chunks = (c.Cin + kc - 1) / kc;
         const int g_units = pw_units(c, n_cap, n_units, n_chunks, g_tune[1]), nt = g_units == 8 ? 128 : g_units == 4 ? 64 : 32;
         const int threads = g_units >= 4 ? g_units * 64 : kPwSplit * 64;
-        const long R = (c.Cout + nt - 1) / nt, tiles = (n_cap + g_units - 1) / g_units * R;
+        const long R = (c.Cout + nt - 1) / nt, groups = (n_cap + g_units - 1) / g_units;
+        const long tiles = (groups + 7) / 8 * 8 * R;      // (whole rounds of the XCDs)
         if (pw_enabled && (double)c.n_streams * c.Hout * c.Wout * c.Cout < 2147483648.0 &&
-            tiles + 8 < 2147483647L / threads) {
+            tiles < 2147483647L / threads) {
             ConvParams P{};
             P.in = c.in; P.w = c.w; P.bias = c.bias; P.out = c.out;
             P.Hin = c.Hin; P.Win = c.Win; P.Cin = c.Cin; P.Hout = c.Hout; P.Wout = c.Wout; P.Cout = c.Cout;
@@ -2045,15 +2120,20 @@ bool launch_conv_fast(const ConvLaunch& c, long n_cap, long n_units, hipStream_t
             P.n_chunks = n_chunks;
             P.in_origin = c.in_origin; P.out_origin = c.out_origin; P.origin_stride = c.origin_stride;
             P.R = (int)R;
-            P.n_wg_tiles = (int)tiles;
-            P.tiles_per_xcd = (int)((tiles + 7) / 8);
+            // the sum with another tensor that follows: in the kernels with a ring, of lists that name the units without work too
+            if (c.add && g_units >= 4 && !torus && (!c.tiles || n_dev) && reinterpret_cast<uintptr_t>(c.add->in) % 16 == 0 &&
+                reinterpret_cast<uintptr_t>(c.add->out) % 16 == 0) {
+                P.add_in = c.add->in; P.add_out = c.add->out; P.add_relu = c.add->relu;
+                c.add->done = true;
+            }
             // Every kernel starts with cold caches, so a workgroup's walk over K is a chain of long-latency loads:
             // up to four chunks are in flight per workgroup, and several workgroups share a CU.
             const int stages = n_chunks < 4 ? n_chunks : 4;
-            const size_t lds = kHeaderBytes + (size_t)stages * (size_t)(g_units * 4096);      // (of the kernels with a ring)
+            const size_t lds = kPwHeaderBytes + (size_t)stages * (size_t)(g_units * 4096);      // (of the kernels with a ring)
             const int bf16 = c.dtype == DC_BF16 ? 1 : 0;
-            if (c.kernel_id) *c.kernel_id = (g_units == 8 ? 127 : g_units == 4 ? 108 : kPwSplitId + g_units - 1) + (g_units >= 4 ? bf16 : 0);
-            const dim3 grid((unsigned)(8 * P.tiles_per_xcd));
+            if (c.kernel_id && P.add_out) *c.kernel_id = kPwAddId + (g_units == 8 ? 2 : 0) + bf16;
+            else if (c.kernel_id) *c.kernel_id = (g_units == 8 ? 127 : g_units == 4 ? 108 : kPwSplitId + g_units - 1) + (g_units >= 4 ? bf16 : 0);
+            const dim3 grid((unsigned)tiles);
             *err = bf16 ? pw_launch<__hip_bfloat16>(g_units, grid, lds, st, P) : pw_launch<float>(g_units, grid, lds, st, P);
             return true;
         }

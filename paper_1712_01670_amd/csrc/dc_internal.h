@@ -80,6 +80,9 @@ inline WindowGeom window_geom(const dc_layer& l) {
 }
 inline bool plain_square(const dc_layer& l) { return !(l.type == DC_CONV && (l.k2 > 0 || l.dil > 1)); }
 
+// The element-wise sum that follows a convolution, for a kernel that writes both (it then sets done).
+struct ConvAdd { const void* in; void* out; int relu; bool done; };
+
 struct ConvLaunch {
     const void* in;
     const void* w;
@@ -102,6 +105,7 @@ struct ConvLaunch {
     const RectDev* rects;  // device
     const RangeDev* ranges;
     int* kernel_id = nullptr;  // out (host): which instantiation ran
+    ConvAdd* add = nullptr;    // optional; with a list built on the GPU only if that list names the units without work too
     void* scratch = nullptr;   // device memory for partial sums when K is split among workgroups (optional)
     size_t scratch_bytes = 0;
 };
@@ -206,7 +210,8 @@ struct PlanConvDev {                     // one conv layer's share of the plan a
     int32_t no_reuse;                    // 1: this layer is computed in full on every frame (its unit masks are all zero)
     int32_t chunk_base;                  // chunks of the conv layers before this one
     int64_t umask_off, count_off, list_off;
-    int32_t bm_off, pad;                 // first word of the output tensor's bitmap
+    int32_t bm_off;                      // first word of the output tensor's bitmap
+    int32_t list_clean;                  // 1: the units without work stand in the list too, from its end backwards
 };
 // One step of the exact reuse maps: a tensor's bitmap from earlier ones.  Layers that leave the map as it is (1x1 / stride 1
 // convolutions, activations, LRN over channels) have none: their tensors share the producer's bitmap.  The steps are
@@ -243,7 +248,7 @@ struct PlanDev {                         // device addresses of one frame's plan
     int32_t* dxy;                        // [stream][tensor][2]
     int32_t* stream_info;                // [stream][2]: reusable blocks, 1 if a list overflowed
     unsigned char* area;                 // base of the per-layer arrays (PlanConvDev offsets)
-    int32_t* n_units;                    // [conv]
+    int32_t* n_units;                    // [conv]: the list's length
     void* stats;                         // PlanStatsHead + n_convs x PlanStatsConv; device memory or pinned host memory
     // exact reuse maps (optional): one bit per pixel, rows of (w + 31) / 32 words, tensor t of stream s at
     // bitmaps + s * bm_words + tensors[t].bm_off
@@ -387,7 +392,7 @@ int run_conv_planned(const dc_layer& l, const void* in, const void* w, const flo
                      bool copy_done = false, void* scratch = nullptr, size_t scratch_bytes = 0,
                      const void* w_packed = nullptr, const TileDev* dev_tiles = nullptr, int dev_capacity = 0,
                      const int* dev_count = nullptr, long dev_hint = -1, const int32_t* in_origin = nullptr,
-                     const int32_t* out_origin = nullptr, int origin_stride = 0, int c_frame = 0);
+                     const int32_t* out_origin = nullptr, int origin_stride = 0, int c_frame = 0, ConvAdd* add = nullptr);
 
 
 }  // namespace dc

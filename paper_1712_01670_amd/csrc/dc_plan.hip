@@ -734,7 +734,12 @@ __global__ __launch_bounds__(kPlanChunk) void plan_lists_kernel(PlanDev P) {
     __syncthreads();
     int pos = (int)before + __popcll(b & ((1ull << lane) - 1ull));
     for (int w = 0; w < wave; ++w) pos += s_wave[w];
-    if (dirty) reinterpret_cast<TileDev*>(P.area + cv.list_off)[pos] = TileDev{stream, ty, tx, (int32_t)mask};
+    TileDev* const list = reinterpret_cast<TileDev*>(P.area + cv.list_off);
+    if (dirty) list[pos] = TileDev{stream, ty, tx, (int32_t)mask};
+    else if (cv.list_clean && u < units) {      // behind the dirty ones, backwards from the end of all units
+        const int at = stream * units + u;
+        list[P.n_streams * units - 1 - (at - pos)] = TileDev{stream, ty, tx, (int32_t)mask};
+    }
     if (last && tid == 0) {
         const int total = (int)before + s_wave[0] + s_wave[1] + s_wave[2] + s_wave[3];
         P.n_units[c] = total;

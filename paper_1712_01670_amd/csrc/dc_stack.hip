@@ -83,6 +83,13 @@ struct DevPlanLayout {
 
 // Tables and sizes for n_streams streams of this stack; ok = false if the device kernels cannot take it (the host
 // path then plans the frame).
+// Layer i is a 1x1 convolution and the next one sums its output with another tensor.
+bool sum_behind(const dc_layer* L, int n_layers, int i) {
+    if (i + 1 >= n_layers || L[i].type != DC_CONV || L[i].k != 1 || !plain_square(L[i]) || L[i + 1].type != DC_ADD) return false;
+    const dc_layer& a = L[i + 1];
+    return a.in0 != a.in1 && (a.in0 == i + 1 || a.in1 == i + 1);
+}
+
 void device_plan_layout(const dc_layer* L, int n_layers, const std::vector<int>& hs, const std::vector<int>& ws,
                         int n_streams, int max_rects, DevPlanLayout& d, const uint8_t* no_reuse = nullptr) {
     d.ok = false;
@@ -181,6 +188,7 @@ void device_plan_layout(const dc_layer* L, int n_layers, const std::vector<int>&
         d.max_chunks = c.n_chunks > d.max_chunks ? c.n_chunks : d.max_chunks;
         c.chunk_base = d.n_chunks; d.n_chunks += c.n_chunks;
         c.bm_off = d.tensors[layer + 1].bm_off;
+        c.list_clean = sum_behind(L, n_layers, layer) ? 1 : 0;
         c.umask_off = (int64_t)area; area += align_up((size_t)n_streams * units * sizeof(uint16_t), 256);
         c.count_off = (int64_t)area; area += align_up((size_t)n_streams * c.n_chunks * 2 * sizeof(int32_t), 256);
         c.list_off = (int64_t)area; area += align_up((size_t)n_streams * units * sizeof(TileDev), 256);
@@ -747,7 +755,8 @@ struct StackCall {
     int plan_on_host();
     int pack_host_plans(unsigned char* staging);
     int emit_copies(int s, hipStream_t st);
-    int emit_layer(int i, hipStream_t st);
+    int emit_layer(int i, hipStream_t st, ConvAdd* add = nullptr);
+    bool sum_with(int i, ConvAdd* add) const;
     int emit_stage(int s, hipStream_t st);
     dc::FrameGraphs* find_graphs();
     int record_graphs(dc::FrameGraphs& g);
@@ -1187,7 +1196,23 @@ int StackCall::emit_copies(int s, hipStream_t st) {
     return flush();
 }
 
-int StackCall::emit_layer(int i, hipStream_t st) {
+// The sum behind conv layer i, where a kernel may write both: in the order of the layers the sum's output is written when the
+// convolution has read its input, so buffers that a caller lets tensors share must not be those.
+bool StackCall::sum_with(int i, ConvAdd* add) const {
+    if (!sum_behind(P.layers.data(), n_layers, i) || (cached && !devplan) || inplace || P.torus || prof || (devplan && P.uses_cache(i + 1))) return false;
+    const dc_layer& sum = P.layers[i + 1];
+    const int other = sum.in0 == i + 1 ? sum.in1 : sum.in0;
+    auto bytes = [&](int t) { return (size_t)n_streams * P.hs[t] * P.ws[t] * P.cs[t] * dtype_size(dtype); };
+    auto apart = [&](int t, int v) {
+        const uintptr_t a = reinterpret_cast<uintptr_t>(eff[t]), b = reinterpret_cast<uintptr_t>(eff[v]);
+        return a + bytes(t) <= b || b + bytes(v) <= a;
+    };
+    if (!apart(i + 2, P.layers[i].in0) || !apart(i + 2, i + 1) || !(eff[i + 2] == eff[other] || apart(i + 2, other)) || !apart(i + 1, other)) return false;
+    *add = ConvAdd{eff[other], eff[i + 2], sum.relu, false};
+    return true;
+}
+
+int StackCall::emit_layer(int i, hipStream_t st, ConvAdd* add) {
     const dc_layer& l = P.layers[i];
     const int a = l.in0, t = i + 1;
     const std::vector<int>&hs = P.hs, &ws = P.ws, &cs = P.cs;
@@ -1209,7 +1234,7 @@ int StackCall::emit_layer(int i, hipStream_t st) {
                                     devplan ? reinterpret_cast<const TileDev*>(pd.area + P.dl.convs[c].list_off) : nullptr,
                                     devplan ? n_streams * P.dl.convs[c].units_x * P.dl.convs[c].units_y : 0,
                                     devplan ? pd.n_units + c : nullptr, devplan ? unit_hint[c] : -1, origin_of(a), origin_of(t),
-                                    2 * (n_layers + 1), a == 0 ? C : 0);
+                                    2 * (n_layers + 1), a == 0 ? C : 0, add);
         }
         case DC_MAXPOOL:
             if (origin_of(a))            // its input lies on a torus, and with the cache its output too
@@ -1262,8 +1287,13 @@ int StackCall::emit_stage(int s, hipStream_t st) {
             const FrameRecord& last = ov->ring[(area + kFramesInFlight - 1) % kFramesInFlight];
             if (last.valid && last.plan == &P && last.partition == P.partition) DC_TRY_HIP(wait(st, last.read[s + 1]));
         }
-        rc = emit_layer(i, st);
+        ConvAdd add{};
+        // (a sum whose buffer the next stage of the last frame may still read has its own wait)
+        const bool awaited = pipe && i + 2 == end && s + 1 < P.n_stages && P.tight[s + 1];
+        const bool both = i + 1 < end && !awaited && sum_with(i, &add);
+        rc = emit_layer(i, st, both ? &add : nullptr);
         if (pipe && i == P.first[s] && P.tight[s] && !rc) DC_TRY_HIP(hipEventRecord(ov->ring[area].read[s], st));
+        if (add.done) ++i;                          // the sum is written
     }
     return rc;
 }

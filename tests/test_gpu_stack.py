@@ -1436,3 +1436,35 @@ def test_stems_with_four_channels_a_pixel(oracle, k, s, p, cout, C, n, H, W, kid
     assert max(reuse) > 0.2
     assert binding.conv_kernel_name(runner.layer_stats()["kernel_id"][0]) == \
         ("conv_stem4_kernel<7, 2, 4, 1, 4>" if k == 7 else f"conv_stem4_kernel<11, 4, 2, {kid}, 1>")
+
+
+@pytest.mark.parametrize("bf16,n", [(True, 1), (True, 3), (False, 12)])
+def test_sums_written_by_the_convolution_before_them(bf16, n):
+    """A residual block's sum is written by the 1x1 convolution before it; with a profile attached it is a launch of its own.
+    The same bits, in full frames and in cached ones (units without work, units with some reusable pixels, layers outside the
+    cache)."""
+    layers = synth.resnet50_trunk()[:24]
+    H = W = 96
+    ws, bs = synth.he_weights(layers, 3, bias_scale=0.05, residual_scale=0.5, input_shape=(H, W, 3))
+    video = np.stack([synth.panning_video(7400 + s, n_frames=4, H=H, W=W, fg=((24, 24),), margin=32) for s in range(n)])
+    dev = torch.from_numpy(np.ascontiguousarray(video.transpose(1, 0, 2, 3, 4))).to(DEV)
+    flags = np.zeros(len(layers), np.uint8)
+    flags[4] = 1
+    for no_reuse in (None, flags):
+        runs = []
+        for profile in (False, True):
+            runner = binding.StackRunner(layers, ws, bs, n, H, W, 3, block=16, radius=16, device_plan=True, exact_masks=True, overlap=False,
+                                         dtype=binding.DC_BF16 if bf16 else binding.DC_F32, no_reuse=no_reuse)
+            runner.enable_profile(profile)
+            frames = []
+            for t in range(4):
+                print(f"[sums] bf16={bf16} n={n} profile={profile} frame {t}", flush=True)
+                got = runner.step(dev[t])
+                torch.cuda.synchronize()
+                names = [binding.conv_kernel_name(k) if k >= 0 else "" for k in runner.layer_stats()["kernel_id"]]
+                frames.append([x.clone() for x in got])
+            runs.append((frames, names))
+        assert any("conv_pw_add_kernel" in v for v in runs[0][1]) and not any("conv_pw_add_kernel" in v for v in runs[1][1])
+        for t in range(4):
+            for i, (a, b) in enumerate(zip(runs[0][0][t], runs[1][0][t])):
+                assert torch.equal(a, b), (t, i)
