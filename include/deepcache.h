@@ -283,7 +283,8 @@ int32_t dc_overlap_stats(const void* overlap, dc_overlap_counters* counters);
  * (0: 64 channels per workgroup; bf16 only: 1: 128 channels, 2: 64 channels in two blocks per wavefront,
  * 3: the persistent kernel with the weights in registers, 64 input channels only, 4: 128 channels on twelve
  * wavefronts with 13..18 units per workgroup, 5: the kernel whose weights go straight to registers, 6..8 units,
- * multiples of 128 channels; a K split of 2 selects its 128-channel workgroups), units per workgroup
+ * multiples of 128 channels; a K split of 2 selects its 128-channel workgroups, 6: the kernel
+ * that takes whole maps of up to 14x14 pixels, 4 units: 128 channels per workgroup), units per workgroup
  * (1..18; for the 1x1 kernel 4 or 8 selects its 64 x 64 or 128 x 128 tile), number of workgroups that split K,
  * channel chunk index (0, 1).  A negative value leaves that choice to the library; values a layer cannot use are
  * ignored for that layer.

@@ -121,7 +121,8 @@ int run_conv_planned(const dc_layer& l, const void* in, const void* w, const flo
                      const ConvTiling& tiling, const LayerPlan* plan, const PlanAddr* addr, hipStream_t st,
                      Profile* prof, int gemm_slot, int copy_slot, int* kernel_id, bool copy_done, void* scratch, size_t scratch_bytes,
                      const void* w_packed, const TileDev* dev_tiles, int dev_capacity, const int* dev_count, long dev_hint,
-                     const int32_t* in_origin, const int32_t* out_origin, int origin_stride, int c_frame, ConvAdd* add) {
+                     const int32_t* in_origin, const int32_t* out_origin, int origin_stride, int c_frame, ConvAdd* add,
+                     const uint16_t* dev_umask) {
     const WindowGeom wg = window_geom(l);
     const int Hout = (Hin + 2 * wg.ph - wg.eh) / l.s + 1, Wout = (Win + 2 * wg.pw - wg.ew) / l.s + 1;
     ConvLaunch c;
@@ -135,7 +136,7 @@ int run_conv_planned(const dc_layer& l, const void* in, const void* w, const flo
     c.scratch = scratch; c.scratch_bytes = scratch_bytes;
     c.in_origin = in_origin; c.out_origin = out_origin; c.origin_stride = origin_stride;
     if (dev_tiles) {      // a list the planning kernels built: its length is in device memory, the copies are done
-        c.tiles = dev_tiles; c.n_tiles = dev_capacity; c.n_tiles_dev = dev_count; c.n_tiles_hint = dev_hint;
+        c.tiles = dev_tiles; c.n_tiles = dev_capacity; c.n_tiles_dev = dev_count; c.n_tiles_hint = dev_hint; c.umask = dev_umask;
         c.rects = nullptr; c.ranges = nullptr;
         Bracket b(prof, gemm_slot, st);
         DC_TRY_HIP(launch_conv(c, st));
@@ -156,7 +157,8 @@ int run_conv_planned(const dc_layer& l, const void* in, const void* w, const flo
     }
     if (plan->n_tiles) {
         Bracket b(prof, gemm_slot, st);
-        c.tiles = addr->tiles; c.n_tiles = (int)plan->n_tiles; c.rects = addr->rects; c.ranges = addr->ranges;
+        // (without a reusable pixel the list is every unit in raster order)
+        c.tiles = plan->rects.empty() ? nullptr : addr->tiles; c.n_tiles = (int)plan->n_tiles; c.rects = addr->rects; c.ranges = addr->ranges;
         DC_TRY_HIP(launch_conv(c, st));
     }
     return DC_OK;
@@ -289,7 +291,7 @@ int32_t dc_probe_mfma_rate(int32_t lds_reads, void* scratch_dev, size_t scratch_
 }
 
 int32_t dc_conv_tuning(int32_t arrangement, int32_t units_per_workgroup, int32_t k_split, int32_t chunk_index) {
-    if (arrangement > 5 || units_per_workgroup > 18 || chunk_index > 1) return DC_ERR_INVALID_ARG;
+    if (arrangement > 6 || units_per_workgroup > 18 || chunk_index > 1) return DC_ERR_INVALID_ARG;
     conv_set_tuning(arrangement, units_per_workgroup, k_split, chunk_index);
     return DC_OK;
 }

@@ -62,6 +62,7 @@ struct ConvParams {
     const void* add_in;     // 1x1 kernel: the tensor summed with the output into add_out (null: no sum)
     void* add_out;
     int add_relu;
+    const uint16_t* umask;  // conv_map_kernel: [stream][unit] reusable pixels; null: none
 };
 
 template <typename T>

@@ -1,7 +1,8 @@
 // Cache-aware convolution (Section 5 "Reuse", steps 2-3), the kernels for the common layer shape: 3x3 taps,
-// stride 1.  Four kernels share this file:
+// stride 1.  Five kernels share this file:
 //   conv_fast_kernel   channel counts that are whole 64-byte rows, 64 or 128 output channels per workgroup (5x5 taps
 //                      as well, in bf16);
+//   conv_map_kernel    bf16, 3x3, maps of up to 14x14 of which nearly every unit has work (see there);
 //   conv_deep_kernel   bf16, 3x3, many units: weights from L2 into registers (see there);
 //   conv_regw_kernel   64 input channels in bf16 and many units: persistent, weights in registers (see there);
 //   conv_first_kernel  input pixels of one 16-byte vector (the padded first layer), nothing staged (see there).
@@ -586,6 +587,203 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
         }
         *reinterpret_cast<uintx4*>(px) = uintx4{v[0], v[1], v[2], v[3]};
         *reinterpret_cast<uintx4*>(px + 8) = uintx4{v[4], v[5], v[6], v[7]};
+    }
+}
+
+// ---- 3x3, bf16, small maps of which (nearly) every pixel is computed ----------------------------------------------
+// On a 13x13 map the 4x4 units cover 256 pixels for 169, on 14x14 256 for 196: MFMAs, LDS reads and patch loads for
+// nothing.  Where nearly every unit has work, a workgroup takes a whole map instead: the rows of the GEMM are the map's
+// pixels one after another, 16 to a tile, and the map with its border lies in LDS once (16 slots a line, so maps of up to
+// 14x14) where units have a patch each: 15 KB per 32 channels for 11 tiles, which leaves room for two workgroups per CU.
+// Everything else is conv_fast_kernel: stages of one kernel row, double buffers, eight wavefronts (four rows of tiles, dealt
+// round-robin, x two halves of the channels), and the order of the sums with chunks of 32 channels: the same bits.
+// The reusable pixels of a cached frame come from the units' masks, so a list that is shorter than expected costs time only.
+// 13x13 384->384 on 64 streams 44 -> 36 us, 512->1024 on 16 streams 36 -> 30, 14x14 512->512 on 64 streams 61 -> 52.  What bounds it:
+// a barrier per kernel row at two wavefronts per SIMD, and few workgroups (192 to 512 for 256 CUs).
+// LDS: the row of slot (line, column) at (16 line + column) * 64 bytes, its 16-byte chunk c at c ^ 2 (column / 4 % 2): a read
+// of 16 neighbouring pixels of a line is free of conflicts, one across a line's end has a few of two.
+template <int UPW, int NBW>
+__global__ __launch_bounds__(512) void conv_map_kernel(ConvParams P) {
+    typedef __hip_bfloat16 T;
+    typedef Frag<T> F;
+    typedef F::vec vec;
+    constexpr int WM = 4, WN = 2, NW = 8, NT = WN * NBW * 16, RB = 64, KC = 32, LINES = 16, PBYTES = LINES * 1024;
+    constexpr int W_INSTR = 3 * NT / 16, NWI = (W_INSTR + NW - 1) / NW, WBYTES = W_INSTR * 1024, NPI = 2;
+
+    extern __shared__ __align__(16) unsigned char smem[];
+    unsigned char* const patch0 = smem;
+    unsigned char* const wts0 = smem + 2 * PBYTES;
+    const int tid = threadIdx.x;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave_n = wave % WN, wave_m = wave / WN;
+    const int l16 = lane & 15, q = lane >> 4;
+    int stream, ntile;
+    decode_workgroup(P.R, stream, ntile);
+    const int n0 = ntile * NT;
+    const __amdgpu_buffer_rsrc_t in_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        reinterpret_cast<void*>(keep_scalar(reinterpret_cast<uintptr_t>(P.in))), 0, keep_scalar(P.in_bytes), kBufferFlags);
+    const __amdgpu_buffer_rsrc_t w_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        reinterpret_cast<void*>(keep_scalar(reinterpret_cast<uintptr_t>(P.w))), 0, keep_scalar(P.w_bytes), kBufferFlags);
+    const int CinES = keep_scalar(P.Cin * 2);
+    const bool packed = keep_scalar(P.w_packed) != 0;
+    const int H = P.Hout, W = P.Wout;
+
+    const int lrow = lane >> 2, lpos = lane & 3;
+    uint32_t wgo[NWI];
+#pragma unroll
+    for (int i = 0; i < NWI; ++i) {
+        const int row = (wave + i * NW) * 16 + lrow;   // tl * NT + n
+        const int tl = row / NT, n = row - tl * NT;
+        const int c = lpos ^ ((row / 2) % 4);
+        const uint32_t off = packed ? (uint32_t)((((n0 + n) / 16 * (CinES / 64) * 9 + tl) * 16 + n % 16) * 64 + (c << 4))
+                                    : (uint32_t)(((n0 + n) * 9 + tl) * CinES + (c << 4));
+        wgo[i] = tl < 3 ? off : kOob;
+    }
+    auto issue_w = [&](int chunk, int ky, int wbuf) {
+        unsigned char* dst = wts0 + wbuf * WBYTES + wave * 1024;
+        const int so = packed ? (chunk * 3 + ky) * (3 * 1024) : ky * 3 * CinES + chunk * RB;
+#pragma unroll
+        for (int i = 0; i < NWI; ++i) {
+            const uint32_t off = wgo[i];
+            if ((i + 1) * NW <= W_INSTR || wave + i * NW < W_INSTR)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rsrc, (__attribute__((address_space(3))) void*)(dst + i * (NW * 1024)),
+                                                         16, off, so, 0, 0);
+        }
+    };
+    issue_w(0, 0, 0);
+
+    // patch: instruction j brings line j (row j - 1 of the map), a slot per four lanes
+    uint32_t pgo[NPI];
+    int iox = 0, ioy = 0, oox = 0, ooy = 0;           // tensors on a torus: the stream's origins
+    {
+        const size_t at = (size_t)stream * P.origin_stride;
+        if (P.in_origin) { iox = P.in_origin[at]; ioy = P.in_origin[at + 1]; }
+        if (P.out_origin) { oox = P.out_origin[at]; ooy = P.out_origin[at + 1]; }
+    }
+#pragma unroll
+    for (int i = 0; i < NPI; ++i) {
+        const int y = wave + i * NW - 1, x = lrow - 1;
+        const bool ok = (unsigned)y < (unsigned)H && (unsigned)x < (unsigned)W;
+        int iy = y, ix = x;
+        if (P.in_origin && ok) { iy = torus_wrap(y, ioy, H); ix = torus_wrap(x, iox, W); }
+        pgo[i] = ok ? (uint32_t)(((stream * H + iy) * W + ix) * CinES + ((lpos ^ (lrow / 4 % 2 * 2)) << 4)) : kOob;
+    }
+    auto issue_p = [&](int chunk, int part, int pbuf) {          // part < 0: all lines, else every third instruction
+        unsigned char* dst = patch0 + pbuf * PBYTES + wave * 1024;
+        const int so = chunk * RB;
+#pragma unroll
+        for (int i = 0; i < NPI; ++i) {
+            if (part >= 0 && i % 3 != part) continue;
+            const uint32_t off = pgo[i];
+            if (wave + i * NW < H + 2)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(in_rsrc, (__attribute__((address_space(3))) void*)(dst + i * (NW * 1024)),
+                                                         16, off, so, 0, 0);
+        }
+    };
+
+    // read side: this lane's pixel of every tile of the wavefront; keep: the pixels to be stored
+    int paddr[UPW][3];
+    unsigned keep = 0;
+#pragma unroll
+    for (int u = 0; u < UPW; ++u) {
+        const int p = (wave_m + u * WM) * 16 + l16;
+        const bool in = p < H * W;
+        const int y = in ? fast_div(p, P.pw_magic) : 0, x = in ? p - y * W : 0;
+        const bool reused = in && P.umask && ((P.umask[(size_t)stream * (P.units_x * P.units_y) + (y >> 2) * P.units_x + (x >> 2)] >> ((y & 3) * 4 + (x & 3))) & 1);
+        keep |= in && !reused ? 1u << u : 0u;
+#pragma unroll
+        for (int kx = 0; kx < 3; ++kx)
+            paddr[u][kx] = (y * 16 + x + kx) * RB + ((q ^ ((x + kx) / 4 % 2 * 2)) << 4);
+    }
+    const int waddr = (wave_n * NBW * 16 + l16) * RB + ((q ^ ((l16 / 2) % 4)) << 4);
+
+    floatx4 acc[UPW][NBW];
+#pragma unroll
+    for (int u = 0; u < UPW; ++u)
+#pragma unroll
+        for (int j = 0; j < NBW; ++j) acc[u][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    const int chan = n0 + wave_n * NBW * 16 + 4 * q;
+    floatx4 bias[NBW];
+#pragma unroll
+    for (int j = 0; j < NBW; ++j)
+        bias[j] = P.bias ? *reinterpret_cast<const floatx4*>(P.bias + chan + j * 16) : floatx4{0.f, 0.f, 0.f, 0.f};
+
+    const int n_ch = keep_scalar(P.n_chunks);
+    auto issue_stage = [&](int c, int ky, int s) {     // as in conv_fast_kernel
+        if (c >= n_ch) return;
+        issue_w(c, ky, s & 1);
+        if (ky == 0) { if (c > 0) issue_p(c, 2, c & 1); }
+        else if (c + 1 < n_ch) issue_p(c + 1, ky - 1, (c + 1) & 1);
+    };
+    auto main_loop = [&](auto nu_tag) {
+        constexpr int NU = decltype(nu_tag)::value;
+        vec x[2][NU > 0 ? NU : 1], w[2][NBW];
+        auto frag = [&](int pbuf, int wbuf, int ky, int kx, int b) {
+            const unsigned char* xp = patch0 + pbuf * PBYTES + ky * 1024;
+#pragma unroll
+            for (int u = 0; u < NU; ++u) x[b][u] = *reinterpret_cast<const vec*>(xp + paddr[u][kx]);
+            const unsigned char* wp = wts0 + wbuf * WBYTES + waddr + kx * (NT * RB);
+#pragma unroll
+            for (int j = 0; j < NBW; ++j) w[b][j] = *reinterpret_cast<const vec*>(wp + j * (16 * RB));
+        };
+        auto mma = [&](int b) {
+#pragma unroll
+            for (int u = 0; u < NU; ++u)
+#pragma unroll
+                for (int j = 0; j < NBW; ++j) F::mma1(w[b][j], x[b][u], acc[u][j], 0);
+        };
+        issue_p(0, -1, 0);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        issue_stage(0, 1, 1);
+        frag(0, 0, 0, 0, 0);
+        int sidx = 0;
+        for (int c = 0; c < n_ch; ++c) {
+            const int pbuf = c & 1;
+#pragma unroll
+            for (int ky = 0; ky < 3; ++ky, ++sidx) {
+#pragma unroll
+                for (int kx = 0; kx < 2; ++kx) {
+                    frag(pbuf, sidx & 1, ky, kx + 1, (ky * 3 + kx + 1) & 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                    mma((ky * 3 + kx) & 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                __syncthreads();
+                if (ky == 0) issue_stage(c, 2, sidx + 2);
+                else issue_stage(c + 1, ky - 1, sidx + 2);
+                if (ky < 2) frag(pbuf, (sidx + 1) & 1, ky + 1, 0, ((ky + 1) * 3) & 1);
+                else if (c + 1 < n_ch) frag(pbuf ^ 1, (sidx + 1) & 1, 0, 0, 1);
+                __builtin_amdgcn_sched_barrier(0);
+                mma((ky * 3 + 2) & 1);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int u = 0; u < NU; ++u) x[0][u] = x[1][u];          // nine steps: the next chunk expects its first fragments in buffer 0
+#pragma unroll
+            for (int j = 0; j < NBW; ++j) w[0][j] = w[1][j];
+        }
+    };
+    const int n_tiles = (H * W + 15) >> 4;
+    const int n_u = keep_scalar((n_tiles - wave_m + WM - 1) / WM);
+    if (n_u == UPW) main_loop(std::integral_constant<int, UPW>());
+    else main_loop(std::integral_constant<int, UPW - 1>());
+
+    const bool relu = P.relu != 0;
+#pragma unroll
+    for (int u = 0; u < UPW; ++u) {
+        if (!((keep >> u) & 1)) continue;
+        const int p = (wave_m + u * WM) * 16 + l16;
+        int y = fast_div(p, P.pw_magic), x = p - y * W;
+        if (P.out_origin) { y = torus_wrap(y, ooy, H); x = torus_wrap(x, oox, W); }
+        T* px = reinterpret_cast<T*>(P.out) + ((stream * H + y) * W + x) * P.Cout + chan;
+#pragma unroll
+        for (int j = 0; j < NBW; ++j) {
+            floatx4 v = acc[u][j] + bias[j];
+            if (relu) activate4(v, P.relu);
+            F::store4(px + j * 16, v);
+        }
     }
 }
 
@@ -1800,6 +1998,42 @@ ConvTuning g_tune_shared{{-1, -1, -1, -1}};
 constexpr int kDeep = 4, kDeepMinUnits = 6, kDeepMaxUnits = 8;
 constexpr int kDeepId = 416;          // kernel ids: + units - 1, + 8 for two wavefronts
 inline size_t deep_lds_bytes(int g) { return kHeaderBytes + 2 * (size_t)((g * 36 + 15) / 16) * 1024; }
+// conv_map_kernel: tiles of 16 pixels per wavefront 1 .. 4, 64 or 128 channels per workgroup.
+constexpr int kMapId = 448;           // kernel ids: + tiles per wavefront - 1, + 4 for 128 channels
+constexpr size_t map_lds_bytes(int nbw) { return 2 * 16 * 1024 + 2 * (size_t)(6 * nbw) * 1024; }
+// A layer the kernel can run: the map with its border fits 16 x 16 slots, and a list built elsewhere comes with the units' masks.
+bool map_shape(const ConvLaunch& c) {
+    return c.dtype == DC_BF16 && c.k == 3 && c.p == 1 && c.Hout == c.Hin && c.Wout == c.Win && c.Hout <= 14 && c.Wout <= 14 && c.Cout % 64 == 0 &&
+           (!c.tiles || c.umask) && (long)c.n_streams * (c.Cout / 64) < 2147483647L;
+}
+// Blocks of 16 channels per wavefront where it is the faster one, 0: it is not.  It takes at least an eighth off the rows (and
+// few tiles leave a stage too short), and a workgroup per map and 64 channels for three CUs in four; 128 channels a workgroup
+// if that many are left (us, conv_fast_kernel's best -> 64 / 128 channels: 13x13 384->384 64 streams 44 -> 37 / 36, 384->256 30 -> 25 /
+// 34, 512->1024 16 streams 36 -> 30 / 42, 14x14 512->512 64 streams 61 -> 64 / 52; with fewer workgroups 14x14 512->512
+// 16 streams 23 -> 30, 256->256 11 -> 18).
+int map_blocks(const ConvLaunch& c) {
+    const int tiles = (c.Hout * c.Wout + 15) / 16, units = ((c.Hout + 3) / 4) * ((c.Wout + 3) / 4);
+    if (!map_shape(c) || tiles < 9 || tiles * 8 > units * 7) return 0;
+    const long wgs = (long)c.n_streams * (c.Cout / 64);
+    return c.Cout % 128 == 0 && wgs / 2 >= 192 ? 4 : wgs >= 192 ? 2 : 0;
+}
+template <int NBW>
+hipError_t map_launch(int upw, dim3 grid, hipStream_t st, const ConvParams& P) {
+    static std::atomic<bool> raised{false};
+    if (map_lds_bytes(NBW) > 64 * 1024 && !raised.load()) {
+        hipError_t a = hipSuccess;
+        for (const void* fn : {reinterpret_cast<const void*>(conv_map_kernel<1, NBW>), reinterpret_cast<const void*>(conv_map_kernel<2, NBW>),
+                               reinterpret_cast<const void*>(conv_map_kernel<3, NBW>), reinterpret_cast<const void*>(conv_map_kernel<4, NBW>)})
+            if (a == hipSuccess) a = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)map_lds_bytes(NBW));
+        if (a != hipSuccess) return a;
+        raised.store(true);
+    }
+    if (upw == 1) hipLaunchKernelGGL((conv_map_kernel<1, NBW>), grid, dim3(512), map_lds_bytes(NBW), st, P);
+    else if (upw == 2) hipLaunchKernelGGL((conv_map_kernel<2, NBW>), grid, dim3(512), map_lds_bytes(NBW), st, P);
+    else if (upw == 3) hipLaunchKernelGGL((conv_map_kernel<3, NBW>), grid, dim3(512), map_lds_bytes(NBW), st, P);
+    else hipLaunchKernelGGL((conv_map_kernel<4, NBW>), grid, dim3(512), map_lds_bytes(NBW), st, P);
+    return hipGetLastError();
+}
 template <int NW>
 hipError_t deep_launch(int g, dim3 grid, hipStream_t st, const ConvParams& P) {
     if (g == 8) hipLaunchKernelGGL((conv_deep_kernel<NW, 8>), grid, dim3(NW * 64), deep_lds_bytes(8), st, P);
@@ -1906,6 +2140,7 @@ FastChoice choose_fast(const ConvLaunch& c, long n_units, long n_cap, size_t scr
 // Ids 64.. name the instantiations of this file: 64 + ((bf16 * 2 + kci) * 8 + UPW - 1), 96.. the first-layer kernel,
 // 110.. the wide arrangement.
 bool conv_kernel_built(int id) {
+    if (id >= kMapId) return id < kMapId + 8;
     if (id >= kPwAddId) return id < kPwAddId + 4;
     if (id >= kStem4Id) return id < kStem4Id + 4;
     if (id >= kDeepId) return id < kDeepId + 16 && id % 8 + 1 >= kDeepMinUnits;
@@ -1917,6 +2152,10 @@ void conv_fast_kernel_name(int id, char* buf, size_t n) {
     if (id == 129) { snprintf(buf, n, "conv_fast_kernel<__hip_bfloat16, 3, 32, 3, 6, 2, 4>"); return; }     // the tall arrangement
     if (id == 127 || id == 128 || id == 108 || id == 109) {      // 108 + bf16 (64 x 64 tile), 127 + bf16 (128 x 128): conv_pw_kernel (1x1)
         snprintf(buf, n, "conv_pw_kernel<%s, %d>", id == 109 || id == 128 ? "__hip_bfloat16" : "float", id >= 127 ? 4 : 2);
+        return;
+    }
+    if (id >= kMapId) {
+        snprintf(buf, n, "conv_map_kernel<%d, %d>", (id - kMapId) % 4 + 1, id >= kMapId + 4 ? 4 : 2);
         return;
     }
     if (id >= kPwAddId) {
@@ -2211,6 +2450,9 @@ bool launch_conv_fast(const ConvLaunch& c, long n_cap, long n_units, hipStream_t
         }
     }
     if (ch.g < 1) return false;
+    const bool untuned = g_tune[0] < 0 && g_tune[1] < 0 && g_tune[2] < 0 && g_tune[3] < 0;
+    const int map_nbw = g_tune[0] == 6 ? (map_shape(c) ? (g_tune[1] == 4 && c.Cout % 128 == 0 ? 4 : 2) : 0)
+                      : untuned && ch.kci == 0 && (ch.geom == kDeep || ch.ks == 1) && n_units * 10 >= n_cap * 9 ? map_blocks(c) : 0;
     const bool deep = ch.geom == kDeep;
     const int nt = deep ? 64 * ch.ks : geom_nt(ch.geom), ks = deep ? 1 : ch.ks;
     const int upw = deep ? ch.g : (ch.g + kGeom[ch.geom].wm - 1) / kGeom[ch.geom].wm;
@@ -2239,6 +2481,16 @@ bool launch_conv_fast(const ConvLaunch& c, long n_cap, long n_units, hipStream_t
     if (c.k == 3 && packed) { P.w = c.w_packed; P.w_packed = 1; }
 
     if (c.kernel_id) *c.kernel_id = deep ? kDeepId + (ch.ks == 2 ? 8 : 0) + ch.g - 1 : c.k == 5 ? 132 + ch.geom * 8 + upw - 1 : ch.geom == 3 ? 129 : ch.geom ? 110 + (ch.geom - 1) * 8 + ch.kci * 4 + upw - 1 : 64 + ((c.dtype == DC_BF16 ? 2 : 0) + ch.kci) * 8 + upw - 1;
+    if (map_nbw) {
+        const int upw = ((c.Hout * c.Wout + 15) / 16 + 3) / 4;
+        P.R = c.Cout / (32 * map_nbw); P.n_chunks = c.Cin / 32;
+        P.umask = c.tiles ? c.umask : nullptr;
+        P.pw_magic = (uint32_t)((0x100000000ull + (uint64_t)c.Wout - 1) / (uint64_t)c.Wout);        // pixels are divided here
+        if (c.kernel_id) *c.kernel_id = kMapId + (map_nbw == 4 ? 4 : 0) + upw - 1;
+        const dim3 grid((unsigned)(c.n_streams * P.R));
+        *err = map_nbw == 4 ? map_launch<4>(upw, grid, st, P) : map_launch<2>(upw, grid, st, P);
+        return true;
+    }
     const long groups = (n_cap + ch.g - 1) / ch.g;
     const long wgx = groups * P.R;
     if (wgx > 2147483647L || ks > 65535) { *err = hipErrorInvalidValue; return true; }

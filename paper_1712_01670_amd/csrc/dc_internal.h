@@ -105,6 +105,7 @@ struct ConvLaunch {
     const RectDev* rects;  // device
     const RangeDev* ranges;
     int* kernel_id = nullptr;  // out (host): which instantiation ran
+    const uint16_t* umask = nullptr;     // with tiles, optional (device): [stream][unit] the units' masks of reusable pixels
     ConvAdd* add = nullptr;    // optional; with a list built on the GPU only if that list names the units without work too
     void* scratch = nullptr;   // device memory for partial sums when K is split among workgroups (optional)
     size_t scratch_bytes = 0;
@@ -242,7 +243,6 @@ struct PlanDev {                         // device addresses of one frame's plan
     const PlanOpDev* ops;                // exact reuse maps
     int32_t n_layers, n_convs, n_streams, cap;
     int32_t n_ops, n_chunks;             // n_chunks: of all conv layers together (per stream)
-    int32_t want_umasks;                 // 0: nothing is copied from the previous frame, the unit masks are not needed
     dc_rect* rects;                      // [stream][tensor][cap]
     int32_t* nrect;                      // [stream][tensor]
     int32_t* dxy;                        // [stream][tensor][2]
@@ -392,7 +392,8 @@ int run_conv_planned(const dc_layer& l, const void* in, const void* w, const flo
                      bool copy_done = false, void* scratch = nullptr, size_t scratch_bytes = 0,
                      const void* w_packed = nullptr, const TileDev* dev_tiles = nullptr, int dev_capacity = 0,
                      const int* dev_count = nullptr, long dev_hint = -1, const int32_t* in_origin = nullptr,
-                     const int32_t* out_origin = nullptr, int origin_stride = 0, int c_frame = 0, ConvAdd* add = nullptr);
+                     const int32_t* out_origin = nullptr, int origin_stride = 0, int c_frame = 0, ConvAdd* add = nullptr,
+                     const uint16_t* dev_umask = nullptr);
 
 
 }  // namespace dc

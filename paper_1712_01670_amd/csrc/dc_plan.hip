@@ -721,7 +721,7 @@ __global__ __launch_bounds__(kPlanChunk) void plan_lists_kernel(PlanDev P) {
             for (int r = 0; r < 4; ++r)
                 if (ty * 4 + r < cv.Hout) mask |= ((map[(ty * 4 + r) * wpr] >> ((tx * 4) & 31)) & 0xfu) << (4 * r);
             if (cv.no_reuse) mask = 0;                       // a layer that does not use the cache
-            if (P.want_umasks) *umask = (uint16_t)mask;
+            *umask = (uint16_t)mask;
         } else {
             mask = *umask;
         }

@@ -931,7 +931,6 @@ int StackCall::prepare_device_plan() {
     pd.ops = reinterpret_cast<const PlanOpDev*>(tables_dev + dl.off_ops);
     pd.n_layers = n_layers; pd.n_convs = (int32_t)dl.convs.size(); pd.n_streams = n_streams; pd.cap = dl.cap;
     pd.n_ops = (int32_t)dl.ops.size(); pd.n_chunks = dl.n_chunks;
-    pd.want_umasks = P.torus ? 0 : 1;
     pd.rects = reinterpret_cast<dc_rect*>(frame);
     pd.nrect = reinterpret_cast<int32_t*>(frame + dl.off_nrect);
     pd.dxy = reinterpret_cast<int32_t*>(frame + dl.off_dxy);
@@ -1234,7 +1233,8 @@ int StackCall::emit_layer(int i, hipStream_t st, ConvAdd* add) {
                                     devplan ? reinterpret_cast<const TileDev*>(pd.area + P.dl.convs[c].list_off) : nullptr,
                                     devplan ? n_streams * P.dl.convs[c].units_x * P.dl.convs[c].units_y : 0,
                                     devplan ? pd.n_units + c : nullptr, devplan ? unit_hint[c] : -1, origin_of(a), origin_of(t),
-                                    2 * (n_layers + 1), a == 0 ? C : 0, add);
+                                    2 * (n_layers + 1), a == 0 ? C : 0, add,
+                                    devplan ? reinterpret_cast<const uint16_t*>(pd.area + P.dl.convs[c].umask_off) : nullptr);
         }
         case DC_MAXPOOL:
             if (origin_of(a))            // its input lies on a torus, and with the cache its output too

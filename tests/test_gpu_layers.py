@@ -1008,3 +1008,33 @@ def test_deep_conv_kernel_bits_and_borders():
         base = out.pop((1, 8, 1, 0))
         for tuning, got in out.items():
             assert torch.equal(got, base), tuning
+
+
+# The bf16 kernel that takes whole maps (arrangement 6): one tile of pixels per row of wavefronts to four, tiles that end
+# inside the map, one channel chunk and more, 64 and 128 channels per workgroup.  Same bits as the kernel it stands in for.
+@pytest.mark.parametrize("H,W,cin,cout,n", [(13, 13, 64, 128, 3), (14, 14, 32, 64, 2), (14, 9, 96, 192, 1), (1, 1, 32, 64, 4), (5, 14, 160, 128, 2),
+                                            (14, 3, 64, 256, 2), (7, 7, 128, 64, 3)])
+def test_whole_map_kernel(oracle, H, W, cin, cout, n):
+    rng = np.random.default_rng(H * 100 + W)
+    x = oracle.round_bf16(rng.standard_normal((n, H, W, cin)).astype(np.float32))
+    w = oracle.round_bf16((rng.standard_normal((cout, 3, 3, cin)) * np.sqrt(2.0 / (cin * 9))).astype(np.float32))
+    b = (rng.standard_normal(cout) * 0.1).astype(np.float32)
+    xd, wd, bd = _to_dev(x, True), _to_dev(w, True), torch.from_numpy(b).to(DEV)
+    for relu, bias in ((1, bd), (2, bd), (0, None)):
+        layer = dict(_layer(cin, cout, 3, 1, 1, True), relu=relu)
+        wp = binding.dc_pack_conv_weights(layer, wd)
+        out = {}
+        for tuning in ((0, 4, 1, 0), (6, 2, -1, -1), (6, 4, -1, -1)):
+            for packed in (None, wp):
+                print(f"[whole map] {H}x{W} {cin}->{cout} n={n} relu={relu} {tuning} packed={packed is not None}", flush=True)
+                binding.dc_conv_tuning(*tuning)
+                try:
+                    out[tuning, packed is None] = binding.dc_cached_conv_layer(layer, xd, wd, bias, packed=packed)
+                finally:
+                    binding.dc_conv_tuning()
+        base = out[(0, 4, 1, 0), True]
+        for key, got in out.items():
+            assert torch.equal(got.view(torch.int16), base.view(torch.int16)), key
+        if relu == 1:
+            for i in range(n):
+                assert _rel_err(_to_np(base)[i], oracle.conv_cached(x[i], w, b, 3, 1, 1, True, bf16=True)) <= 2e-2

@@ -1468,3 +1468,22 @@ def test_sums_written_by_the_convolution_before_them(bf16, n):
         for t in range(4):
             for i, (a, b) in enumerate(zip(runs[0][0][t], runs[1][0][t])):
                 assert torch.equal(a, b), (t, i)
+
+
+@pytest.mark.parametrize("torus", [False, True])
+@pytest.mark.parametrize("H,W", [(52, 52), (56, 40)])
+def test_whole_map_kernel_in_cached_frames(oracle, H, W, torus):
+    """Maps of 13x13 and 14x10 in frames planned on the GPU, some of whose pixels come from the cache, through the kernel that
+    takes whole maps: reusable pixels keep their values (oracle), on a torus as well."""
+    video = np.stack([synth.panning_video(7500 + s, n_frames=5, H=H, W=W, fg=((12, 12),), margin=32) for s in range(3)])
+    layers = synth._chain([("c", 64, 3, 1, 1), ("p", 2, 2, 0), ("c", 64, 3, 1, 1), ("p", 2, 2, 0), ("c", 128, 3, 1, 1), ("c", 64, 3, 1, 1)], 3)
+    convs = [i for i, L in enumerate(layers) if L["type"] == synth.CONV][-2:]
+    binding.dc_conv_tuning(6, 4, -1, -1)
+    try:
+        runner, reuse = _run_one(oracle, layers, video, 4, 8, True, device_plan=True, exact_masks=True, torus=torus, resets=(2,), bias_scale=0.02)
+        stats = runner.layer_stats()
+    finally:
+        binding.dc_conv_tuning()
+    upw = (((H // 4) * (W // 4) + 15) // 16 + 3) // 4
+    assert [binding.conv_kernel_name(stats["kernel_id"][i]) for i in convs] == [f"conv_map_kernel<{upw}, 4>", f"conv_map_kernel<{upw}, 2>"]
+    assert runner.read_stats() and runner.layer_stats()["reused_px"][convs[0]] > 0
