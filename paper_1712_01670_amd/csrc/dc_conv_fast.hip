@@ -2006,16 +2006,21 @@ bool map_shape(const ConvLaunch& c) {
     return c.dtype == DC_BF16 && c.k == 3 && c.p == 1 && c.Hout == c.Hin && c.Wout == c.Win && c.Hout <= 14 && c.Wout <= 14 && c.Cout % 64 == 0 &&
            (!c.tiles || c.umask) && (long)c.n_streams * (c.Cout / 64) < 2147483647L;
 }
-// Blocks of 16 channels per wavefront where it is the faster one, 0: it is not.  It takes at least an eighth off the rows (and
-// few tiles leave a stage too short), and a workgroup per map and 64 channels for three CUs in four; 128 channels a workgroup
-// if that many are left (us, conv_fast_kernel's best -> 64 / 128 channels: 13x13 384->384 64 streams 44 -> 37 / 36, 384->256 30 -> 25 /
-// 34, 512->1024 16 streams 36 -> 30 / 42, 14x14 512->512 64 streams 61 -> 64 / 52; with fewer workgroups 14x14 512->512
-// 16 streams 23 -> 30, 256->256 11 -> 18).
+// Blocks of 16 channels per wavefront where it is the faster one, 0: it is not.  It has to take at least an eighth off the rows,
+// with enough tiles for a stage (us, conv_fast_kernel's best -> this: 14x14 256->256 16 streams 11 -> 18), and its workgroups
+// have to fill the CUs: of 128 channels (or four tiles a wavefront) a CU holds one, so the share of the CUs that the last of
+// the rounds of 256 leaves busy must make up for the rows saved (13x13 512->1024 28 / 40 / 56 streams 52 -> 44, 79 -> 81,
+// 101 -> 84, 384->384 64 streams 44 -> 36, 14x14 512->512 56 / 64 streams 53 -> 47, 61 -> 52); of 64 channels and three
+// tiles it holds two (13x13 512->1024 12 / 16 / 20 streams 28 -> 28, 36 -> 30, 41 -> 43, 384->384 40 / 56 streams 28 -> 23,
+// 36 -> 34; 14x14 512->512 28 / 40 streams 34 -> 31, 41 -> 57).
 int map_blocks(const ConvLaunch& c) {
     const int tiles = (c.Hout * c.Wout + 15) / 16, units = ((c.Hout + 3) / 4) * ((c.Wout + 3) / 4);
     if (!map_shape(c) || tiles < 9 || tiles * 8 > units * 7) return 0;
-    const long wgs = (long)c.n_streams * (c.Cout / 64);
-    return c.Cout % 128 == 0 && wgs / 2 >= 192 ? 4 : wgs >= 192 ? 2 : 0;
+    const long w64 = (long)c.n_streams * (c.Cout / 64);
+    auto fills = [&](long wgs) { return wgs * units * 20 >= (wgs + 255) / 256 * 256 * tiles * 21; };
+    if (c.Cout % 128 == 0 && fills(w64 / 2)) return 4;
+    if (tiles > 12) return fills(w64) ? 2 : 0;
+    return (w64 >= 208 && w64 <= 256) || (w64 >= 352 && w64 <= 512) ? 2 : 0;
 }
 template <int NBW>
 hipError_t map_launch(int upw, dim3 grid, hipStream_t st, const ConvParams& P) {
@@ -2053,7 +2058,7 @@ double deep_cost(const ConvLaunch& c, long n_units, int g) {
     const long wgs = (n_units + g - 1) / g * (c.Cout / (64 * nw));
     if (nw == 2 && wgs < 2048) return 1e300;
     const double m = 576.0 * g * n_ch, look = 2 * 4608.0 * 1.08 * n_ch;
-    const double pair = (2.6 * m > look ? 2.6 * m : look) + (nw == 2 ? 20000 : 10000), lone = 1.45 * m + 7000;
+    const double pair = (2.6 * m > look ? 2.6 * m : look) + (nw == 2 ? 20000 : 10000), lone = 1.45 * m + 20000;
     const long per_cu = nw == 2 ? (wgs + 511) / 512 : (wgs + 255) / 256;
     return (per_cu / 2) * pair + (per_cu % 2) * lone;
 }
