@@ -2050,15 +2050,15 @@ hipError_t deep_launch(int g, dim3 grid, hipStream_t st, const ConvParams& P) {
 // a pair of them takes the longer of its MFMAs and its weight fragments' cache look-ups (two per four lanes), a lone one
 // more than half of a pair.  Measured, us, conv_fast_kernel's best -> units per workgroup 6 / 7 / 8: 56x56 256->256 64 streams
 // 214 -> 212 / 175 / 181, 16 streams 60 -> 68 / 51 / 54; 28x28 512->512 64 streams 199 -> 219 / 186 / 221, 16 streams
-// 60 -> 83 / 55 / 60; 112x112 128->128 64 streams 254 -> 233 / 222 / 223; launches of less than one workgroup per CU
-// lose (13x13 512->1024 16 streams 34 -> 41 / 45 / 50), and so do few workgroups of two wavefronts (13x13 384->384 64
+// 60 -> 83 / 55 / 60; 112x112 128->128 64 / 28 / 20 streams 254 -> 233 / 222 / 223, 114 -> 106 / 103 / 100,
+// 84 -> 83 / 80 / 73; launches of less than one workgroup per CU lose (13x13 512->1024 16 streams 34 -> 41 / 45 / 50), and so do few workgroups of two wavefronts (13x13 384->384 64
 // streams 40 -> 49 / 56 / 65), hence the least number of those.
 double deep_cost(const ConvLaunch& c, long n_units, int g) {
     const int nw = c.Cout % 256 ? 2 : 4, n_ch = c.Cin / 32;
     const long wgs = (n_units + g - 1) / g * (c.Cout / (64 * nw));
-    if (nw == 2 && wgs < 2048) return 1e300;
+    if (nw == 2 && wgs < 1500) return 1e300;
     const double m = 576.0 * g * n_ch, look = 2 * 4608.0 * 1.08 * n_ch;
-    const double pair = (2.6 * m > look ? 2.6 * m : look) + (nw == 2 ? 20000 : 10000), lone = 1.45 * m + 20000;
+    const double pair = (2.6 * m > look ? 2.6 * m : look) + (nw == 2 ? 14000 : 10000), lone = 1.45 * m + 20000;
     const long per_cu = nw == 2 ? (wgs + 511) / 512 : (wgs + 255) / 256;
     return (per_cu / 2) * pair + (per_cu % 2) * lone;
 }
