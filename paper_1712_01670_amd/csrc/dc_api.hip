@@ -122,7 +122,7 @@ int run_conv_planned(const dc_layer& l, const void* in, const void* w, const flo
                      Profile* prof, int gemm_slot, int copy_slot, int* kernel_id, bool copy_done, void* scratch, size_t scratch_bytes,
                      const void* w_packed, const TileDev* dev_tiles, int dev_capacity, const int* dev_count, long dev_hint,
                      const int32_t* in_origin, const int32_t* out_origin, int origin_stride, int c_frame, ConvAdd* add,
-                     const uint16_t* dev_umask) {
+                     const uint16_t* dev_umask, ConvBatch* batch) {
     const WindowGeom wg = window_geom(l);
     const int Hout = (Hin + 2 * wg.ph - wg.eh) / l.s + 1, Wout = (Win + 2 * wg.pw - wg.ew) / l.s + 1;
     ConvLaunch c;
@@ -135,17 +135,22 @@ int run_conv_planned(const dc_layer& l, const void* in, const void* w, const flo
     c.dtype = dtype; c.tiling = tiling; c.c_frame = c_frame; c.add = add;
     c.scratch = scratch; c.scratch_bytes = scratch_bytes;
     c.in_origin = in_origin; c.out_origin = out_origin; c.origin_stride = origin_stride;
+    auto launch = [&]() {
+        if (!batch) return launch_conv(c, st);
+        batch->c[batch->n++] = c;
+        return hipSuccess;
+    };
     if (dev_tiles) {      // a list the planning kernels built: its length is in device memory, the copies are done
         c.tiles = dev_tiles; c.n_tiles = dev_capacity; c.n_tiles_dev = dev_count; c.n_tiles_hint = dev_hint; c.umask = dev_umask;
         c.rects = nullptr; c.ranges = nullptr;
         Bracket b(prof, gemm_slot, st);
-        DC_TRY_HIP(launch_conv(c, st));
+        DC_TRY_HIP(launch());
         return DC_OK;
     }
     if (!plan) {
         c.tiles = nullptr; c.n_tiles = 0; c.rects = nullptr; c.ranges = nullptr;
         Bracket b(prof, gemm_slot, st);
-        DC_TRY_HIP(launch_conv(c, st));
+        DC_TRY_HIP(launch());
         return DC_OK;
     }
     int mw = 0, mh = 0;
@@ -159,7 +164,7 @@ int run_conv_planned(const dc_layer& l, const void* in, const void* w, const flo
         Bracket b(prof, gemm_slot, st);
         // (without a reusable pixel the list is every unit in raster order)
         c.tiles = plan->rects.empty() ? nullptr : addr->tiles; c.n_tiles = (int)plan->n_tiles; c.rects = addr->rects; c.ranges = addr->ranges;
-        DC_TRY_HIP(launch_conv(c, st));
+        DC_TRY_HIP(launch());
     }
     return DC_OK;
 }

@@ -531,17 +531,22 @@ void conv_kernel_name(int id, char* buf, size_t n) {
              bf16 ? "__hip_bfloat16" : "float", S.g, S.nt, S.wm, S.wn, S.wk, kc);
 }
 
+bool conv_list_length(const ConvLaunch& c, long* n_cap, long* n_hint) {
+    const int units_y = (c.Hout + 3) / 4, units_x = (c.Wout + 3) / 4;
+    *n_cap = c.tiles ? c.n_tiles : (long)c.n_streams * units_x * units_y;
+    *n_hint = (c.tiles && c.n_tiles_dev && c.n_tiles_hint >= 0) ? std::max(1L, std::min(c.n_tiles_hint, *n_cap)) : *n_cap;
+    // buffer loads address each tensor with 31-bit byte offsets
+    return *n_cap > 0 && (double)c.n_streams * c.Hin * c.Win * c.Cin * dtype_size(c.dtype) < 2147483648.0 &&
+           (double)c.Cout * c.k * tap_cols(c) * c.Cin * dtype_size(c.dtype) < 2147483648.0;
+}
+
 hipError_t launch_conv(const ConvLaunch& c, hipStream_t st) {
     const int units_y = (c.Hout + 3) / 4, units_x = (c.Wout + 3) / 4;
-    const long n_units = c.tiles ? c.n_tiles : (long)c.n_streams * units_x * units_y;
-    if (n_units <= 0) return hipSuccess;
-    const long n_hint = (c.tiles && c.n_tiles_dev && c.n_tiles_hint >= 0) ? std::max(1L, std::min(c.n_tiles_hint, n_units)) : n_units;
     const int kh = c.k, kw = tap_cols(c), dil = c.dil > 1 ? c.dil : 1;
-    if (kh > kMaxK || kw > kMaxK) return hipErrorInvalidValue;
-    // buffer loads address each tensor with 31-bit byte offsets
-    if ((double)c.n_streams * c.Hin * c.Win * c.Cin * dtype_size(c.dtype) >= 2147483648.0 ||
-        (double)c.Cout * kh * kw * c.Cin * dtype_size(c.dtype) >= 2147483648.0)
-        return hipErrorInvalidValue;
+    long n_units, n_hint;
+    const bool fits = conv_list_length(c, &n_units, &n_hint);
+    if (n_units <= 0) return hipSuccess;
+    if (!fits || kh > kMaxK || kw > kMaxK) return hipErrorInvalidValue;
     if (c.kw == 0 && dil == 1) {      // the kernels for the common shapes take square kernels without dilation
         hipError_t fe = hipSuccess;
         if (launch_conv_fast(c, n_units, n_hint, st, &fe)) return fe;

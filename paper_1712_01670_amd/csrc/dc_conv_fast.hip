@@ -1118,7 +1118,7 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(const uintx4* src, ui
 // Units without work stand behind the others in the list (plan_lists_kernel); a group of them only adds.
 constexpr int kPwHeaderBytes = 1536;
 template <typename T, int WM, bool ADD>
-__device__ __forceinline__ void conv_pw_body(const ConvParams& P) {
+__device__ __forceinline__ void conv_pw_body(const ConvParams& P, const int block) {
     typedef Frag<T> F;
     typedef typename F::vec vec;
     constexpr int ES = (int)sizeof(T), VE = F::VE;
@@ -1142,8 +1142,8 @@ __device__ __forceinline__ void conv_pw_body(const ConvParams& P) {
     const int wave_n = wave % WN, wave_m = wave / WN;
     const int l16 = lane & 15, q = lane >> 4;
 
-    const int xj = (int)(blockIdx.x >> 3) / P.R, ntile = (int)(blockIdx.x >> 3) - xj * P.R;
-    const int ug = xj * 8 + (int)(blockIdx.x & 7);
+    const int xj = (block >> 3) / P.R, ntile = (block >> 3) - xj * P.R;
+    const int ug = xj * 8 + (block & 7);
     const int n_cap = P.n_units;                    // what the launch is sized for
     if (ug * G >= n_cap) return;                    // the whole workgroup, before any barrier
     TileDev td{0, 0, 0, 0};
@@ -1368,9 +1368,25 @@ __device__ __forceinline__ void conv_pw_body(const ConvParams& P) {
     }
 }
 template <typename T, int WM>
-__global__ __launch_bounds__(WM * 128) void conv_pw_kernel(ConvParams P) { conv_pw_body<T, WM, false>(P); }
+__global__ __launch_bounds__(WM * 128) void conv_pw_kernel(ConvParams P) { conv_pw_body<T, WM, false>(P, (int)blockIdx.x); }
 template <typename T, int WM>
-__global__ __launch_bounds__(WM * 128) void conv_pw_add_kernel(ConvParams P) { conv_pw_body<T, WM, true>(P); }
+__global__ __launch_bounds__(WM * 128) void conv_pw_add_kernel(ConvParams P) { conv_pw_body<T, WM, true>(P, (int)blockIdx.x); }
+// Several 1x1 layers that read one tensor, in one launch: workgroups first[j] .. first[j + 1] - 1 are those that layer j's own launch
+// would have (whole rounds of the XCDs each), so the sums are the same.  An inception module's branches have 32 to 600
+// workgroups of a few us each, less than the chip holds: alone, each branch pays for a launch and for its own chain of loads.
+struct PwMany {
+    ConvParams p[kConvBatch];
+    int first[kConvBatch];
+};
+template <typename T, int WM>
+__global__ __launch_bounds__(WM * 128) void conv_pw_many_kernel(PwMany M) {
+    const int b = (int)blockIdx.x;
+    int j = 0;
+#pragma unroll
+    for (int i = 1; i < kConvBatch; ++i) j += b >= M.first[i] ? 1 : 0;
+    conv_pw_body<T, WM, false>(M.p[j], b - M.first[j]);
+}
+constexpr int kPwManyId = 464;        // kernel ids: + 2 for the 128 x 128 tile + bf16
 constexpr int kPwAddId = 440;         // kernel ids: + 2 for the 128 x 128 tile + bf16
 
 constexpr int kPwSplit = 4;           // wavefronts that share a tile's K
@@ -2145,6 +2161,7 @@ FastChoice choose_fast(const ConvLaunch& c, long n_units, long n_cap, size_t scr
 // Ids 64.. name the instantiations of this file: 64 + ((bf16 * 2 + kci) * 8 + UPW - 1), 96.. the first-layer kernel,
 // 110.. the wide arrangement.
 bool conv_kernel_built(int id) {
+    if (id >= kPwManyId) return id < kPwManyId + 4;
     if (id >= kMapId) return id < kMapId + 8;
     if (id >= kPwAddId) return id < kPwAddId + 4;
     if (id >= kStem4Id) return id < kStem4Id + 4;
@@ -2157,6 +2174,10 @@ void conv_fast_kernel_name(int id, char* buf, size_t n) {
     if (id == 129) { snprintf(buf, n, "conv_fast_kernel<__hip_bfloat16, 3, 32, 3, 6, 2, 4>"); return; }     // the tall arrangement
     if (id == 127 || id == 128 || id == 108 || id == 109) {      // 108 + bf16 (64 x 64 tile), 127 + bf16 (128 x 128): conv_pw_kernel (1x1)
         snprintf(buf, n, "conv_pw_kernel<%s, %d>", id == 109 || id == 128 ? "__hip_bfloat16" : "float", id >= 127 ? 4 : 2);
+        return;
+    }
+    if (id >= kPwManyId) {
+        snprintf(buf, n, "conv_pw_many_kernel<%s, %d>", id & 1 ? "__hip_bfloat16" : "float", id >= kPwManyId + 2 ? 4 : 2);
         return;
     }
     if (id >= kMapId) {
@@ -2243,34 +2264,6 @@ hipError_t regw_launch_t(dim3 grid, hipStream_t st, const ConvParams& P) {
     return hipGetLastError();
 }
 
-// Launches the layer with the kernel of this file if its shape qualifies; returns false otherwise.
-template <typename T, int WM>
-hipError_t pw_launch_n(dim3 grid, size_t lds, hipStream_t st, const ConvParams& P) {
-    static std::atomic<bool> raised{false};
-    if (lds > 64 * 1024 && !raised.load()) {
-        hipError_t a = hipFuncSetAttribute(reinterpret_cast<const void*>(conv_pw_kernel<T, WM>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes);
-        if (a == hipSuccess) a = hipFuncSetAttribute(reinterpret_cast<const void*>(conv_pw_add_kernel<T, WM>),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes);
-        if (a != hipSuccess) return a;
-        raised.store(true);
-    }
-    if (P.add_out) hipLaunchKernelGGL((conv_pw_add_kernel<T, WM>), grid, dim3(WM * 128), lds, st, P);
-    else hipLaunchKernelGGL((conv_pw_kernel<T, WM>), grid, dim3(WM * 128), lds, st, P);
-    return hipGetLastError();
-}
-// units: 1, 2 (fp32: split K, 32 channels), 4 (64 channels), 8 (128 channels)
-template <typename T>
-hipError_t pw_launch(int units, dim3 grid, size_t lds, hipStream_t st, const ConvParams& P) {
-    if (units == 8) return pw_launch_n<T, 4>(grid, lds, st, P);
-    if (units == 4) return pw_launch_n<T, 2>(grid, lds, st, P);
-    if constexpr (sizeof(T) == 4) {
-        if (units == 2) hipLaunchKernelGGL((conv_pw_split_kernel<2, 2, kPwSplit>), grid, dim3(kPwSplit * 64), 0, st, P);
-        else hipLaunchKernelGGL((conv_pw_split_kernel<1, 2, kPwSplit>), grid, dim3(kPwSplit * 64), 0, st, P);
-        return hipGetLastError();
-    }
-    return hipErrorInvalidValue;
-}
 // Units per workgroup of a 1x1 layer.
 //   fp32: the kernel that splits K adds in another order than the ring, so the length that decides between them is the longest
 //   the list can be, not the one an earlier frame had: a frame's bits do not depend on counters that may have arrived or not,
@@ -2288,6 +2281,129 @@ int pw_units(const ConvLaunch& c, long n_cap, long n_units, int n_chunks, int fo
     if (!bf16 && (n_cap + 1) / 2 * r32 <= 512) return 2;
     return small_tiles >= 4096 && c.Cout >= 128 && (bf16 || n_chunks >= 32) ? 8 : 4;
 }
+// The launch of a 1x1 layer; false if its shape does not qualify.
+struct PwLaunch {
+    ConvParams P;
+    int units;            // per workgroup: 1, 2 (fp32: split K, 32 channels), 4 (64 channels), 8 (128 channels)
+    int wgs;
+    size_t lds;           // of the kernels with a ring
+};
+bool pw_prepare(const ConvLaunch& c, long n_cap, long n_units, PwLaunch& L) {
+    const size_t esz = dtype_size(c.dtype);
+    if ((c.in_origin || c.out_origin) && c.s != 1) return false;
+    if (c.k != 1 || c.p != 0 || (c.s != 1 && c.s != 2) || (c.Cin * esz) % 16 || c.Cout % 8) return false;
+    if (reinterpret_cast<uintptr_t>(c.in) % 16 || reinterpret_cast<uintptr_t>(c.w) % 16 || reinterpret_cast<uintptr_t>(c.out) % 16 ||
+        (c.bias && reinterpret_cast<uintptr_t>(c.bias) % 16))
+        return false;
+    const int units_y = (c.Hout + 3) / 4, units_x = (c.Wout + 3) / 4;
+    const int kc = (int)(128 / esz), n_chunks = (c.Cin + kc - 1) / kc;
+    L.units = pw_units(c, n_cap, n_units, n_chunks, conv_tuning().v[1]);
+    const int nt = L.units == 8 ? 128 : L.units == 4 ? 64 : 32, threads = L.units >= 4 ? L.units * 64 : kPwSplit * 64;
+    const long R = (c.Cout + nt - 1) / nt, groups = (n_cap + L.units - 1) / L.units;
+    const long tiles = (groups + 7) / 8 * 8 * R;      // (whole rounds of the XCDs)
+    if ((double)c.n_streams * c.Hout * c.Wout * c.Cout >= 2147483648.0 || tiles >= 2147483647L / threads) return false;
+    L.wgs = (int)tiles;
+    ConvParams& P = L.P;
+    P = ConvParams{};
+    P.in = c.in; P.w = c.w; P.bias = c.bias; P.out = c.out;
+    P.Hin = c.Hin; P.Win = c.Win; P.Cin = c.Cin; P.Hout = c.Hout; P.Wout = c.Wout; P.Cout = c.Cout;
+    P.k = c.k; P.s = c.s; P.p = c.p; P.relu = c.relu;
+    P.units = c.tiles; P.n_units = (int)n_cap; P.n_units_dev = c.tiles ? c.n_tiles_dev : nullptr;
+    P.units_x = units_x; P.units_y = units_y;
+    P.npix_magic = (uint32_t)((0x100000000ull + (uint64_t)(units_x * units_y) - 1) / (uint64_t)(units_x * units_y));
+    P.pw_magic = (uint32_t)((0x100000000ull + (uint64_t)units_x - 1) / (uint64_t)units_x);
+    P.in_bytes = (uint32_t)((size_t)c.n_streams * c.Hin * c.Win * c.Cin * esz);
+    P.w_bytes = (uint32_t)((size_t)c.Cout * c.Cin * esz);
+    P.n_chunks = n_chunks;
+    P.in_origin = c.in_origin; P.out_origin = c.out_origin; P.origin_stride = c.origin_stride;
+    P.R = (int)R;
+    // Every kernel starts with cold caches, so a workgroup's walk over K is a chain of long-latency loads:
+    // up to four chunks are in flight per workgroup, and several workgroups share a CU.
+    const int stages = n_chunks < 4 ? n_chunks : 4;
+    L.lds = kPwHeaderBytes + (size_t)stages * (size_t)(L.units * 4096);
+    return true;
+}
+template <typename T, int WM>
+hipError_t pw_raise() {
+    static std::atomic<bool> raised{false};
+    if (raised.load()) return hipSuccess;
+    for (const void* f : {reinterpret_cast<const void*>(conv_pw_kernel<T, WM>), reinterpret_cast<const void*>(conv_pw_add_kernel<T, WM>),
+                          reinterpret_cast<const void*>(conv_pw_many_kernel<T, WM>)}) {
+        const hipError_t a = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes);
+        if (a != hipSuccess) return a;
+    }
+    raised.store(true);
+    return hipSuccess;
+}
+template <typename T, int WM>
+hipError_t pw_launch_n(const PwLaunch& L, hipStream_t st) {
+    if (L.lds > 64 * 1024) {
+        const hipError_t a = pw_raise<T, WM>();
+        if (a != hipSuccess) return a;
+    }
+    const dim3 grid((unsigned)L.wgs);
+    if (L.P.add_out) hipLaunchKernelGGL((conv_pw_add_kernel<T, WM>), grid, dim3(WM * 128), L.lds, st, L.P);
+    else hipLaunchKernelGGL((conv_pw_kernel<T, WM>), grid, dim3(WM * 128), L.lds, st, L.P);
+    return hipGetLastError();
+}
+template <typename T>
+hipError_t pw_launch(const PwLaunch& L, hipStream_t st) {
+    if (L.units == 8) return pw_launch_n<T, 4>(L, st);
+    if (L.units == 4) return pw_launch_n<T, 2>(L, st);
+    if constexpr (sizeof(T) == 4) {
+        const dim3 grid((unsigned)L.wgs);
+        if (L.units == 2) hipLaunchKernelGGL((conv_pw_split_kernel<2, 2, kPwSplit>), grid, dim3(kPwSplit * 64), 0, st, L.P);
+        else hipLaunchKernelGGL((conv_pw_split_kernel<1, 2, kPwSplit>), grid, dim3(kPwSplit * 64), 0, st, L.P);
+        return hipGetLastError();
+    }
+    return hipErrorInvalidValue;
+}
+template <typename T, int WM>
+hipError_t pw_many_launch(const PwMany& M, unsigned wgs, size_t lds, hipStream_t st) {
+    if (lds > 64 * 1024) {
+        const hipError_t a = pw_raise<T, WM>();
+        if (a != hipSuccess) return a;
+    }
+    hipLaunchKernelGGL((conv_pw_many_kernel<T, WM>), dim3(wgs), dim3(WM * 128), lds, st, M);
+    return hipGetLastError();
+}
+hipError_t launch_conv_batch(const ConvBatch& b, hipStream_t st) {
+    PwLaunch L[kConvBatch];
+    for (int i = 0; i < b.n; ++i) {
+        const ConvLaunch& c = b.c[i];
+        long n_cap = 0, n_units = 0;
+        L[i].units = 0;
+        if (c.kw || c.dil > 1 || !conv_list_length(c, &n_cap, &n_units) || !pw_prepare(c, n_cap, n_units, L[i])) L[i].units = 0;
+    }
+    for (int units : {4, 8}) {
+        PwMany M{};
+        int of[kConvBatch], n = 0, wgs = 0;
+        size_t lds = 0;
+        for (int i = 0; i < b.n; ++i)
+            if (L[i].units == units && b.c[i].dtype == b.c[0].dtype && wgs <= 2147483647 / 512 - L[i].wgs) {
+                of[n] = i; M.p[n] = L[i].P; M.first[n++] = wgs;
+                wgs += L[i].wgs; lds = std::max(lds, L[i].lds);
+            }
+        if (n < 2) continue;
+        for (int j = n; j < kConvBatch; ++j) M.first[j] = wgs;      // (no workgroup)
+        const int bf16 = b.c[0].dtype == DC_BF16 ? 1 : 0;
+        hipError_t e;
+        if (units == 8) e = bf16 ? pw_many_launch<__hip_bfloat16, 4>(M, (unsigned)wgs, lds, st) : pw_many_launch<float, 4>(M, (unsigned)wgs, lds, st);
+        else e = bf16 ? pw_many_launch<__hip_bfloat16, 2>(M, (unsigned)wgs, lds, st) : pw_many_launch<float, 2>(M, (unsigned)wgs, lds, st);
+        if (e != hipSuccess) return e;
+        for (int j = 0; j < n; ++j) {
+            if (b.c[of[j]].kernel_id) *b.c[of[j]].kernel_id = kPwManyId + (units == 8 ? 2 : 0) + bf16;
+            L[of[j]].units = -1;
+        }
+    }
+    for (int i = 0; i < b.n; ++i)
+        if (L[i].units >= 0) {
+            const hipError_t e = launch_conv(b.c[i], st);
+            if (e != hipSuccess) return e;
+        }
+    return hipSuccess;
+}
+// Launches the layer with the kernel of this file if its shape qualifies; returns false otherwise.
 bool launch_conv_fast(const ConvLaunch& c, long n_cap, long n_units, hipStream_t st, hipError_t* err) {
     // below, n_units is the length the launch is tuned for and n_cap the length it must cover; they differ only
     // when the list is built on the GPU (then the kernels read the real length from memory)
@@ -2339,48 +2455,19 @@ bool launch_conv_fast(const ConvLaunch& c, long n_cap, long n_units, hipStream_t
             return true;
         }
     }
-    if (enabled && (!torus || c.s == 1) && c.k == 1 && c.p == 0 && (c.s == 1 || c.s == 2) && (c.Cin * esz) % 16 == 0 && c.Cout % 8 == 0 &&
-        reinterpret_cast<uintptr_t>(c.in) % 16 == 0 && reinterpret_cast<uintptr_t>(c.w) % 16 == 0 &&
-        reinterpret_cast<uintptr_t>(c.out) % 16 == 0 && (!c.bias || reinterpret_cast<uintptr_t>(c.bias) % 16 == 0)) {
-        constexpr bool pw_enabled = true;
-        const int units_y = (c.Hout + 3) / 4, units_x = (c.Wout + 3) / 4;
-        const int kc = (int)(128 / esz), n_chunks = (c.Cin + kc - 1) / kc;
-        const int g_units = pw_units(c, n_cap, n_units, n_chunks, g_tune[1]), nt = g_units == 8 ? 128 : g_units == 4 ? 64 : 32;
-        const int threads = g_units >= 4 ? g_units * 64 : kPwSplit * 64;
-        const long R = (c.Cout + nt - 1) / nt, groups = (n_cap + g_units - 1) / g_units;
-        const long tiles = (groups + 7) / 8 * 8 * R;      // (whole rounds of the XCDs)
-        if (pw_enabled && (double)c.n_streams * c.Hout * c.Wout * c.Cout < 2147483648.0 &&
-            tiles < 2147483647L / threads) {
-            ConvParams P{};
-            P.in = c.in; P.w = c.w; P.bias = c.bias; P.out = c.out;
-            P.Hin = c.Hin; P.Win = c.Win; P.Cin = c.Cin; P.Hout = c.Hout; P.Wout = c.Wout; P.Cout = c.Cout;
-            P.k = c.k; P.s = c.s; P.p = c.p; P.relu = c.relu;
-            P.units = c.tiles; P.n_units = (int)n_cap; P.n_units_dev = n_dev;
-            P.units_x = units_x; P.units_y = units_y;
-            P.npix_magic = (uint32_t)((0x100000000ull + (uint64_t)(units_x * units_y) - 1) / (uint64_t)(units_x * units_y));
-            P.pw_magic = (uint32_t)((0x100000000ull + (uint64_t)units_x - 1) / (uint64_t)units_x);
-            P.in_bytes = (uint32_t)((size_t)c.n_streams * c.Hin * c.Win * c.Cin * esz);
-            P.w_bytes = (uint32_t)((size_t)c.Cout * c.Cin * esz);
-            P.n_chunks = n_chunks;
-            P.in_origin = c.in_origin; P.out_origin = c.out_origin; P.origin_stride = c.origin_stride;
-            P.R = (int)R;
-            // the sum with another tensor that follows: in the kernels with a ring, of lists that name the units without work too
-            if (c.add && g_units >= 4 && !torus && (!c.tiles || n_dev) && reinterpret_cast<uintptr_t>(c.add->in) % 16 == 0 &&
-                reinterpret_cast<uintptr_t>(c.add->out) % 16 == 0) {
-                P.add_in = c.add->in; P.add_out = c.add->out; P.add_relu = c.add->relu;
-                c.add->done = true;
-            }
-            // Every kernel starts with cold caches, so a workgroup's walk over K is a chain of long-latency loads:
-            // up to four chunks are in flight per workgroup, and several workgroups share a CU.
-            const int stages = n_chunks < 4 ? n_chunks : 4;
-            const size_t lds = kPwHeaderBytes + (size_t)stages * (size_t)(g_units * 4096);      // (of the kernels with a ring)
-            const int bf16 = c.dtype == DC_BF16 ? 1 : 0;
-            if (c.kernel_id && P.add_out) *c.kernel_id = kPwAddId + (g_units == 8 ? 2 : 0) + bf16;
-            else if (c.kernel_id) *c.kernel_id = (g_units == 8 ? 127 : g_units == 4 ? 108 : kPwSplitId + g_units - 1) + (g_units >= 4 ? bf16 : 0);
-            const dim3 grid((unsigned)tiles);
-            *err = bf16 ? pw_launch<__hip_bfloat16>(g_units, grid, lds, st, P) : pw_launch<float>(g_units, grid, lds, st, P);
-            return true;
+    PwLaunch pw;
+    if (pw_prepare(c, n_cap, n_units, pw)) {
+        // the sum with another tensor that follows: in the kernels with a ring, of lists that name the units without work too
+        if (c.add && pw.units >= 4 && !torus && (!c.tiles || n_dev) && reinterpret_cast<uintptr_t>(c.add->in) % 16 == 0 &&
+            reinterpret_cast<uintptr_t>(c.add->out) % 16 == 0) {
+            pw.P.add_in = c.add->in; pw.P.add_out = c.add->out; pw.P.add_relu = c.add->relu;
+            c.add->done = true;
         }
+        const int bf16 = c.dtype == DC_BF16 ? 1 : 0;
+        if (c.kernel_id && pw.P.add_out) *c.kernel_id = kPwAddId + (pw.units == 8 ? 2 : 0) + bf16;
+        else if (c.kernel_id) *c.kernel_id = (pw.units == 8 ? 127 : pw.units == 4 ? 108 : kPwSplitId + pw.units - 1) + (pw.units >= 4 ? bf16 : 0);
+        *err = bf16 ? pw_launch<__hip_bfloat16>(pw, st) : pw_launch<float>(pw, st);
+        return true;
     }
     if (!enabled || (c.k != 3 && !(c.k == 5 && c.dtype == DC_BF16 && !torus)) || c.s != 1 || c.Cout % geom_nt(0) != 0 || c.Cin % (64 / esz) != 0) return false;
     if (reinterpret_cast<uintptr_t>(c.in) % 16 || reinterpret_cast<uintptr_t>(c.w) % 16) return false;

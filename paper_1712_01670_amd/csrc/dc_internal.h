@@ -111,6 +111,10 @@ struct ConvLaunch {
     size_t scratch_bytes = 0;
 };
 
+// 1x1 layers that read the same tensor, to be launched together.
+constexpr int kConvBatch = 3;
+struct ConvBatch { ConvLaunch c[kConvBatch]; int n = 0; };
+
 // Upper bound of the scratch a convolution launch can make use of.
 constexpr size_t kConvScratchBytes = (size_t)32 << 20;
 // n_units: list length the launch must cover; n_hint: the length to tune for (equal unless the list is built on the GPU)
@@ -125,7 +129,11 @@ bool conv_kernel_built(int id);        // ids from 132 on
 struct ConvTuning { int v[4]; };             // dc_conv_tuning's arguments, -1: chosen by the model
 void conv_set_tuning(int geom, int g, int ks, int kci);
 ConvTuning conv_tuning();
+// Units a launch must cover and units to tune for; false: there is nothing to launch, or the tensors are too large.
+bool conv_list_length(const ConvLaunch& c, long* n_cap, long* n_hint);
 hipError_t launch_conv(const ConvLaunch& c, hipStream_t st);
+// As launch_conv for each, with as few launches as the kernels allow; the order among the layers is left open.
+hipError_t launch_conv_batch(const ConvBatch& b, hipStream_t st);
 
 hipError_t launch_shifted_copy(const RectDev* rects_dev, int n_rects, int max_rect_w, int max_rect_h,
                                const void* prev, void* out, int Hout, int Wout, int Cout,
@@ -393,7 +401,7 @@ int run_conv_planned(const dc_layer& l, const void* in, const void* w, const flo
                      const void* w_packed = nullptr, const TileDev* dev_tiles = nullptr, int dev_capacity = 0,
                      const int* dev_count = nullptr, long dev_hint = -1, const int32_t* in_origin = nullptr,
                      const int32_t* out_origin = nullptr, int origin_stride = 0, int c_frame = 0, ConvAdd* add = nullptr,
-                     const uint16_t* dev_umask = nullptr);
+                     const uint16_t* dev_umask = nullptr, ConvBatch* batch = nullptr);
 
 
 }  // namespace dc

@@ -310,6 +310,8 @@ struct dc::FrameGraphs {
     ~FrameGraphs() { drop(); }
 };
 
+constexpr int kSiblingReach = 12;            // layers between two that StackCall::run_with may launch together, at most
+
 // ---- what dc_run_stack derives from a stack's description ------------------------------------------------------
 // Depends on the layer table, the sizes and the options, not on the frame, its buffers or the weights.  An overlap
 // handle keeps the last few (a caller runs one stack, frame after frame); without a handle it is made on every call.
@@ -323,6 +325,7 @@ struct dc::StackPlan {
     std::vector<int> last_reader;           // [tensor]: last layer that reads it (-1: none)
     std::vector<ConvTiling> tilings;        // [layer]
     std::vector<int> conv_of;               // [layer]: index among the conv layers (-1)
+    std::vector<int> sibling;               // [layer]: the next 1x1 convolution of the same tensor with the same stride (-1)
     DevPlanLayout dl;                       // planning on the GPU
     bool dl_fits_host = false;              // its tables fit their place in the host workspace
     std::vector<unsigned char> tables;
@@ -503,6 +506,11 @@ int make_plan(StackPlan& P, const dc_layer* layers, int n_layers, int n_streams,
     workspace_sizes(layers, n_layers, n_streams, H, W, block, max_rects, P.hs, P.ws, P.dl, &P.need_dev, &P.need_host);
     P.last_reader.assign(n_layers + 1, -1);
     P.conv_of.assign(n_layers, -1);
+    P.sibling.assign(n_layers, -1);
+    auto pointwise = [&](int i) { return layers[i].type == DC_CONV && layers[i].k == 1 && plain_square(layers[i]); };
+    for (int i = 0; i < n_layers; ++i)
+        for (int j = i + 1; pointwise(i) && j < n_layers && j <= i + kSiblingReach; ++j)      // (one with a sum behind it writes that too)
+            if (pointwise(j) && layers[j].in0 == layers[i].in0 && layers[j].s == layers[i].s && !sum_behind(layers, n_layers, j)) { P.sibling[i] = j; break; }
     P.tilings.resize(n_layers);
     P.issued_full.assign(n_layers, 0);
     int conv = 0;
@@ -755,7 +763,10 @@ struct StackCall {
     int plan_on_host();
     int pack_host_plans(unsigned char* staging);
     int emit_copies(int s, hipStream_t st);
-    int emit_layer(int i, hipStream_t st, ConvAdd* add = nullptr);
+    int emit_layer(int i, hipStream_t st, ConvAdd* add = nullptr, ConvBatch* batch = nullptr);
+    int run_with(int i, int end, int* with) const;
+    bool apart(int t, int v) const;
+    bool apart(int t, int v, const void* at_v) const;
     bool sum_with(int i, ConvAdd* add) const;
     int emit_stage(int s, hipStream_t st);
     dc::FrameGraphs* find_graphs();
@@ -1195,23 +1206,45 @@ int StackCall::emit_copies(int s, hipStream_t st) {
     return flush();
 }
 
+// No byte of tensor t lies in tensor v.
+bool StackCall::apart(int t, int v) const { return apart(t, v, eff[v]); }
+bool StackCall::apart(int t, int v, const void* at_v) const {
+    auto bytes = [&](int x) { return (size_t)n_streams * P.hs[x] * P.ws[x] * P.cs[x] * dtype_size(dtype); };
+    const uintptr_t a = reinterpret_cast<uintptr_t>(eff[t]), b = reinterpret_cast<uintptr_t>(at_v);
+    return a + bytes(t) <= b || b + bytes(v) <= a;
+}
+
+// The later 1x1 convolutions (before layer `end`) that may be launched with layer i because they read its input: the layers
+// between must neither read nor write their outputs, which buffers that a caller lets tensors share could make them do.
+int StackCall::run_with(int i, int end, int* with) const {
+    if (prof || inplace || P.torus) return 0;
+    int n = 0;
+    for (int j = P.sibling[i]; j >= 0 && j < end && n < kConvBatch - 1; j = P.sibling[j]) {
+        bool free = true;
+        for (int k = i; k < j && free; ++k) {
+            int ids[4];
+            const int m = layer_inputs(P.layers[k], ids);
+            for (int x = 0; x < m; ++x) free = free && apart(j + 1, ids[x]);
+            free = free && apart(j + 1, k + 1);
+            if (cached && (P.layers[k].type == DC_CONV || P.uses_cache(k))) free = free && apart(j + 1, k + 1, tensors_prev[k + 1]);
+        }
+        if (free) with[n++] = j;
+    }
+    return n;
+}
+
 // The sum behind conv layer i, where a kernel may write both: in the order of the layers the sum's output is written when the
 // convolution has read its input, so buffers that a caller lets tensors share must not be those.
 bool StackCall::sum_with(int i, ConvAdd* add) const {
     if (!sum_behind(P.layers.data(), n_layers, i) || (cached && !devplan) || inplace || P.torus || prof || (devplan && P.uses_cache(i + 1))) return false;
     const dc_layer& sum = P.layers[i + 1];
     const int other = sum.in0 == i + 1 ? sum.in1 : sum.in0;
-    auto bytes = [&](int t) { return (size_t)n_streams * P.hs[t] * P.ws[t] * P.cs[t] * dtype_size(dtype); };
-    auto apart = [&](int t, int v) {
-        const uintptr_t a = reinterpret_cast<uintptr_t>(eff[t]), b = reinterpret_cast<uintptr_t>(eff[v]);
-        return a + bytes(t) <= b || b + bytes(v) <= a;
-    };
     if (!apart(i + 2, P.layers[i].in0) || !apart(i + 2, i + 1) || !(eff[i + 2] == eff[other] || apart(i + 2, other)) || !apart(i + 1, other)) return false;
     *add = ConvAdd{eff[other], eff[i + 2], sum.relu, false};
     return true;
 }
 
-int StackCall::emit_layer(int i, hipStream_t st, ConvAdd* add) {
+int StackCall::emit_layer(int i, hipStream_t st, ConvAdd* add, ConvBatch* batch) {
     const dc_layer& l = P.layers[i];
     const int a = l.in0, t = i + 1;
     const std::vector<int>&hs = P.hs, &ws = P.ws, &cs = P.cs;
@@ -1234,7 +1267,7 @@ int StackCall::emit_layer(int i, hipStream_t st, ConvAdd* add) {
                                     devplan ? n_streams * P.dl.convs[c].units_x * P.dl.convs[c].units_y : 0,
                                     devplan ? pd.n_units + c : nullptr, devplan ? unit_hint[c] : -1, origin_of(a), origin_of(t),
                                     2 * (n_layers + 1), a == 0 ? C : 0, add,
-                                    devplan ? reinterpret_cast<const uint16_t*>(pd.area + P.dl.convs[c].umask_off) : nullptr);
+                                    devplan ? reinterpret_cast<const uint16_t*>(pd.area + P.dl.convs[c].umask_off) : nullptr, batch);
         }
         case DC_MAXPOOL:
             if (origin_of(a))            // its input lies on a torus, and with the cache its output too
@@ -1280,7 +1313,10 @@ int StackCall::emit_layer(int i, hipStream_t st, ConvAdd* add) {
 int StackCall::emit_stage(int s, hipStream_t st) {
     int rc = emit_copies(s, st);
     const int end = pipe ? P.first[s + 1] : n_layers;
-    for (int i = pipe ? P.first[s] : 0; i < end && !rc; ++i) {
+    static_assert((kConvBatch - 1) * kSiblingReach < 32, "a bit for every layer that may run early");
+    uint32_t done = 0;                              // bit d: layer i + d has been launched
+    for (int i = pipe ? P.first[s] : 0; i < end && !rc; ++i, done >>= 1) {
+        if (done & 1) continue;
         if (pipe && i + 1 == end && s + 1 < P.n_stages && P.tight[s + 1]) {
             // the last frame's next stage has to have read the tensor that this layer writes (with another cut its end
             // has been waited for)
@@ -1291,9 +1327,21 @@ int StackCall::emit_stage(int s, hipStream_t st) {
         // (a sum whose buffer the next stage of the last frame may still read has its own wait)
         const bool awaited = pipe && i + 2 == end && s + 1 < P.n_stages && P.tight[s + 1];
         const bool both = i + 1 < end && !awaited && sum_with(i, &add);
-        rc = emit_layer(i, st, both ? &add : nullptr);
+        int with[kConvBatch - 1];
+        const int n_with = both ? 0 : run_with(i, pipe && s + 1 < P.n_stages && P.tight[s + 1] ? end - 1 : end, with);
+        if (n_with) {
+            ConvBatch batch;
+            rc = emit_layer(i, st, nullptr, &batch);
+            for (int m = 0; m < n_with && !rc; ++m) {
+                rc = emit_layer(with[m], st, nullptr, &batch);
+                done |= 1u << (with[m] - i);
+            }
+            if (!rc) DC_TRY_HIP(launch_conv_batch(batch, st));
+        } else {
+            rc = emit_layer(i, st, both ? &add : nullptr);
+        }
         if (pipe && i == P.first[s] && P.tight[s] && !rc) DC_TRY_HIP(hipEventRecord(ov->ring[area].read[s], st));
-        if (add.done) ++i;                          // the sum is written
+        if (add.done) { ++i; done >>= 1; }          // the sum is written
     }
     return rc;
 }

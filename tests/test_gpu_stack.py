@@ -1487,3 +1487,39 @@ def test_whole_map_kernel_in_cached_frames(oracle, H, W, torus):
     upw = (((H // 4) * (W // 4) + 15) // 16 + 3) // 4
     assert [binding.conv_kernel_name(stats["kernel_id"][i]) for i in convs] == [f"conv_map_kernel<{upw}, 4>", f"conv_map_kernel<{upw}, 2>"]
     assert runner.read_stats() and runner.layer_stats()["reused_px"][convs[0]] > 0
+
+
+@pytest.mark.parametrize("device_plan", [True, False])
+@pytest.mark.parametrize("bf16,n", [(True, 1), (True, 6), (False, 40)])
+def test_pointwise_layers_of_one_tensor_in_one_launch(bf16, n, device_plan):
+    """The three 1x1 convolutions of an inception module that read the module's input go out as one launch; with a profile
+    attached they are three.  The same bits in full frames and in cached ones, with the stem outside the cache or not."""
+    layers = synth.googlenet(width=0.5)[:23]
+    H = W = 64
+    ws, bs = synth.he_weights(layers, 3, bias_scale=0.05, input_shape=(H, W, 3))
+    video = np.stack([synth.panning_video(7600 + s, n_frames=4, H=H, W=W, fg=((24, 24),), margin=32) for s in range(n)])
+    dev = torch.from_numpy(np.ascontiguousarray(video.transpose(1, 0, 2, 3, 4))).to(DEV)
+    together = [i for i, L in enumerate(layers) if L["type"] == synth.CONV and L["k"] == 1 and sum(o["type"] == synth.CONV and o["k"] == 1 and o["in0"] == L["in0"] for o in layers) == 3]
+    assert len(together) == 6
+    flags = np.zeros(len(layers), np.uint8)
+    flags[together[1]] = 1
+    for no_reuse in (None, flags):
+        runs = []
+        for profile in (False, True):
+            runner = binding.StackRunner(layers, ws, bs, n, H, W, 3, block=16, radius=16, device_plan=device_plan, exact_masks=device_plan, overlap=False,
+                                         dtype=binding.DC_BF16 if bf16 else binding.DC_F32, no_reuse=no_reuse)
+            runner.enable_profile(profile)
+            frames = []
+            for t in range(4):
+                print(f"[pointwise] bf16={bf16} n={n} device_plan={device_plan} profile={profile} frame {t}", flush=True)
+                got = runner.step(dev[t])
+                torch.cuda.synchronize()
+                names = [binding.conv_kernel_name(k) if k >= 0 else "" for k in runner.layer_stats()["kernel_id"]]
+                frames.append([x.clone() for x in got])
+            runs.append((frames, names))
+        if bf16:      # (fp32: whole tiles where the maps are large enough)
+            assert all("conv_pw_many_kernel" in runs[0][1][i] for i in together)
+        assert not any("conv_pw_many_kernel" in v for v in runs[1][1])
+        for t in range(4):
+            for i, (a, b) in enumerate(zip(runs[0][0][t], runs[1][0][t])):
+                assert torch.equal(a, b), (t, i)

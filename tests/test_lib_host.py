@@ -465,8 +465,10 @@ def test_kernel_names_of_stems_sums_and_whole_maps():
     names = {432: "conv_stem4_kernel<7, 2, 4, 1, 4>", **{432 + w: f"conv_stem4_kernel<11, 4, 2, {w}, 1>" for w in (1, 2, 3)},
              440: "conv_pw_add_kernel<float, 2>", 441: "conv_pw_add_kernel<__hip_bfloat16, 2>", 442: "conv_pw_add_kernel<float, 4>",
              443: "conv_pw_add_kernel<__hip_bfloat16, 4>",
-             **{448 + 4 * (b == 4) + u - 1: f"conv_map_kernel<{u}, {b}>" for b in (2, 4) for u in (1, 2, 3, 4)}}
-    for kid in range(432, 464):
+             **{448 + 4 * (b == 4) + u - 1: f"conv_map_kernel<{u}, {b}>" for b in (2, 4) for u in (1, 2, 3, 4)},
+             464: "conv_pw_many_kernel<float, 2>", 465: "conv_pw_many_kernel<__hip_bfloat16, 2>", 466: "conv_pw_many_kernel<float, 4>",
+             467: "conv_pw_many_kernel<__hip_bfloat16, 4>"}
+    for kid in range(432, 480):
         buf = C.create_string_buffer(160)
         rc = binding.lib().dc_conv_kernel_name(kid, buf, 160)
         assert (buf.value.decode() if rc == 0 else None) == names.get(kid), kid
