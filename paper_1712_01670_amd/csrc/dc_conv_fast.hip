@@ -1,9 +1,11 @@
 // Cache-aware convolution (Section 5 "Reuse", steps 2-3), the kernels for the common layer shape: 3x3 taps,
-// stride 1.  Five kernels share this file:
+// stride 1, and their neighbours.  The kernels of this file:
 //   conv_fast_kernel   channel counts that are whole 64-byte rows, 64 or 128 output channels per workgroup (5x5 taps
 //                      as well, in bf16);
 //   conv_map_kernel    bf16, 3x3, maps of up to 14x14 of which nearly every unit has work (see there);
 //   conv_deep_kernel   bf16, 3x3, many units: weights from L2 into registers (see there);
+//   conv_pw_kernel     1x1 layers, with a residual sum behind or several of one tensor in a launch (see there);
+//   conv_stem4_kernel  7x7 and 11x11 stems in bf16 (see there);
 //   conv_regw_kernel   64 input channels in bf16 and many units: persistent, weights in registers (see there);
 //   conv_first_kernel  input pixels of one 16-byte vector (the padded first layer), nothing staged (see there).
 //
@@ -1374,6 +1376,8 @@ __global__ __launch_bounds__(WM * 128) void conv_pw_add_kernel(ConvParams P) { c
 // Several 1x1 layers that read one tensor, in one launch: workgroups first[j] .. first[j + 1] - 1 are those that layer j's own launch
 // would have (whole rounds of the XCDs each), so the sums are the same.  An inception module's branches have 32 to 600
 // workgroups of a few us each, less than the chip holds: alone, each branch pays for a launch and for its own chain of loads.
+// GoogLeNet 224x224, ten frames in bf16, 1 / 4 / 16 / 64 streams: 2458 / 2458 / 3630 / 9184 us -> 2247 / 2356 / 3341 / 8804;
+// fp32, 16 streams, where the tiles fill the chip and the matrix pipes are the bound: 7839 -> 7817.
 struct PwMany {
     ConvParams p[kConvBatch];
     int first[kConvBatch];
@@ -2067,8 +2071,9 @@ hipError_t deep_launch(int g, dim3 grid, hipStream_t st, const ConvParams& P) {
 // more than half of a pair.  Measured, us, conv_fast_kernel's best -> units per workgroup 6 / 7 / 8: 56x56 256->256 64 streams
 // 214 -> 212 / 175 / 181, 16 streams 60 -> 68 / 51 / 54; 28x28 512->512 64 streams 199 -> 219 / 186 / 221, 16 streams
 // 60 -> 83 / 55 / 60; 112x112 128->128 64 / 28 / 20 streams 254 -> 233 / 222 / 223, 114 -> 106 / 103 / 100,
-// 84 -> 83 / 80 / 73; launches of less than one workgroup per CU lose (13x13 512->1024 16 streams 34 -> 41 / 45 / 50), and so do few workgroups of two wavefronts (13x13 384->384 64
-// streams 40 -> 49 / 56 / 65), hence the least number of those.
+// 84 -> 83 / 80 / 73; launches of less than one workgroup per CU lose (13x13 512->1024
+// 16 streams 34 -> 41 / 45 / 50), and so do few workgroups of two wavefronts (13x13 384->384 64 streams 40 -> 49 / 56 / 65;
+// 52x52 128->384 8 streams, 1014 of them, 23 -> 27), hence the least number of those.
 double deep_cost(const ConvLaunch& c, long n_units, int g) {
     const int nw = c.Cout % 256 ? 2 : 4, n_ch = c.Cin / 32;
     const long wgs = (n_units + g - 1) / g * (c.Cout / (64 * nw));

@@ -687,7 +687,7 @@ __global__ __launch_bounds__(kPlanChunk) void plan_masks_kernel(PlanDev P) {
     }
 }
 
-// EXACT: the unit's mask is cut out of the tensor's bitmap here (and stored for the shifted copies, if there are any).
+// EXACT: the unit's mask is cut out of the tensor's bitmap here and stored (for the shifted copies and for conv_map_kernel).
 template <bool EXACT>
 __global__ __launch_bounds__(kPlanChunk) void plan_lists_kernel(PlanDev P) {
     const int chunk = blockIdx.x, stream = blockIdx.y, c = blockIdx.z, tid = threadIdx.x;
