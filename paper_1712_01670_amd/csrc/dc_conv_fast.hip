@@ -603,7 +603,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
 // 13x13 384->384 on 64 streams 44 -> 36 us, 512->1024 on 16 streams 36 -> 30, 14x14 512->512 on 64 streams 61 -> 52.  What bounds it:
 // a barrier per kernel row at two wavefronts per SIMD, and few workgroups (192 to 512 for 256 CUs).
 // LDS: the row of slot (line, column) at (16 line + column) * 64 bytes, its 16-byte chunk c at c ^ 2 (column / 4 % 2): a read
-// of 16 neighbouring pixels of a line is free of conflicts, one across a line's end has a few of two.
+// of 16 neighbouring pixels of a line is free of conflicts, one across a line's end is not (14x14: 0.29 of the LDS cycles).
 template <int UPW, int NBW>
 __global__ __launch_bounds__(512) void conv_map_kernel(ConvParams P) {
     typedef __hip_bfloat16 T;
