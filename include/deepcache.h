@@ -285,7 +285,8 @@ int32_t dc_overlap_stats(const void* overlap, dc_overlap_counters* counters);
  * wavefronts with 13..18 units per workgroup, 5: the kernel whose weights go straight to registers, 6..8 units,
  * multiples of 128 channels; a K split of 2 selects its 128-channel workgroups, 6: the kernel
  * that takes whole maps of up to 14x14 pixels, 4 units: 128 channels per workgroup), units per workgroup
- * (1..18; for the 1x1 kernel 4 or 8 selects its 64 x 64 or 128 x 128 tile), number of workgroups that split K,
+ * (1..18; for the 1x1 kernel 4 or 8 selects its 64 x 64 or 128 x 128 tile, for the bf16 stems of a frame 4 the kernel
+ * that takes the patch through LDS, 1 the other), number of workgroups that split K,
  * channel chunk index (0, 1).  A negative value leaves that choice to the library; values a layer cannot use are
  * ignored for that layer.
  */

@@ -1724,26 +1724,33 @@ __global__ __launch_bounds__(256) void conv_stem11_kernel(ConvParams P) { conv_f
 
 // ---- bf16 stems whose input pixels hold at most four channels ---------------------------------------------------
 // Tensor 0 of a stack has eight channels per pixel (one 16-byte vector), of which a frame fills three or four; the rest are
-// exact zeros.  The kernels above multiply all eight (11x11: 33 MFMAs per unit and 16 channels, 7x7: 14), and every block
-// of 16 or 32 channels fetches every input vector again: AlexNet's first layer loads 33 KiB per unit and block.  Here the
-// unit's patch is brought into LDS once, four channels a pixel, for all channels of the workgroup: a fragment of eight
-// elements is two taps, K is 17 groups (7x7: 7), and a wavefront keeps the weights of 16 NB channels in registers.
+// exact zeros.  In the kernels above every block of 16 or 32 channels fetches every input vector again: AlexNet's first layer
+// loads 33 KiB per unit and block.  Here the unit's patch is brought into LDS once, four channels a pixel, for all channels
+// of the workgroup, and a wavefront keeps the weights of 16 NB channels in registers.
 //   workgroup = NU units at a time, NWC wavefronts of 16 NB channels each per unit; persistent, walks the unit list
-//   K groups  = kernel rows of PPR tap pairs: 4 pairs (7x7) are one group; 6 pairs (11x11): rows in twos, group 0 and 1 the
-//               first four pairs of each, group 2 the other two pairs of both; the last row alone takes two groups
-// LDS rows are RS bytes apart, chosen so that the four rows a read touches fall into different banks.
+//   K groups  = four taps of a kernel row, one per quarter of a wavefront, row after row: those of the kernels above, in their
+//               order.  Two groups share the registers of a fragment (four channels of each); the MFMA of one multiplies
+//               the other's pixels by zeros, as the kernels above do with channels four to seven: the same bits.  (Both
+//               in one MFMA, or MFMAs of half the K, would add in another order: measured, one value in 65 000 rounds
+//               to another bf16.)  The weights with their zeros are made by two moves per MFMA; kept in registers for one
+//               block of channels per wavefront they take longer (11x11 on 64 streams 85 us), the pixels being read twice as often.
+// LDS: rows are RS bytes apart and, 11x11, column x of row y lies at x ^ 2 (y / 4 % 2): the 32 reads of half a wavefront (pixels
+// of two quarters) fall into different banks.
 // Channels four to seven of the weights meet zeros and are not read.
-// 227x227 11x11 -> 96 on 64 streams: 91.4 -> 28.1 us (37 MB out and 53 MB in: 18 at the copy's rate), 224x224 7x7 -> 64 on 16
-// streams 23.1 -> 16.0.  What bounds it now: a step's chain of load, LDS write, barrier and reads at two workgroups per CU.
+// 227x227 11x11 -> 96 on 1 / 4 / 16 / 64 streams, against the kernel above: 9.0 -> 7.8, 16.8 -> 14.2, 44.8 -> 22.8, 145.6 -> 57.8 us (37 MB
+// out and 53 MB in on 64: 18 at the copy's rate); 224x224 7x7 -> 64 on 1 / 4 / 8 / 16 / 64: 5.9 -> 7.7, 11.1 -> 13.3, 17.3 -> 16.4, 28.2 -> 22.6, 92.3 -> 55.6.
+// What bounds it: a step's chain of load, LDS write, barrier, reads and dependent MFMAs at two workgroups per CU (the
+// pixels requested two steps ahead: 11x11 64 us, 7x7 85: the registers cost more than the wait).
 template <int K, int S, int NB, int NWC, int NU>
 __global__ __launch_bounds__(NWC * NU * 64) void conv_stem4_kernel(ConvParams P) {
     typedef __hip_bfloat16 T;
     typedef Frag<T> F;
     typedef F::vec vec;
-    constexpr int PPR = (K + 1) / 2, PH = 3 * S + K, PWX = 3 * S + 2 * PPR, RS = K == 11 ? 224 : 160;
-    constexpr int NG = PPR == 4 ? K : K / 2 * 3 + 2;
+    constexpr int TG = (K + 3) / 4, NG = K * TG, NP = (NG + 1) / 2;      // groups of a kernel row, all groups, pairs of them
+    constexpr bool kSwizzle = K == 11;
+    constexpr int PH = 3 * S + K, PWX = 3 * S + 4 * TG, RS = K == 11 ? 208 : 160;
     constexpr int GT = NWC * 64, NPT = (PH * PWX + GT - 1) / GT, PATCH = PH * RS;
-    static_assert((PPR == 4 || (PPR == 6 && K % 2)) && PWX * 8 <= RS, "shape");
+    static_assert(PWX * 8 <= RS && (!kSwizzle || PWX % 4 == 0), "shape; a swizzled column stays in its row");
 
     __shared__ __align__(16) unsigned char smem[NU * 2 * PATCH];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1753,26 +1760,28 @@ __global__ __launch_bounds__(NWC * NU * 64) void conv_stem4_kernel(ConvParams P)
     const __amdgpu_buffer_rsrc_t in_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(P.in), 0, P.in_bytes, kBufferFlags);
     const __amdgpu_buffer_rsrc_t w_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(P.w), 0, P.w_bytes, kBufferFlags);
 
-    // group g, quarter q: kernel row and tap pair
-    auto row_of = [&](int g) { return PPR == 4 ? g : g < NG - 2 ? g / 3 * 2 + (g % 3 == 2 ? q >> 1 : g % 3) : K - 1; };
-    auto pair_of = [&](int g) { return PPR == 4 ? q : g < NG - 2 ? (g % 3 == 2 ? 4 + (q & 1) : q) : g == NG - 2 ? q : 4 + q; };
-    vec wv[NG][NB];
+    // group g, quarter q: tap 4 (g % TG) + q of kernel row g / TG; groups 2 i and 2 i + 1 in the halves of wv[i]
+    uintx4 wv[NP][NB];
 #pragma unroll
-    for (int g = 0; g < NG; ++g)
+    for (int i = 0; i < NP; ++i)
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
             // row l16 of block j: channel (l16 / 4) * 4 NB + 4 j + l16 % 4, so that a lane ends with 4 NB consecutive ones
             const int co = n0 + (l16 >> 2) * (4 * NB) + j * 4 + (l16 & 3);
-            uintx4 v;
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-                const int tap = 2 * pair_of(g) + h;
-                const uint32_t off = tap < K ? (uint32_t)((co * (K * K) + row_of(g) * K + tap) * 16) : kOob;
+                const int g = 2 * i + h, tap = g % TG * 4 + q;
+                const uint32_t off = g < NG && tap < K ? (uint32_t)((co * (K * K) + g / TG * K + tap) * 16) : kOob;
                 const uintx2 d = __builtin_bit_cast(uintx2, __builtin_amdgcn_raw_buffer_load_b64(w_rsrc, off, 0, 0));
-                v[2 * h] = d[0]; v[2 * h + 1] = d[1];
+                wv[i][j][2 * h] = d[0]; wv[i][j][2 * h + 1] = d[1];
             }
-            wv[g][j] = __builtin_bit_cast(vec, v);
         }
+    uintx4 w_lo[NB], w_hi[NB];                       // one group's weights beside zeros
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+        w_lo[j] = w_hi[j] = uintx4{0, 0, 0, 0};
+        asm volatile("" : "+v"(w_lo[j]), "+v"(w_hi[j]));       // (the zeros stay in registers)
+    }
     const int chan = n0 + 4 * NB * q;
     floatx4 bias[NB];
 #pragma unroll
@@ -1782,12 +1791,13 @@ __global__ __launch_bounds__(NWC * NU * 64) void conv_stem4_kernel(ConvParams P)
 
     // the pixels of a patch that this thread brings: row and column in the patch, byte offset in LDS
     const int gt = wave_c * 64 + lane;
-    int ppy[NPT], ppx[NPT];
+    int ppy[NPT], ppx[NPT], ppos[NPT];
 #pragma unroll
     for (int i = 0; i < NPT; ++i) {
         const int at = gt + i * GT;
         ppy[i] = at / PWX;
         ppx[i] = at - ppy[i] * PWX;
+        ppos[i] = ppy[i] * RS + (kSwizzle ? ppx[i] ^ (ppy[i] >> 2 & 1) * 2 : ppx[i]) * 8;
     }
     const int n_units = unit_count(P), per = P.units_x * P.units_y;
     struct UnitPos { int stream, uy, ux, mixed; };     // mixed == -1: no such unit
@@ -1816,9 +1826,12 @@ __global__ __launch_bounds__(NWC * NU * 64) void conv_stem4_kernel(ConvParams P)
             px[i] = __builtin_bit_cast(uintx2, __builtin_amdgcn_raw_buffer_load_b64(in_rsrc, off, 0, 0));
         }
     };
-    // read side: quarter q reads pair q of a row, or (group 2 of two rows) pair 4 + q % 2 of row q / 2
-    const int xaddr = (l16 >> 2) * (S * RS) + (l16 & 3) * (S * 8) + q * 16;
-    const int xaddr3 = (l16 >> 2) * (S * RS) + (l16 & 3) * (S * 8) + (4 + (q & 1)) * 16, xaddr2 = xaddr3 + (q >> 1) * RS;
+    // read side: this quarter's tap of group 0, for kernel rows ky with ky / 4 even and odd
+    static_assert(!kSwizzle || S == 4, "line l16 / 4 of the output starts at row 4 (l16 / 4) of the patch");
+    int xaddr[2];
+#pragma unroll
+    for (int o = 0; o < 2; ++o)
+        xaddr[o] = (l16 >> 2) * (S * RS) + (l16 & 3) * (S * 8) + (kSwizzle ? q ^ (((l16 >> 2) + o) & 1) * 2 : q) * 8;
 
     const int step = (int)gridDim.x * NU, first = (int)blockIdx.x * NU;
     if (first >= n_units) return;                      // the whole workgroup, before any barrier
@@ -1830,7 +1843,7 @@ __global__ __launch_bounds__(NWC * NU * 64) void conv_stem4_kernel(ConvParams P)
         unsigned char* const patch = smem + (wave_u * 2 + buf) * PATCH;
 #pragma unroll
         for (int i = 0; i < NPT; ++i)
-            if ((i + 1) * GT <= PH * PWX || gt + i * GT < PH * PWX) *reinterpret_cast<uintx2*>(patch + ppy[i] * RS + ppx[i] * 8) = px[i];
+            if ((i + 1) * GT <= PH * PWX || gt + i * GT < PH * PWX) *reinterpret_cast<uintx2*>(patch + ppos[i]) = px[i];
         if constexpr (NWC > 1) lds_barrier();      // the patch is in LDS; nobody reads the other buffer any more
         const bool more = base + step < n_units;
         UnitPos after{0, 0, 0, -1};
@@ -1840,16 +1853,23 @@ __global__ __launch_bounds__(NWC * NU * 64) void conv_stem4_kernel(ConvParams P)
         }
         floatx4 acc[NB];
 #pragma unroll
-        for (int j = 0; j < NB; ++j) acc[j] = bias[j];
+        for (int j = 0; j < NB; ++j) acc[j] = bias[j] + 0.f;      // (-0: products with the zeros may be -0 here, and +0 is what a sum of both is)
 #pragma unroll
-        for (int g = 0; g < NG; ++g) {
-            const unsigned char* xp = patch;
-            if (PPR == 4) xp += xaddr + g * RS;
-            else if (g < NG - 2) xp += g % 3 == 2 ? xaddr2 + g / 3 * 2 * RS : xaddr + (g / 3 * 2 + g % 3) * RS;
-            else xp += (g == NG - 2 ? xaddr : xaddr3) + (K - 1) * RS;   // (the weights of the last group's quarters 2 and 3 are zero)
-            const vec x = *reinterpret_cast<const vec*>(xp);
+        for (int i = 0; i < NP; ++i) {
+            auto read_x = [&](int g) { return *reinterpret_cast<const uintx2*>(patch + xaddr[g / TG >> 2 & 1] + g / TG * RS + g % TG * 32); };
+            const bool two = 2 * i + 1 < NG;
+            const uintx2 lo = read_x(2 * i), hi = two ? read_x(2 * i + 1) : lo;
+            const vec x = __builtin_bit_cast(vec, uintx4{lo[0], lo[1], hi[0], hi[1]});
 #pragma unroll
-            for (int j = 0; j < NB; ++j) F::mma1(wv[g][j], x, acc[j], 0);
+            for (int j = 0; j < NB; ++j) {
+                w_lo[j][0] = wv[i][j][0]; w_lo[j][1] = wv[i][j][1];
+                F::mma1(__builtin_bit_cast(vec, w_lo[j]), x, acc[j], 0);
+            }
+#pragma unroll
+            for (int j = 0; two && j < NB; ++j) {
+                w_hi[j][2] = wv[i][j][2]; w_hi[j][3] = wv[i][j][3];
+                F::mma1(__builtin_bit_cast(vec, w_hi[j]), x, acc[j], 0);
+            }
         }
         const int y = pos.uy * 4 + (l16 >> 2), x = pos.ux * 4 + (l16 & 3);
         if (pos.mixed >= 0 && y < P.Hout && x < P.Wout && !((pos.mixed >> l16) & 1)) {      // a reusable pixel holds the cached value
@@ -1877,14 +1897,16 @@ __global__ __launch_bounds__(NWC * NU * 64) void conv_stem4_kernel(ConvParams P)
     }
 }
 
-// Workgroups of a launch: two per CU, which is what the registers allow (11x11: 256 / 512 / 768 / 1024 of them 42 / 28 / 38 /
-// 35 us on 64 streams, 7x7 on 16 streams 18 / 16 / 19 / 21: every further one loads its weights again).
+// Workgroups of a launch: two per CU, which is what the registers allow (11x11: 256 / 384 / 512 / 768 of them 78 / 71 / 58 /
+// 66 us on 64 streams, 7x7 71 / 66 / 56 / 60: every further one loads its weights again).
 constexpr int kStem4Wgs = 512;
 constexpr int kStem4Id = 432;         // kernel ids: 7x7, then 11x11 with 1, 2, 3 wavefronts a unit
-// Wavefronts per unit of conv_stem4_kernel, 0: not its shape.
-int stem4_waves(const ConvLaunch& c) {
-    if (c.dtype != DC_BF16 || c.c_frame < 1 || c.c_frame > 4 || c.Cin != 8) return 0;
-    if (c.k == 7 && c.s == 2) return c.Cout % 64 == 0 ? 1 : 0;
+// Wavefronts per unit of conv_stem4_kernel, 0: not its shape, or too few units for it: a 7x7 layer's patches are small and what
+// they save only pays for the longer start of a workgroup from about 6000 units of 64 channels on (times above; 8 streams of
+// 224x224 have 6272).  Both kernels give the same bits.  Units per workgroup 1 or 4 in dc_conv_tuning choose one.
+int stem4_waves(const ConvLaunch& c, long n_units, int forced) {
+    if (c.dtype != DC_BF16 || c.c_frame < 1 || c.c_frame > 4 || c.Cin != 8 || forced == 1) return 0;
+    if (c.k == 7 && c.s == 2) return c.Cout % 64 == 0 && (forced == 4 || n_units * (c.Cout / 64) >= 6000) ? 1 : 0;
     return c.k == 11 && c.s == 4 ? (c.Cout % 96 == 0 ? 3 : c.Cout % 64 == 0 ? 2 : c.Cout % 32 == 0 ? 1 : 0) : 0;
 }
 hipError_t stem4_launch(int k, int nwc, dim3 grid, hipStream_t st, const ConvParams& P) {
@@ -2448,7 +2470,7 @@ bool launch_conv_fast(const ConvLaunch& c, long n_cap, long n_units, hipStream_t
                 *c.kernel_id = c.k == 11 ? 106 + (c.dtype == DC_BF16 ? 1 : 0)
                              : c.k == 7 ? 102 + (c.dtype == DC_BF16 ? 2 : 0) + (nb == 2 ? 1 : 0)
                                         : 96 + (c.dtype == DC_BF16 ? 3 : 0) + (nb == 4 ? 2 : (nb == 2 ? 1 : 0));
-            if (const int nwc = stem4_waves(c)) {
+            if (const int nwc = stem4_waves(c, n_units, g_tune[1])) {
                 const int gy = c.Cout / (c.k == 7 ? 64 : 32 * nwc);
                 const long nu = c.k == 7 ? 4 : 1, wgs = std::min((n_cap + nu - 1) / nu, std::max(1L, (long)kStem4Wgs / gy));
                 if (c.kernel_id) *c.kernel_id = kStem4Id + (c.k == 7 ? 0 : nwc);

@@ -1432,10 +1432,67 @@ def test_stems_with_four_channels_a_pixel(oracle, k, s, p, cout, C, n, H, W, kid
     if C == 4:
         video = np.concatenate([video, video[..., :1] ^ 85], axis=-1)
     layers = [dict(type=synth.CONV, k=k, s=s, p=p, cin=C, cout=cout, relu=1, in0=0, in1=-1)]
-    runner, reuse = _run_one(oracle, layers, video, 16, 8, True, device_plan=True, exact_masks=True, bias_scale=0.1)
+    binding.dc_conv_tuning(-1, 4, -1, -1)           # (few units: a 7x7 layer would take the other kernel)
+    try:
+        runner, reuse = _run_one(oracle, layers, video, 16, 8, True, device_plan=True, exact_masks=True, bias_scale=0.1)
+        kernel_id = runner.layer_stats()["kernel_id"][0]
+    finally:
+        binding.dc_conv_tuning()
     assert max(reuse) > 0.2
-    assert binding.conv_kernel_name(runner.layer_stats()["kernel_id"][0]) == \
+    assert binding.conv_kernel_name(kernel_id) == \
         ("conv_stem4_kernel<7, 2, 4, 1, 4>" if k == 7 else f"conv_stem4_kernel<11, 4, 2, {kid}, 1>")
+
+
+@pytest.mark.parametrize("k,s,p,cout,C,n,H,W", [
+    (7, 2, 3, 64, 3, 8, 224, 224), (7, 2, 3, 128, 4, 5, 301, 203), (7, 2, 0, 64, 1, 2, 64, 48),
+    (11, 4, 0, 96, 3, 6, 227, 227), (11, 4, 2, 192, 4, 3, 170, 199), (11, 4, 2, 64, 3, 8, 224, 224), (11, 4, 5, 32, 2, 9, 196, 264)])
+def test_both_stem_kernels_give_the_same_bits(k, s, p, cout, C, n, H, W):
+    """Frames through the kernel with the patch in LDS and through the other, and the layer alone over all eight channels of a
+    pixel: the same sums in the same order, so the same bits.  Channel 0 has an infinite weight, channel 1 nothing but
+    zeros of both signs and a bias of -0."""
+    layers = [dict(type=synth.CONV, k=k, s=s, p=p, cin=C, cout=cout, relu=0, in0=0, in1=-1)]
+    ws, bs = synth.he_weights(layers, 3, bias_scale=0.1)
+    w = np.array(ws[0], np.float32).reshape(cout, k, k, C)
+    b = np.array(bs[0], np.float32)
+    w[0, 1, 2, 0] = np.inf
+    w[1], b[1] = np.where(np.arange(k * k * C).reshape(k, k, C) % 2, -0.0, 0.0), -0.0
+    video = np.stack([synth.panning_video(7700 + i, n_frames=3, H=H, W=W, fg=((24, 24),), margin=32) for i in range(n)])
+    video = np.concatenate([video, video[..., :1] ^ 85], axis=-1)[..., :C]
+    dev = torch.from_numpy(np.ascontiguousarray(video.transpose(1, 0, 2, 3, 4))).to(DEV)
+    runs = {}
+    for units in (1, 4):
+        binding.dc_conv_tuning(-1, units, -1, -1)
+        try:
+            runner = binding.StackRunner(layers, [w.reshape(ws[0].shape)], [b], n, H, W, C, block=16, radius=8, dtype=binding.DC_BF16,
+                                         device_plan=True, exact_masks=True)
+            frames = []
+            for t in range(3):
+                print(f"[stems] k={k} cout={cout} C={C} n={n} {H}x{W} units={units} frame {t}", flush=True)
+                got = runner.step(dev[t])
+                torch.cuda.synchronize()
+                frames.append((got[0].clone(), got[1].clone()))
+            name = binding.conv_kernel_name(runner.layer_stats()["kernel_id"][0])
+        finally:
+            binding.dc_conv_tuning()
+        assert name.startswith("conv_stem4_kernel" if units == 4 else f"conv_stem{11 if k == 11 else ''}_kernel"), name
+        runs[units] = frames
+    for t in range(3):
+        assert torch.equal(runs[1][t][1].view(torch.int16), runs[4][t][1].view(torch.int16)), t
+    wide = np.zeros((cout, k, k, 8), np.float32)
+    wide[..., :C] = w
+    alone = binding.dc_cached_conv_layer(dict(layers[0], cin=8), runs[4][0][0], torch.from_numpy(wide).bfloat16().to(DEV), torch.from_numpy(b).to(DEV))
+    assert torch.equal(alone.view(torch.int16), runs[4][0][1].view(torch.int16))
+
+
+def test_stem_kernel_follows_the_number_of_units():
+    """7x7 in bf16: the kernel with the patch in LDS from about 6000 units of 64 channels on."""
+    for n, cout, name in ((2, 64, "conv_stem_kernel<__hip_bfloat16, 2>"), (8, 64, "conv_stem4_kernel<7, 2, 4, 1, 4>"), (4, 128, "conv_stem4_kernel<7, 2, 4, 1, 4>")):
+        layers = [dict(type=synth.CONV, k=7, s=2, p=3, cin=3, cout=cout, relu=1, in0=0, in1=-1)]
+        ws, bs = synth.he_weights(layers, 3)
+        runner = binding.StackRunner(layers, ws, bs, n, 224, 224, 3, dtype=binding.DC_BF16)
+        runner.step(torch.zeros((n, 224, 224, 3), dtype=torch.uint8, device=DEV))
+        torch.cuda.synchronize()
+        assert binding.conv_kernel_name(runner.layer_stats()["kernel_id"][0]) == name, (n, cout)
 
 
 @pytest.mark.parametrize("bf16,n", [(True, 1), (True, 3), (False, 12)])
