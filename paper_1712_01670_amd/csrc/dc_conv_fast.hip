@@ -1109,16 +1109,17 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(const uintx4* src, ui
 // Cin only has to be a whole number of 16-byte vectors (the last chunk is filled with zeros), Cout a multiple of 8.
 // Workgroups are numbered so that the channel tiles of one unit group run on the same XCD at about the same time:
 // the second to last of them find the input pixels in that XCD's L2; the groups go round the XCDs.
-// What a short launch waits for is its chain of loads, so the list entries are fetched together with the list's length,
-// the bias and the first weights while the unit table is made, and no load is waited for between the stores.  The 15 layer
-// shapes of ResNet-50 on 1 / 16 / 64 streams, us in all: 104.8 -> 98.3, 182.5 -> 172.0, 459.5 -> 447.1 (one got longer:
-// 56x56 64->256 on more than 16 streams, 31 -> 36).
+// What a short launch waits for is its chain of loads, so the list entries are fetched together with the list's length and
+// the bias while the unit table is made, and no load is waited for between the stores.  The 15 layer shapes of ResNet-50 on
+// 1 / 16 / 64 streams in bf16, us in all: 107.9 -> 93.2, 179.7 -> 163.4, 450.7 -> 420.9; fp32 on 1 / 6 / 16: 117.1 -> 116.2, 276.7 -> 269.9,
+// 489.0 -> 477.1; no shape takes longer.  (The first weights ahead of the unit table as well: 95.9, 163.7, 426.6 and 117.2, 273.6, 484.4, with
+// 56x56 64->256 in fp32 on 6 streams at 16 us for 15: they delay the patches, which take longer to come.)
 //
 // ADD: the layer is followed by the element-wise sum of its output with another tensor (a residual block's end), and the
 // sum is written here as well: the convolution's output is rounded as it is stored and summed as the sum's own kernel
 // does (ResNet-50 on one stream, frame after frame without stages: 497 -> 462 us, on 16 streams 874 -> 830).  Where a pixel is reusable its output is the copied value, fetched beside the other summand while K is walked.
 // Units without work stand behind the others in the list (plan_lists_kernel); a group of them only adds.
-constexpr int kPwHeaderBytes = 1536;
+constexpr int kPwHeaderBytes = 2048;
 template <typename T, int WM, bool ADD>
 __device__ __forceinline__ void conv_pw_body(const ConvParams& P, const int block) {
     typedef Frag<T> F;
@@ -1136,8 +1137,9 @@ __device__ __forceinline__ void conv_pw_body(const ConvParams& P, const int bloc
     int4* const uq = reinterpret_cast<int4*>(smem);                   // [G] {stream, row, column of the unit, its reuse mask; -1: none}
     int2* const px = reinterpret_cast<int2*>(smem + 128);             // [16 G] byte offset in the input, element offset in the output
     unsigned char* const px_skip = smem + 1152;                       // [16 G] 1: not stored; 3: no such pixel
+    const float* const bias_at = reinterpret_cast<const float*>(smem + 1280);     // [NT]
     unsigned char* const ring = smem + kPwHeaderBytes;
-    static_assert(G <= 8, "tables");
+    static_assert(G <= 8 && NT <= 128, "tables");
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1171,34 +1173,20 @@ __device__ __forceinline__ void conv_pw_body(const ConvParams& P, const int bloc
         const int ch = n0 + row / (NBW * 16) * (NBW * 16) + ((row & 15) >> 2) * (4 * NBW) + ((row >> 4) % NBW) * 4 + (row & 3);
         wgo[i] = ch < P.Cout ? (uint32_t)(ch * CinES + (c << 4)) : kOob;
     }
-    auto issue_w = [&](int chunk, int slot) {
-        unsigned char* dst = ring + slot * STAGE + PBYTES + wave * 1024;
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const bool in_k = chunk * KC + lch[i] < P.Cin;
-            const uint32_t off = in_k ? wgo[i] + (uint32_t)(chunk * RB) : kOob;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rsrc, (__attribute__((address_space(3))) void*)(dst + i * (NW * 1024)),
-                                                     16, off, 0, 0, 0);
-        }
-    };
     // Every unit group starts its walk over K at another chunk: rows are Cin * ES bytes apart, a power of two for
     // most layers, so workgroups that all read chunk c of their rows at the same time would all hit the few memory
     // channels those addresses map to.
     const int n_ch = P.n_chunks;
     const int start = ug % n_ch;
     auto chunk_of = [&](int c) { const int cc = start + c; return cc < n_ch ? cc : cc - n_ch; };
-    // the bias now: in the epilogue its wait would be one for the stores before it as well
+    // The bias goes to LDS, ahead of every other load (fetched in the epilogue it would wait for the stores before it; 16 more
+    // registers leave room for two workgroups of eight wavefronts on a CU instead of three: 56x56 64->256 on 64 streams 31 -> 35 us).
     const int chan0 = n0 + wave_n * (NBW * 16) + q * (4 * NBW);
-    floatx4 b[NBW];
-#pragma unroll
-    for (int j = 0; j < NBW; ++j)
-        b[j] = (P.bias && chan0 + j * 4 < P.Cout) ? *reinterpret_cast<const floatx4*>(P.bias + chan0 + j * 4) : floatx4{0.f, 0.f, 0.f, 0.f};
+    const __amdgpu_buffer_rsrc_t b_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(P.bias), 0, P.bias ? P.Cout * 4 : 0, kBufferFlags);
+    if (gemm && wave < NT / 64)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(b_rsrc, (__attribute__((address_space(3))) void*)(smem + 1280 + wave * 256), 4,
+                                                 (uint32_t)((n0 + wave * 64 + lane) * 4), 0, 0, 0);
     asm volatile("" ::: "memory");
-    if (gemm) {
-#pragma unroll
-        for (int d = 0; d < D; ++d)
-            if (d < n_ch) issue_w(chunk_of(d), d);
-    }
 
     // tables of the group's units and pixels
     if (tid < G) {
@@ -1235,13 +1223,14 @@ __device__ __forceinline__ void conv_pw_body(const ConvParams& P, const int bloc
         const int c = lpos ^ ((row >> 1) & 7);
         pgo[i] = px_skip[row] & 2 ? kOob : (uint32_t)px[row].x + (uint32_t)(c << 4);
     }
-    auto issue_p = [&](int chunk, int slot) {
+    auto issue = [&](int chunk, int slot) {
         unsigned char* dst = ring + slot * STAGE + wave * 1024;
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const bool in_k = chunk * KC + lch[i] < P.Cin;
-            const uint32_t off = in_k ? pgo[i] + (uint32_t)(chunk * RB) : kOob;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(in_rsrc, (__attribute__((address_space(3))) void*)(dst + i * (NW * 1024)),
+        for (int i = 0; i < 4; ++i) {               // the patch rows, then the weight rows
+            const bool in_k = chunk * KC + lch[i % 2] < P.Cin;
+            const uint32_t off = in_k ? (i < 2 ? pgo[i % 2] : wgo[i % 2]) + (uint32_t)(chunk * RB) : kOob;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(i < 2 ? in_rsrc : w_rsrc,
+                                                     (__attribute__((address_space(3))) void*)(dst + i / 2 * PBYTES + i % 2 * (NW * 1024)),
                                                      16, off, 0, 0, 0);
         }
     };
@@ -1283,22 +1272,16 @@ __device__ __forceinline__ void conv_pw_body(const ConvParams& P, const int bloc
     if (gemm) {
 #pragma unroll
         for (int d = 0; d < D; ++d)
-            if (d < n_ch) issue_p(chunk_of(d), d);
+            if (d < n_ch) issue(chunk_of(d), d);
     }
     for (int c = 0; gemm && c < n_ch; ++c) {
-        // the loads of chunk c are complete when at most the later chunks' are outstanding: four instructions each, of the
-        // first three chunks (whose weights went ahead) two
+        // the loads of chunk c are complete when at most the later chunks' (4 instructions each) are outstanding
         const int ahead = n_ch - 1 - c < D - 1 ? n_ch - 1 - c : D - 1;
-        if (c >= 2 && ahead >= 2) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
-        else if (c == 1 && ahead >= 2) asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
-        else if (c == 0 ? ahead >= 2 : c >= 2 && ahead == 1) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-        else if (ahead == 1) asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
+        if (ahead >= 2) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+        else if (ahead == 1) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
         else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         lds_barrier();                              // chunk c is in LDS; everyone is done with chunk c - 1
-        if (c + D < n_ch) {
-            issue_p(chunk_of(c + D), (c + D) % NSTG);
-            issue_w(chunk_of(c + D), (c + D) % NSTG);
-        }
+        if (c + D < n_ch) issue(chunk_of(c + D), (c + D) % NSTG);
         const unsigned char* sb = ring + (c % NSTG) * STAGE;
 #pragma unroll
         for (int g = 0; g < GPC; ++g) {
@@ -1316,9 +1299,10 @@ __device__ __forceinline__ void conv_pw_body(const ConvParams& P, const int bloc
         }
     }
 
-    // The compiler's own waits for the early loads end here: between the stores they would wait for those too.
+    floatx4 b[NBW];
 #pragma unroll
-    for (int j = 0; j < NBW; ++j) asm volatile("" : "+v"(b[j]));
+    for (int j = 0; j < NBW; ++j) b[j] = *reinterpret_cast<const floatx4*>(bias_at + (chan0 - n0) + j * 4);
+    // The compiler's own waits for the early loads end here: between the stores they would wait for those too.
     if constexpr (ADD)
 #pragma unroll
         for (int u = 0; u < UPW; ++u)
