@@ -764,7 +764,7 @@ struct StackCall {
     int pack_host_plans(unsigned char* staging);
     int emit_copies(int s, hipStream_t st);
     int emit_layer(int i, hipStream_t st, ConvAdd* add = nullptr, ConvBatch* batch = nullptr);
-    int run_with(int i, int end, int* with) const;
+    int run_with(int i, int end, uint32_t done, int* with) const;
     bool apart(int t, int v) const;
     bool apart(int t, int v, const void* at_v) const;
     bool sum_with(int i, ConvAdd* add) const;
@@ -1216,11 +1216,12 @@ bool StackCall::apart(int t, int v, const void* at_v) const {
 
 // The later 1x1 convolutions (before layer `end`) that may be launched with layer i because they read its input: the layers
 // between must neither read nor write their outputs, which buffers that a caller lets tensors share could make them do.
-int StackCall::run_with(int i, int end, int* with) const {
+// Bit d of `done`: layer i + d has been launched (with a layer before i, where one between them could not be).
+int StackCall::run_with(int i, int end, uint32_t done, int* with) const {
     if (prof || inplace || P.torus) return 0;
     int n = 0;
     for (int j = P.sibling[i]; j >= 0 && j < end && n < kConvBatch - 1; j = P.sibling[j]) {
-        bool free = true;
+        bool free = !((done >> (j - i)) & 1);
         for (int k = i; k < j && free; ++k) {
             int ids[4];
             const int m = layer_inputs(P.layers[k], ids);
@@ -1328,7 +1329,7 @@ int StackCall::emit_stage(int s, hipStream_t st) {
         const bool awaited = pipe && i + 2 == end && s + 1 < P.n_stages && P.tight[s + 1];
         const bool both = i + 1 < end && !awaited && sum_with(i, &add);
         int with[kConvBatch - 1];
-        const int n_with = both ? 0 : run_with(i, pipe && s + 1 < P.n_stages && P.tight[s + 1] ? end - 1 : end, with);
+        const int n_with = both ? 0 : run_with(i, pipe && s + 1 < P.n_stages && P.tight[s + 1] ? end - 1 : end, done, with);
         if (n_with) {
             ConvBatch batch;
             rc = emit_layer(i, st, nullptr, &batch);

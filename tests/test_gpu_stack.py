@@ -1580,3 +1580,45 @@ def test_pointwise_layers_of_one_tensor_in_one_launch(bf16, n, device_plan):
         for t in range(4):
             for i, (a, b) in enumerate(zip(runs[0][0][t], runs[1][0][t])):
                 assert torch.equal(a, b), (t, i)
+
+
+def _c11(cin, cout, in0, relu=1, k=1):
+    return dict(type=synth.CONV, k=k, s=1, p=k // 2, cin=cin, cout=cout, relu=relu, in0=in0, in1=-1)
+
+
+def _full_frame(layers, share, profile, n=3, H=40, W=36):
+    """One full frame through a runner whose tensor t lies in tensor share[t]'s buffer; the last tensor and the kernels."""
+    ws, bs = synth.he_weights(layers, 3, bias_scale=0.05, residual_scale=0.5, input_shape=(H, W, 3))
+    video = np.stack([synth.panning_video(7800 + s, n_frames=1, H=H, W=W, fg=((16, 16),)) for s in range(n)])
+    runner = binding.StackRunner(layers, ws, bs, n, H, W, 3, block=8, radius=8, dtype=binding.DC_BF16, device_plan=True, exact_masks=True, overlap=False)
+    runner.enable_profile(profile)
+    for t, v in share.items():
+        assert runner.bufs[0][t].shape == runner.bufs[0][v].shape
+        for tables in runner._tp:
+            for table in tables:
+                table[t] = table[v]
+    runner.step(torch.from_numpy(video[:, 0].copy()).to(DEV), force_full=True)
+    torch.cuda.synchronize()
+    return runner.bufs[0][len(layers)].clone(), [binding.conv_kernel_name(k) if k >= 0 else "" for k in runner.layer_stats()["kernel_id"]]
+
+
+MANY = "conv_pw_many_kernel<__hip_bfloat16, 2>"
+ALONE = "conv_pw_kernel<__hip_bfloat16, 2>"
+
+
+@pytest.mark.parametrize("share,kernels", [
+    ({}, (MANY, MANY, MANY)),                      # three layers of one tensor
+    ({4: 2}, (MANY, ALONE, MANY)),                 # the second writes over what the 3x3 layer before it reads: it waits for its turn,
+                                                   # and the third, launched with the first, is not launched again with it
+    ({5: 2}, (MANY, MANY, ALONE)),                 # the same for the third
+    ({4: 2, 5: 3}, (ALONE, MANY, MANY)),           # neither may move up to the first, but the third to the second
+])
+def test_layers_of_one_tensor_whose_buffers_are_shared(share, kernels):
+    """1x1 layers that read one tensor are launched with the first of them only where nothing between them reads or writes
+    their outputs' memory.  (With a profile attached every layer is a launch of its own.)"""
+    layers = [dict(_c11(3, 64, 0), k=3, p=1), _c11(64, 64, 1), _c11(64, 64, 2, k=3), _c11(64, 64, 1), _c11(64, 64, 1)]
+    layers += [synth._concat([64, 64, 64, 64], [2, 3, 4, 5]) if not share else synth._concat([64, 64], [4, 5])]
+    got, names = _full_frame(layers, share, False)
+    want, apart = _full_frame(layers, {}, True)
+    assert (names[1], names[3], names[4]) == kernels and {apart[i] for i in (1, 3, 4)} == {ALONE}
+    assert torch.equal(got, want)
