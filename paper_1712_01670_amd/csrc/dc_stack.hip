@@ -1325,9 +1325,8 @@ int StackCall::emit_stage(int s, hipStream_t st) {
             if (last.valid && last.plan == &P && last.partition == P.partition) DC_TRY_HIP(wait(st, last.read[s + 1]));
         }
         ConvAdd add{};
-        // (a sum whose buffer the next stage of the last frame may still read has its own wait)
-        const bool awaited = pipe && i + 2 == end && s + 1 < P.n_stages && P.tight[s + 1];
-        const bool both = i + 1 < end && !awaited && sum_with(i, &add);
+        // (no such wait for a sum: its tensor has a buffer per frame, and only one of a single buffer is waited for)
+        const bool both = i + 1 < end && sum_with(i, &add);
         int with[kConvBatch - 1];
         const int n_with = both ? 0 : run_with(i, pipe && s + 1 < P.n_stages && P.tight[s + 1] ? end - 1 : end, done, with);
         if (n_with) {

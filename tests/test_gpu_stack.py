@@ -1622,3 +1622,48 @@ def test_layers_of_one_tensor_whose_buffers_are_shared(share, kernels):
     want, apart = _full_frame(layers, {}, True)
     assert (names[1], names[3], names[4]) == kernels and {apart[i] for i in (1, 3, 4)} == {ALONE}
     assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("share,fused", [({}, True), ({4: 1}, True),       # the sum may replace its other summand
+                                         ({4: 2}, False),                  # the convolution's input
+                                         ({4: 3}, False)])                 # the convolution's output
+def test_sums_whose_buffers_are_shared(share, fused):
+    """A sum is written by the convolution before it only where that convolution does not read the sum's memory."""
+    layers = [dict(_c11(3, 64, 0), k=3, p=1), _c11(64, 64, 1), _c11(64, 64, 2, relu=0), synth._add(64, 3, 1, True), _c11(64, 32, 4)]
+    got, names = _full_frame(layers, share, False)
+    want, apart = _full_frame(layers, {}, True)
+    assert names[2] == ("conv_pw_add_kernel<__hip_bfloat16, 2>" if fused else ALONE) and apart[2] == ALONE
+    assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("net,bf16,units", [("resnet50", True, 4), ("resnet50", True, 8), ("resnet50", False, 8),
+                                            ("googlenet", True, 4), ("googlenet", False, 8)])
+def test_layers_launched_together_under_several_stages(net, bf16, units):
+    """Sums written by the convolution before them and 1x1 layers of one tensor in one launch, in frames that are cut into stages,
+    launched and replayed, with the tiles of both sizes: every tensor bit for bit that of the same layers launched one by one
+    (a profile attached, no stages).  The launch shapes are fixed."""
+    layers = synth.resolve_global_pooling(synth.resnet50_trunk() if net == "resnet50" else synth.googlenet(), 224, 224, 3)
+    ws, bs = synth.he_weights(layers, 3, bias_scale=0.05, residual_scale=0.5, input_shape=(224, 224, 3))
+    T = 5
+    video = torch.from_numpy(synth.panning_video(95, n_frames=T, H=224, W=224, fg=((24, 24), (16, 32)))).to(DEV)
+    frames = [video[t:t + 1].contiguous() for t in range(T)]
+    torch.cuda.synchronize()
+    order = (list(range(T)) + [None]) * 12
+    binding.dc_conv_tuning(0, units, 1, 0)
+    try:
+        runs = {}
+        for mode in (0, 1, None):
+            print(f"[together] {net} bf16={bf16} units={units} mode={mode}", flush=True)
+            runs[mode] = _replay_run(layers, ws, bs, frames, 16, bf16, mode, order,
+                                     before=lambda j, r: r.enable_profile(True) if mode is None and j == 0 else None)
+    finally:
+        binding.dc_conv_tuning()
+    names = {mode: {binding.conv_kernel_name(k) for k in runs[mode][2] if k >= 0} for mode in runs}
+    together = f"conv_pw_{'add' if net == 'resnet50' else 'many'}_kernel<{'__hip_bfloat16' if bf16 else 'float'}, {units // 2}>"
+    assert together in names[0] and together in names[1] and together not in names[None], names
+    assert runs[0][1].stages > 1 and runs[1][1].stages > 1 and runs[1][1].replayed > 0 and runs[0][1].replayed == 0
+    assert int(runs[0][0][0][-2].sum()) > 0
+    for mode in (0, 1):
+        for f, (a, b) in enumerate(zip(runs[mode][0], runs[None][0])):
+            for i, (x, y) in enumerate(zip(a, b)):
+                assert torch.equal(x, y), (mode, f, i)
