@@ -976,11 +976,27 @@ DEEP_CASES = [
 ]
 
 
+def _kernel_of(cin, cout, n, H, W, tuning):
+    """The kernel that a 3x3 bf16 layer of this shape takes under a tuning (a full frame of a stack of this layer alone)."""
+    layer = dict(_layer(cin, cout, 3, 1, 1, True), in0=0, in1=-1)
+    binding.dc_conv_tuning(*tuning)
+    try:
+        runner = binding.StackRunner([layer], [np.zeros((cout, 3, 3, cin), np.float32)], [np.zeros(cout, np.float32)], n, H, W, cin,
+                                     block=1, radius=1, dtype=binding.DC_BF16, overlap=False)
+        runner.step(torch.zeros((n, H, W, cin), dtype=torch.uint8, device=DEV))
+        torch.cuda.synchronize()
+        return binding.conv_kernel_name(runner.layer_stats()["kernel_id"][0])
+    finally:
+        binding.dc_conv_tuning()
+
+
 @pytest.mark.parametrize("cached", [False, True])
 @pytest.mark.parametrize("case", DEEP_CASES)
 def test_deep_conv_kernel_shapes(oracle, case, cached):
     if cached and case[1] < 8:
         pytest.skip("the rectangles of the cached case need a wider map")
+    H, W, cin, cout, tuning = case
+    assert _kernel_of(cin, cout, 2, H, W, tuning) == f"conv_deep_kernel<{2 if cout % 256 or tuning[2] == 2 else 4}, {tuning[1]}>"
     test_fast_conv_kernel_shapes(oracle, case, True, cached)
 
 
@@ -994,6 +1010,9 @@ def test_deep_conv_kernel_bits_and_borders():
     x[0, 0, 0, 5], x[1, H - 1, W - 1, 7], x[2, 4, 4, 0] = float("inf"), float("-inf"), float("nan")
     w = (torch.randn((cout, 3, 3, cin), generator=g, device=DEV) * 0.05).bfloat16()
     b = torch.randn(cout, generator=g, device=DEV)
+    assert _kernel_of(cin, cout, n, H, W, (1, 8, 1, 0)).startswith("conv_fast_kernel")
+    for tuning, name in (((5, 8, -1, -1), "conv_deep_kernel<4, 8>"), ((5, 7, -1, -1), "conv_deep_kernel<4, 7>"), ((5, 6, 2, -1), "conv_deep_kernel<2, 6>")):
+        assert _kernel_of(cin, cout, n, H, W, tuning) == name
     for relu, bias in ((0, b), (1, b), (2, None)):
         layer = dict(_layer(cin, cout, 3, 1, 1, True), relu=relu)
         wp = binding.dc_pack_conv_weights(layer, w)
@@ -1020,6 +1039,9 @@ def test_whole_map_kernel(oracle, H, W, cin, cout, n):
     w = oracle.round_bf16((rng.standard_normal((cout, 3, 3, cin)) * np.sqrt(2.0 / (cin * 9))).astype(np.float32))
     b = (rng.standard_normal(cout) * 0.1).astype(np.float32)
     xd, wd, bd = _to_dev(x, True), _to_dev(w, True), torch.from_numpy(b).to(DEV)
+    assert _kernel_of(cin, cout, n, H, W, (0, 4, 1, 0)).startswith("conv_fast_kernel")
+    for units, blocks in ((2, 2), (4, 2 if cout % 128 else 4)):
+        assert _kernel_of(cin, cout, n, H, W, (6, units, -1, -1)) == f"conv_map_kernel<{((H * W + 15) // 16 + 3) // 4}, {blocks}>"
     for relu, bias in ((1, bd), (2, bd), (0, None)):
         layer = dict(_layer(cin, cout, 3, 1, 1, True), relu=relu)
         wp = binding.dc_pack_conv_weights(layer, wd)

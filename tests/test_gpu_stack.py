@@ -1495,11 +1495,19 @@ def test_stem_kernel_follows_the_number_of_units():
         assert binding.conv_kernel_name(runner.layer_stats()["kernel_id"][0]) == name, (n, cout)
 
 
-@pytest.mark.parametrize("bf16,n", [(True, 1), (True, 3), (False, 12)])
-def test_sums_written_by_the_convolution_before_them(bf16, n):
+@pytest.mark.parametrize("bf16,n,units", [(True, 1, -1), (True, 3, -1), (False, 12, -1), (True, 1, 8), (True, 3, 8), (False, 3, 8)])
+def test_sums_written_by_the_convolution_before_them(bf16, n, units):
     """A residual block's sum is written by the 1x1 convolution before it; with a profile attached it is a launch of its own.
     The same bits, in full frames and in cached ones (units without work, units with some reusable pixels, layers outside the
-    cache)."""
+    cache); the 64 x 64 tile and the 128 x 128 one, which so few units would not choose."""
+    try:
+        binding.dc_conv_tuning(-1, units, -1, -1)
+        _check_sums(bf16, n, f"conv_pw_add_kernel<{'__hip_bfloat16' if bf16 else 'float'}, {4 if units == 8 else 2}>")
+    finally:
+        binding.dc_conv_tuning()
+
+
+def _check_sums(bf16, n, kernel):
     layers = synth.resnet50_trunk()[:24]
     H = W = 96
     ws, bs = synth.he_weights(layers, 3, bias_scale=0.05, residual_scale=0.5, input_shape=(H, W, 3))
@@ -1515,13 +1523,14 @@ def test_sums_written_by_the_convolution_before_them(bf16, n):
             runner.enable_profile(profile)
             frames = []
             for t in range(4):
-                print(f"[sums] bf16={bf16} n={n} profile={profile} frame {t}", flush=True)
+                print(f"[sums] {kernel} n={n} profile={profile} frame {t}", flush=True)
                 got = runner.step(dev[t])
                 torch.cuda.synchronize()
-                names = [binding.conv_kernel_name(k) if k >= 0 else "" for k in runner.layer_stats()["kernel_id"]]
+                names = {binding.conv_kernel_name(k) for k in runner.layer_stats()["kernel_id"] if k >= 0}
+                sums = {v for v in names if v.startswith("conv_pw_add_kernel")}
+                assert sums == (set() if profile else {kernel}), (t, names)
                 frames.append([x.clone() for x in got])
-            runs.append((frames, names))
-        assert any("conv_pw_add_kernel" in v for v in runs[0][1]) and not any("conv_pw_add_kernel" in v for v in runs[1][1])
+            runs.append((frames,))
         for t in range(4):
             for i, (a, b) in enumerate(zip(runs[0][0][t], runs[1][0][t])):
                 assert torch.equal(a, b), (t, i)
@@ -1547,10 +1556,20 @@ def test_whole_map_kernel_in_cached_frames(oracle, H, W, torus):
 
 
 @pytest.mark.parametrize("device_plan", [True, False])
-@pytest.mark.parametrize("bf16,n", [(True, 1), (True, 6), (False, 40)])
-def test_pointwise_layers_of_one_tensor_in_one_launch(bf16, n, device_plan):
+@pytest.mark.parametrize("bf16,n,units", [(True, 1, -1), (True, 6, -1), (False, 40, -1), (True, 1, 8), (True, 3, 8), (False, 3, 4), (False, 3, 8)])
+def test_pointwise_layers_of_one_tensor_in_one_launch(bf16, n, units, device_plan):
     """The three 1x1 convolutions of an inception module that read the module's input go out as one launch; with a profile
-    attached they are three.  The same bits in full frames and in cached ones, with the stem outside the cache or not."""
+    attached they are three.  The same bits in full frames and in cached ones, with the stem outside the cache or not; the
+    64 x 64 tile and the 128 x 128 one, which so few units would not choose.  (In fp32 maps as small as these split K instead, and
+    such layers go out alone.)"""
+    try:
+        binding.dc_conv_tuning(-1, units, -1, -1)
+        _check_pointwise(bf16, n, units, device_plan)
+    finally:
+        binding.dc_conv_tuning()
+
+
+def _check_pointwise(bf16, n, units, device_plan):
     layers = synth.googlenet(width=0.5)[:23]
     H = W = 64
     ws, bs = synth.he_weights(layers, 3, bias_scale=0.05, input_shape=(H, W, 3))
@@ -1568,15 +1587,17 @@ def test_pointwise_layers_of_one_tensor_in_one_launch(bf16, n, device_plan):
             runner.enable_profile(profile)
             frames = []
             for t in range(4):
-                print(f"[pointwise] bf16={bf16} n={n} device_plan={device_plan} profile={profile} frame {t}", flush=True)
+                print(f"[pointwise] bf16={bf16} n={n} units={units} device_plan={device_plan} profile={profile} frame {t}", flush=True)
                 got = runner.step(dev[t])
                 torch.cuda.synchronize()
                 names = [binding.conv_kernel_name(k) if k >= 0 else "" for k in runner.layer_stats()["kernel_id"]]
+                many = f"conv_pw_many_kernel<{'__hip_bfloat16' if bf16 else 'float'}, {4 if units == 8 else 2}>"
+                if profile or (not bf16 and units < 0):
+                    assert not any("conv_pw_many_kernel" in v for v in names), (t, names)
+                else:
+                    assert all(names[i] == many for i in together), (t, names)
                 frames.append([x.clone() for x in got])
-            runs.append((frames, names))
-        if bf16:      # (fp32: whole tiles where the maps are large enough)
-            assert all("conv_pw_many_kernel" in runs[0][1][i] for i in together)
-        assert not any("conv_pw_many_kernel" in v for v in runs[1][1])
+            runs.append((frames,))
         for t in range(4):
             for i, (a, b) in enumerate(zip(runs[0][0][t], runs[1][0][t])):
                 assert torch.equal(a, b), (t, i)
@@ -1637,7 +1658,7 @@ def test_sums_whose_buffers_are_shared(share, fused):
 
 
 @pytest.mark.parametrize("net,bf16,units", [("resnet50", True, 4), ("resnet50", True, 8), ("resnet50", False, 8),
-                                            ("googlenet", True, 4), ("googlenet", False, 8)])
+                                            ("googlenet", True, 4), ("googlenet", True, 8), ("googlenet", False, 8)])
 def test_layers_launched_together_under_several_stages(net, bf16, units):
     """Sums written by the convolution before them and 1x1 layers of one tensor in one launch, in frames that are cut into stages,
     launched and replayed, with the tiles of both sizes: every tensor bit for bit that of the same layers launched one by one
