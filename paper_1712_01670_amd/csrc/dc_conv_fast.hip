@@ -596,12 +596,12 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
 // On a 13x13 map the 4x4 units cover 256 pixels for 169, on 14x14 256 for 196: MFMAs, LDS reads and patch loads for
 // nothing.  Where nearly every unit has work, a workgroup takes a whole map instead: the rows of the GEMM are the map's
 // pixels one after another, 16 to a tile, and the map with its border lies in LDS once (16 slots a line, so maps of up to
-// 14x14) where units have a patch each: 15 KB per 32 channels for 11 tiles, which leaves room for two workgroups per CU.
+// 14x14) where units have a patch each: 15 KB per 32 channels for 11 tiles.
 // Everything else is conv_fast_kernel: stages of one kernel row, double buffers, eight wavefronts (four rows of tiles, dealt
 // round-robin, x two halves of the channels), and the order of the sums with chunks of 32 channels: the same bits.
 // The reusable pixels of a cached frame come from the units' masks, so a list that is shorter than expected costs time only.
 // 13x13 384->384 on 64 streams 44 -> 36 us, 512->1024 on 16 streams 36 -> 30, 14x14 512->512 on 64 streams 61 -> 52.  What bounds it:
-// a barrier per kernel row at two wavefronts per SIMD, and few workgroups (192 to 512 for 256 CUs).
+// a barrier per kernel row at two wavefronts per SIMD (registers allow no more), and few workgroups (192 to 512 for 256 CUs).
 // LDS: the row of slot (line, column) at (16 line + column) * 64 bytes, its 16-byte chunk c at c ^ 2 (column / 4 % 2): a read
 // of 16 neighbouring pixels of a line is free of conflicts, one across a line's end is not (14x14: 0.29 of the LDS cycles).
 template <int UPW, int NBW>
@@ -2032,21 +2032,31 @@ bool map_shape(const ConvLaunch& c) {
     return c.dtype == DC_BF16 && c.k == 3 && c.p == 1 && c.Hout == c.Hin && c.Wout == c.Win && c.Hout <= 14 && c.Wout <= 14 && c.Cout % 64 == 0 &&
            (!c.tiles || c.umask) && (long)c.n_streams * (c.Cout / 64) < 2147483647L;
 }
-// Blocks of 16 channels per wavefront where it is the faster one, 0: it is not.  It has to take at least an eighth off the rows,
-// with enough tiles for a stage (us, conv_fast_kernel's best -> this: 14x14 256->256 16 streams 11 -> 18), and its workgroups
-// have to fill the CUs: of 128 channels (or four tiles a wavefront) a CU holds one, so the share of the CUs that the last of
-// the rounds of 256 leaves busy must make up for the rows saved (13x13 512->1024 28 / 40 / 56 streams 52 -> 44, 79 -> 81,
-// 101 -> 84, 384->384 64 streams 44 -> 36, 14x14 512->512 56 / 64 streams 53 -> 47, 61 -> 52); of 64 channels and three
-// tiles it holds two (13x13 512->1024 12 / 16 / 20 streams 28 -> 28, 36 -> 30, 41 -> 43, 384->384 40 / 56 streams 28 -> 23,
-// 36 -> 34; 14x14 512->512 28 / 40 streams 34 -> 31, 41 -> 57).
-int map_blocks(const ConvLaunch& c) {
+// Blocks of 16 channels per wavefront (2 or 4) where it is the faster one, 0: it is not.  Maps of at least nine tiles (with fewer a stage
+// is mostly its barrier: 14x14 256->256 on 16 streams 11 -> 18 us) that it takes at least an eighth of the rows off, by cost in
+// the unit of the model below, against `other`, the cheapest of the other kernels.  The two wavefronts of a SIMD hold half of the
+// tiles between them, rounded up: 288 cycles of MFMAs for two blocks of channels per tile and 32 channels.  Registers, not LDS, limit
+// the variant with four blocks, and both with four tiles a wavefront, to one workgroup per CU; with two blocks and up to three tiles
+// two share it, which takes 1.5 times as long as one of them.  Measured, us, model in brackets, of two blocks / four blocks / the others:
+//   13x13  384->384  40 streams (one workgroup per CU) 24 (21) / 32 (30) / 29 (26);  56 (two) 33 (33) / 32 (30) / 37 (35);
+//          96 (three) 50 (49) / 61 (60) / 62 (62);  128 51 (49) / 61 (60) / 81 (77);  160 (four) 64 (66) / 63 (60) / 86 (88)
+//   13x13 512->1024  8 streams 26 (26) / 38 (38) / 22 (21);  16 28 (26) / 38 (38) / 33 (33);  34 63 (63) / 78 (76) / 58 (64);
+//          44 63 (63) / 78 (76) / 80 (85);  80 105 (104) / 117 (113) / 125 (146)
+//   14x14  512->512  28 streams 29 (29) / 41 (42) / 33 (30);  40 55 (58) / 42 (42) / 40 (39);  64 56 (58) / 47 (42) / 56 (57);
+//          144 136 (144) / 130 (127) / 119 (129)
+//   11x13  256->512  30 streams 15 (15) / 20 (20) / 16 (16);  40 22 (22) / 21 (20) / 20 (19);  64 23 (22) / 22 (20) / 26 (25);  160 50 (54) / 57 (60) / 53 (53)
+// The model of the others is good to a tenth, so this kernel has to win by more than that can hide; for up to a workgroup per CU
+// it finds the others too fast instead (14x14 256->256 on 56 streams 19.6, by the model 17.2).
+int map_blocks(const ConvLaunch& c, double other) {
     const int tiles = (c.Hout * c.Wout + 15) / 16, units = ((c.Hout + 3) / 4) * ((c.Wout + 3) / 4);
     if (!map_shape(c) || tiles < 9 || tiles * 8 > units * 7) return 0;
-    const long w64 = (long)c.n_streams * (c.Cout / 64);
-    auto fills = [&](long wgs) { return wgs * units * 20 >= (wgs + 255) / 256 * 256 * tiles * 21; };
-    if (c.Cout % 128 == 0 && fills(w64 / 2)) return 4;
-    if (tiles > 12) return fills(w64) ? 2 : 0;
-    return (w64 >= 208 && w64 <= 256) || (w64 >= 352 && w64 <= 512) ? 2 : 0;
+    const int half = (tiles + 1) / 2, n_ch = c.Cin / 32;
+    const long w64 = (long)c.n_streams * (c.Cout / 64), per_cu = (w64 + 255) / 256;
+    const double four = c.Cout % 128 ? 1e300 : (double)((w64 / 2 + 255) / 256) * (13000 + n_ch * (576.0 * half + 460));
+    const double lone = 11600 + n_ch * (326.0 * half + 600), pair = 15400 + n_ch * (576.0 * half + 750);
+    const double two = tiles > 12 ? per_cu * lone : (per_cu / 2) * pair + (per_cu % 2) * (per_cu > 1 ? lone - 10000 : lone);
+    if (std::min(four, two) < 0.92 * other) return four <= two ? 4 : 2;
+    return per_cu == 1 && two < 1.02 * other ? 2 : 0;
 }
 template <int NBW>
 hipError_t map_launch(int upw, dim3 grid, hipStream_t st, const ConvParams& P) {
@@ -2555,7 +2565,7 @@ bool launch_conv_fast(const ConvLaunch& c, long n_cap, long n_units, hipStream_t
     if (ch.g < 1) return false;
     const bool untuned = g_tune[0] < 0 && g_tune[1] < 0 && g_tune[2] < 0 && g_tune[3] < 0;
     const int map_nbw = g_tune[0] == 6 ? (map_shape(c) ? (g_tune[1] == 4 && c.Cout % 128 == 0 ? 4 : 2) : 0)
-                      : untuned && ch.kci == 0 && (ch.geom == kDeep || ch.ks == 1) && n_units * 10 >= n_cap * 9 ? map_blocks(c) : 0;
+                      : untuned && ch.kci == 0 && (ch.geom == kDeep || ch.ks == 1) && n_units * 10 >= n_cap * 9 ? map_blocks(c, ch.cost) : 0;
     const bool deep = ch.geom == kDeep;
     const int nt = deep ? 64 * ch.ks : geom_nt(ch.geom), ks = deep ? 1 : ch.ks;
     const int upw = deep ? ch.g : (ch.g + kGeom[ch.geom].wm - 1) / kGeom[ch.geom].wm;

@@ -1060,3 +1060,17 @@ def test_whole_map_kernel(oracle, H, W, cin, cout, n):
         if relu == 1:
             for i in range(n):
                 assert _rel_err(_to_np(base)[i], oracle.conv_cached(x[i], w, b, 3, 1, 1, True, bf16=True)) <= 2e-2
+
+
+@pytest.mark.parametrize("H,W,cin,cout,kernels", [
+    (13, 13, 384, 384, {16: None, 40: (3, 2), 64: (3, 4), 107: (3, 2), 160: (3, 4)}),
+    (13, 13, 512, 1024, {8: None, 16: (3, 2), 34: None, 44: (3, 2)}),
+    (14, 14, 512, 512, {28: (4, 2), 40: None, 64: (4, 4), 144: None}),
+    (11, 13, 256, 512, {30: (3, 2), 40: None, 64: (3, 4), 160: None}), (12, 12, 384, 384, {64: None})])
+def test_where_whole_maps_are_taken(H, W, cin, cout, kernels):
+    """The kernel that takes whole maps runs where its rounds of workgroups cost less than the other kernels' (numbers of streams
+    on both sides of the line, measured); maps that its tiles save nothing on never take it."""
+    for n, want in kernels.items():
+        print(f"[whole maps] {H}x{W} {cin}->{cout} n={n}", flush=True)
+        name = _kernel_of(cin, cout, n, H, W, (-1, -1, -1, -1))
+        assert name == f"conv_map_kernel<{want[0]}, {want[1]}>" if want else not name.startswith("conv_map_kernel"), (n, name)
