@@ -182,7 +182,10 @@ typedef struct {
     int32_t* layer_kernel_id;   /* optional host [n_layers]: which GEMM instantiation ran (-1: none) */
     void* profile;              /* optional dc_profile handle with >= 2*n_layers slots: slot i brackets
                                    the GEMM kernel of conv layer i, slot n_layers+i its shifted copy; when the copies
-                                   of all layers run as one launch, slot n_layers brackets that launch */
+                                   of all layers run as one launch, slot n_layers brackets that launch.  With a profile
+                                   every layer is a launch of its own: 1x1 layers that otherwise share a launch or write
+                                   the sum behind them as well do neither (same values, more launches than a frame has
+                                   without it) */
 } dc_stack_stats;
 
 const char* dc_status_string(int32_t status);

@@ -707,7 +707,8 @@ class StackRunner:
         return self.stats
 
     def enable_profile(self, on=True):
-        """Attach (or detach) HIP-event brackets around every conv GEMM and copy launch."""
+        """Attach (or detach) HIP-event brackets around every conv GEMM and copy launch.  Every layer is a launch of its own then:
+        1x1 convolutions that share a launch without a profile, or write the sum behind them as well, do neither."""
         if on and not self.stats.profile:
             h = C.c_void_p()
             _check("dc_profile_create", lib().dc_profile_create(2 * len(self.layers), C.byref(h)))
