@@ -1711,32 +1711,37 @@ __global__ __launch_bounds__(256) void conv_stem11_kernel(ConvParams P) { conv_f
 // exact zeros.  In the kernels above every block of 16 or 32 channels fetches every input vector again: AlexNet's first layer
 // loads 33 KiB per unit and block.  Here the unit's patch is brought into LDS once, four channels a pixel, for all channels
 // of the workgroup, and a wavefront keeps the weights of 16 NB channels in registers.
-//   workgroup = NU units at a time, NWC wavefronts of 16 NB channels each per unit; persistent, walks the unit list
+//   workgroup = NU groups of two units at a time, NWC wavefronts of 16 NB channels each per group; persistent, walks the unit list
+//               (one unit at a time: 96 channels on 64 streams 58.8 us for 52.8; four chains of MFMAs instead of two, and a weight
+//               fragment with its zeros serves both.  The 32-channel form takes one: a wavefront brings whole patches there, and
+//               the registers do not hold two.)
 //   K groups  = four taps of a kernel row, one per quarter of a wavefront, row after row: those of the kernels above, in their
 //               order.  Two groups share the registers of a fragment (four channels of each); the MFMA of one multiplies
 //               the other's pixels by zeros, as the kernels above do with channels four to seven: the same bits.  (Both
 //               in one MFMA, or MFMAs of half the K, would add in another order: measured, one value in 65 000 rounds
-//               to another bf16.)  The weights with their zeros are made by two moves per MFMA; kept in registers for one
+//               to another bf16.)  The weights with their zeros are made by two moves per two MFMAs; kept in registers for one
 //               block of channels per wavefront they take longer (11x11 on 64 streams 85 us), the pixels being read twice as often.
 // LDS: rows are RS bytes apart and, 11x11, column x of row y lies at x ^ 2 (y / 4 % 2): the 32 reads of half a wavefront (pixels
 // of two quarters) fall into different banks.
 // Channels four to seven of the weights meet zeros and are not read.
-// 227x227 11x11 -> 96 on 1 / 4 / 16 / 64 streams, against the kernel above: 9.0 -> 7.8, 16.8 -> 14.2, 44.8 -> 22.8, 145.6 -> 57.8 us (37 MB
-// out and 53 MB in on 64: 18 at the copy's rate); 224x224 7x7 -> 64 on 1 / 4 / 8 / 16 / 64: 5.9 -> 7.7, 11.1 -> 13.3, 17.3 -> 16.4, 28.2 -> 22.6, 92.3 -> 55.6.
-// What bounds it: a step's chain of load, LDS write, barrier, reads and dependent MFMAs at two workgroups per CU (the
-// pixels requested two steps ahead: 11x11 64 us, 7x7 85: the registers cost more than the wait).
+// 227x227 11x11 -> 96 on 1 / 4 / 16 / 64 streams, against the kernel above: 9.3 -> 8.4, 17.0 -> 13.6, 45.7 -> 23.2, 148.5 -> 52.4 us (37 MB
+// out and 53 MB in on 64: 18 at the copy's rate); 224x224 7x7 -> 64 on 1 / 4 / 8 / 16 / 64: 6.2 -> 8.5, 11.3 -> 12.8, 17.3 -> 16.8, 28.0 -> 21.5, 92.0 -> 48.6.
+// What bounds it: a step's chain of load, LDS write, barrier, reads and MFMAs at two workgroups per CU (the pixels requested
+// two steps ahead, with one unit: 11x11 64 us for 58, 7x7 85 for 56: the registers cost more than the wait).
+constexpr int stem4_units(int k, int nwc) { return k == 11 && nwc == 1 ? 1 : 2; }      // of a wavefront at a time
 template <int K, int S, int NB, int NWC, int NU>
-__global__ __launch_bounds__(NWC * NU * 64) void conv_stem4_kernel(ConvParams P) {
+__global__ __launch_bounds__(NWC * NU * 64) __attribute__((amdgpu_waves_per_eu(2))) void conv_stem4_kernel(ConvParams P) {
     typedef __hip_bfloat16 T;
     typedef Frag<T> F;
     typedef F::vec vec;
     constexpr int TG = (K + 3) / 4, NG = K * TG, NP = (NG + 1) / 2;      // groups of a kernel row, all groups, pairs of them
+    constexpr int UW = stem4_units(K, NWC);
     constexpr bool kSwizzle = K == 11;
     constexpr int PH = 3 * S + K, PWX = 3 * S + 4 * TG, RS = K == 11 ? 208 : 160;
     constexpr int GT = NWC * 64, NPT = (PH * PWX + GT - 1) / GT, PATCH = PH * RS;
     static_assert(PWX * 8 <= RS && (!kSwizzle || PWX % 4 == 0), "shape; a swizzled column stays in its row");
 
-    __shared__ __align__(16) unsigned char smem[NU * 2 * PATCH];
+    __shared__ __align__(16) unsigned char smem[NU * UW * 2 * PATCH];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l16 = lane & 15, q = lane >> 4;
     const int wave_u = wave / NWC, wave_c = wave % NWC;
@@ -1799,15 +1804,15 @@ __global__ __launch_bounds__(NWC * NU * 64) void conv_stem4_kernel(ConvParams P)
         }
         return r;
     };
-    uintx2 px[NPT];
-    auto load_px = [&](const UnitPos& pos) {
+    uintx2 px[UW][NPT];
+    auto load_px = [&](int w, const UnitPos& pos) {
         const int y0 = pos.uy * (4 * S) - P.p, x0 = pos.ux * (4 * S) - P.p;
 #pragma unroll
         for (int i = 0; i < NPT; ++i) {
             const int iy = y0 + ppy[i], ix = x0 + ppx[i];
             const bool ok = pos.mixed >= 0 && (unsigned)iy < (unsigned)P.Hin && (unsigned)ix < (unsigned)P.Win;
             const uint32_t off = ok ? (uint32_t)(((pos.stream * P.Hin + iy) * P.Win + ix) * 16) : kOob;
-            px[i] = __builtin_bit_cast(uintx2, __builtin_amdgcn_raw_buffer_load_b64(in_rsrc, off, 0, 0));
+            px[w][i] = __builtin_bit_cast(uintx2, __builtin_amdgcn_raw_buffer_load_b64(in_rsrc, off, 0, 0));
         }
     };
     // read side: this quarter's tap of group 0, for kernel rows ky with ky / 4 even and odd
@@ -1817,72 +1822,96 @@ __global__ __launch_bounds__(NWC * NU * 64) void conv_stem4_kernel(ConvParams P)
     for (int o = 0; o < 2; ++o)
         xaddr[o] = (l16 >> 2) * (S * RS) + (l16 & 3) * (S * 8) + (kSwizzle ? q ^ (((l16 >> 2) + o) & 1) * 2 : q) * 8;
 
-    const int step = (int)gridDim.x * NU, first = (int)blockIdx.x * NU;
+    const int step = (int)gridDim.x * (NU * UW), first = (int)blockIdx.x * (NU * UW);
     if (first >= n_units) return;                      // the whole workgroup, before any barrier
-    int u = first + wave_u;
-    UnitPos pos = locate(u), pos_next = locate(u + step);
-    load_px(pos);
+    int u = first + wave_u * UW;
+    UnitPos pos[UW], pos_next[UW];
+#pragma unroll
+    for (int w = 0; w < UW; ++w) {
+        pos[w] = locate(u + w);
+        pos_next[w] = locate(u + w + step);
+        load_px(w, pos[w]);
+    }
     int buf = 0;
     for (int base = first;; base += step, buf ^= 1) {
-        unsigned char* const patch = smem + (wave_u * 2 + buf) * PATCH;
+        unsigned char* const patch = smem + (wave_u * 2 + buf) * (UW * PATCH);
 #pragma unroll
-        for (int i = 0; i < NPT; ++i)
-            if ((i + 1) * GT <= PH * PWX || gt + i * GT < PH * PWX) *reinterpret_cast<uintx2*>(patch + ppos[i]) = px[i];
-        if constexpr (NWC > 1) lds_barrier();      // the patch is in LDS; nobody reads the other buffer any more
+        for (int w = 0; w < UW; ++w)
+#pragma unroll
+            for (int i = 0; i < NPT; ++i)
+                if ((i + 1) * GT <= PH * PWX || gt + i * GT < PH * PWX) *reinterpret_cast<uintx2*>(patch + w * PATCH + ppos[i]) = px[w][i];
+        if constexpr (NWC > 1) lds_barrier();      // the patches are in LDS; nobody reads the other buffer any more
         const bool more = base + step < n_units;
-        UnitPos after{0, 0, 0, -1};
+        UnitPos after[UW];
         if (more) {
-            load_px(pos_next);
-            after = locate(u + 2 * step);
-        }
-        floatx4 acc[NB];
 #pragma unroll
-        for (int j = 0; j < NB; ++j) acc[j] = bias[j] + 0.f;      // (-0: products with the zeros may be -0 here, and +0 is what a sum of both is)
+            for (int w = 0; w < UW; ++w) {
+                load_px(w, pos_next[w]);
+                after[w] = locate(u + w + 2 * step);
+            }
+        }
+        floatx4 acc[UW][NB];
+#pragma unroll
+        for (int w = 0; w < UW; ++w)
+#pragma unroll
+            for (int j = 0; j < NB; ++j) acc[w][j] = bias[j] + 0.f;      // (-0: products with the zeros may be -0 here, and +0 is what a sum of both is)
 #pragma unroll
         for (int i = 0; i < NP; ++i) {
-            auto read_x = [&](int g) { return *reinterpret_cast<const uintx2*>(patch + xaddr[g / TG >> 2 & 1] + g / TG * RS + g % TG * 32); };
+            auto read_x = [&](int w, int g) { return *reinterpret_cast<const uintx2*>(patch + w * PATCH + xaddr[g / TG >> 2 & 1] + g / TG * RS + g % TG * 32); };
             const bool two = 2 * i + 1 < NG;
-            const uintx2 lo = read_x(2 * i), hi = two ? read_x(2 * i + 1) : lo;
-            const vec x = __builtin_bit_cast(vec, uintx4{lo[0], lo[1], hi[0], hi[1]});
+            vec x[UW];
+#pragma unroll
+            for (int w = 0; w < UW; ++w) {
+                const uintx2 lo = read_x(w, 2 * i), hi = two ? read_x(w, 2 * i + 1) : lo;
+                x[w] = __builtin_bit_cast(vec, uintx4{lo[0], lo[1], hi[0], hi[1]});
+            }
 #pragma unroll
             for (int j = 0; j < NB; ++j) {
                 w_lo[j][0] = wv[i][j][0]; w_lo[j][1] = wv[i][j][1];
-                F::mma1(__builtin_bit_cast(vec, w_lo[j]), x, acc[j], 0);
+#pragma unroll
+                for (int w = 0; w < UW; ++w) F::mma1(__builtin_bit_cast(vec, w_lo[j]), x[w], acc[w][j], 0);
             }
 #pragma unroll
             for (int j = 0; two && j < NB; ++j) {
                 w_hi[j][2] = wv[i][j][2]; w_hi[j][3] = wv[i][j][3];
-                F::mma1(__builtin_bit_cast(vec, w_hi[j]), x, acc[j], 0);
+#pragma unroll
+                for (int w = 0; w < UW; ++w) F::mma1(__builtin_bit_cast(vec, w_hi[j]), x[w], acc[w][j], 0);
             }
         }
-        const int y = pos.uy * 4 + (l16 >> 2), x = pos.ux * 4 + (l16 & 3);
-        if (pos.mixed >= 0 && y < P.Hout && x < P.Wout && !((pos.mixed >> l16) & 1)) {      // a reusable pixel holds the cached value
-            int yo = y, xo = x;
-            if (P.out_origin) {
-                xo = torus_wrap(x, P.out_origin[(size_t)pos.stream * P.origin_stride], P.Wout);
-                yo = torus_wrap(y, P.out_origin[(size_t)pos.stream * P.origin_stride + 1], P.Hout);
-            }
-            T* out = reinterpret_cast<T*>(P.out) + ((pos.stream * P.Hout + yo) * P.Wout + xo) * P.Cout + chan;
-            uint32_t v[2 * NB];
 #pragma unroll
-            for (int j = 0; j < NB; ++j) {
-                if (relu) activate4(acc[j], P.relu);
-                v[2 * j] = (uint32_t)F::bits(acc[j][0]) | ((uint32_t)F::bits(acc[j][1]) << 16);
-                v[2 * j + 1] = (uint32_t)F::bits(acc[j][2]) | ((uint32_t)F::bits(acc[j][3]) << 16);
-            }
+        for (int w = 0; w < UW; ++w) {
+            const int y = pos[w].uy * 4 + (l16 >> 2), x = pos[w].ux * 4 + (l16 & 3);
+            if (pos[w].mixed >= 0 && y < P.Hout && x < P.Wout && !((pos[w].mixed >> l16) & 1)) {      // a reusable pixel holds the cached value
+                int yo = y, xo = x;
+                if (P.out_origin) {
+                    xo = torus_wrap(x, P.out_origin[(size_t)pos[w].stream * P.origin_stride], P.Wout);
+                    yo = torus_wrap(y, P.out_origin[(size_t)pos[w].stream * P.origin_stride + 1], P.Hout);
+                }
+                T* out = reinterpret_cast<T*>(P.out) + ((pos[w].stream * P.Hout + yo) * P.Wout + xo) * P.Cout + chan;
+                uint32_t v[2 * NB];
 #pragma unroll
-            for (int j = 0; j < NB; j += 2)
-                *reinterpret_cast<uintx4*>(out + j * 4) = uintx4{v[2 * j], v[2 * j + 1], v[2 * j + 2], v[2 * j + 3]};
+                for (int j = 0; j < NB; ++j) {
+                    if (relu) activate4(acc[w][j], P.relu);
+                    v[2 * j] = (uint32_t)F::bits(acc[w][j][0]) | ((uint32_t)F::bits(acc[w][j][1]) << 16);
+                    v[2 * j + 1] = (uint32_t)F::bits(acc[w][j][2]) | ((uint32_t)F::bits(acc[w][j][3]) << 16);
+                }
+#pragma unroll
+                for (int j = 0; j < NB; j += 2)
+                    *reinterpret_cast<uintx4*>(out + j * 4) = uintx4{v[2 * j], v[2 * j + 1], v[2 * j + 2], v[2 * j + 3]};
+            }
         }
         if (!more) break;
         u += step;
-        pos = pos_next;
-        pos_next = after;
+#pragma unroll
+        for (int w = 0; w < UW; ++w) {
+            pos[w] = pos_next[w];
+            pos_next[w] = after[w];
+        }
     }
 }
 
-// Workgroups of a launch: two per CU, which is what the registers allow (11x11: 256 / 384 / 512 / 768 of them 78 / 71 / 58 /
-// 66 us on 64 streams, 7x7 71 / 66 / 56 / 60: every further one loads its weights again).
+// Workgroups of a launch: two per CU, which is what the registers allow (256 / 512 of them: 11x11 67 / 53 us on 64 streams, 7x7 with one
+// unit a wavefront 71 / 56, and 768 66 / 60: every further one loads its weights again).
 constexpr int kStem4Wgs = 512;
 constexpr int kStem4Id = 432;         // kernel ids: 7x7, then 11x11 with 1, 2, 3 wavefronts a unit
 // Wavefronts per unit of conv_stem4_kernel, 0: not its shape, or too few units for it: a 7x7 layer's patches are small and what
@@ -2466,7 +2495,7 @@ bool launch_conv_fast(const ConvLaunch& c, long n_cap, long n_units, hipStream_t
                                         : 96 + (c.dtype == DC_BF16 ? 3 : 0) + (nb == 4 ? 2 : (nb == 2 ? 1 : 0));
             if (const int nwc = stem4_waves(c, n_units, g_tune[1])) {
                 const int gy = c.Cout / (c.k == 7 ? 64 : 32 * nwc);
-                const long nu = c.k == 7 ? 4 : 1, wgs = std::min((n_cap + nu - 1) / nu, std::max(1L, (long)kStem4Wgs / gy));
+                const long nu = (c.k == 7 ? 4 : 1) * stem4_units(c.k, nwc), wgs = std::min((n_cap + nu - 1) / nu, std::max(1L, (long)kStem4Wgs / gy));
                 if (c.kernel_id) *c.kernel_id = kStem4Id + (c.k == 7 ? 0 : nwc);
                 *err = stem4_launch(c.k, nwc, dim3((unsigned)wgs, (unsigned)gy), st, P);
                 return true;
