@@ -1074,3 +1074,28 @@ def test_where_whole_maps_are_taken(H, W, cin, cout, kernels):
         print(f"[whole maps] {H}x{W} {cin}->{cout} n={n}", flush=True)
         name = _kernel_of(cin, cout, n, H, W, (-1, -1, -1, -1))
         assert name == f"conv_map_kernel<{want[0]}, {want[1]}>" if want else not name.startswith("conv_map_kernel"), (n, name)
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("pw_tile", [4, 8], indirect=True)
+@pytest.mark.parametrize("cin,cout", [(8, 8), (64, 72), (96, 200), (320, 136)])
+def test_pointwise_kernel_without_a_bias(cin, cout, pw_tile, bf16):
+    """No bias is a bias of zeros, and a bias that is not aligned to a channel tile is read to its end and no further: the last
+    channel's value lies before a NaN."""
+    g = torch.Generator(DEV)
+    g.manual_seed(cin + cout)
+    x = torch.randn((3, 13, 11, cin), generator=g, device=DEV)
+    w = torch.randn((cout, 1, 1, cin), generator=g, device=DEV) * 0.1
+    store = torch.full((cout + 64,), float("nan"), device=DEV)
+    store[:cout] = torch.randn(cout, generator=g, device=DEV)
+    if bf16:
+        x, w = x.bfloat16(), w.bfloat16()
+    layer = _layer(cin, cout, 1, 1, 0, False)
+    run = lambda bias: binding.dc_cached_conv_layer(layer, x, w, bias)
+    none, zero, some = run(None), run(torch.zeros(cout, device=DEV)), run(store[:cout])
+    assert torch.equal(none, zero)
+    want = x.double().reshape(-1, cin) @ w.double().reshape(cout, cin).T + store[:cout].double()
+    got = some.double().reshape(-1, cout)
+    # K + 2 roundings to 2^-24 of the terms' absolute sum, and one to the storage type
+    bound = (cin + 2) * 2.0 ** -24 * (x.double().abs().reshape(-1, cin) @ w.double().abs().reshape(cout, cin).T + store[:cout].double().abs())
+    assert bool(((got - want).abs() <= bound + (2.0 ** -8 if bf16 else 0.0) * want.abs()).all())
