@@ -1915,11 +1915,13 @@ __global__ __launch_bounds__(NWC * NU * 64) __attribute__((amdgpu_waves_per_eu(2
 constexpr int kStem4Wgs = 512;
 constexpr int kStem4Id = 432;         // kernel ids: 7x7, then 11x11 with 1, 2, 3 wavefronts a unit
 // Wavefronts per unit of conv_stem4_kernel, 0: not its shape, or too few units for it: a 7x7 layer's patches are small and what
-// they save only pays for the longer start of a workgroup from about 6000 units of 64 channels on (times above; 8 streams of
-// 224x224 have 6272).  Both kernels give the same bits.  Units per workgroup 1 or 4 in dc_conv_tuning choose one.
+// they save has to pay for the longer start of a workgroup.  Full frames (units of 64 channels, us, the other kernel / this one): 3136
+// units 11.3 / 12.8, 5488 15.6 / 14.8, 6272 17.3 / 16.8.  The units of a list lie apart, which costs the other kernel more (it fetches
+// every input vector of a unit by itself): 1850 units 9.6 / 10.8, 2792 12.6 / 13.3, 3448 14.3 / 13.7, 5684 21.4 / 15.5, 11 500 36.8 / 23.8.
+// Both kernels give the same bits.  Units per workgroup 1 or 4 in dc_conv_tuning choose one.
 int stem4_waves(const ConvLaunch& c, long n_units, int forced) {
     if (c.dtype != DC_BF16 || c.c_frame < 1 || c.c_frame > 4 || c.Cin != 8 || forced == 1) return 0;
-    if (c.k == 7 && c.s == 2) return c.Cout % 64 == 0 && (forced == 4 || n_units * (c.Cout / 64) >= 6000) ? 1 : 0;
+    if (c.k == 7 && c.s == 2) return c.Cout % 64 == 0 && (forced == 4 || n_units * (c.Cout / 64) >= (c.tiles ? 3000 : 6000)) ? 1 : 0;
     return c.k == 11 && c.s == 4 ? (c.Cout % 96 == 0 ? 3 : c.Cout % 64 == 0 ? 2 : c.Cout % 32 == 0 ? 1 : 0) : 0;
 }
 hipError_t stem4_launch(int k, int nwc, dim3 grid, hipStream_t st, const ConvParams& P) {

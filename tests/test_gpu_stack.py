@@ -1485,14 +1485,16 @@ def test_both_stem_kernels_give_the_same_bits(k, s, p, cout, C, n, H, W):
 
 
 def test_stem_kernel_follows_the_number_of_units():
-    """7x7 in bf16: the kernel with the patch in LDS from about 6000 units of 64 channels on."""
-    for n, cout, name in ((2, 64, "conv_stem_kernel<__hip_bfloat16, 2>"), (8, 64, "conv_stem4_kernel<7, 2, 4, 1, 4>"), (4, 128, "conv_stem4_kernel<7, 2, 4, 1, 4>")):
+    """7x7 in bf16: the kernel with the patch in LDS from about 6000 units of 64 channels on, on lists from 3000."""
+    few, many = "conv_stem_kernel<__hip_bfloat16, 2>", "conv_stem4_kernel<7, 2, 4, 1, 4>"
+    for n, cout, full, cached in ((2, 64, few, few), (7, 64, few, many), (8, 64, many, many), (4, 128, many, many)):
         layers = [dict(type=synth.CONV, k=7, s=2, p=3, cin=3, cout=cout, relu=1, in0=0, in1=-1)]
         ws, bs = synth.he_weights(layers, 3)
-        runner = binding.StackRunner(layers, ws, bs, n, 224, 224, 3, dtype=binding.DC_BF16)
-        runner.step(torch.zeros((n, 224, 224, 3), dtype=torch.uint8, device=DEV))
-        torch.cuda.synchronize()
-        assert binding.conv_kernel_name(runner.layer_stats()["kernel_id"][0]) == name, (n, cout)
+        runner = binding.StackRunner(layers, ws, bs, n, 224, 224, 3, dtype=binding.DC_BF16, device_plan=True, exact_masks=True, no_reuse=[1])
+        for want in (full, cached):         # (a layer outside the cache: its list names every unit)
+            runner.step(torch.zeros((n, 224, 224, 3), dtype=torch.uint8, device=DEV))
+            torch.cuda.synchronize()
+            assert binding.conv_kernel_name(runner.layer_stats()["kernel_id"][0]) == want, (n, cout)
 
 
 @pytest.mark.parametrize("bf16,n,units", [(True, 1, -1), (True, 3, -1), (False, 12, -1), (True, 1, 8), (True, 3, 8), (False, 3, 8)])
